@@ -26,7 +26,6 @@ from paper_2509_04377_amd.engine import LayeredCache, PagedCache
 
 DEVICE = "cuda"
 DTYPES = {"f32": torch.float32, "bf16": torch.bfloat16}
-PAGES = (16, 32, 64, 128)
 
 
 def _decode(name, dtype, seqs, kv_heads, q_heads, head_dim, page, budget, layers, driver="layers", layout="per_head",
