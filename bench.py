@@ -75,7 +75,7 @@ def kernel_source_hash():
     the sources it was measured on, and is only quoted while they are unchanged."""
     import hashlib
     h = hashlib.sha256()
-    for name in ("paged_decode.hip", "pe_device.h", "pe_launch.h"):
+    for name in ("paged_decode_bf16.hip", "paged_decode.hip", "pe_device.h", "pe_launch.h"):
         with open(os.path.join(ROOT, "paper_2509_04377_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]

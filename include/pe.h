@@ -87,9 +87,10 @@ typedef struct pe_cache_desc {
    * and the launch read the same fields and agree by construction. */
   int32_t decode_splits;   /* 0: chosen from the shape and the device's compute-unit count; 1..256: that many
                               splits of every row (1 = no partials, no workspace) */
-  int32_t decode_shape;    /* 0: default; else waves*100 + buffers*10 + loads of the attention workgroup.  Built:
-                              422 (default), 424, 432, 822, and only for bf16, D = 128, Hq/Hk = 4, per-head layout;
-                              anything else returns PE_ERR_UNSUPPORTED from the attention calls */
+  int32_t decode_shape;    /* 0: default.  Others for tuning, only for bf16, D = 128, Hq/Hk = 4, per-head layout (422
+                              anywhere): 422 = the default; 424 and 432 = four waves per workgroup, 822 = eight, whatever
+                              the number of workgroups.  Anything else returns PE_ERR_UNSUPPORTED from the attention
+                              calls */
   int32_t decode_flat_order; /* 0: workgroup order that keeps the splits of a row on one XCD; 1: plain row-major */
 } pe_cache_desc;
 

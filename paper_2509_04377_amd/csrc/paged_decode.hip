@@ -1,9 +1,11 @@
-// Paged decode attention (Eq. 1 for one new query per sequence; Alg. 3 "PagedAttention(Q,K,V)").
+// Paged decode attention (Eq. 1 for one new query per sequence; Alg. 3 "PagedAttention(Q,K,V)"): the kernel of fp32
+// caches, the merge of the splits, and the choice of the kernel (bfloat16 caches: paged_decode_bf16.hip).
 //
-// A workgroup owns one split of one (sequence, KV head) row: every splits-th group of four consecutive tiles
-// of the row's tokens.  Each of its four waves walks tiles with a two-deep register pipeline.  Inside a tile every
-// lane holds 16 bytes of four K rows and four V rows (consecutive lanes = consecutive addresses, so
-// each wave-load is 1 KiB of one page, found through the block table with scalar loads).
+// fp32: QK and PV run on the vector units (the fp32 matrix instructions have no higher rate).  A workgroup owns one
+// split of one (sequence, KV head) row: every splits-th group of four consecutive tiles of the row's tokens.  Each of
+// its four waves walks tiles with a two-deep register pipeline.  Inside a tile every lane holds 16 bytes of two K rows
+// and two V rows (consecutive lanes = consecutive addresses, so each wave-load is 1 KiB of one page, found through the
+// block table with scalar loads).
 //
 //   QK:  each lane multiplies its K slice with the matching slice of all G query heads that share this
 //        KV head; the partial dots are reduced over the lanes of a token row with a reduce-scatter over
@@ -36,13 +38,8 @@ constexpr float kNegInf = -__builtin_inff();
 
 constexpr int next_pow2(int x) { return x <= 1 ? 1 : 2 * next_pow2((x + 1) / 2); }
 
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
-
 // The 16 bytes of one query head that face a lane's 16-byte K slice.
-template <typename T>
-struct QSlice;
-template <>
-struct QSlice<float> {
+struct QSlice {
   float v[4];
   __device__ __forceinline__ void load(const float* p) {
     const uint4 r = *reinterpret_cast<const uint4*>(p);
@@ -57,29 +54,6 @@ struct QSlice<float> {
     a = fmaf(__uint_as_float(k.y), v[1], a);
     a = fmaf(__uint_as_float(k.z), v[2], a);
     a = fmaf(__uint_as_float(k.w), v[3], a);
-    return a;
-  }
-};
-template <>
-struct QSlice<bf16_t> {
-  uint32_t v[4];  // 8 bf16, packed as in memory
-  __device__ __forceinline__ void load(const bf16_t* p) {
-    const uint4 r = *reinterpret_cast<const uint4*>(p);
-    v[0] = r.x;
-    v[1] = r.y;
-    v[2] = r.z;
-    v[3] = r.w;
-  }
-  __device__ __forceinline__ void zero() { v[0] = v[1] = v[2] = v[3] = 0u; }
-  static __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c) {
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a), __builtin_bit_cast(bf16x2_t, b), c,
-                                           false);
-  }
-  __device__ __forceinline__ float dot(const uint4& k) const {
-    float a = dot2(k.x, v[0], 0.f);
-    a = dot2(k.y, v[1], a);
-    a = dot2(k.z, v[2], a);
-    a = dot2(k.w, v[3], a);
     return a;
   }
 };
@@ -164,13 +138,17 @@ struct DecodeParams {
   int n_spare;
 };
 
-template <typename T, int D, int G, int LOADS>
+// Four waves, two register buffers, two wave-loads of K and of V per tile (4 KiB per tile, 8 KiB per wave in flight
+// while it waits): the stream runs fastest at about 8 MiB in flight over the chip.
+constexpr int kWaves = 4, kDepth = 2, kLoads = 2;
+
+template <int D, int G>
 struct Tile {
-  using Geo = RowGeom<T, D>;
+  using Geo = RowGeom<float, D>;
   static constexpr int EPL = Geo::kPerVec;
   static constexpr int LPR = Geo::kLanesPerRow;
   static constexpr int TPL = Geo::kTokensPerLoad;
-  static constexpr int NLT = LOADS;  // wave-loads of K (and of V) per tile
+  static constexpr int NLT = kLoads;  // wave-loads of K (and of V) per tile
   static constexpr int TT = NLT * TPL;  // tokens per tile
   static constexpr int GP = next_pow2(G);
   static_assert(GP <= LPR && GP <= 8, "query group too large");
@@ -200,7 +178,7 @@ struct Tile {
   // unconditional, which keeps the order of outstanding loads known at compile time, so waiting for the
   // oldest tile leaves the younger ones in flight.
   static __device__ __forceinline__ void issue(uint4 (&kb)[NLT], uint4 (&vb)[NLT], int tile, const int (&phys)[NPT],
-                                               const T* k_pool, const T* v_pool, int log2_block, int lane_off,
+                                               const float* k_pool, const float* v_pool, int log2_block, int lane_off,
                                                int row_vecs = LPR) {
     const int tok0 = tile * TT;
 #pragma unroll
@@ -220,7 +198,7 @@ struct Tile {
   // Consume NL wave-loads whose first token is tok0: logits, online softmax update, PV accumulation.
   template <int NL>
   static __device__ __forceinline__ void compute(uint4 (&kb)[NL], uint4 (&vb)[NL], int tok0, int len, int grp,
-                                                 float scale_log2e, const QSlice<T> (&qs)[GP], float& m_run,
+                                                 float scale_log2e, const QSlice (&qs)[GP], float& m_run,
                                                  float& l_run, float (&acc)[G][EPL]) {
     float x[NL];
 #pragma unroll
@@ -260,16 +238,17 @@ struct Tile {
     for (int i = 0; i < NL; ++i) {
       float ve[EPL];
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) ve[e] = vec_elem<T>(vb[i], e);
+      for (int e = 0; e < EPL; ++e) ve[e] = vec_elem<float>(vb[i], e);
       accumulate_pv<G, GP, EPL>(acc, pr[i], ve);
     }
   }
 };
 
-template <typename T, int D, int G, int WAVES, int DEPTH, int LOADS, bool FUSED, bool SHARED = false>
-__global__ __launch_bounds__(WAVES * kWave) void paged_decode_kernel(const DecodeParams p) {
+template <int D, int G, bool FUSED, bool SHARED>
+__global__ __launch_bounds__(kWaves * kWave) void paged_decode_kernel(const DecodeParams p) {
   static_assert(!(FUSED && SHARED), "the fused append is per-head only");
-  using TL = Tile<T, D, G, LOADS>;
+  using TL = Tile<D, G>;
+  constexpr int WAVES = kWaves, DEPTH = kDepth;
   constexpr int EPL = TL::EPL, LPR = TL::LPR, TPL = TL::TPL, NLT = TL::NLT, TT = TL::TT, GP = TL::GP;
   constexpr int GBITS = ilog2(GP);
   constexpr int NCONTRIB = WAVES * TPL;
@@ -305,17 +284,17 @@ __global__ __launch_bounds__(WAVES * kWave) void paged_decode_kernel(const Decod
   const int32_t* bt = p.block_table + (int64_t)(SHARED ? s : row) * p.max_blocks;
   const int row_vecs = SHARED ? LPR * p.num_kv_heads : LPR;
   const int lane_vec = SHARED ? (grp * p.num_kv_heads + hk) * LPR + u : lane;
-  const T* k_pool = static_cast<const T*>(p.k_pool);
-  const T* v_pool = static_cast<const T*>(p.v_pool);
+  const float* k_pool = static_cast<const float*>(p.k_pool);
+  const float* v_pool = static_cast<const float*>(p.v_pool);
 
   // ---- prologue: everything that does not depend on the row length is requested first --------------
   // query slices: slot i holds head (i ^ c_lane) of this KV head's group (heads past the group: zeros)
-  QSlice<T> qs[GP];
+  QSlice qs[GP];
 #pragma unroll
   for (int i = 0; i < GP; ++i) {
     const int head = i ^ c_lane;
     const int head_ld = head < p.g_real ? head : 0;
-    qs[i].load(static_cast<const T*>(p.q) + ((int64_t)s * p.num_q_heads + hk * p.g_real + head_ld) * D + u * EPL);
+    qs[i].load(static_cast<const float*>(p.q) + ((int64_t)s * p.num_q_heads + hk * p.g_real + head_ld) * D + u * EPL);
   }
   uint4 nk[1], nv[1];  // FUSED: the new token's K/V rows, held by the first lane group of every wave
   if constexpr (FUSED) {
@@ -464,11 +443,7 @@ __global__ __launch_bounds__(WAVES * kWave) void paged_decode_kernel(const Decod
       if (p.splits == 1) {
         const float r = ll > 0.f ? o / ll : 0.f;
         const int64_t off = ((int64_t)s * p.num_q_heads + hk * p.g_real + h) * D + d;
-        if constexpr (sizeof(T) == 4) {
-          static_cast<float*>(p.out)[off] = r;
-        } else {
-          static_cast<uint16_t*>(p.out)[off] = f32_to_bf16(r);
-        }
+        static_cast<float*>(p.out)[off] = r;
       } else {
         float* part = p.partials + (((int64_t)row * p.splits + split) * p.g_real + h) * (D + 2);
         part[d] = o;
@@ -517,7 +492,7 @@ __global__ __launch_bounds__(D) void paged_decode_reduce_kernel(const float* __r
   }
 }
 
-template <typename T, int D, int G, int WAVES, int DEPTH, int LOADS>
+template <int D, int G>
 hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
   DecodeParams p;
   p.q = a.q;
@@ -545,59 +520,34 @@ hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
   p.xcd_map = (a.xcd_map && rows % 8 == 0) ? 1 : 0;
   const int64_t grid = rows * a.splits;
   if (grid <= 0 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  const dim3 blocks((unsigned)grid), threads(kWaves * kWave);
   if (a.shared) {
     if (a.new_k != nullptr) return hipErrorInvalidValue;
-    if constexpr (WAVES == 4 && DEPTH == 2 && LOADS == 2) {
-      hipLaunchKernelGGL((paged_decode_kernel<T, D, G, WAVES, DEPTH, LOADS, false, true>), dim3((unsigned)grid),
-                         dim3(WAVES * kWave), 0, stream, p);
-    } else {
-      return hipErrorInvalidValue;
-    }
+    hipLaunchKernelGGL((paged_decode_kernel<D, G, false, true>), blocks, threads, 0, stream, p);
   } else if (a.new_k != nullptr) {
-    hipLaunchKernelGGL((paged_decode_kernel<T, D, G, WAVES, DEPTH, LOADS, true>), dim3((unsigned)grid), dim3(WAVES * kWave), 0,
-                       stream, p);
+    hipLaunchKernelGGL((paged_decode_kernel<D, G, true, false>), blocks, threads, 0, stream, p);
   } else {
-    hipLaunchKernelGGL((paged_decode_kernel<T, D, G, WAVES, DEPTH, LOADS, false>), dim3((unsigned)grid), dim3(WAVES * kWave),
-                       0, stream, p);
+    hipLaunchKernelGGL((paged_decode_kernel<D, G, false, false>), blocks, threads, 0, stream, p);
   }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.splits == 1) return e;
-  hipLaunchKernelGGL((paged_decode_reduce_kernel<T, D>), dim3((unsigned)(a.num_seqs * a.num_q_heads)), dim3(D), 0,
-                     stream, a.partials, a.out, a.num_kv_heads, p.g_real, a.splits);
   return hipGetLastError();
 }
 
-// Workgroup shape: four waves, two register buffers, two wave-loads of K and of V per tile (4 KiB per tile,
-// 8 KiB per wave in flight while it waits).  On an MI355X the stream runs fastest at about 8 MiB in flight
-// over the chip: measured on the headline shape 45.0 us per launch against 46.8 (4 loads per tile),
-// 45.9 (three buffers), 47.3 (eight waves) and 62 (one load per tile).  The other shapes are selectable
-// for tuning on the headline instantiation only.
-template <typename T, int D, int G>
-hipError_t launch_variant(const DecodeArgs& a, hipStream_t stream) {
-  if constexpr (sizeof(T) == 2 && D == 128 && G == 4) {
-    switch (a.waves * 100 + a.depth * 10 + a.loads) {
-      case 422: return launch_one<T, D, G, 4, 2, 2>(a, stream);
-      case 424: return launch_one<T, D, G, 4, 2, 4>(a, stream);
-      case 432: return launch_one<T, D, G, 4, 3, 2>(a, stream);
-      case 822: return launch_one<T, D, G, 8, 2, 2>(a, stream);
-      default: return hipErrorInvalidValue;
-    }
-  } else {
-    return launch_one<T, D, G, 4, 2, 2>(a, stream);
+template <int D>
+hipError_t launch_group(const DecodeArgs& a, hipStream_t stream) {
+  switch (a.num_q_heads / a.num_kv_heads) {
+    case 1: return launch_one<D, 1>(a, stream);
+    case 2: return launch_one<D, 2>(a, stream);
+    case 3: return launch_one<D, 3>(a, stream);
+    case 4: return launch_one<D, 4>(a, stream);
+    case 5: case 6: case 7: case 8: return launch_one<D, 8>(a, stream);
+    default: return hipErrorInvalidValue;
   }
 }
 
 template <typename T, int D>
-hipError_t launch_group(const DecodeArgs& a, hipStream_t stream) {
-  const int g = a.num_q_heads / a.num_kv_heads;
-  switch (g) {
-    case 1: return launch_variant<T, D, 1>(a, stream);
-    case 2: return launch_variant<T, D, 2>(a, stream);
-    case 3: return launch_variant<T, D, 3>(a, stream);
-    case 4: return launch_variant<T, D, 4>(a, stream);
-    case 5: case 6: case 7: case 8: return launch_variant<T, D, 8>(a, stream);
-    default: return hipErrorInvalidValue;
-  }
+void launch_reduce(const DecodeArgs& a, hipStream_t stream) {
+  hipLaunchKernelGGL((paged_decode_reduce_kernel<T, D>), dim3((unsigned)(a.num_seqs * a.num_q_heads)), dim3(D), 0, stream,
+                     a.partials, a.out, a.num_kv_heads, a.num_q_heads / a.num_kv_heads, a.splits);
 }
 
 }  // namespace
@@ -608,14 +558,17 @@ size_t decode_partials_bytes(int num_seqs, int num_q_heads, int head_dim, int sp
 }
 
 hipError_t launch_paged_decode(const DecodeArgs& a, hipStream_t stream) {
-  if (a.is_bf16) {
-    if (a.head_dim == 64) return launch_group<bf16_t, 64>(a, stream);
-    if (a.head_dim == 128) return launch_group<bf16_t, 128>(a, stream);
-  } else {
-    if (a.head_dim == 64) return launch_group<float, 64>(a, stream);
-    if (a.head_dim == 128) return launch_group<float, 128>(a, stream);
-  }
-  return hipErrorInvalidValue;
+  if (a.head_dim != 64 && a.head_dim != 128) return hipErrorInvalidValue;
+  const bool d64 = a.head_dim == 64;
+  const hipError_t e = a.is_bf16 ? launch_paged_decode_bf16(a, stream)
+                       : d64     ? launch_group<64>(a, stream)
+                                 : launch_group<128>(a, stream);
+  if (e != hipSuccess || a.splits == 1) return e;
+  if (a.is_bf16)
+    d64 ? launch_reduce<bf16_t, 64>(a, stream) : launch_reduce<bf16_t, 128>(a, stream);
+  else
+    d64 ? launch_reduce<float, 64>(a, stream) : launch_reduce<float, 128>(a, stream);
+  return hipGetLastError();
 }
 
 }  // namespace pe

@@ -15,7 +15,7 @@ namespace {
 
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 
-// The decode workgroup shapes that are built (waves*100 + register buffers*10 + wave-loads per tile).
+// The decode workgroup shapes that a descriptor may name.
 bool decode_shape_built(int shape) { return shape == 422 || shape == 424 || shape == 432 || shape == 822; }
 
 // PE_OK if the descriptor names a shape the kernels are built for.
@@ -99,12 +99,22 @@ pe::DecodeArgs decode_args(const pe_cache_desc* desc, int splits) {
   a.max_blocks = desc->max_blocks;
   a.splits = splits;
   a.xcd_map = desc->decode_flat_order ? 0 : 1;
-  const int shape = desc->decode_shape != 0 ? desc->decode_shape : 422;
-  a.waves = shape / 100;
-  a.depth = shape / 10 % 10;
-  a.loads = shape % 10;
+  // bfloat16 kernel: four waves a workgroup and two tiles in flight per wave.  Where rows of D = 128 give every compute
+  // unit a workgroup: eight waves (more bytes in flight against the latency of pages scattered over a large pool; with
+  // fewer workgroups, or a tile half as large, the longer prologue and merge cost as much as they gain), but in the
+  // head-shared layout, whose wave-loads are runs of 256 bytes, four and a single tile.  Measured on an MI355X, four / eight
+  // waves: 256 rows x 2048 tokens of D = 128 out of an 8.6 GB pool 44.5 / 44.0 us (head-shared 47.2 / 47.1, one tile 45.6),
+  // 192 ragged rows in 768 splits 72.3 / 68.9, 1024 ragged rows 101.5 / 95.5; 64 rows x 1024 of D = 64 in 256 splits
+  // 8.5 / 8.75.
+  const int64_t groups = (int64_t)desc->num_seqs * desc->num_kv_heads * splits;
+  const bool full = desc->head_dim == 128 && groups >= compute_units();
+  const bool shared = desc->layout == PE_LAYOUT_SHARED;
+  a.waves = full && !shared ? 8 : 4;
+  a.depth = full && shared ? 1 : 2;
+  if (desc->decode_shape == 424 || desc->decode_shape == 432) a.waves = 4;
+  if (desc->decode_shape == 822) a.waves = 8;
   a.is_bf16 = desc->dtype == PE_BF16;
-  a.shared = desc->layout == PE_LAYOUT_SHARED;
+  a.shared = shared;
   return a;
 }
 

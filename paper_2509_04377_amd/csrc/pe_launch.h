@@ -77,8 +77,7 @@ struct DecodeArgs {
   int num_seqs, num_kv_heads, num_q_heads, head_dim, block_size, max_blocks;
   int splits;
   int xcd_map;
-  int waves, depth;  // workgroup size in waves, register pipeline depth
-  int loads = 2;     // wave-loads of K (and of V) per tile
+  int waves, depth;  // bfloat16 kernel: workgroup size in waves, tiles in flight per wave: 4 x 2; D = 128: 8 x 2, 4 x 1 too
   bool is_bf16;
   // fused append: all null / 0 for plain attention
   const void* new_k = nullptr;
@@ -91,6 +90,7 @@ struct DecodeArgs {
   bool shared = false;  // one table row per sequence, pages [B][Hk][D]; plain attention only
 };
 hipError_t launch_paged_decode(const DecodeArgs& a, hipStream_t stream);
+hipError_t launch_paged_decode_bf16(const DecodeArgs& a, hipStream_t stream);  // the attention kernel alone (no merge)
 size_t decode_partials_bytes(int num_seqs, int num_q_heads, int head_dim, int splits);
 
 struct PruneArgs {

@@ -331,6 +331,52 @@ def test_paged_decode_masks_junk_and_extreme_logits():
     assert e2 <= 1e-5 and emax <= 1e-5, (e2, emax)
 
 
+@pytest.mark.parametrize("D,B", [(64, 16), (128, 16), (64, 32), (128, 64)])
+@pytest.mark.parametrize("G", [1, 4, 5, 8])
+def test_paged_decode_bf16_tiles(D, B, G):
+    """The bf16 kernel at the edges of its tiles (16 tokens) and rounds (64 tokens, 128 with two tiles in flight), with
+    non-finite junk behind every row's end and in page 0, which the kernel reads for entries a row does not use; the
+    logits climb along the row, so the softmax reference has to move in later tiles.  Tolerance: the rounding of the
+    bf16 result is 2^-9 of a value; twice that in the 2-norm, and in the max-norm of a vector."""
+    print("case paged_decode_bf16_tiles", D, B, G, flush=True)
+    Hk = 3
+    lens = [1, 2, 15, 16, 17, 31, 33, 63, 64, 65, 127, 128, 129, 513, 1025]
+    k_pool, v_pool, table, sl = make_paged(1700 + D + B + G, lens, Hk, D, B, torch.bfloat16)
+    # one page more in front: page 0 is nobody's
+    k_pool, v_pool = torch.cat([k_pool[:1], k_pool]), torch.cat([v_pool[:1], v_pool])
+    table = torch.where(table >= 0, table + 1, table)
+    P = k_pool.shape[0]
+    g = torch.Generator().manual_seed(1701)
+    S, Hq = len(lens), Hk * G
+    q = torch.randn((S, Hq, D), generator=g)
+    for s, L in enumerate(lens):   # head 0 of each group sees logits that grow with the position
+        for h in range(Hk):
+            for j in range((L + B - 1) // B):
+                pos = torch.arange(j * B, j * B + B, dtype=torch.float32)
+                u = q[s, h * G] / q[s, h * G].norm()
+                k_pool[int(table[s, h, j])] += (0.02 * pos[:, None] * u[None]).to(torch.bfloat16)
+    k_clean, v_clean = k_pool.clone(), v_pool.clone()
+    for s, L in enumerate(lens):
+        for h in range(Hk):
+            if L % B:
+                p = int(table[s, h, L // B])
+                k_pool[p, L % B:], v_pool[p, L % B:] = float("nan"), float("inf")
+    k_pool[0], v_pool[0] = float("nan"), float("-inf")
+    q = q.to(torch.bfloat16)
+    want = oracle.paged_decode(f32(q), f32(k_clean), f32(v_clean), i32(table), i32(sl))
+    desc = pe.make_desc(torch.bfloat16, S, Hk, Hq, D, B, table.shape[2], P)
+    kd, vd, td, ld, qd = (x.contiguous().to(DEV) for x in (k_pool, v_pool, table, sl, q))
+    for splits in (0, 1, 2, 7):
+        desc.decode_splits = splits
+        ws = pe.alloc_workspace(pe.PE_OP_PAGED_DECODE, desc)
+        for call in range(2):
+            out = torch.full((S, Hq, D), 7.0, dtype=torch.bfloat16, device=DEV)
+            pe.pe_paged_decode(desc, qd, kd, vd, td, ld, D ** -0.5, out, ws)
+            torch.cuda.synchronize()
+            e2, emax = rel_err(f32(out), want)
+            assert e2 <= 2 ** -8 and emax <= 2 ** -8, (splits, call, e2, emax)
+
+
 def _prompt(seed, lens, Hk, D, dtype, ties=False):
     g = torch.Generator().manual_seed(seed)
     T = sum(lens)
