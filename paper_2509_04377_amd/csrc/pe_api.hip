@@ -63,21 +63,39 @@ int compute_units() {
   return n;
 }
 
-// Number of splits of a row in the attention calls.  The kernel streams best with ONE four-wave workgroup per
-// compute unit (each wave keeps a tile in flight while it consumes another; more resident workgroups only
-// add prologue, epilogue and merge work), so rows are split just enough to cover the compute units of the
-// device, and never into splits shorter than 256 tokens.
+// Number of splits of a row in the attention calls, chosen from the shape (a row is taken to be as long as its table row).
+// Just enough to give every compute unit a workgroup, and none shorter than 128 tokens: a launch streams best with one
+// workgroup per compute unit, and splits cost a second launch that merges them (2.2 to 2.7 us).  From there
+//   - one, where two would do and a row holds at most 512 KiB of K and V: half of the compute units stream that
+//     much in less than the merge takes (128 rows x 1024 tokens of bf16, D = 128: 15.6 us whole, 16.9 in two splits);
+//   - twice as many, where pieces of 1 MiB remain: rows of unequal length then fill the chip more evenly (192 rows of
+//     up to 8192 tokens: ragged 87 us in two splits, 72 in four; all 8192 long 130 and 128; 128 such rows 55 and 53, 85 and 86).
 int decode_splits(const pe_cache_desc* d) {
   if (d->decode_splits > 0) return d->decode_splits;
   const int64_t rows = (int64_t)d->num_seqs * d->num_kv_heads;
-  const int64_t cus = compute_units();
-  int64_t splits = (cus + rows - 1) / rows;
   const int64_t max_tokens = (int64_t)d->max_blocks * d->block_size;
-  const int64_t max_by_len = max_tokens / 256 > 1 ? max_tokens / 256 : 1;
-  if (splits > max_by_len) splits = max_by_len;
+  const int64_t row_bytes = max_tokens * d->head_dim * (d->dtype == PE_BF16 ? 4 : 8);
+  const int64_t by_rows = (compute_units() + rows - 1) / rows;
+  const int64_t by_len = max_tokens / 128 > 1 ? max_tokens / 128 : 1;
+  int64_t splits = by_rows < by_len ? by_rows : by_len;
+  if (splits == 2 && row_bytes <= (512 << 10)) splits = 1;
+  if (by_rows > 1 && row_bytes / (2 * by_rows) >= (1 << 20)) splits = 2 * by_rows;
   if (splits > 64) splits = 64;
-  if (splits < 1) splits = 1;
   return (int)splits;
+}
+
+// The count that a caller's buffer of `have` bytes allows: the library's own choice may fall back to one workgroup per
+// compute unit in splits of 256 tokens and more, a count that the descriptor names may not.
+int decode_splits_within(const pe_cache_desc* d, size_t have) {
+  int splits = decode_splits(d);
+  if (d->decode_splits > 0) return splits;
+  const int64_t rows = (int64_t)d->num_seqs * d->num_kv_heads;
+  const int64_t by_rows = (compute_units() + rows - 1) / rows;
+  const int64_t by_len = (int64_t)d->max_blocks * d->block_size / 256;
+  int64_t least = by_rows < by_len ? by_rows : by_len;
+  if (least > 64) least = 64;
+  while (splits > least && pe::decode_partials_bytes(d->num_seqs, d->num_q_heads, d->head_dim, splits) > have) --splits;
+  return splits;
 }
 
 int check_workspace(const void* ws, size_t have, size_t need) {
@@ -349,7 +367,7 @@ int pe_paged_decode(const pe_cache_desc* desc, const void* q, const void* k_pool
   if (!q || !k_pool || !v_pool || !block_table || !seq_lens || !out) return PE_ERR_INVALID_ARG;
   if (!aligned(k_pool, 16) || !aligned(v_pool, 16) || !aligned(q, 16)) return PE_ERR_INVALID_ARG;
   if (!finite(softmax_scale)) return PE_ERR_INVALID_ARG;
-  const int splits = decode_splits(desc);
+  const int splits = decode_splits_within(desc, workspace_bytes);
   const int ws = check_workspace(
       workspace, workspace_bytes,
       pe::decode_partials_bytes(desc->num_seqs, desc->num_q_heads, desc->head_dim, splits));
@@ -432,7 +450,7 @@ int pe_append_paged_decode(const pe_cache_desc* desc, const void* new_k, const v
   if (!aligned(k_pool, 16) || !aligned(v_pool, 16) || !aligned(q, 16) || !aligned(new_k, 16) || !aligned(new_v, 16))
     return PE_ERR_INVALID_ARG;
   if (!finite(softmax_scale)) return PE_ERR_INVALID_ARG;
-  const int splits = decode_splits(desc);
+  const int splits = decode_splits_within(desc, workspace_bytes);
   const int ws = check_workspace(
       workspace, workspace_bytes,
       pe::decode_partials_bytes(desc->num_seqs, desc->num_q_heads, desc->head_dim, splits));

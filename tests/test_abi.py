@@ -130,6 +130,24 @@ def test_workspace_checks():
     assert pe.pe_workspace_bytes(pe.PE_OP_SCORE_BLOCKS, d) == 0 and pe.pe_workspace_bytes(pe.PE_OP_EVICT_BLOCKS, d) == 0
 
 
+@pytest.mark.parametrize("kw,want", [
+    (dict(num_seqs=32, max_blocks=128), 1), (dict(num_seqs=16, max_blocks=64), 1),    # 512 KiB a row: whole
+    (dict(num_seqs=16, max_blocks=65), 2), (dict(num_seqs=16, max_blocks=255), 2),
+    (dict(num_seqs=16, max_blocks=256), 2), (dict(num_seqs=16, max_blocks=512), 4),   # pieces of 1 MiB: twice as many
+    (dict(num_seqs=24, max_blocks=512), 4), (dict(num_seqs=32, max_blocks=4096), 1),
+    (dict(num_seqs=4, max_blocks=256), 8), (dict(num_seqs=4, max_blocks=7), 1), (dict(num_seqs=4, max_blocks=24), 3),
+    (dict(num_seqs=1, num_kv_heads=1, num_q_heads=4, max_blocks=100000), 64),
+    (dict(num_seqs=16, head_dim=64, max_blocks=128), 1), (dict(num_seqs=16, dtype=pe.PE_F32, max_blocks=64), 2)])
+def test_decode_split_rule(kw, want):
+    """The automatic split count of a 256-CU device at the edges of its rule; the workspace follows it."""
+    if pe.pe_decode_splits(_desc(num_seqs=1, num_kv_heads=1, num_q_heads=1, max_blocks=1 << 20)) != 64:
+        pytest.skip("a device with another number of compute units")
+    d = _desc(**kw)
+    assert pe.pe_decode_splits(d) == want
+    assert pe.pe_workspace_bytes(pe.PE_OP_PAGED_DECODE, d) == (
+        0 if want == 1 else want * d.num_seqs * d.num_q_heads * (d.head_dim + 2) * 4)
+
+
 def test_static_scratch_rejects_oversized_partials():
     """pe_paged_decode_static refuses a shape whose split partials exceed its static array (host check)."""
     S, Hk, Hq, D = 64, 8, 64, 128

@@ -377,6 +377,34 @@ def test_paged_decode_bf16_tiles(D, B, G):
             assert e2 <= 2 ** -8 and emax <= 2 ** -8, (splits, call, e2, emax)
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_paged_decode_with_a_smaller_workspace(dt):
+    """An automatic split count falls back to what the caller's workspace holds, down to splits of 256 tokens."""
+    print("case paged_decode_smaller_workspace", dt, flush=True)
+    Hk, G, D, B = 4, 2, 128, 16
+    lens = [2048, 700, 0, 1]
+    k_pool, v_pool, table, sl = make_paged(1800, lens, Hk, D, B, DTYPES[dt], extra=0)
+    q = torch.randn((len(lens), Hk * G, D), generator=torch.Generator().manual_seed(1801)).to(DTYPES[dt])
+    want = oracle.paged_decode(f32(q), f32(k_pool), f32(v_pool), i32(table), i32(sl))
+    desc = pe.make_desc(DTYPES[dt], len(lens), Hk, Hk * G, D, B, table.shape[2], k_pool.shape[0])
+    per_split = len(lens) * Hk * G * (D + 2) * 4
+    assert pe.pe_decode_splits(desc) == 16
+    args = [x.to(DEV) for x in (q, k_pool, v_pool, table, sl)]
+    for splits in (16, 11, 8, 7):
+        out = torch.full(q.shape, 7.0, dtype=DTYPES[dt], device=DEV)
+        ws = torch.empty(per_split * splits, dtype=torch.uint8, device=DEV)
+        if splits < 8:
+            with pytest.raises(pe.PeError):
+                pe.pe_paged_decode(desc, *args, D ** -0.5, out, ws)
+            continue
+        pe.pe_paged_decode(desc, *args, D ** -0.5, out, ws)
+        torch.cuda.synchronize()
+        assert np.all(f32(out)[2] == 0.0)
+        live = [0, 1, 3]
+        e2, emax = rel_err(f32(out)[live], want[live])
+        assert e2 <= TOL[dt] and emax <= TOL[dt], (splits, e2, emax)
+
+
 def _prompt(seed, lens, Hk, D, dtype, ties=False):
     g = torch.Generator().manual_seed(seed)
     T = sum(lens)
