@@ -89,6 +89,17 @@ __device__ __forceinline__ double lane_xor_f64(double v) {
   return __hiloint2double(hi, lo);
 }
 
+// Inclusive prefix sum over the 64 lanes (DPP row shifts, then row broadcasts: no LDS traffic).
+__device__ __forceinline__ uint32_t wave_prefix_sum_u32(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111 /* row_shr:1 */, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112 /* row_shr:2 */, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114 /* row_shr:4 */, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118 /* row_shr:8 */, 0xf, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142 /* row_bcast:15 */, 0xa, 0xf, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143 /* row_bcast:31 */, 0xc, 0xf, false);
+  return v;
+}
+
 // Value of lane ((lane & ~(W-1)) | J): broadcast of position J of every aligned group of W lanes.
 template <int W, int J>
 __device__ __forceinline__ float group_bcast_f32(float v) {

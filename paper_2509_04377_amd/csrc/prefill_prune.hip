@@ -35,7 +35,7 @@ __host__ __device__ inline size_t align256(size_t x) { return (x + 255) & ~(size
 struct Workspace {
   float* scores;  // [Hk][total_tokens]; shared mode: one more row, the mean over heads
   uint32_t* sel;  // [rows][2]: threshold bits T, tie quota q
-  int32_t* cnt;   // [Hk][chunk_slots][2]: (#score > T, #score == T) per chunk
+  int32_t* before;  // [Hk][chunk_slots][2]: (#score > T, #score == T) in the earlier chunks of the row
   int64_t chunk_slots;
 };
 
@@ -50,7 +50,7 @@ __host__ inline Workspace carve(void* base, int num_seqs, int num_kv_heads, int6
   p += align256(sizeof(float) * (size_t)(num_kv_heads + (shared ? 1 : 0)) * (size_t)total_tokens);
   w.sel = reinterpret_cast<uint32_t*>(p);
   p += align256(sizeof(uint32_t) * 2 * (size_t)num_seqs * num_kv_heads);
-  w.cnt = reinterpret_cast<int32_t*>(p);
+  w.before = reinterpret_cast<int32_t*>(p);
   w.chunk_slots = chunk_slots_for(total_tokens, num_seqs);
   return w;
 }
@@ -151,194 +151,283 @@ __global__ __launch_bounds__(kThreads) void head_mean_kernel(const float* __rest
 // One workgroup of 1024 threads per row.  Radix select on the row's fp32 bit patterns, most significant digit
 // first: 12 bits (sign, exponent, top three mantissa bits: scores of one row cluster in a few exponents, and a
 // narrower first digit would pile every LDS atomic onto three or four bins), then 10 + 10 bits.  After a pass
-// the digit that holds rank k is found with a workgroup-wide scan.  The first pass reads the whole row with
-// 16-byte loads, eight in flight per thread.  The tokens that fall into the first digit's bin are then
-// collected in LDS (a few percent of the row for any spread-out score distribution), so the second and third
-// pass never touch memory; a row with more candidates than the LDS buffer holds (e.g. all scores equal) falls
-// back to passes over memory.  With the threshold known the same workgroup counts, per chunk of 1024 tokens,
-// how many scores are > T and how many == T (one wave per chunk): the gather turns these into destinations.
-// A row is worked on by one compute unit, and one compute unit pulls about 45 GB/s from L2 however many loads
-// it keeps in flight: that, not the histogram atomics, bounds a pass over a long row (a finer first digit of
-// 16384 bins was measured and changed nothing).  Spreading a row over several workgroups needs a launch per
-// stage (pivots, counting pass, exact selection, chunk counts), which costs most of what it saves at these
-// row lengths.
+// the digit that holds rank k is found with a workgroup-wide scan.  The tokens that fall into the first digit's bin
+// are collected in LDS (a few percent of the row for any spread-out score distribution), so the second and third
+// pass see only them; a row with more candidates than the LDS buffer holds (e.g. all scores equal) goes over all of
+// its scores again.  With the threshold known the same workgroup counts, per chunk of 1024 tokens, how many scores are
+// > T and how many == T: the gather turns these into destinations.
+// A row is worked on by one compute unit, and one compute unit pulls about 45 GB/s from L2 however many loads it keeps
+// in flight: that, not the histogram atomics, bounds the reading of a long row.  So it is read once, into registers (4*NV
+// scores a thread, NV by the longest row of the call), and every pass works from there; only what a row has beyond
+// 65536 tokens is read from memory in each pass.  Also kept out of the serial chain of a short row: cross-lane sums go
+// through DPP, the wave totals of a scan are read at once, places in the candidate list are taken once per wave, four
+// histograms share the atomics of the first digit.  Measured on an MI355X, before (every pass from memory, three more
+// barriers a pass) / now: 64 rows x 4096 scores 10.4 / 6.9 us, 128 ragged rows of up to 16384 13.4 / 11.2, 256 x 16384 17.6 / 14.3,
+// 32 x 65536 30.5 / 26.3.
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / kWave;
 constexpr int kSelBins = 4096;
 constexpr int kSelUnroll = 8;
 constexpr int kSelCand = 8192;  // candidates kept in LDS after the first pass (32 KiB)
+constexpr int kSelMaxVecs = 16;
+constexpr int kSelCopies = 4;
 
-// f(bits) for every element of bits[0 .. L): a scalar head up to 16-byte alignment, 16-byte loads with
-// kSelUnroll in flight per thread, a scalar tail.  The order of visits is unspecified.
-template <typename F>
-__device__ __forceinline__ void visit_row(const uint32_t* bits, int L, int tid, F f) {
-  int mis = (int)((4u - (uint32_t)((reinterpret_cast<uintptr_t>(bits) >> 2) & 3u)) & 3u);
-  mis = mis < L ? mis : L;
-  if (tid < mis) f(bits[tid]);
-  const uint4* v = reinterpret_cast<const uint4*>(bits + mis);
-  const int nvec = (L - mis) >> 2;
-  for (int base = tid; base < nvec; base += kSelUnroll * kSelThreads) {
-    uint4 r[kSelUnroll];
+struct __attribute__((packed, aligned(4))) Unaligned4 {  // 16 bytes at any 4-byte boundary, in one load
+  uint32_t v[4];
+};
+
+// The scores of a row as its workgroup holds them: score 4*(j*1024 + tid) + e is reg[j].v[e] of thread tid.
+template <int NV>
+struct RowScores {
+  static constexpr int kHeld = 4 * NV * kSelThreads;
+  const uint32_t* bits;
+  int L, tid;
+  Unaligned4 reg[NV];
+
+  __device__ __forceinline__ int index(int j) const { return 4 * (j * kSelThreads + tid); }
+
+  __device__ __forceinline__ void load() {
 #pragma unroll
-    for (int j = 0; j < kSelUnroll; ++j) {
-      const int i = base + j * kSelThreads;
-      r[j] = v[i < nvec ? i : nvec - 1];
+    for (int j = 0; j < NV; ++j) {  // unconditional, so that all are in flight: past the end the row's last four again
+      const int i = index(j);
+      const int last = L >= 4 ? L - 4 : 0;
+      reg[j] = L >= 4 ? *reinterpret_cast<const Unaligned4*>(bits + (i < last ? i : last)) : Unaligned4{{0u, 0u, 0u, 0u}};
     }
 #pragma unroll
-    for (int j = 0; j < kSelUnroll; ++j) {
-      if (base + j * kSelThreads < nvec) {
-        f(r[j].x);
-        f(r[j].y);
-        f(r[j].z);
-        f(r[j].w);
+    for (int j = 0; j < NV; ++j) {  // the one vector that the row's end cuts
+      const int i = index(j);
+      if (i < L && i + 4 > L) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) reg[j].v[e] = i + e < L ? bits[i + e] : 0u;
       }
     }
   }
-  const int tail0 = mis + nvec * 4;
-  if (tail0 + tid < L) f(bits[tail0 + tid]);
-}
 
+  // f(score) for every score that the registers hold ...
+  template <typename F>
+  __device__ __forceinline__ void visit_held(F f) const {
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      if (4 * (j + 1) * kSelThreads <= L) {  // the same for all threads
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f(reg[j].v[e]);
+      } else {
+        const int left = L - index(j);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (e < left) f(reg[j].v[e]);
+      }
+    }
+  }
+  // ... and for the rest of the row, from memory
+  template <typename F>
+  __device__ __forceinline__ void visit_rest(F f) const {
+    for (int i0 = kHeld + tid; i0 < L; i0 += kSelUnroll * kSelThreads) {
+      uint32_t r[kSelUnroll];
+#pragma unroll
+      for (int k = 0; k < kSelUnroll; ++k) {
+        const int i = i0 + k * kSelThreads;
+        r[k] = bits[i < L ? i : L - 1];
+      }
+#pragma unroll
+      for (int k = 0; k < kSelUnroll; ++k)
+        if (i0 + k * kSelThreads < L) f(r[k]);
+    }
+  }
+  template <typename F>
+  __device__ __forceinline__ void visit(F f) const {
+    visit_held(f);
+    visit_rest(f);
+  }
+};
+
+template <int NV>
 __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __restrict__ scores,
                                                              const int32_t* __restrict__ cu_seqlens,
-                                                             uint32_t* __restrict__ sel, int32_t* __restrict__ cnt,
+                                                             uint32_t* __restrict__ sel, int32_t* __restrict__ before,
                                                              int32_t* __restrict__ seq_lens_out,
                                                              int32_t* __restrict__ kept_idx_out, int64_t total_tokens,
                                                              int64_t chunk_slots, int num_kv_heads, int budget) {
-  __shared__ uint32_t hist[kSelBins];
-  __shared__ uint32_t cand[kSelCand];
-  __shared__ uint32_t wave_tot[kSelWaves];
-  __shared__ uint32_t sh_prefix, sh_k, sh_ncand;
+  constexpr int kHeldChunks = RowScores<NV>::kHeld / kChunk;
+  constexpr int kBinsPerThread = kSelBins / kSelThreads;
+  // First digit: kSelCopies histograms side by side (bin * kSelCopies + lane % kSelCopies), so that fewer lanes of a
+  // wave meet in one word.  The 1024 bins of a later digit use the front of it.
+  __shared__ __attribute__((aligned(16))) uint32_t hist[kSelBins * kSelCopies];
+  __shared__ uint32_t cand[kSelCand];  // candidates; at the end, the counts of up to kSelCand chunks at a time
+  __shared__ __attribute__((aligned(16))) uint32_t wave_tot[kSelWaves];
+  __shared__ uint32_t sh_prefix, sh_k, sh_in_bin, sh_ncand;
   const int row = (int)blockIdx.x;
   const int s = row / num_kv_heads, h = row % num_kv_heads;
   const int t0 = cu_seqlens[s];
   const int L = cu_seqlens[s + 1] - t0;
   const int keep = L < budget ? L : budget;
   const int E = L - keep;
-  const uint32_t* bits = reinterpret_cast<const uint32_t*>(scores) + (int64_t)h * total_tokens + t0;
   const int tid = (int)threadIdx.x;
-  const int lane = tid & (kWave - 1), wave = tid / kWave;
+  const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  RowScores<NV> rs;
+  rs.bits = reinterpret_cast<const uint32_t*>(scores) + (int64_t)h * total_tokens + t0;
+  rs.L = L;
+  rs.tid = tid;
+  rs.load();
 
   if (h == 0 && tid == 0) seq_lens_out[s] = keep;
   if (kept_idx_out != nullptr)
     for (int i = keep + tid; i < budget; i += kSelThreads) kept_idx_out[(int64_t)row * budget + i] = -1;
 
-  // E == 0, nothing to evict: T = +0.0, q = 0 keeps every token (scores are >= +0)
-  uint32_t prefix = 0u, mask = 0u;
-  uint32_t k = (uint32_t)(E > 0 ? E - 1 : 0);  // 0-based rank of the threshold element among the remaining ones
-  bool in_lds = false;                         // the remaining candidates are cand[0 .. ncand)
-  uint32_t ncand = 0u;
-  if (E > 0) {
-#pragma unroll 1
-    for (int pass = 0; pass < 3; ++pass) {
-      const int shift = pass == 0 ? 20 : pass == 1 ? 10 : 0;
-      const int nbins = pass == 0 ? kSelBins : 1024;
-      constexpr int kMaxPerThread = kSelBins / kSelThreads;
-      const int per_thread = nbins / kSelThreads;  // 4 or 1 consecutive bins per thread
-      for (int i = tid; i < nbins; i += kSelThreads) hist[i] = 0u;
-      __syncthreads();
-      const uint32_t bmask = (uint32_t)(nbins - 1);
-      if (in_lds) {
-        for (uint32_t i = (uint32_t)tid; i < ncand; i += kSelThreads) {
-          const uint32_t b = cand[i];
-          if ((b & mask) == prefix) atomicAdd(&hist[(b >> shift) & bmask], 1u);
+  // The bin that rank k falls into: c[j] elements in the calling thread's bin number bin0 + j.
+  const auto find_bin = [&](const uint32_t (&c)[kBinsPerThread], uint32_t bin0, uint32_t k) {
+    uint32_t tot = 0u;
+#pragma unroll
+    for (int j = 0; j < kBinsPerThread; ++j) tot += c[j];
+    const uint32_t incl = wave_prefix_sum_u32(tot);
+    if (lane == kWave - 1) wave_tot[wave] = incl;
+    __syncthreads();
+    uint32_t first = incl - tot;  // elements in lower bins
+#pragma unroll
+    for (int w = 0; w < kSelWaves; ++w) first += w < wave ? wave_tot[w] : 0u;
+    if (k >= first && k < first + tot) {  // exactly one thread
+#pragma unroll
+      for (int j = 0; j < kBinsPerThread; ++j) {
+        if (k >= first && k < first + c[j]) {
+          sh_prefix = bin0 + j;
+          sh_k = k - first;
+          sh_in_bin = c[j];
         }
-      } else {
-        visit_row(bits, L, tid, [&](uint32_t b) {
-          if ((b & mask) == prefix) atomicAdd(&hist[(b >> shift) & bmask], 1u);
-        });
-      }
-      __syncthreads();
-      // workgroup-wide exclusive scan of the per-thread bin totals, in bin order
-      uint32_t c[kMaxPerThread], tot = 0u;
-#pragma unroll
-      for (int j = 0; j < kMaxPerThread; ++j) {
-        const int bin = tid * per_thread + j;
-        c[j] = (j < per_thread && bin < nbins) ? hist[bin] : 0u;
-        tot += c[j];
-      }
-      uint32_t incl = tot;
-#pragma unroll
-      for (int off = 1; off < kWave; off <<= 1) {
-        const uint32_t o = (uint32_t)__shfl_up((int)incl, off, kWave);
-        if (lane >= off) incl += o;
-      }
-      if (lane == kWave - 1) wave_tot[wave] = incl;
-      __syncthreads();
-      uint32_t before = incl - tot;
-      for (int w = 0; w < wave; ++w) before += wave_tot[w];
-      if (k >= before && k < before + tot) {  // exactly one thread: rank k falls into one of its bins
-#pragma unroll
-        for (int j = 0; j < kMaxPerThread; ++j) {
-          if (k >= before && k < before + c[j]) {
-            sh_prefix = prefix | ((uint32_t)(tid * per_thread + j) << shift);
-            sh_k = k - before;
-            sh_ncand = c[j];
-          }
-          before += c[j];
-        }
-      }
-      __syncthreads();
-      prefix = sh_prefix;
-      k = sh_k;
-      const uint32_t in_bin = sh_ncand;
-      mask |= bmask << shift;
-      __syncthreads();
-      if (pass == 0 && in_bin <= (uint32_t)kSelCand) {
-        // collect the tokens of the chosen bin in LDS (their order does not matter: only values are counted)
-        if (tid == 0) sh_ncand = 0u;
-        __syncthreads();
-        visit_row(bits, L, tid, [&](uint32_t b) {
-          if ((b & mask) == prefix) cand[atomicAdd(&sh_ncand, 1u)] = b;
-        });
-        __syncthreads();
-        ncand = sh_ncand;  // == in_bin
-        in_lds = true;
-        __syncthreads();
+        first += c[j];
       }
     }
+    __syncthreads();
+  };
+
+  // E == 0, nothing to evict: T = +0.0, q = 0 keeps every token (scores are >= +0)
+  uint32_t T = 0u, k = (uint32_t)(E > 0 ? E - 1 : 0);  // k: 0-based rank of the threshold among the remaining ones
+  if (E > 0) {
+    for (int i = tid; i < kSelBins * kSelCopies / 4; i += kSelThreads)
+      reinterpret_cast<uint4*>(hist)[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (tid == 0) sh_ncand = 0u;
+    __syncthreads();
+    const uint32_t copy = (uint32_t)lane % kSelCopies;
+    rs.visit([&](uint32_t b) { atomicAdd(&hist[(b >> 20) * kSelCopies + copy], 1u); });
+    __syncthreads();
+    uint32_t c[kBinsPerThread];
+#pragma unroll
+    for (int j = 0; j < kBinsPerThread; ++j) {
+      c[j] = 0u;
+#pragma unroll
+      for (int i = 0; i < kSelCopies; ++i) c[j] += hist[(tid * kBinsPerThread + j) * kSelCopies + i];
+    }
+    find_bin(c, (uint32_t)(tid * kBinsPerThread), k);
+    uint32_t prefix = sh_prefix << 20, mask = 0xfff00000u;
+    k = sh_k;
+    const bool in_lds = sh_in_bin <= (uint32_t)kSelCand;
+    const uint32_t ncand = sh_in_bin;
+    hist[tid] = 0u;  // the next digit's bins
+    if (in_lds) {  // collect the bin's tokens (their order does not matter: only values are counted)
+      // places for what the registers hold are taken once per wave: an atomic per score would be waited for each time
+      uint32_t mine = 0u;
+      rs.visit_held([&](uint32_t b) { mine += (b & mask) == prefix ? 1u : 0u; });
+      const uint32_t upto = wave_prefix_sum_u32(mine);
+      uint32_t at = 0u;
+      if (lane == kWave - 1) at = atomicAdd(&sh_ncand, upto);
+      at = (uint32_t)__builtin_amdgcn_readlane((int)at, kWave - 1) + upto - mine;
+      rs.visit_held([&](uint32_t b) {
+        if ((b & mask) == prefix) cand[at++] = b;
+      });
+      rs.visit_rest([&](uint32_t b) {
+        if ((b & mask) == prefix) cand[atomicAdd(&sh_ncand, 1u)] = b;
+      });
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int shift = 10; shift >= 0; shift -= 10) {
+      const auto count = [&](uint32_t b) {
+        if ((b & mask) == prefix) atomicAdd(&hist[(b >> shift) & 1023u], 1u);
+      };
+      if (in_lds) {
+        for (uint32_t i = (uint32_t)tid; i < ncand; i += kSelThreads) count(cand[i]);
+      } else {
+        rs.visit(count);
+      }
+      __syncthreads();
+      c[0] = hist[tid];
+#pragma unroll
+      for (int j = 1; j < kBinsPerThread; ++j) c[j] = 0u;
+      find_bin(c, (uint32_t)tid, k);
+      prefix |= sh_prefix << shift;
+      mask |= 1023u << shift;
+      k = sh_k;
+      hist[tid] = 0u;
+      __syncthreads();
+    }
+    T = prefix;  // threshold score (bit pattern)
   }
-  const uint32_t T = prefix;                         // threshold score (bit pattern)
   if (tid == 0) {
     sel[2 * row] = T;
     sel[2 * row + 1] = E > 0 ? k + 1 : 0u;           // q: the first q tokens (index order) with score == T go
   }
 
-  // per-chunk counts, one wave per chunk: 16 tokens per lane, all loads issued before the first compare
+  // Scores > T (lower half) and == T (upper half) per chunk, then how many there are before each chunk of the row.
   const int nchunks = (L + kChunk - 1) / kChunk;
-  int32_t* crow = cnt + ((int64_t)h * chunk_slots + chunk_slot(t0, s, 0)) * 2;
-  for (int c = wave; c < nchunks; c += kSelWaves) {
-    constexpr int kPerLane = kChunk / kWave;
-    uint32_t b[kPerLane];
+  int32_t* brow = before + ((int64_t)h * chunk_slots + chunk_slot(t0, s, 0)) * 2;
+  int gt_total = 0, eq_total = 0;  // of the pieces done
+  for (int c0 = 0; c0 < nchunks; c0 += kSelCand) {
+    const int nc = nchunks - c0 < kSelCand ? nchunks - c0 : kSelCand;
+    __syncthreads();
+    if (c0 == 0) {  // what the registers hold: a chunk is one vector of four waves
+      if (tid < kHeldChunks) cand[tid] = 0u;
+      __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kPerLane; ++j) {
-      const int i = c * kChunk + j * kWave + lane;
-      b[j] = bits[i < L ? i : L - 1];
-    }
-    int gt = 0, eq = 0;
+      for (int j = 0; j < NV; ++j) {
+        const int left = L - rs.index(j);
+        uint32_t n = 0u;
 #pragma unroll
-    for (int j = 0; j < kPerLane; ++j) {
-      const bool in = c * kChunk + j * kWave + lane < L;
-      gt += __popcll(__builtin_amdgcn_ballot_w64(in && b[j] > T));
-      eq += __popcll(__builtin_amdgcn_ballot_w64(in && b[j] == T));
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t b = rs.reg[j].v[e];
+          n += e < left ? (b > T ? 1u : 0u) + (b == T ? 0x10000u : 0u) : 0u;
+        }
+        n = wave_prefix_sum_u32(n);
+        if (lane == kWave - 1) atomicAdd(&cand[(j * kSelThreads + wave * kWave) * 4 / kChunk], n);
+      }
     }
-    if (lane == 0) {
-      crow[2 * c] = gt;
-      crow[2 * c + 1] = eq;
+    // beyond them, one wave per chunk: 16 tokens per lane, all loads issued before the first compare
+    for (int cc = (c0 == 0 ? kHeldChunks : 0) + wave; cc < nc; cc += kSelWaves) {
+      constexpr int kPerLane = kChunk / kWave;
+      const int i0 = (c0 + cc) * kChunk + lane;
+      uint32_t b[kPerLane], n = 0u;
+#pragma unroll
+      for (int j = 0; j < kPerLane; ++j) b[j] = rs.bits[i0 + j * kWave < L ? i0 + j * kWave : L - 1];
+#pragma unroll
+      for (int j = 0; j < kPerLane; ++j)
+        n += i0 + j * kWave < L ? (b[j] > T ? 1u : 0u) + (b[j] == T ? 0x10000u : 0u) : 0u;
+      n = wave_prefix_sum_u32(n);
+      if (lane == kWave - 1) cand[cc] = n;
+    }
+    __syncthreads();
+    if (wave == 0) {
+      for (int cc = 0; cc < nc; cc += kWave) {
+        const uint32_t n = cc + lane < nc ? cand[cc + lane] : 0u;
+        const int gt = (int)wave_prefix_sum_u32(n & 0xffffu), eq = (int)wave_prefix_sum_u32(n >> 16);
+        if (cc + lane < nc) {
+          const int2 v = make_int2(gt_total + gt - (int)(n & 0xffffu), eq_total + eq - (int)(n >> 16));
+          *reinterpret_cast<int2*>(brow + 2 * (c0 + cc + lane)) = v;
+        }
+        gt_total += __builtin_amdgcn_readlane(gt, kWave - 1);
+        eq_total += __builtin_amdgcn_readlane(eq, kWave - 1);
+      }
     }
   }
 }
 
-__device__ __forceinline__ int block_sum(int v, int* sh /* [kWaves] */) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, kWave);
-  const int wave = (int)(threadIdx.x / kWave);
-  __syncthreads();
-  if (lane_id() == 0) sh[wave] = v;
-  __syncthreads();
-  int t = 0;
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w) t += sh[w];
-  return t;
+// The smallest register holding that covers rows of max_seqlen tokens (or the largest there is).  A larger one than needed
+// costs its compare instructions on nothing; 64 scores a thread is what 1024 threads have registers for.
+using SelectKernel = void (*)(const float*, const int32_t*, uint32_t*, int32_t*, int32_t*, int32_t*, int64_t, int64_t, int, int);
+SelectKernel select_kernel_for(int max_seqlen) {
+  const int vecs = (max_seqlen + 4 * kSelThreads - 1) / (4 * kSelThreads);
+  if (vecs <= 1) return select_kernel<1>;
+  if (vecs <= 2) return select_kernel<2>;
+  if (vecs <= 4) return select_kernel<4>;
+  if (vecs <= 8) return select_kernel<8>;
+  return select_kernel<kSelMaxVecs>;
 }
 
 // ---- 3. gather ----------------------------------------------------------------------------------------
@@ -349,19 +438,20 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(const uint4* __restric
                                                           const float* __restrict__ scores,
                                                           const int32_t* __restrict__ cu_seqlens,
                                                           const uint32_t* __restrict__ sel,
-                                                          const int32_t* __restrict__ cnt,
+                                                          const int32_t* __restrict__ before,
                                                           const int32_t* __restrict__ block_table,
                                                           uint4* __restrict__ k_pool, uint4* __restrict__ v_pool,
                                                           int32_t* __restrict__ kept_idx_out, int64_t total_tokens,
-                                                          int64_t chunk_slots, int num_kv_heads, int chunks_per_row,
-                                                          int block_size, int max_blocks, int budget, int vpr_rt) {
-  __shared__ int sh[kWaves];
-  __shared__ int wave_off[kWaves][2];
-  __shared__ int32_t src_tok[kChunk];  // kept tokens of this chunk: in-sequence index
-  __shared__ int32_t dst_pos[kChunk];  // and their position in the pruned row
+                                                          int64_t chunk_slots, int num_kv_heads, int rows,
+                                                          int log2_block, int max_blocks, int budget, int vpr_rt) {
+  __shared__ uint32_t wave_sum[kWaves];
+  __shared__ int32_t src_tok[kChunk];  // kept tokens of this chunk, in order: in-sequence index
   __shared__ int n_kept_sh;
-  const int row = (int)(blockIdx.x / chunks_per_row);
-  const int chunk = (int)(blockIdx.x % chunks_per_row);
+  // Rows fastest: the first chunks of a ragged batch, which short sequences keep most of, spread over all XCDs (workgroup
+  // number % 8).  Chunks fastest put the first chunks of all sequences on one: 47 us instead of 30 for 16 sequences of
+  // 2048 to 16384 tokens, 8 heads, 1024 kept of each (134 MB moved; the other prompts below did not change).
+  const int row = (int)(blockIdx.x % (unsigned)rows);
+  const int chunk = (int)(blockIdx.x / (unsigned)rows);
   const int s = row / num_kv_heads, h = row % num_kv_heads;
   const int t0 = cu_seqlens[s];
   const int L = cu_seqlens[s + 1] - t0;
@@ -372,17 +462,9 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(const uint4* __restric
   const uint32_t T = sel[2 * row];
   const int q = (int)sel[2 * row + 1];
 
-  // counts of all earlier chunks of this row
-  int gt_before = 0, eq_before = 0;
-  {
-    const int32_t* c = cnt + ((int64_t)h * chunk_slots + chunk_slot(t0, s, 0)) * 2;
-    for (int cc = tid; cc < chunk; cc += kThreads) {
-      gt_before += c[2 * cc];
-      eq_before += c[2 * cc + 1];
-    }
-    gt_before = block_sum(gt_before, sh);
-    eq_before = block_sum(eq_before, sh);
-  }
+  // counts over all earlier chunks of this row
+  const int2 earlier = reinterpret_cast<const int2*>(before)[(int64_t)h * chunk_slots + chunk_slot(t0, s, chunk)];
+  const int gt_before = earlier.x, eq_before = earlier.y;
 
   // this thread's kTokPerThread consecutive tokens
   const uint32_t* bits = reinterpret_cast<const uint32_t*>(scores) + (int64_t)h * total_tokens + t0;
@@ -396,28 +478,16 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(const uint4* __restric
     n_gt += in && b[j] > T;
     n_eq += in && b[j] == T;
   }
-  // exclusive scan of (n_gt, n_eq) over the 256 threads, in thread (= index) order
-  int inc_gt = n_gt, inc_eq = n_eq;
-#pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const int a = __shfl_up(inc_gt, off, kWave);
-    const int c2 = __shfl_up(inc_eq, off, kWave);
-    if (lane >= off) {
-      inc_gt += a;
-      inc_eq += c2;
-    }
-  }
-  if (lane == kWave - 1) {
-    wave_off[wave][0] = inc_gt;
-    wave_off[wave][1] = inc_eq;
-  }
+  // exclusive scan of (n_gt, n_eq) over the 256 threads, in thread (= index) order; each fits 16 bits
+  const uint32_t n_both = (uint32_t)n_gt | ((uint32_t)n_eq << 16);
+  const uint32_t inc = wave_prefix_sum_u32(n_both);
+  if (lane == kWave - 1) wave_sum[wave] = inc;
   __syncthreads();
-  int ex_gt = inc_gt - n_gt + gt_before, ex_eq = inc_eq - n_eq + eq_before;
-  for (int w = 0; w < wave; ++w) {
-    ex_gt += wave_off[w][0];
-    ex_eq += wave_off[w][1];
-  }
-  // kept tokens before this chunk's start (needed to make dst relative positions dense in LDS)
+  uint32_t ex = inc - n_both;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) ex += w < wave ? wave_sum[w] : 0u;
+  int ex_gt = (int)(ex & 0xffffu) + gt_before, ex_eq = (int)(ex >> 16) + eq_before;
+  // kept tokens before this chunk's start: the chunk's kept tokens take consecutive positions from here
   const int kept_before_chunk = gt_before + (eq_before > q ? eq_before - q : 0);
 #pragma unroll
   for (int j = 0; j < kTokPerThread; ++j) {
@@ -427,9 +497,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(const uint4* __restric
     const bool kept = is_gt || (is_eq && ex_eq >= q);
     if (kept) {
       const int pos = ex_gt + (ex_eq > q ? ex_eq - q : 0);  // kept tokens before this one in the row
-      const int slot = pos - kept_before_chunk;
-      src_tok[slot] = i0 + j;
-      dst_pos[slot] = pos;
+      src_tok[pos - kept_before_chunk] = i0 + j;
     }
     ex_gt += is_gt;
     ex_eq += is_eq;
@@ -438,33 +506,32 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(const uint4* __restric
   __syncthreads();
   const int n_kept = n_kept_sh;
 
-  // copy the kept rows: VEC_PER_ROW lanes per token row, K and V
+  if (kept_idx_out != nullptr)  // consecutive positions: whole lines
+    for (int e = tid; e < n_kept; e += kThreads) kept_idx_out[(int64_t)row * budget + kept_before_chunk + e] = src_tok[e];
+
+  // copy the kept rows: VEC_PER_ROW lanes per token row, K and V (two or four rows of a thread in flight: no faster)
   const int32_t* bt = block_table + (int64_t)row * max_blocks;
+  const int block_mask = (1 << log2_block) - 1;
   if constexpr (VPR_T > 0) {
     constexpr int VEC_PER_ROW = VPR_T;
     constexpr int kRowsPerPass = kThreads / VEC_PER_ROW;
     const int u = tid % VEC_PER_ROW, r = tid / VEC_PER_ROW;
-    for (int base = 0; base < n_kept; base += kRowsPerPass) {
-      const int e = base + r;
-      if (e < n_kept) {
-        const int tok = src_tok[e], pos = dst_pos[e];
-        const int64_t src = ((int64_t)(t0 + tok) * num_kv_heads + h) * VEC_PER_ROW + u;
-        const int64_t dst = ((int64_t)bt[pos / block_size] * block_size + pos % block_size) * VEC_PER_ROW + u;
-        k_pool[dst] = k_in[src];
-        v_pool[dst] = v_in[src];
-        if (kept_idx_out != nullptr && u == 0) kept_idx_out[(int64_t)row * budget + pos] = tok;
-      }
+    for (int e = r; e < n_kept; e += kRowsPerPass) {
+      const int pos = kept_before_chunk + e;
+      const int64_t src = ((int64_t)(t0 + src_tok[e]) * num_kv_heads + h) * VEC_PER_ROW + u;
+      const int64_t dst = (((int64_t)bt[pos >> log2_block] << log2_block) + (pos & block_mask)) * VEC_PER_ROW + u;
+      k_pool[dst] = k_in[src];
+      v_pool[dst] = v_in[src];
     }
   } else {
     const int total_vecs = n_kept * vpr_rt;
     for (int f = tid; f < total_vecs; f += kThreads) {
       const int e = f / vpr_rt, u = f - e * vpr_rt;
-      const int tok = src_tok[e], pos = dst_pos[e];
+      const int tok = src_tok[e], pos = kept_before_chunk + e;
       const int64_t src = ((int64_t)(t0 + tok) * num_kv_heads + h) * vpr_rt + u;
-      const int64_t dst = ((int64_t)bt[pos / block_size] * block_size + pos % block_size) * vpr_rt + u;
+      const int64_t dst = (((int64_t)bt[pos >> log2_block] << log2_block) + (pos & block_mask)) * vpr_rt + u;
       k_pool[dst] = k_in[src];
       v_pool[dst] = v_in[src];
-      if (kept_idx_out != nullptr && u == 0) kept_idx_out[(int64_t)row * budget + pos] = tok;
     }
   }
 }
@@ -498,8 +565,8 @@ hipError_t launch(const PruneArgs& a, hipStream_t stream) {
     sel_scores = mean;
   }
   const int rows = a.num_seqs * heads;
-  hipLaunchKernelGGL(select_kernel, dim3((unsigned)rows), dim3(kSelThreads), 0, stream, sel_scores, a.cu_seqlens,
-                     w.sel, w.cnt, a.seq_lens_out, a.kept_idx_out, a.total_tokens, w.chunk_slots, heads, a.budget);
+  hipLaunchKernelGGL(select_kernel_for(a.max_seqlen), dim3((unsigned)rows), dim3(kSelThreads), 0, stream, sel_scores, a.cu_seqlens,
+                     w.sel, w.before, a.seq_lens_out, a.kept_idx_out, a.total_tokens, w.chunk_slots, heads, a.budget);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const int chunks_per_row = (a.max_seqlen + kChunk - 1) / kChunk;
   if (chunks_per_row == 0) return hipSuccess;
@@ -508,14 +575,14 @@ hipError_t launch(const PruneArgs& a, hipStream_t stream) {
   constexpr int VPR = G::kLanesPerRow;
   if (a.shared) {
     hipLaunchKernelGGL((gather_kernel<0>), dim3((unsigned)grid2), dim3(kThreads), 0, stream, (const uint4*)a.k_in,
-                       (const uint4*)a.v_in, sel_scores, a.cu_seqlens, w.sel, w.cnt, a.block_table, (uint4*)a.k_pool,
-                       (uint4*)a.v_pool, a.kept_idx_out, a.total_tokens, w.chunk_slots, heads, chunks_per_row,
-                       a.block_size, a.max_blocks, a.budget, VPR * a.num_kv_heads);
+                       (const uint4*)a.v_in, sel_scores, a.cu_seqlens, w.sel, w.before, a.block_table, (uint4*)a.k_pool,
+                       (uint4*)a.v_pool, a.kept_idx_out, a.total_tokens, w.chunk_slots, heads, rows,
+                       ilog2(a.block_size), a.max_blocks, a.budget, VPR * a.num_kv_heads);
   } else {
     hipLaunchKernelGGL((gather_kernel<VPR>), dim3((unsigned)grid2), dim3(kThreads), 0, stream, (const uint4*)a.k_in,
-                       (const uint4*)a.v_in, sel_scores, a.cu_seqlens, w.sel, w.cnt, a.block_table, (uint4*)a.k_pool,
-                       (uint4*)a.v_pool, a.kept_idx_out, a.total_tokens, w.chunk_slots, heads, chunks_per_row,
-                       a.block_size, a.max_blocks, a.budget, VPR);
+                       (const uint4*)a.v_in, sel_scores, a.cu_seqlens, w.sel, w.before, a.block_table, (uint4*)a.k_pool,
+                       (uint4*)a.v_pool, a.kept_idx_out, a.total_tokens, w.chunk_slots, heads, rows,
+                       ilog2(a.block_size), a.max_blocks, a.budget, VPR);
   }
   return hipGetLastError();
 }
