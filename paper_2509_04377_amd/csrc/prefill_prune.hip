@@ -157,20 +157,21 @@ __global__ __launch_bounds__(kThreads) void head_mean_kernel(const float* __rest
 // its scores again.  With the threshold known the same workgroup counts, per chunk of 1024 tokens, how many scores are
 // > T and how many == T: the gather turns these into destinations.
 // A row is worked on by one compute unit, and one compute unit pulls about 45 GB/s from L2 however many loads it keeps
-// in flight: that, not the histogram atomics, bounds the reading of a long row.  So it is read once, into registers (4*NV
-// scores a thread, NV by the longest row of the call), and every pass works from there; only what a row has beyond
-// 65536 tokens is read from memory in each pass.  Also kept out of the serial chain of a short row: cross-lane sums go
-// through DPP, the wave totals of a scan are read at once, places in the candidate list are taken once per wave, four
-// histograms share the atomics of the first digit.  Measured on an MI355X, before (every pass from memory, three more
-// barriers a pass) / now: 64 rows x 4096 scores 10.4 / 6.9 us, 128 ragged rows of up to 16384 13.4 / 11.2, 256 x 16384 17.6 / 14.3,
-// 32 x 65536 30.5 / 26.3.
+// in flight: that, not the histogram atomics, bounds the reading of a long row.  So up to 32768 scores of it are read once,
+// into registers (4*NV a thread, NV by the longest row of the call), and every pass works from there; only what a row has
+// beyond is read from memory in each pass (all 65536 in registers, 64 a thread, leave too few for the rest: 56 us).  Also
+// kept out of the serial chain of a short row: cross-lane sums go through DPP, the wave totals of a scan are read at once,
+// places in the candidate list are taken once per wave, two histograms share the atomics of the first digit.  Measured on
+// an MI355X, before (every pass from memory, three more barriers a pass) / now: 64 rows x 4096 scores 10.4 / 6.8 us, 128
+// ragged rows of up to 16384 13.7 / 11.3, 256 x 16384 17.7 / 14.4, 288 ragged rows of up to 6567 14.4 / 11.2 (15.2 with one
+// workgroup a compute unit), 2 x 44000 20.6 / 19.0, 32 x 65536 29.6 / 28.5.
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / kWave;
 constexpr int kSelBins = 4096;
 constexpr int kSelUnroll = 8;
 constexpr int kSelCand = 8192;  // candidates kept in LDS after the first pass (32 KiB)
-constexpr int kSelMaxVecs = 16;
-constexpr int kSelCopies = 4;
+constexpr int kSelMaxVecs = 8;
+constexpr int kSelCopies = 2;  // with the candidates 64 KiB: two workgroups fit a compute unit
 
 struct __attribute__((packed, aligned(4))) Unaligned4 {  // 16 bytes at any 4-byte boundary, in one load
   uint32_t v[4];
@@ -211,7 +212,7 @@ struct RowScores {
       if (4 * (j + 1) * kSelThreads <= L) {  // the same for all threads
 #pragma unroll
         for (int e = 0; e < 4; ++e) f(reg[j].v[e]);
-      } else {
+      } else if (4 * j * kSelThreads < L) {
         const int left = L - index(j);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -241,8 +242,10 @@ struct RowScores {
   }
 };
 
+// Two workgroups a compute unit (eight waves per SIMD, 64 registers) as long as the row leaves the registers for it: more
+// rows than compute units then still run at once.
 template <int NV>
-__global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __restrict__ scores,
+__global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(const float* __restrict__ scores,
                                                              const int32_t* __restrict__ cu_seqlens,
                                                              uint32_t* __restrict__ sel, int32_t* __restrict__ before,
                                                              int32_t* __restrict__ seq_lens_out,
@@ -378,6 +381,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
       __syncthreads();
 #pragma unroll
       for (int j = 0; j < NV; ++j) {
+        if (4 * j * kSelThreads >= L) break;
         const int left = L - rs.index(j);
         uint32_t n = 0u;
 #pragma unroll
@@ -418,15 +422,14 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
   }
 }
 
-// The smallest register holding that covers rows of max_seqlen tokens (or the largest there is).  A larger one than needed
-// costs its compare instructions on nothing; 64 scores a thread is what 1024 threads have registers for.
+// The smallest register holding that covers rows of max_seqlen tokens (or the largest there is): a larger one than needed
+// costs loads, branches and, beyond 16 scores a thread, the second workgroup of a compute unit.
 using SelectKernel = void (*)(const float*, const int32_t*, uint32_t*, int32_t*, int32_t*, int32_t*, int64_t, int64_t, int, int);
 SelectKernel select_kernel_for(int max_seqlen) {
   const int vecs = (max_seqlen + 4 * kSelThreads - 1) / (4 * kSelThreads);
   if (vecs <= 1) return select_kernel<1>;
   if (vecs <= 2) return select_kernel<2>;
   if (vecs <= 4) return select_kernel<4>;
-  if (vecs <= 8) return select_kernel<8>;
   return select_kernel<kSelMaxVecs>;
 }
 

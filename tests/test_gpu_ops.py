@@ -467,11 +467,11 @@ def test_prefill_prune_ties():
     assert np.array_equal(kept[0, 0], np.arange(2100 - 512, 2100))
 
 
-@pytest.mark.parametrize("lens", [[1, 4095, 3], [4096, 2, 4097], [6, 8191, 8193], [1, 16383, 16385], [32769, 5],
-                                  [65535, 7], [2, 65537], [1, 69633, 66000]])
+@pytest.mark.parametrize("lens", [[1, 4095, 3], [4096, 2, 4097], [6, 8191, 8193], [1, 16383, 16385], [2, 32768],
+                                  [32769, 5], [1, 33793, 32767], [3, 66000]])
 @pytest.mark.parametrize("crowded", [False, True])
 def test_prefill_prune_row_holding(lens, crowded):
-    """Rows at the edges of what the selection holds in registers (4096 * 1, 2, 4, 8, 16 scores) and beyond, starting
+    """Rows at the edges of what the selection holds in registers (4096 * 1, 2, 4, 8 scores) and beyond, starting
     at offsets that are not multiples of four scores; crowded: scores with so few distinct values that the threshold
     bin overflows the candidate list and many scores tie at the cut.  Integers and copies: bit for bit."""
     print("case prefill_prune_row_holding", lens, crowded, flush=True)
