@@ -63,25 +63,40 @@ int compute_units() {
   return n;
 }
 
+// Bytes of K and V of a row as long as its table row.
+int64_t row_bytes(const pe_cache_desc* d) {
+  return (int64_t)d->max_blocks * d->block_size * d->head_dim * (d->dtype == PE_BF16 ? 4 : 8);
+}
+
 // Number of splits of a row in the attention calls, chosen from the shape (a row is taken to be as long as its table row).
-// Just enough to give every compute unit a workgroup, and none shorter than 128 tokens: a launch streams best with one
-// workgroup per compute unit, and splits cost a second launch that merges them (2.2 to 2.7 us).  From there
-//   - one, where two would do and a row holds at most 512 KiB of K and V: half of the compute units stream that
-//     much in less than the merge takes (128 rows x 1024 tokens of bf16, D = 128: 15.6 us whole, 16.9 in two splits);
-//   - twice as many, where pieces of 1 MiB remain: rows of unequal length then fill the chip more evenly (192 rows of
-//     up to 8192 tokens: ragged 87 us in two splits, 72 in four; all 8192 long 130 and 128; 128 such rows 55 and 53, 85 and 86).
+// As many as the compute units have room for with one workgroup each, none shorter than 128 tokens, and none at all of
+// rows under 512 tokens (8 rows x 1000 tokens: three splits 9.1 us, seven 7.2; 16 rows x 512: two 8.0, four 7.0; 8 rows of
+// 228 are through before a second launch is issued: 8.7 whole, 12.7 in two).  One workgroup too many is much worse than
+// some too few: it shares its compute unit's part of the memory with another one while the rest of the chip runs dry (90 rows x 2080 tokens of bf16, D = 128: two splits 19.7 us, three 25.3; 18 rows x 5952: 14 splits 15.4,
+// 15 19.1; 160 rows x 2048: one 27.8, two 35.0, three 30.9; 192 rows 32.1 / 36.8 / 39.1).  From there
+//   - one, where two would do, nearly half of the compute units have a row and a row holds at most 512 KiB: they stream
+//     that in less than the second launch takes that merges splits (2.2 to 2.7 us; 128 rows x 1024 14.4 us whole, 15.4 in
+//     two; 96 rows 13.7 and 13.0);
+//   - four or twice as many, where pieces of 1 MiB remain: rows of unequal length fill the chip more evenly (192 rows of up
+//     to 8192 tokens, ragged: 88 us whole, 72 in four; all full 120 and 128; 128 such rows 55 in two and 53 in four, full
+//     85 and 86);
+//   - four, for somewhat more rows than compute units: whole, they would leave most of the chip idle for the second half
+//     (264 / 288 / 320 rows x 2048: 59 / 60 / 62 us whole, 50 / 52 / 57 in four; 384 rows 64 and 67).
 int decode_splits(const pe_cache_desc* d) {
   if (d->decode_splits > 0) return d->decode_splits;
   const int64_t rows = (int64_t)d->num_seqs * d->num_kv_heads;
-  const int64_t max_tokens = (int64_t)d->max_blocks * d->block_size;
-  const int64_t row_bytes = max_tokens * d->head_dim * (d->dtype == PE_BF16 ? 4 : 8);
-  const int64_t by_rows = (compute_units() + rows - 1) / rows;
-  const int64_t by_len = max_tokens / 128 > 1 ? max_tokens / 128 : 1;
-  int64_t splits = by_rows < by_len ? by_rows : by_len;
-  if (splits == 2 && row_bytes <= (512 << 10)) splits = 1;
-  if (by_rows > 1 && row_bytes / (2 * by_rows) >= (1 << 20)) splits = 2 * by_rows;
+  const int64_t cus = compute_units();
+  const int64_t bytes = row_bytes(d);
+  if (rows > cus) return rows * 10 <= cus * 13 && bytes >= (512 << 10) ? 4 : 1;
+  const int64_t fit = cus / rows;
+  const int64_t tokens = (int64_t)d->max_blocks * d->block_size;
+  const int64_t by_len = tokens < 512 ? 1 : tokens / 128;
+  int64_t splits = fit < by_len ? fit : by_len;
+  if (splits == 2 && rows * 16 >= cus * 7 && bytes <= (512 << 10)) splits = 1;
+  const int64_t finer = fit == 1 ? 4 : 2 * fit;
+  if (rows < cus && bytes / finer >= (1 << 20)) splits = finer;
   if (splits > 64) splits = 64;
-  return (int)splits;
+  return splits < 1 ? 1 : (int)splits;
 }
 
 // The count that a caller's buffer of `have` bytes allows: the library's own choice may fall back to one workgroup per
@@ -117,19 +132,24 @@ pe::DecodeArgs decode_args(const pe_cache_desc* desc, int splits) {
   a.max_blocks = desc->max_blocks;
   a.splits = splits;
   a.xcd_map = desc->decode_flat_order ? 0 : 1;
-  // bfloat16 kernel: four waves a workgroup and two tiles in flight per wave.  Where rows of D = 128 give every compute
-  // unit a workgroup: eight waves (more bytes in flight against the latency of pages scattered over a large pool; with
-  // fewer workgroups, or a tile half as large, the longer prologue and merge cost as much as they gain), but in the
-  // head-shared layout, whose wave-loads are runs of 256 bytes, four and a single tile.  Measured on an MI355X, four / eight
-  // waves: 256 rows x 2048 tokens of D = 128 out of an 8.6 GB pool 44.5 / 44.0 us (head-shared 47.2 / 47.1, one tile 45.6),
-  // 192 ragged rows in 768 splits 72.3 / 68.9, 1024 ragged rows 101.5 / 95.5; 64 rows x 1024 of D = 64 in 256 splits
-  // 8.5 / 8.75.
+  // bfloat16 kernel: four waves a workgroup and two tiles in flight per wave.  Where rows of D = 128 give the chip enough
+  // workgroups (measured on an MI355X):
+  //   - eight waves, if a workgroup has 1 MiB or more to read: more bytes in flight against the latency of pages that lie
+  //     scattered over a large pool (256 rows x 2048 tokens out of 8.6 GB 44.5 us with four, 44.0 with eight; 192 ragged rows
+  //     in 768 splits 72.3 and 68.9, with eight query heads 79 and 72; but 288 rows x 512 18.0 and 19.2, and 256 splits of
+  //     256 tokens of D = 64 8.5 and 8.75);
+  //   - in the head-shared layout, whose wave-loads are runs of 256 bytes, four waves with a single tile instead (47.2 us
+  //     with two, 47.1 with eight waves, 45.6);
+  //   - a single tile too for splits of less than 512 KiB (33 rows x 4800 tokens in seven 18.5 and 17.7).
   const int64_t groups = (int64_t)desc->num_seqs * desc->num_kv_heads * splits;
-  const bool full = desc->head_dim == 128 && groups >= compute_units();
+  const int64_t piece = row_bytes(desc) / splits;
   const bool shared = desc->layout == PE_LAYOUT_SHARED;
-  a.waves = full && !shared ? 8 : 4;
-  a.depth = full && shared ? 1 : 2;
-  if (desc->decode_shape == 424 || desc->decode_shape == 432) a.waves = 4;
+  const bool d128 = desc->head_dim == 128;
+  const bool large = d128 && groups >= compute_units() && piece >= (1 << 20);
+  const bool small = d128 && groups * 4 >= (int64_t)compute_units() * 3 && splits > 1 && piece < (512 << 10);
+  a.waves = large && !shared ? 8 : 4;
+  a.depth = (large && shared) || small ? 1 : 2;
+  if (desc->decode_shape == 424 || desc->decode_shape == 432) a.waves = 4, a.depth = 2;
   if (desc->decode_shape == 822) a.waves = 8;
   a.is_bf16 = desc->dtype == PE_BF16;
   a.shared = shared;
