@@ -296,8 +296,8 @@ int pe_append_kv(const pe_cache_desc* desc, const void* new_k, const void* new_v
  * to seq_lens_out [S], which must not alias seq_lens (callers keep two arrays and swap them), so that no
  * workgroup of the launch can observe a length that another one has already bumped.
  * workspace: pe_workspace_bytes(PE_OP_APPEND_PAGED_DECODE, desc, 0).
- * shared: same contract and shapes as pe_append_kv / pe_paged_decode in that layout, carried out as two launches
- * (one workgroup per sequence does the page bookkeeping for all heads before the attention reads it).
+ * shared: same contract and shapes as pe_append_kv / pe_paged_decode in that layout (fp32: carried out as two launches, the
+ * append before the attention).
  */
 int pe_append_paged_decode(const pe_cache_desc* desc, const void* new_k, const void* new_v, const void* q,
                            void* k_pool, void* v_pool, int32_t* block_table, const int32_t* seq_lens,

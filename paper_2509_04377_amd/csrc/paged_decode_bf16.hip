@@ -41,7 +41,8 @@
 // length that another one has already bumped.
 //
 // SHARED reads the head-shared cache layout: one table row per sequence and pages of [B][Hk][D], so the token rows of
-// this workgroup's head are Hk rows apart.
+// this workgroup's head are Hk rows apart.  (FUSED there took the place of an append launch in front of the attention:
+// 32 sequences x 8 heads x 2048 tokens 45.7 us a layer in two launches, 43.6 in one; 8 x 4 x 2304 13.9 and 11.1.)
 #include "pe_device.h"
 #include "pe_launch.h"
 
@@ -206,7 +207,6 @@ template <int D, int HG, int WAVES, int DEPTH, bool FUSED, bool SHARED>
 // (the 2 asks for two waves per SIMD at least, i.e. at most 256 registers: the compiler then keeps the accumulators in
 // vector registers instead of moving them to and from accumulation registers in every step)
 __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(const Params p) {
-  static_assert(!(FUSED && SHARED), "the fused append is per-head only");
   using TL = Tile<D, HG>;
   constexpr int LPR = TL::LPR, TPL = TL::TPL, NL = TL::NL, NT = TL::NT;
   constexpr int GH = 4 * HG;  // heads computed; p.g_real of them exist
@@ -232,7 +232,8 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(con
   }
   const int s = row / p.num_kv_heads;
   const int hk = row % p.num_kv_heads;
-  const int32_t* bt = p.block_table + (int64_t)(SHARED ? s : row) * p.max_blocks;
+  const int table_row = SHARED ? s : row;
+  const int32_t* bt = p.block_table + (int64_t)table_row * p.max_blocks;
 
   TL tl;
   tl.k_pool = static_cast<const u32x4_t*>(p.k_pool);
@@ -282,8 +283,8 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(con
   if constexpr (FUSED) {
     nk = static_cast<const u32x4_t*>(p.new_k)[(int64_t)row * LPR + k_slice];
     nv = static_cast<const u32x4_t*>(p.new_v)[(int64_t)row * LPR + v_slice];
-    ap_freed = p.freed_phys[row];
-    ap_used = p.spare_used[row];
+    ap_freed = p.freed_phys[table_row];
+    ap_used = p.spare_used[table_row];
   }
   int ap_page = -1;  // the tail page, where it is not full
   if constexpr (FUSED) {
@@ -439,24 +440,37 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(con
       const int slot = len_pool & (B - 1);
       const int jb = len_pool >> p.log2_block;
       if (len_pool >= 0 && jb < p.max_blocks) {  // a length outside the table row is a caller error: touch nothing
-        int page;
-        if (slot == 0) {
+        // head-shared: a page that has to be linked first is head 0's to link and to fill for all heads, so that no
+        // workgroup has to learn from another one which page it is
+        const bool link = slot == 0;
+        int page = ap_page;
+        if (link) {
           page = ap_freed;
-          if (page < 0) {
-            page = ap_used < p.n_spare ? p.spare[(int64_t)row * p.n_spare + ap_used] : -1;
-            if (lane == 0) p.spare_used[row] = ap_used + 1;
-          } else if (lane == 0) {
-            p.freed_phys[row] = -1;
+          if (!SHARED || hk == 0) {
+            if (page < 0) {
+              page = ap_used < p.n_spare ? p.spare[(int64_t)table_row * p.n_spare + ap_used] : -1;
+              if (lane == 0) p.spare_used[table_row] = ap_used + 1;
+            } else if (lane == 0) {
+              p.freed_phys[table_row] = -1;
+            }
+            if (lane == 0) const_cast<int32_t*>(bt)[jb] = page;
           }
-          if (lane == 0) const_cast<int32_t*>(bt)[jb] = page;
-        } else {
-          page = ap_page;
         }
-        if (page >= 0) {
-          const int64_t vec = (((int64_t)page << p.log2_block) + slot) * LPR;
+        u32x4_t* k_pool = static_cast<u32x4_t*>(const_cast<void*>(p.k_pool));
+        u32x4_t* v_pool = static_cast<u32x4_t*>(const_cast<void*>(p.v_pool));
+        if (SHARED && link) {
+          if (hk == 0 && page >= 0) {
+            const int64_t to = ((int64_t)page << p.log2_block) * tl.row_vecs, from = (int64_t)s * tl.row_vecs;
+            for (int i = lane; i < tl.row_vecs; i += kWave) {
+              k_pool[to + i] = static_cast<const u32x4_t*>(p.new_k)[from + i];
+              v_pool[to + i] = static_cast<const u32x4_t*>(p.new_v)[from + i];
+            }
+          }
+        } else if (page >= 0) {
+          const int64_t base = (((int64_t)page << p.log2_block) + slot) * tl.row_vecs + (SHARED ? hk * LPR : 0);
           // the lanes of the first token row of a wave-load hold the whole row between them
-          if (tl.k_tok == 0) static_cast<u32x4_t*>(const_cast<void*>(p.k_pool))[vec + k_slice] = nk;
-          if (tl.v_tok == 0) static_cast<u32x4_t*>(const_cast<void*>(p.v_pool))[vec + v_slice] = nv;
+          if (tl.k_tok == 0) k_pool[base + k_slice] = nk;
+          if (tl.v_tok == 0) v_pool[base + v_slice] = nv;
         }
       }
       if (hk == 0 && lane == 0) p.seq_lens_out[s] = len_pool + 1;
@@ -493,10 +507,12 @@ hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
   const int64_t grid = rows * a.splits;
   if (grid <= 0 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
   const dim3 blocks((unsigned)grid), threads(WAVES * kWave);
-  if (a.shared) {
-    if (a.new_k != nullptr) return hipErrorInvalidValue;
+  const bool fused = a.new_k != nullptr;
+  if (a.shared && fused) {
+    hipLaunchKernelGGL((paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, true, true>), blocks, threads, 0, stream, p);
+  } else if (a.shared) {
     hipLaunchKernelGGL((paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, false, true>), blocks, threads, 0, stream, p);
-  } else if (a.new_k != nullptr) {
+  } else if (fused) {
     hipLaunchKernelGGL((paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, true, false>), blocks, threads, 0, stream, p);
   } else {
     hipLaunchKernelGGL((paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, false, false>), blocks, threads, 0, stream, p);

@@ -491,10 +491,10 @@ int pe_append_paged_decode(const pe_cache_desc* desc, const void* new_k, const v
   a.spare_used = spare_used;
   a.seq_lens_out = seq_lens_out;
   a.n_spare = n_spare;
-  if (desc->layout == PE_LAYOUT_SHARED) {
-    // One table row per sequence: the workgroups of a sequence's heads would race on its page bookkeeping
-    // inside one launch, so the same effect is produced by two launches (append, then attention over the
-    // new lengths).
+  if (desc->layout == PE_LAYOUT_SHARED && desc->dtype == PE_F32) {
+    // One table row per sequence: the workgroups of a sequence's heads would race on its page bookkeeping inside one
+    // launch of the fp32 kernel, so the same effect is produced by two launches (append, then attention over the new
+    // lengths).
     pe::AppendArgs ap;
     ap.new_k = new_k;
     ap.new_v = new_v;

@@ -87,7 +87,7 @@ struct DecodeArgs {
   int32_t* spare_used = nullptr;
   int32_t* seq_lens_out = nullptr;
   int n_spare = 0;
-  bool shared = false;  // one table row per sequence, pages [B][Hk][D]; plain attention only
+  bool shared = false;  // one table row per sequence, pages [B][Hk][D]; with fp32 plain attention only
 };
 hipError_t launch_paged_decode(const DecodeArgs& a, hipStream_t stream);
 hipError_t launch_paged_decode_bf16(const DecodeArgs& a, hipStream_t stream);  // the attention kernel alone (no merge)

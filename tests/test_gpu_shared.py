@@ -164,6 +164,47 @@ def test_shared_append(dt, D, B, Hk):
         assert np.array_equal(f32(vd).view(np.int32), o["v"].view(np.int32))
 
 
+@pytest.mark.parametrize("dt,D,B,Hk,G", [("bf16", 128, 16, 8, 4), ("bf16", 64, 16, 3, 2), ("bf16", 128, 32, 2, 8),
+                                         ("bf16", 64, 128, 5, 1), ("f32", 64, 32, 3, 2)])
+def test_shared_append_paged_decode(dt, D, B, Hk, G):
+    """The combined call against append then attention of the oracle: first, middle and last slots
+    of a page, pages taken from the eviction just before and from the spare list."""
+    print("case shared append_paged_decode", dt, D, B, Hk, G, flush=True)
+    lens = [0, 1, B - 2, B - 1, B, 2 * B, 5 * B + 3, 7 * B - 1, 40 * B - 1]
+    k, v, table, sl = make_shared(850 + D + B, lens, Hk, D, B, DTYPES[dt], extra=2, pad=40)
+    S, mb = table.shape
+    P = k.shape[0]
+    n_spare = 2
+    free = sorted(set(range(P)) - set(int(x) for x in table.flatten() if x >= 0))
+    spare = torch.tensor(free[:S * n_spare], dtype=torch.int32).reshape(S, n_spare)
+    freed = torch.full((S,), -1, dtype=torch.int32)
+    freed[4] = free[S * n_spare]            # sequence 4 sits at a page boundary and holds a freed page
+    used = torch.zeros((S,), dtype=torch.int32)
+    used[5] = n_spare - 1                   # sequence 5 too, and takes the last of its spare pages
+    o = dict(k=f32(k).copy(), v=f32(v).copy(), t=i32(table).copy(), l=i32(sl).copy(), f=i32(freed).copy(),
+             u=i32(used).copy())
+    kd, vd, td, ld, fd, ud, sd = (x.to(DEV) for x in (k, v, table, sl, freed, used, spare))
+    g = torch.Generator().manual_seed(851)
+    for step, splits in enumerate((0, 1, 3)):
+        desc = _desc(DTYPES[dt], S, Hk, Hk * G, D, B, mb, P)
+        desc.decode_splits = splits
+        nk, nv = (torch.randn((S, Hk, D), generator=g).to(DTYPES[dt]) for _ in range(2))
+        q = torch.randn((S, Hk * G, D), generator=g).to(DTYPES[dt])
+        osh.append_kv(f32(nk), f32(nv), o["k"], o["v"], o["t"], o["l"], o["f"], i32(spare), o["u"])
+        want = osh.paged_decode(f32(q), o["k"], o["v"], o["t"], o["l"])
+        lens_out, out = torch.full_like(ld, -5), torch.full(q.shape, 7.0, dtype=DTYPES[dt], device=DEV)
+        pe.pe_append_paged_decode(desc, nk.to(DEV), nv.to(DEV), q.to(DEV), kd, vd, td, ld, lens_out, fd, sd, ud,
+                                  D ** -0.5, out, pe.alloc_workspace(pe.PE_OP_APPEND_PAGED_DECODE, desc))
+        torch.cuda.synchronize()
+        ld = lens_out
+        for name, t in (("t", td), ("l", ld), ("f", fd), ("u", ud)):
+            assert np.array_equal(t.cpu().numpy(), o[name]), (step, name)
+        assert np.array_equal(f32(kd).view(np.int32), o["k"].view(np.int32))
+        assert np.array_equal(f32(vd).view(np.int32), o["v"].view(np.int32))
+        e2, emax = rel_err(f32(out), want)
+        assert e2 <= TOL[dt] and emax <= TOL[dt], (step, e2, emax)
+
+
 def _prompt(seed, lens, Hk, D, dtype, ties=False):
     g = torch.Generator().manual_seed(seed)
     T = sum(lens)
