@@ -151,6 +151,32 @@ def ws_args(workspace):
     return ctypes.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size()
 
 
+# What the calls below pass: the checks of ptr() and the values of stream_arg() and ws_args(), as plain numbers.  A small
+# launch is over sooner than its arguments are put together (5 us against 13), and of those the stream object and a
+# ctypes object per pointer were the larger half; ctypes converts numbers by the declared argument types.
+def _addr(t, name, dtype=None):
+    if t is not None and t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype is dtype):
+        return t.data_ptr()
+    return ptr(t, name, dtype).value   # raises what is wrong
+
+
+def _addr_opt(t, name, dtype=None):
+    return None if t is None else _addr(t, name, dtype)
+
+
+def _ws(workspace):
+    return (None, 0) if workspace is None else (workspace.data_ptr(), workspace.nbytes)
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream():
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
+
+
 def pe_workspace_bytes(op: int, desc: pe_cache_desc, total_tokens: int = 0) -> int:
     return int(lib().pe_workspace_bytes(int(op), ctypes.byref(desc), int(total_tokens)))
 
@@ -164,121 +190,121 @@ def alloc_workspace(op: int, desc: pe_cache_desc, total_tokens: int = 0, device=
 
 
 def pe_score_blocks(desc, k_pool, v_pool, block_table, seq_lens, scores_out, workspace=None):
-    wp, wn = ws_args(workspace)
-    check(lib().pe_score_blocks(ctypes.byref(desc), ptr(k_pool, "k_pool"), ptr(v_pool, "v_pool"),
-                                 ptr(block_table, "block_table", torch.int32), ptr(seq_lens, "seq_lens", torch.int32),
-                                 ptr(scores_out, "scores_out", torch.float32), wp, wn, stream_arg()), "pe_score_blocks")
+    wp, wn = _ws(workspace)
+    check(lib().pe_score_blocks(ctypes.byref(desc), _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
+                                 _addr(block_table, "block_table", torch.int32), _addr(seq_lens, "seq_lens", torch.int32),
+                                 _addr(scores_out, "scores_out", torch.float32), wp, wn, _stream()), "pe_score_blocks")
 
 
 def pe_prefill_prune(desc, k_in, v_in, cu_seqlens, total_tokens, max_seqlen, budget_tokens, k_pool, v_pool,
                      block_table, seq_lens_out, kept_idx_out, workspace):
-    wp, wn = ws_args(workspace)
-    check(lib().pe_prefill_prune(ctypes.byref(desc), ptr(k_in, "k_in"), ptr(v_in, "v_in"),
-                                  ptr(cu_seqlens, "cu_seqlens", torch.int32), int(total_tokens), int(max_seqlen),
-                                  int(budget_tokens), ptr(k_pool, "k_pool"), ptr(v_pool, "v_pool"),
-                                  ptr(block_table, "block_table", torch.int32),
-                                  ptr(seq_lens_out, "seq_lens_out", torch.int32),
-                                  ptr(kept_idx_out, "kept_idx_out", torch.int32, optional=True), wp, wn, stream_arg()),
+    wp, wn = _ws(workspace)
+    check(lib().pe_prefill_prune(ctypes.byref(desc), _addr(k_in, "k_in"), _addr(v_in, "v_in"),
+                                  _addr(cu_seqlens, "cu_seqlens", torch.int32), int(total_tokens), int(max_seqlen),
+                                  int(budget_tokens), _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
+                                  _addr(block_table, "block_table", torch.int32),
+                                  _addr(seq_lens_out, "seq_lens_out", torch.int32),
+                                  _addr_opt(kept_idx_out, "kept_idx_out", torch.int32), wp, wn, _stream()),
            "pe_prefill_prune")
 
 
 def pe_evict_blocks(desc, scores, block_table, seq_lens, budget_tokens, evicted_logical_out, freed_phys_out):
-    check(lib().pe_evict_blocks(ctypes.byref(desc), ptr(scores, "scores", torch.float32),
-                                 ptr(block_table, "block_table", torch.int32), ptr(seq_lens, "seq_lens", torch.int32),
-                                 int(budget_tokens), ptr(evicted_logical_out, "evicted_logical_out", torch.int32),
-                                 ptr(freed_phys_out, "freed_phys_out", torch.int32), stream_arg()), "pe_evict_blocks")
+    check(lib().pe_evict_blocks(ctypes.byref(desc), _addr(scores, "scores", torch.float32),
+                                 _addr(block_table, "block_table", torch.int32), _addr(seq_lens, "seq_lens", torch.int32),
+                                 int(budget_tokens), _addr(evicted_logical_out, "evicted_logical_out", torch.int32),
+                                 _addr(freed_phys_out, "freed_phys_out", torch.int32), _stream()), "pe_evict_blocks")
 
 
 def pe_score_triggered_blocks(desc, k_pool, v_pool, block_table, seq_lens, budget_tokens, scores_inout):
-    check(lib().pe_score_triggered_blocks(ctypes.byref(desc), ptr(k_pool, "k_pool"), ptr(v_pool, "v_pool"),
-                                           ptr(block_table, "block_table", torch.int32),
-                                           ptr(seq_lens, "seq_lens", torch.int32), int(budget_tokens),
-                                           ptr(scores_inout, "scores_inout", torch.float32), stream_arg()),
+    check(lib().pe_score_triggered_blocks(ctypes.byref(desc), _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
+                                           _addr(block_table, "block_table", torch.int32),
+                                           _addr(seq_lens, "seq_lens", torch.int32), int(budget_tokens),
+                                           _addr(scores_inout, "scores_inout", torch.float32), _stream()),
            "pe_score_triggered_blocks")
 
 
 def pe_score_evict(desc, k_pool, v_pool, block_table, seq_lens, budget_tokens, scores_out, evicted_logical_out,
                    freed_phys_out):
-    check(lib().pe_score_evict(ctypes.byref(desc), ptr(k_pool, "k_pool"), ptr(v_pool, "v_pool"),
-                                ptr(block_table, "block_table", torch.int32), ptr(seq_lens, "seq_lens", torch.int32),
-                                int(budget_tokens), ptr(scores_out, "scores_out", torch.float32, optional=True),
-                                ptr(evicted_logical_out, "evicted_logical_out", torch.int32),
-                                ptr(freed_phys_out, "freed_phys_out", torch.int32), stream_arg()), "pe_score_evict")
+    check(lib().pe_score_evict(ctypes.byref(desc), _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
+                                _addr(block_table, "block_table", torch.int32), _addr(seq_lens, "seq_lens", torch.int32),
+                                int(budget_tokens), _addr_opt(scores_out, "scores_out", torch.float32),
+                                _addr(evicted_logical_out, "evicted_logical_out", torch.int32),
+                                _addr(freed_phys_out, "freed_phys_out", torch.int32), _stream()), "pe_score_evict")
 
 
 def pe_score_recent_blocks(desc, k_pool, v_pool, block_table, seq_lens, recent, scores_inout):
-    check(lib().pe_score_recent_blocks(ctypes.byref(desc), ptr(k_pool, "k_pool"), ptr(v_pool, "v_pool"),
-                                        ptr(block_table, "block_table", torch.int32),
-                                        ptr(seq_lens, "seq_lens", torch.int32), int(recent),
-                                        ptr(scores_inout, "scores_inout", torch.float32), stream_arg()),
+    check(lib().pe_score_recent_blocks(ctypes.byref(desc), _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
+                                        _addr(block_table, "block_table", torch.int32),
+                                        _addr(seq_lens, "seq_lens", torch.int32), int(recent),
+                                        _addr(scores_inout, "scores_inout", torch.float32), _stream()),
            "pe_score_recent_blocks")
 
 
 def pe_evict_blocks_cached(desc, scores_inout, block_table, seq_lens, budget_tokens, evicted_logical_out,
                            freed_phys_out):
-    check(lib().pe_evict_blocks_cached(ctypes.byref(desc), ptr(scores_inout, "scores_inout", torch.float32),
-                                        ptr(block_table, "block_table", torch.int32),
-                                        ptr(seq_lens, "seq_lens", torch.int32), int(budget_tokens),
-                                        ptr(evicted_logical_out, "evicted_logical_out", torch.int32),
-                                        ptr(freed_phys_out, "freed_phys_out", torch.int32), stream_arg()),
+    check(lib().pe_evict_blocks_cached(ctypes.byref(desc), _addr(scores_inout, "scores_inout", torch.float32),
+                                        _addr(block_table, "block_table", torch.int32),
+                                        _addr(seq_lens, "seq_lens", torch.int32), int(budget_tokens),
+                                        _addr(evicted_logical_out, "evicted_logical_out", torch.int32),
+                                        _addr(freed_phys_out, "freed_phys_out", torch.int32), _stream()),
            "pe_evict_blocks_cached")
 
 
 def pe_evict_blocks_ex(desc, opts, scores, block_table, seq_lens, budget_tokens, evicted_logical_out, freed_phys_out):
     check(lib().pe_evict_blocks_ex(ctypes.byref(desc), ctypes.byref(opts),
-                                    ptr(scores, "scores", torch.float32, optional=True),
-                                    ptr(block_table, "block_table", torch.int32),
-                                    ptr(seq_lens, "seq_lens", torch.int32), int(budget_tokens),
-                                    ptr(evicted_logical_out, "evicted_logical_out", torch.int32),
-                                    ptr(freed_phys_out, "freed_phys_out", torch.int32), stream_arg()),
+                                    _addr_opt(scores, "scores", torch.float32),
+                                    _addr(block_table, "block_table", torch.int32),
+                                    _addr(seq_lens, "seq_lens", torch.int32), int(budget_tokens),
+                                    _addr(evicted_logical_out, "evicted_logical_out", torch.int32),
+                                    _addr(freed_phys_out, "freed_phys_out", torch.int32), _stream()),
            "pe_evict_blocks_ex")
 
 
 def pe_paged_decode(desc, q, k_pool, v_pool, block_table, seq_lens, softmax_scale, out, workspace=None):
-    wp, wn = ws_args(workspace)
-    check(lib().pe_paged_decode(ctypes.byref(desc), ptr(q, "q"), ptr(k_pool, "k_pool"), ptr(v_pool, "v_pool"),
-                                 ptr(block_table, "block_table", torch.int32), ptr(seq_lens, "seq_lens", torch.int32),
-                                 ctypes.c_float(softmax_scale), ptr(out, "out"), wp, wn, stream_arg()), "pe_paged_decode")
+    wp, wn = _ws(workspace)
+    check(lib().pe_paged_decode(ctypes.byref(desc), _addr(q, "q"), _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
+                                 _addr(block_table, "block_table", torch.int32), _addr(seq_lens, "seq_lens", torch.int32),
+                                 float(softmax_scale), _addr(out, "out"), wp, wn, _stream()), "pe_paged_decode")
 
 
 def pe_paged_decode_static(desc, q, k_pool, v_pool, block_table, seq_lens, softmax_scale, out):
-    check(lib().pe_paged_decode_static(ctypes.byref(desc), ptr(q, "q"), ptr(k_pool, "k_pool"), ptr(v_pool, "v_pool"),
-                                       ptr(block_table, "block_table", torch.int32),
-                                       ptr(seq_lens, "seq_lens", torch.int32), ctypes.c_float(softmax_scale),
-                                       ptr(out, "out"), stream_arg()), "pe_paged_decode_static")
+    check(lib().pe_paged_decode_static(ctypes.byref(desc), _addr(q, "q"), _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
+                                       _addr(block_table, "block_table", torch.int32),
+                                       _addr(seq_lens, "seq_lens", torch.int32), float(softmax_scale),
+                                       _addr(out, "out"), _stream()), "pe_paged_decode_static")
 
 
 def pe_append_kv(desc, new_k, new_v, k_pool, v_pool, block_table, seq_lens, freed_phys, spare, spare_used):
-    check(lib().pe_append_kv(ctypes.byref(desc), ptr(new_k, "new_k"), ptr(new_v, "new_v"), ptr(k_pool, "k_pool"),
-                              ptr(v_pool, "v_pool"), ptr(block_table, "block_table", torch.int32),
-                              ptr(seq_lens, "seq_lens", torch.int32), ptr(freed_phys, "freed_phys", torch.int32),
-                              ptr(spare, "spare", torch.int32), ptr(spare_used, "spare_used", torch.int32),
-                              int(spare.shape[-1]), stream_arg()), "pe_append_kv")
+    check(lib().pe_append_kv(ctypes.byref(desc), _addr(new_k, "new_k"), _addr(new_v, "new_v"), _addr(k_pool, "k_pool"),
+                              _addr(v_pool, "v_pool"), _addr(block_table, "block_table", torch.int32),
+                              _addr(seq_lens, "seq_lens", torch.int32), _addr(freed_phys, "freed_phys", torch.int32),
+                              _addr(spare, "spare", torch.int32), _addr(spare_used, "spare_used", torch.int32),
+                              int(spare.shape[-1]), _stream()), "pe_append_kv")
 
 
 def pe_append_paged_decode(desc, new_k, new_v, q, k_pool, v_pool, block_table, seq_lens, seq_lens_out, freed_phys, spare,
                            spare_used, softmax_scale, out, workspace=None):
-    wp, wn = ws_args(workspace)
-    check(lib().pe_append_paged_decode(ctypes.byref(desc), ptr(new_k, "new_k"), ptr(new_v, "new_v"), ptr(q, "q"),
-                                        ptr(k_pool, "k_pool"), ptr(v_pool, "v_pool"),
-                                        ptr(block_table, "block_table", torch.int32),
-                                        ptr(seq_lens, "seq_lens", torch.int32),
-                                        ptr(seq_lens_out, "seq_lens_out", torch.int32),
-                                        ptr(freed_phys, "freed_phys", torch.int32), ptr(spare, "spare", torch.int32),
-                                        ptr(spare_used, "spare_used", torch.int32), int(spare.shape[-1]),
-                                        ctypes.c_float(softmax_scale), ptr(out, "out"), wp, wn, stream_arg()),
+    wp, wn = _ws(workspace)
+    check(lib().pe_append_paged_decode(ctypes.byref(desc), _addr(new_k, "new_k"), _addr(new_v, "new_v"), _addr(q, "q"),
+                                        _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
+                                        _addr(block_table, "block_table", torch.int32),
+                                        _addr(seq_lens, "seq_lens", torch.int32),
+                                        _addr(seq_lens_out, "seq_lens_out", torch.int32),
+                                        _addr(freed_phys, "freed_phys", torch.int32), _addr(spare, "spare", torch.int32),
+                                        _addr(spare_used, "spare_used", torch.int32), int(spare.shape[-1]),
+                                        float(softmax_scale), _addr(out, "out"), wp, wn, _stream()),
            "pe_append_paged_decode")
 
 
 def pe_append_paged_decode_layers(desc, num_layers, new_k, new_v, q, k_pool, v_pool, block_table, seq_lens, seq_lens_out,
                                   freed_phys, spare, spare_used, softmax_scale, out, workspace=None):
-    wp, wn = ws_args(workspace)
-    check(lib().pe_append_paged_decode_layers(ctypes.byref(desc), int(num_layers), ptr(new_k, "new_k"), ptr(new_v, "new_v"),
-                                              ptr(q, "q"), ptr(k_pool, "k_pool"), ptr(v_pool, "v_pool"),
-                                              ptr(block_table, "block_table", torch.int32),
-                                              ptr(seq_lens, "seq_lens", torch.int32),
-                                              ptr(seq_lens_out, "seq_lens_out", torch.int32),
-                                              ptr(freed_phys, "freed_phys", torch.int32), ptr(spare, "spare", torch.int32),
-                                              ptr(spare_used, "spare_used", torch.int32), int(spare.shape[-1]),
-                                              ctypes.c_float(softmax_scale), ptr(out, "out"), wp, wn, stream_arg()),
+    wp, wn = _ws(workspace)
+    check(lib().pe_append_paged_decode_layers(ctypes.byref(desc), int(num_layers), _addr(new_k, "new_k"), _addr(new_v, "new_v"),
+                                              _addr(q, "q"), _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
+                                              _addr(block_table, "block_table", torch.int32),
+                                              _addr(seq_lens, "seq_lens", torch.int32),
+                                              _addr(seq_lens_out, "seq_lens_out", torch.int32),
+                                              _addr(freed_phys, "freed_phys", torch.int32), _addr(spare, "spare", torch.int32),
+                                              _addr(spare_used, "spare_used", torch.int32), int(spare.shape[-1]),
+                                              float(softmax_scale), _addr(out, "out"), wp, wn, _stream()),
           "pe_append_paged_decode_layers")

@@ -12,7 +12,6 @@ dimension").  Scoring, eviction and the prefill prune see the folded table in ON
 attention are launched per layer, in layer order, because in a model layer l+1's query depends on layer l's
 output.
 """
-import ctypes
 from dataclasses import dataclass
 from typing import List, Optional
 
@@ -127,38 +126,14 @@ class PagedCache:
     def any_trigger(self) -> bool:
         return any(self.triggers())
 
-    def _sp(self, name, dtype=None):
-        """Checked device pointer of one of the cache's own tensors, remembered per tensor object (the state
-        tensors are passed on every call of a decode loop; their checks need not be repeated)."""
-        t = getattr(self, name)
-        memo = self.__dict__.setdefault("_ptr_memo", {})
-        hit = memo.get(name)
-        if hit is not None and hit[0] is t:
-            return hit[1]
-        alt = memo.get(name + "~")          # the two lengths arrays alternate
-        if alt is not None and alt[0] is t:
-            memo[name], memo[name + "~"] = alt, hit
-            return alt[1]
-        p = pe.ptr(t, name, dtype)
-        if hit is not None:
-            memo[name + "~"] = hit
-        memo[name] = (t, p)
-        return p
-
     def append_paged_decode(self, new_k, new_v, q, out, softmax_scale=None):
         if softmax_scale is None:
             softmax_scale = float(self.desc.head_dim) ** -0.5
         if self.seq_lens_alt is None:
             self.seq_lens_alt = torch.empty_like(self.seq_lens)
-        if not HostOnly.active:
-            i32 = torch.int32
-            wp, wn = pe.ws_args(self.decode_ws)
-            pe.check(pe.lib().pe_append_paged_decode(
-                ctypes.byref(self.desc), pe.ptr(new_k, "new_k"), pe.ptr(new_v, "new_v"), pe.ptr(q, "q"),
-                self._sp("k_pool"), self._sp("v_pool"), self._sp("block_table", i32), self._sp("seq_lens", i32),
-                self._sp("seq_lens_alt", i32), self._sp("freed_phys", i32), self._sp("spare", i32),
-                self._sp("spare_used", i32), int(self.spare.shape[-1]), ctypes.c_float(softmax_scale),
-                pe.ptr(out, "out"), wp, wn, pe.stream_arg()), "pe_append_paged_decode")
+        _launch(pe.pe_append_paged_decode, self.desc, new_k, new_v, q, self.k_pool, self.v_pool, self.block_table,
+                self.seq_lens, self.seq_lens_alt, self.freed_phys, self.spare, self.spare_used, softmax_scale, out,
+                self.decode_ws)
         self.seq_lens, self.seq_lens_alt = self.seq_lens_alt, self.seq_lens
 
     def decode_step(self, new_k, new_v, q, out, softmax_scale=None, fused=True):
@@ -221,24 +196,14 @@ class PagedCache:
         self.host_scored = [f - 1 if t else f for f, t in zip(full, self.triggers())]
 
     def append_kv(self, new_k, new_v):
-        if HostOnly.active:
-            return
-        i32 = torch.int32
-        pe.check(pe.lib().pe_append_kv(ctypes.byref(self.desc), pe.ptr(new_k, "new_k"), pe.ptr(new_v, "new_v"),
-                                  self._sp("k_pool"), self._sp("v_pool"), self._sp("block_table", i32),
-                                  self._sp("seq_lens", i32), self._sp("freed_phys", i32), self._sp("spare", i32),
-                                  self._sp("spare_used", i32), int(self.spare.shape[-1]), pe.stream_arg()), "pe_append_kv")
+        _launch(pe.pe_append_kv, self.desc, new_k, new_v, self.k_pool, self.v_pool, self.block_table, self.seq_lens,
+                self.freed_phys, self.spare, self.spare_used)
 
     def paged_decode(self, q, out, softmax_scale=None):
         if softmax_scale is None:
             softmax_scale = float(self.desc.head_dim) ** -0.5
-        if HostOnly.active:
-            return
-        wp, wn = pe.ws_args(self.decode_ws)
-        pe.check(pe.lib().pe_paged_decode(ctypes.byref(self.desc), pe.ptr(q, "q"), self._sp("k_pool"), self._sp("v_pool"),
-                                     self._sp("block_table", torch.int32), self._sp("seq_lens", torch.int32),
-                                     ctypes.c_float(softmax_scale), pe.ptr(out, "out"), wp, wn, pe.stream_arg()),
-               "pe_paged_decode")
+        _launch(pe.pe_paged_decode, self.desc, q, self.k_pool, self.v_pool, self.block_table, self.seq_lens, softmax_scale,
+                out, self.decode_ws)
 
 
 class LayeredCache:
