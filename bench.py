@@ -54,7 +54,7 @@ def parse_args():
                     help="score + evict of a trigger step in one pass over the pages (pe_score_evict)")
     ap.add_argument("--layout", choices=("per_head", "shared"), default="per_head",
                     help="shared: one block-table row and one eviction decision per sequence, pages [B, Hk, D] "
-                         "(separate append and attention launches)")
+                         "(fp32: separate append and attention launches)")
     ap.add_argument("--stagger", action="store_true",
                     help="prompts of budget - (s mod B) tokens instead of the workload's: sequences reach their page "
                          "boundaries at different steps, as in a serving batch (the prefill prune is then a plain copy)")
@@ -258,9 +258,9 @@ def run_workload(wl, args, dev, steps, warmup, shared=False, stagger=False, deco
 
     graph = args.graph if graph is None else graph
     eng, lens, prune_ms, prune_bytes = build_engine(wl, args.seed, dev, shared, stagger, decode_opts)
-    # shared layout: the combined call is two launches inside the library; issue them separately here so that the
+    # shared layout, fp32: the combined call is two launches inside the library; issue them separately here so that the
     # events bracket the attention kernel alone
-    eng.fused = not args.unfused and not shared
+    eng.fused = not args.unfused and not (shared and wl.dtype == "f32")
     eng.folded.cached_scores = args.cached_scores
     eng.folded.fused_evict = args.fused_evict
     L, S, Hk, Hq, D = wl.layers, wl.num_seqs, wl.num_kv_heads, wl.num_q_heads, wl.head_dim

@@ -9,9 +9,10 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libpe.so")
 SOURCES = ["pe_api.hip", "score_blocks.hip", "evict_blocks.hip", "paged_decode.hip", "paged_decode_bf16.hip",
            "prefill_prune.hip"]
-# Packed fp32 VALU ops are switched off for all device code.
+# Packed fp32 VALU ops are switched off for all device code.  The leading kernel arguments (up to 14 dwords) are preloaded
+# into scalar registers instead of being loaded by every wave.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-kernarg-preload-count=14"]
 
 
 def build(verbose: bool = False, extra_flags=()) -> str:

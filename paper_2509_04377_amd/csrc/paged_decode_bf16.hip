@@ -72,24 +72,21 @@ __device__ __forceinline__ float pick4(const f32x4_t& v, bool b0, bool b1) {
   return b1 ? hi : lo;
 }
 
+// Kernel arguments besides the leading ones, which are what a wave needs before its first K/V load (14 registers' worth: the
+// compiler's kernel-argument preloading puts them into scalar registers before the wave starts, and the page lookup does
+// not wait for a load of them.  Layer launches of the 1B shape 8.70 / 8.52 us, 8B long context 17.9 / 17.4, 8B 44.9 / 44.7).
 struct Params {
-  const void* q;
-  const void* k_pool;
-  const void* v_pool;
-  const int32_t* block_table;
-  const int32_t* seq_lens;
   void* out;
   float* partials;
   float scale_log2e;
-  int num_kv_heads, num_q_heads, max_blocks, log2_block, splits, xcd_map, g_real;
   // fused append (FUSED kernels only)
+  int n_spare;
   const void* new_k;
   const void* new_v;
   int32_t* freed_phys;
   const int32_t* spare;
   int32_t* spare_used;
   int32_t* seq_lens_out;  // [S], must not alias seq_lens
-  int n_spare;
 };
 
 // One wave's view of a tile.  HG: groups of four query heads (G <= 4: 1, G <= 8: 2).
@@ -206,14 +203,17 @@ __device__ __forceinline__ int lookup(const int32_t* bt, int tile, int max_block
 template <int D, int HG, int WAVES, int DEPTH, bool FUSED, bool SHARED>
 // (the 2 asks for two waves per SIMD at least, i.e. at most 256 registers: the compiler then keeps the accumulators in
 // vector registers instead of moving them to and from accumulation registers in every step)
-__global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(const Params p) {
+__global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(
+    const int32_t* seq_lens, const int32_t* block_table, const void* q, const void* k_pool, const void* v_pool,
+    const int num_kv_heads, const int max_blocks, const int splits, const uint32_t shape, const Params p) {
   using TL = Tile<D, HG>;
   constexpr int LPR = TL::LPR, TPL = TL::TPL, NL = TL::NL, NT = TL::NT;
-  constexpr int GH = 4 * HG;  // heads computed; p.g_real of them exist
+  constexpr int GH = 4 * HG;  // heads computed; g_real of them exist
 
   __shared__ float sm_ml[WAVES][GH][2];
   __shared__ __attribute__((aligned(16))) float sm_acc[WAVES][GH][D];
 
+  const int log2_block = (int)(shape & 0xffu), g_real = (int)(shape >> 8 & 0xffu), num_q_heads = num_kv_heads * g_real;
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int g = lane >> 4, m = lane & 15, c = lane & 3;
@@ -221,24 +221,24 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(con
   int row, split;
   {
     const int b = (int)blockIdx.x;
-    if (p.xcd_map) {  // workgroup b runs on XCD b % 8: keep all splits of a row on one XCD
+    if (shape >> 16) {  // workgroup b runs on XCD b % 8: keep all splits of a row on one XCD
       const int xcd = b & 7, k = b >> 3;
-      row = (k / p.splits) * 8 + xcd;
-      split = k % p.splits;
+      row = (k / splits) * 8 + xcd;
+      split = k % splits;
     } else {
-      row = b / p.splits;
-      split = b % p.splits;
+      row = b / splits;
+      split = b % splits;
     }
   }
-  const int s = row / p.num_kv_heads;
-  const int hk = row % p.num_kv_heads;
+  const int s = row / num_kv_heads;
+  const int hk = row % num_kv_heads;
   const int table_row = SHARED ? s : row;
-  const int32_t* bt = p.block_table + (int64_t)table_row * p.max_blocks;
+  const int32_t* bt = block_table + (int64_t)table_row * max_blocks;
 
   TL tl;
-  tl.k_pool = static_cast<const u32x4_t*>(p.k_pool);
-  tl.v_pool = static_cast<const u32x4_t*>(p.v_pool);
-  tl.row_vecs = SHARED ? LPR * p.num_kv_heads : LPR;
+  tl.k_pool = static_cast<const u32x4_t*>(k_pool);
+  tl.v_pool = static_cast<const u32x4_t*>(v_pool);
+  tl.row_vecs = SHARED ? LPR * num_kv_heads : LPR;
   tl.g = g;
   tl.b0 = (c & 1) != 0;
   tl.b1 = (c & 2) != 0;
@@ -257,24 +257,24 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(con
   tl.v_off = tl.v_tok * tl.row_vecs + (SHARED ? hk * LPR : 0) + v_slice;
 
   // ---- prologue: everything that does not depend on the row length is requested first --------------
-  const int stride = p.splits * WAVES;
+  const int stride = splits * WAVES;
   const int first = split * WAVES + wave;
   int phys[DEPTH + 1];
 #pragma unroll
-  for (int d = 0; d <= DEPTH; ++d) phys[d] = lookup(bt, first + d * stride, p.max_blocks, p.log2_block);
-  const int len_pool = p.seq_lens[s];               // tokens that are read from the pool
+  for (int d = 0; d <= DEPTH; ++d) phys[d] = lookup(bt, first + d * stride, max_blocks, log2_block);
+  const int len_pool = seq_lens[s];               // tokens that are read from the pool
   const int len = FUSED ? len_pool + 1 : len_pool;  // tokens attended to
   // query operand: column n = 4*h + c holds the class-c slices of head h (heads past the group: zeros)
   bf16x8_t qop[HG][NT];
 #pragma unroll
   for (int hg = 0; hg < HG; ++hg) {
     const int h = 4 * hg + (m >> 2);
-    const int64_t head = (int64_t)s * p.num_q_heads + hk * p.g_real + (h < p.g_real ? h : 0);
-    const u32x4_t raw = static_cast<const u32x4_t*>(p.q)[head * LPR + k_slice];
+    const int64_t head = (int64_t)s * num_q_heads + hk * g_real + (h < g_real ? h : 0);
+    const u32x4_t raw = static_cast<const u32x4_t*>(q)[head * LPR + k_slice];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const u32x4_t zero = {0u, 0u, 0u, 0u};
-      const bool in = h < p.g_real && (NT == 1 || (g >> 1) == t);
+      const bool in = h < g_real && (NT == 1 || (g >> 1) == t);
       qop[hg][t] = __builtin_bit_cast(bf16x8_t, in ? raw : zero);
     }
   }
@@ -288,12 +288,12 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(con
   }
   int ap_page = -1;  // the tail page, where it is not full
   if constexpr (FUSED) {
-    const int jb = len_pool >> p.log2_block;
-    ap_page = bt[jb < 0 ? 0 : jb < p.max_blocks ? jb : p.max_blocks - 1];
+    const int jb = len_pool >> log2_block;
+    ap_page = bt[jb < 0 ? 0 : jb < max_blocks ? jb : max_blocks - 1];
   }
   const int ntiles = (len + kTile - 1) / kTile;
   const int n_mine = first < ntiles ? (ntiles - first + stride - 1) / stride : 0;
-  const int block_mask = (1 << p.log2_block) - 1;
+  const int block_mask = (1 << log2_block) - 1;
 
   float m_run[HG], m_ref[HG], l_run[HG];
   f32x4_t acc[HG][8];
@@ -311,7 +311,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(con
   // unconditionally, past the end all lanes fetch the same 16 bytes: the order of outstanding loads is known at
   // compile time, so that waiting for the oldest leaves the younger ones in flight.
   const auto base_of = [&](int tile, int ph) {
-    return (((int64_t)ph << p.log2_block) + ((tile * kTile) & block_mask)) * tl.row_vecs;
+    return (((int64_t)ph << log2_block) + ((tile * kTile) & block_mask)) * tl.row_vecs;
   };
   if (n_mine > 0) {
     u32x4_t kb[DEPTH][NL], vb[DEPTH][NL];
@@ -345,7 +345,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(con
         const bool more = i + d + DEPTH < n_mine;
         const int ahead = tile + DEPTH * stride;
         const int64_t base = more ? base_of(ahead, ph_next) : 0;
-        ph_next = lookup(bt, ahead + stride, p.max_blocks, p.log2_block);
+        ph_next = lookup(bt, ahead + stride, max_blocks, log2_block);
         tl.issue(kb[d], tl.k_pool, base, more ? tl.k_off : 0);
         if (tail) {  // mask logits past the row's end, keep junk V out of the sum
 #pragma unroll
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(con
     }
   }
   __syncthreads();
-  for (int idx = (int)threadIdx.x; idx < p.g_real * (D / 2); idx += WAVES * kWave) {
+  for (int idx = (int)threadIdx.x; idx < g_real * (D / 2); idx += WAVES * kWave) {
     const int h = idx / (D / 2), d = idx % (D / 2) * 2;
     float mm = kNegInf;
 #pragma unroll
@@ -419,12 +419,12 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(con
       o0 = fmaf(a.x, f, o0);
       o1 = fmaf(a.y, f, o1);
     }
-    if (p.splits == 1) {
+    if (splits == 1) {
       const float r0 = ll > 0.f ? o0 / ll : 0.f, r1 = ll > 0.f ? o1 / ll : 0.f;
-      const int64_t off = ((int64_t)s * p.num_q_heads + hk * p.g_real + h) * D + d;
+      const int64_t off = ((int64_t)s * num_q_heads + hk * g_real + h) * D + d;
       static_cast<uint32_t*>(p.out)[off / 2] = (uint32_t)f32_to_bf16(r0) | ((uint32_t)f32_to_bf16(r1) << 16);
     } else {
-      float* part = p.partials + (((int64_t)row * p.splits + split) * p.g_real + h) * (D + 2);
+      float* part = p.partials + (((int64_t)row * splits + split) * g_real + h) * (D + 2);
       *reinterpret_cast<float2*>(part + d) = make_float2(o0, o1);
       if (d == 0) *reinterpret_cast<float2*>(part + D) = make_float2(mm, ll);
     }
@@ -436,10 +436,10 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(con
     // launch waits for a store.
     const int owner = len_pool >= 0 ? (len_pool / kTile) % stride : 0;
     if (owner == first) {
-      const int B = 1 << p.log2_block;
+      const int B = 1 << log2_block;
       const int slot = len_pool & (B - 1);
-      const int jb = len_pool >> p.log2_block;
-      if (len_pool >= 0 && jb < p.max_blocks) {  // a length outside the table row is a caller error: touch nothing
+      const int jb = len_pool >> log2_block;
+      if (len_pool >= 0 && jb < max_blocks) {  // a length outside the table row is a caller error: touch nothing
         // head-shared: a page that has to be linked first is head 0's to link and to fill for all heads, so that no
         // workgroup has to learn from another one which page it is
         const bool link = slot == 0;
@@ -456,21 +456,21 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(con
             if (lane == 0) const_cast<int32_t*>(bt)[jb] = page;
           }
         }
-        u32x4_t* k_pool = static_cast<u32x4_t*>(const_cast<void*>(p.k_pool));
-        u32x4_t* v_pool = static_cast<u32x4_t*>(const_cast<void*>(p.v_pool));
+        u32x4_t* k_to = static_cast<u32x4_t*>(const_cast<void*>(k_pool));
+        u32x4_t* v_to = static_cast<u32x4_t*>(const_cast<void*>(v_pool));
         if (SHARED && link) {
           if (hk == 0 && page >= 0) {
-            const int64_t to = ((int64_t)page << p.log2_block) * tl.row_vecs, from = (int64_t)s * tl.row_vecs;
+            const int64_t to = ((int64_t)page << log2_block) * tl.row_vecs, from = (int64_t)s * tl.row_vecs;
             for (int i = lane; i < tl.row_vecs; i += kWave) {
-              k_pool[to + i] = static_cast<const u32x4_t*>(p.new_k)[from + i];
-              v_pool[to + i] = static_cast<const u32x4_t*>(p.new_v)[from + i];
+              k_to[to + i] = static_cast<const u32x4_t*>(p.new_k)[from + i];
+              v_to[to + i] = static_cast<const u32x4_t*>(p.new_v)[from + i];
             }
           }
         } else if (page >= 0) {
-          const int64_t base = (((int64_t)page << p.log2_block) + slot) * tl.row_vecs + (SHARED ? hk * LPR : 0);
+          const int64_t base = (((int64_t)page << log2_block) + slot) * tl.row_vecs + (SHARED ? hk * LPR : 0);
           // the lanes of the first token row of a wave-load hold the whole row between them
-          if (tl.k_tok == 0) k_pool[base + k_slice] = nk;
-          if (tl.v_tok == 0) v_pool[base + v_slice] = nv;
+          if (tl.k_tok == 0) k_to[base + k_slice] = nk;
+          if (tl.v_tok == 0) v_to[base + v_slice] = nv;
         }
       }
       if (hk == 0 && lane == 0) p.seq_lens_out[s] = len_pool + 1;
@@ -481,20 +481,9 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(con
 template <int D, int HG, int WAVES, int DEPTH>
 hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
   Params p;
-  p.q = a.q;
-  p.k_pool = a.k_pool;
-  p.v_pool = a.v_pool;
-  p.block_table = a.block_table;
-  p.seq_lens = a.seq_lens;
   p.out = a.out;
   p.partials = a.partials;
   p.scale_log2e = a.scale * 1.4426950408889634f;
-  p.num_kv_heads = a.num_kv_heads;
-  p.num_q_heads = a.num_q_heads;
-  p.max_blocks = a.max_blocks;
-  p.log2_block = ilog2(a.block_size);
-  p.splits = a.splits;
-  p.g_real = a.num_q_heads / a.num_kv_heads;
   p.new_k = a.new_k;
   p.new_v = a.new_v;
   p.freed_phys = a.freed_phys;
@@ -503,20 +492,19 @@ hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
   p.seq_lens_out = a.seq_lens_out;
   p.n_spare = a.n_spare;
   const int64_t rows = (int64_t)a.num_seqs * a.num_kv_heads;
-  p.xcd_map = (a.xcd_map && rows % 8 == 0) ? 1 : 0;
+  const uint32_t xcd_map = (a.xcd_map && rows % 8 == 0) ? 1u : 0u;
+  const uint32_t shape =
+      (uint32_t)ilog2(a.block_size) | (uint32_t)(a.num_q_heads / a.num_kv_heads) << 8 | xcd_map << 16;
   const int64_t grid = rows * a.splits;
   if (grid <= 0 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
   const dim3 blocks((unsigned)grid), threads(WAVES * kWave);
   const bool fused = a.new_k != nullptr;
-  if (a.shared && fused) {
-    hipLaunchKernelGGL((paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, true, true>), blocks, threads, 0, stream, p);
-  } else if (a.shared) {
-    hipLaunchKernelGGL((paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, false, true>), blocks, threads, 0, stream, p);
-  } else if (fused) {
-    hipLaunchKernelGGL((paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, true, false>), blocks, threads, 0, stream, p);
-  } else {
-    hipLaunchKernelGGL((paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, false, false>), blocks, threads, 0, stream, p);
-  }
+  const auto kernel = a.shared ? (fused ? paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, true, true>
+                                        : paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, false, true>)
+                               : (fused ? paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, true, false>
+                                        : paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, false, false>);
+  hipLaunchKernelGGL(kernel, blocks, threads, 0, stream, a.seq_lens, a.block_table, a.q, a.k_pool, a.v_pool,
+                     a.num_kv_heads, a.max_blocks, a.splits, shape, p);
   return hipGetLastError();
 }
 
