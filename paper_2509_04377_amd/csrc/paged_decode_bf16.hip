@@ -58,6 +58,10 @@ typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
+struct __attribute__((packed, aligned(2))) Pair {  // two bf16 at any 2-byte boundary, in one store
+  uint32_t v;
+};
+
 template <int CTRL>
 __device__ __forceinline__ float quad_perm_add(float v) {
   return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
@@ -262,7 +266,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(
   int phys[DEPTH + 1];
 #pragma unroll
   for (int d = 0; d <= DEPTH; ++d) phys[d] = lookup(bt, first + d * stride, max_blocks, log2_block);
-  const int len_pool = seq_lens[s];               // tokens that are read from the pool
+  const int len_pool = seq_lens[s];                 // tokens that are read from the pool
   const int len = FUSED ? len_pool + 1 : len_pool;  // tokens attended to
   // query operand: column n = 4*h + c holds the class-c slices of head h (heads past the group: zeros)
   bf16x8_t qop[HG][NT];
@@ -422,7 +426,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(
     if (splits == 1) {
       const float r0 = ll > 0.f ? o0 / ll : 0.f, r1 = ll > 0.f ? o1 / ll : 0.f;
       const int64_t off = ((int64_t)s * num_q_heads + hk * g_real + h) * D + d;
-      static_cast<uint32_t*>(p.out)[off / 2] = (uint32_t)f32_to_bf16(r0) | ((uint32_t)f32_to_bf16(r1) << 16);
+      static_cast<Pair*>(p.out)[off / 2].v = (uint32_t)f32_to_bf16(r0) | ((uint32_t)f32_to_bf16(r1) << 16);
     } else {
       float* part = p.partials + (((int64_t)row * splits + split) * g_real + h) * (D + 2);
       *reinterpret_cast<float2*>(part + d) = make_float2(o0, o1);
