@@ -27,9 +27,11 @@
 //   a quad hold the same value, and each turns one term of its exact decomposition into three bfloat16 terms (the
 //   fourth a zero) into the operand, so the columns of C are partial sums that are added once, at the end of the row.
 //
-// Softmax: online, base 2, one reference value m per head and wave.  The reference follows the running maximum only
-// when that has grown by more than kGrow (probabilities then stay below 2^kGrow; the result does not depend on the
-// reference), so that the rescaling of the accumulators, and the exchange between the lane groups, are rare.
+// Softmax: online, base 2, one reference value m per head and wave.  The reference is set kGrow above the largest logit
+// and moves again only when a logit exceeds it (the result does not depend on the reference), so that the rescaling of
+// the accumulators, and the exchange between the lane groups, are rare.  No probability exceeds 1: the accumulators
+// overflow no earlier than the sums that define the result do (a reference that lags behind, with probabilities of up to
+// 2^kGrow, lost finite results from |V| = 2^125 on).
 //
 // At the end the quads' columns are added, the four waves' (m, l, acc) merged through LDS behind one barrier, and the
 // normalised output (or, with more than one split, the partial record) is written.
@@ -50,7 +52,7 @@ namespace pe {
 namespace {
 
 constexpr float kNegInf = -__builtin_inff();
-constexpr float kGrow = 3.f;   // log2 of how far a logit may exceed the reference before it moves
+constexpr float kGrow = 3.f;   // how far above the largest logit (log2) the reference is set
 constexpr int kTile = 16;      // tokens per tile
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
@@ -136,11 +138,12 @@ struct Tile {
     }
   }
 
-  // Move the reference of head group hg to the running maximum.
+  // Move the reference m_run of a head group above the logits of this tile, where one of them exceeds it.  m_ref is the
+  // same, but finite before the first logit (-inf - -inf is no number).
   static __device__ __forceinline__ void regrow(float mx, float& m_run, float& m_ref, float& l_run, f32x4_t (&acc)[8]) {
     mx = fmaxf(mx, lane_xor_f32<16>(mx));
     mx = fmaxf(mx, lane_xor_f32<32>(mx));
-    const float m_new = fmaxf(m_run, mx);
+    const float m_new = mx > m_run ? mx + kGrow : m_run;
     const float ref = m_new == kNegInf ? 0.f : m_new;
     const float alpha = __builtin_amdgcn_exp2f(m_run - ref);
     l_run *= alpha;
@@ -365,7 +368,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(
 #pragma unroll
         for (int hg = 0; hg < HG; ++hg) {
           mx[hg] = fmaxf(fmaxf(x[hg][0], x[hg][1]), fmaxf(x[hg][2], x[hg][3]));
-          grow = grow || mx[hg] > m_run[hg] + kGrow;
+          grow = grow || mx[hg] > m_run[hg];
         }
         if (__builtin_amdgcn_ballot_w64(grow) != 0ull) {
 #pragma unroll

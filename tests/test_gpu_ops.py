@@ -378,6 +378,36 @@ def test_paged_decode_bf16_tiles(D, B, G):
             assert e2 <= 2 ** -8 and emax <= 2 ** -8, (splits, call, e2, emax)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("G,splits", [(1, 1), (4, 2), (5, 1), (8, 2)])
+def test_paged_decode_bf16_large_values(D, G, splits):
+    """Values of V near the end of the range: the logit of a wave's second tile exceeds its first one's by 2.8 (base 2), and
+    a weight of 2^2.8 times 1.5 * 2^126 would leave it, while the weighted sum relative to the larger logit, 1.14 of it,
+    does not.  Both V are equal and all other weights 0, so the result is that value (within twice the rounding of the
+    bf16 result, 2^-9)."""
+    print("case paged_decode_bf16_large_values", D, G, splits, flush=True)
+    B, L, big = 16, 300, 1.5 * 2.0 ** 126
+    k_pool, v_pool, table, sl = make_paged(1750 + D, [L], 1, D, B, torch.bfloat16)
+    v_pool.fill_(0.0)
+    k_pool.fill_(0.0)
+    k_pool[..., 0] = -1000.0                 # no weight
+    q = torch.zeros((1, G, D))
+    q[..., 0] = 8.0
+    step = 2.8 / (8.0 * D ** -0.5 * 1.4426950408889634)
+    for t, x in ((0, 0.0), (16 * 4 * splits, step)):   # the first tokens of the first wave's first and second tile
+        page = int(table[0, 0, t // B])
+        k_pool[page, t % B, 0], v_pool[page, t % B] = x, big
+    desc = pe.make_desc(torch.bfloat16, 1, 1, G, D, B, table.shape[2], k_pool.shape[0])
+    desc.decode_splits = splits
+    out = torch.full((1, G, D), 7.0, dtype=torch.bfloat16, device=DEV)
+    pe.pe_paged_decode(desc, q.to(torch.bfloat16).to(DEV), k_pool.to(DEV), v_pool.to(DEV), table.to(DEV), sl.to(DEV),
+                       D ** -0.5, out, pe.alloc_workspace(pe.PE_OP_PAGED_DECODE, desc))
+    torch.cuda.synchronize()
+    got = f32(out)
+    assert np.all(np.isfinite(got))
+    assert np.abs(got / big - 1.0).max() <= 2 ** -8
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 def test_paged_decode_with_a_smaller_workspace(dt):
     """An automatic split count falls back to what the caller's workspace holds, down to splits of 256 tokens."""
