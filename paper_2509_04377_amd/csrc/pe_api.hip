@@ -68,6 +68,41 @@ int64_t row_bytes(const pe_cache_desc* d) {
   return (int64_t)d->max_blocks * d->block_size * d->head_dim * (d->dtype == PE_BF16 ? 4 : 8);
 }
 
+// The most splits that a table row's length gives reason for.  Rows under 512 tokens are whole, up to sixteen splits are of
+// 128 tokens or more (8 fp32 rows x 1024 in four 12.3 us, in eight 9.4), more than sixteen of 256 or more: the merge walks over
+// the splits one by one, and a table that holds little pays for all (8 fp32 rows in a table of 4096: in sixteen 14.6 us full and
+// 7.3 with 64 tokens a row, in 32 13.8 and 9.4; of 2048: in eight 13.0 and 6.3, in sixteen 10.7 and 7.2).
+int64_t splits_by_length(const pe_cache_desc* d) {
+  const int64_t tokens = (int64_t)d->max_blocks * d->block_size;
+  if (tokens < 512) return 1;
+  const int64_t fine = tokens / 128, coarse = tokens / 256;
+  return fine <= 16 ? fine : coarse > 16 ? coarse : 16;
+}
+
+// Number of splits of a row, fp32.  The kernel computes about as long as it loads (the more so the more query heads share a
+// KV head), several of its workgroups fit a compute unit, and one without tokens is through early; so the rule asks for an
+// even deal, also of rows of unequal length.  Measured on an MI355X with full tables / ragged ones (37 tokens to all), D = 128,
+// 4 query heads a KV head (8 in brackets), us:
+//   - more rows than compute units stay whole: in four, 264 rows x 1024 take 50.7 and not 55.9, but rows of 64 tokens in the
+//     same table 10.4 and not 7.1, and 320 rows (63.0) and not (60.1);
+//   - from half to three quarters of the compute units, four: 136 rows x 4096 104 / 56 (110 / 60), in two 113 / 69 (110 / 85),
+//     whole 122 / 114 (156 / 152); beyond that, two: 224 rows x 4096 146 / 94 (150 / 98), in four 152 / 83 (160 / 88), whole
+//     142 / 119 (162 / 153);
+//   - from a quarter to half, four or six, two workgroups a compute unit: 88 rows x 2048 35 / 25 (37 / 29), in three 41 / 30
+//     (41 / 35), in two 37 / 35 (48 / 47);
+//   - below, as many as leave no compute unit two workgroups: 40 rows x 2048 in six 18.6 / 17.0, in seven 22.0 / 18.4; with more
+//     than four query heads as many as leave none without: 48 rows x 4096 in six (42.6 / 37.4), in five (42.3 / 40.0).
+int decode_splits_f32(const pe_cache_desc* d, int64_t rows, int64_t cus) {
+  if (rows >= cus) return 1;
+  const int64_t fit = cus / rows;
+  int64_t splits = fit >= 4   ? (d->num_q_heads / d->num_kv_heads > 4 ? (cus + rows - 1) / rows : fit)
+                   : fit >= 2 ? 2 * fit
+                              : (rows * 4 <= cus * 3 ? 4 : 2);
+  const int64_t by_len = splits_by_length(d);
+  if (splits > by_len) splits = by_len;
+  return splits > 64 ? 64 : (int)splits;
+}
+
 // Number of splits of a row in the attention calls, chosen from the shape (a row is taken to be as long as its table row).
 // As many as the compute units have room for with one workgroup each, none shorter than 128 tokens, and none at all of
 // rows under 512 tokens (8 rows x 1000 tokens: three splits 9.1 us, seven 7.2; 16 rows x 512: two 8.0, four 7.0; 8 rows of
@@ -86,6 +121,7 @@ int decode_splits(const pe_cache_desc* d) {
   if (d->decode_splits > 0) return d->decode_splits;
   const int64_t rows = (int64_t)d->num_seqs * d->num_kv_heads;
   const int64_t cus = compute_units();
+  if (d->dtype == PE_F32) return decode_splits_f32(d, rows, cus);
   const int64_t bytes = row_bytes(d);
   if (rows > cus) return rows * 10 <= cus * 13 && bytes >= (512 << 10) ? 4 : 1;
   const int64_t fit = cus / rows;

@@ -141,7 +141,14 @@ def test_workspace_checks():
     (dict(num_seqs=4, max_blocks=256), 8), (dict(num_seqs=4, max_blocks=7), 1), (dict(num_seqs=4, max_blocks=31), 1),
     (dict(num_seqs=4, max_blocks=32), 4), (dict(num_seqs=4, max_blocks=40), 5),
     (dict(num_seqs=1, num_kv_heads=1, num_q_heads=4, max_blocks=100000), 64),
-    (dict(num_seqs=16, head_dim=64, max_blocks=128), 1), (dict(num_seqs=16, dtype=pe.PE_F32, max_blocks=64), 2)])
+    (dict(num_seqs=16, head_dim=64, max_blocks=128), 1)] + [(dict(kw, dtype=pe.PE_F32), want) for kw, want in [
+        (dict(num_seqs=33, max_blocks=256), 1), (dict(num_seqs=32, max_blocks=256), 1), (dict(num_seqs=31, max_blocks=256), 2),
+        (dict(num_seqs=25, max_blocks=32), 2), (dict(num_seqs=24, max_blocks=32), 4), (dict(num_seqs=17, max_blocks=512), 4),
+        (dict(num_seqs=17, max_blocks=31), 1), (dict(num_seqs=16, max_blocks=64), 4), (dict(num_seqs=11, max_blocks=64), 4),
+        (dict(num_seqs=9, max_blocks=64), 6), (dict(num_seqs=9, max_blocks=32), 4), (dict(num_seqs=8, max_blocks=64), 4),
+        (dict(num_seqs=6, max_blocks=256), 5), (dict(num_seqs=6, num_q_heads=64, max_blocks=256), 6),
+        (dict(num_seqs=1, max_blocks=100000), 32), (dict(num_seqs=1, max_blocks=128), 16), (dict(num_seqs=1, max_blocks=256), 16),
+        (dict(num_seqs=1, max_blocks=272), 17), (dict(num_seqs=1, num_kv_heads=1, num_q_heads=1, max_blocks=100000), 64)]])
 def test_decode_split_rule(kw, want):
     """The automatic split count of a 256-CU device at the edges of its rule; the workspace follows it."""
     if pe.pe_decode_splits(_desc(num_seqs=1, num_kv_heads=1, num_q_heads=1, max_blocks=1 << 20)) != 64:
