@@ -515,18 +515,17 @@ hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Tiles in flight per wave, measured on an MI355X with four waves, one / two / three / four: 256 rows x 2048 tokens of
-// D = 128 41.7 / 42.1 / 42.5 / 42.6 us (and 44.5 / 44.5 out of a pool of 8.6 GB), 128 rows x 1024 17.0 / 14.4 / 15.5 / 15.2,
-// 128 rows x 8192 98.8 / 92.1, 64 rows x 1024 of D = 64 13.2 / 9.8 / 10.3 / 9.6; 256 rows x 2048 in the head-shared layout
-// 45.6 / 47.2 (append included).  The same rows through the vector units (dot products, a cross-lane reduction per
-// token, broadcast probabilities) took 43.7 us (256 x 2048, 4 query heads per KV head) and 59.8 (8 heads; now 42.6).
+// The workgroup forms that the rule in front of the launch chooses from.  Three and four tiles in flight were no faster than
+// two (256 rows x 2048 tokens of D = 128 42.1 / 42.5 / 42.6 us, 128 rows x 1024 14.4 / 15.5 / 15.2).  The same rows through the
+// vector units (dot products, a cross-lane reduction per token, broadcast probabilities) took 43.7 us (256 x 2048, 4 query
+// heads per KV head) and 59.8 (8 heads; now 42.6).
 template <int D>
 hipError_t launch_shape(const DecodeArgs& a, hipStream_t stream) {
   const bool wide = a.num_q_heads / a.num_kv_heads > 4;
   if constexpr (D == 128) {
     if (a.waves == 8) return wide ? launch_one<D, 2, 8, 2>(a, stream) : launch_one<D, 1, 8, 2>(a, stream);
-    if (a.depth == 1) return wide ? launch_one<D, 2, 4, 1>(a, stream) : launch_one<D, 1, 4, 1>(a, stream);
   }
+  if (a.depth == 1) return wide ? launch_one<D, 2, 4, 1>(a, stream) : launch_one<D, 1, 4, 1>(a, stream);
   return wide ? launch_one<D, 2, 4, 2>(a, stream) : launch_one<D, 1, 4, 2>(a, stream);
 }
 

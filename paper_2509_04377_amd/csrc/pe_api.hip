@@ -103,36 +103,40 @@ int decode_splits_f32(const pe_cache_desc* d, int64_t rows, int64_t cus) {
   return splits > 64 ? 64 : (int)splits;
 }
 
-// Number of splits of a row in the attention calls, chosen from the shape (a row is taken to be as long as its table row).
-// As many as the compute units have room for with one workgroup each, none shorter than 128 tokens, and none at all of
-// rows under 512 tokens (8 rows x 1000 tokens: three splits 9.1 us, seven 7.2; 16 rows x 512: two 8.0, four 7.0; 8 rows of
-// 228 are through before a second launch is issued: 8.7 whole, 12.7 in two).  One workgroup too many is much worse than
-// some too few: it shares its compute unit's part of the memory with another one while the rest of the chip runs dry (90 rows x 2080 tokens of bf16, D = 128: two splits 19.7 us, three 25.3; 18 rows x 5952: 14 splits 15.4,
-// 15 19.1; 160 rows x 2048: one 27.8, two 35.0, three 30.9; 192 rows 32.1 / 36.8 / 39.1).  From there
-//   - one, where two would do, nearly half of the compute units have a row and a row holds at most 512 KiB: they stream
-//     that in less than the second launch takes that merges splits (2.2 to 2.7 us; 128 rows x 1024 14.4 us whole, 15.4 in
-//     two; 96 rows 13.7 and 13.0);
-//   - four or twice as many, where pieces of 1 MiB remain: rows of unequal length fill the chip more evenly (192 rows of up
-//     to 8192 tokens, ragged: 88 us whole, 72 in four; all full 120 and 128; 128 such rows 55 in two and 53 in four, full
-//     85 and 86);
-//   - four, for somewhat more rows than compute units: whole, they would leave most of the chip idle for the second half
-//     (264 / 288 / 320 rows x 2048: 59 / 60 / 62 us whole, 50 / 52 / 57 in four; 384 rows 64 and 67).
+// Number of splits of a row in the attention calls, chosen from the shape.  The host sees the length of a table row, not of
+// the sequences, so a count has to pay on full rows and on rows of unequal length, and cost little where rows are short.
+// bfloat16, measured on an MI355X with full tables / ragged ones (37 tokens to all) / 64 tokens in every row, D = 128, 4 query
+// heads a KV head, us:
+//   - somewhat more rows than compute units, of 2048 tokens or more, in four (264 rows x 2048 49.9 / 30.3 / 10.3, whole 57.7 /
+//     39.2 / 5.6; 320 rows 55.7 / 34.7 / 11.1, whole 60.9 / 40.9 / 5.8; 384 rows 66.5 / 40.9 / 12.2, whole 64.2 / 44.4 / 5.9):
+//     rows shorter than some 300 tokens in such a table pay for it, up to 4.5 us; shorter tables and more rows are whole;
+//   - from half of the compute units on: whole where a full row takes little longer than the launch that merges splits (136 rows
+//     x 2048 26 / 23 / 5; 192 x 2048 32 / 25 / 5), else in five, four or three, about three workgroups a compute unit (136 rows x
+//     8192 in five 90 / 54 / 7, in two 117 / 58 / 8, whole 94 / 81 / 5; 192 in four 126 / 74 / 8, in two 128 / 88 / 9, whole 119 /
+//     89 / 5; 224 in four 148 / 82 / 9, in three 146 / 93 / 8; 248 in three 160 / 99 / 8, in four 161 / 97 / 9; D = 64, 136 x 4096
+//     in five 27 / 19 / 7, in two 34 / 23 / 7, whole 30 / 28 / 5);
+//   - from a quarter to half of them: whole up to 1024 tokens from 7/16 on (128 rows x 1024 14.5, in two 15.0); two workgroups a
+//     compute unit for rows of 4 MiB and more (96 rows x 16384 in two 121 / 98 / 7, in five 126 / 79 / 7; 128 rows in two 165 /
+//     110 / 7, in four 165 / 99 / 7); else one;
+//   - below, as many as leave no compute unit two workgroups (64 rows x 16384 in four 84 / 56 / 7, in eight 85 / 51 / 10).
 int decode_splits(const pe_cache_desc* d) {
   if (d->decode_splits > 0) return d->decode_splits;
   const int64_t rows = (int64_t)d->num_seqs * d->num_kv_heads;
   const int64_t cus = compute_units();
   if (d->dtype == PE_F32) return decode_splits_f32(d, rows, cus);
-  const int64_t bytes = row_bytes(d);
-  if (rows > cus) return rows * 10 <= cus * 13 && bytes >= (512 << 10) ? 4 : 1;
-  const int64_t fit = cus / rows;
   const int64_t tokens = (int64_t)d->max_blocks * d->block_size;
-  const int64_t by_len = tokens < 512 ? 1 : tokens / 128;
-  int64_t splits = fit < by_len ? fit : by_len;
-  if (splits == 2 && rows * 16 >= cus * 7 && bytes <= (512 << 10)) splits = 1;
-  const int64_t finer = fit == 1 ? 4 : 2 * fit;
-  if (rows < cus && bytes / finer >= (1 << 20)) splits = finer;
-  if (splits > 64) splits = 64;
-  return splits < 1 ? 1 : (int)splits;
+  if (rows >= cus) return rows > cus && rows * 10 <= cus * 13 && tokens >= 2048 ? 4 : 1;
+  const int64_t fit = cus / rows;
+  int64_t splits = fit;
+  if (fit == 1) {
+    if (tokens > 16 * d->head_dim) splits = rows * 5 <= cus * 3 ? 5 : rows * 8 <= cus * 7 ? 4 : 3;
+  } else if (fit <= 3) {
+    if (rows * 16 >= cus * 7 && tokens <= 1024) splits = 1;
+    else if (row_bytes(d) >= (4 << 20)) splits = 2 * cus / rows;
+  }
+  const int64_t by_len = splits_by_length(d);
+  if (splits > by_len) splits = by_len;
+  return splits > 64 ? 64 : (int)splits;
 }
 
 // The count that a caller's buffer of `have` bytes allows: the library's own choice may fall back to one workgroup per
@@ -168,23 +172,24 @@ pe::DecodeArgs decode_args(const pe_cache_desc* desc, int splits) {
   a.max_blocks = desc->max_blocks;
   a.splits = splits;
   a.xcd_map = desc->decode_flat_order ? 0 : 1;
-  // bfloat16 kernel: four waves a workgroup and two tiles in flight per wave.  Where rows of D = 128 give the chip enough
-  // workgroups (measured on an MI355X):
-  //   - eight waves, if a workgroup has 1 MiB or more to read: more bytes in flight against the latency of pages that lie
-  //     scattered over a large pool (256 rows x 2048 tokens out of 8.6 GB 44.5 us with four, 44.0 with eight; 192 ragged rows
-  //     in 768 splits 72.3 and 68.9, with eight query heads 79 and 72; but 288 rows x 512 18.0 and 19.2, and 256 splits of
-  //     256 tokens of D = 64 8.5 and 8.75);
-  //   - in the head-shared layout, whose wave-loads are runs of 256 bytes, four waves with a single tile instead (47.2 us
-  //     with two, 47.1 with eight waves, 45.6);
-  //   - a single tile too for splits of less than 512 KiB (33 rows x 4800 tokens in seven 18.5 and 17.7).
+  // bfloat16 kernel, workgroup (waves x tiles in flight per wave), measured on an MI355X:
+  //   - four x one where more workgroups than compute units come, or where rows of D = 128 are split for (nearly) all of them:
+  //     with half the registers several share a compute unit, and one that has no tokens holds up none (192 rows in 768 splits,
+  //     full 8192 tokens / 64 tokens: 126 / 8.3 us, four x two 126 / 9.7, eight x two 126 / 12.7; with eight query heads 127 /
+  //     9.9, 128 / 13.2, 130 / 16.7; 384 whole rows x 2048 64.6 / 5.9, 64.2 / 6.7, 65.2 / 8.1; D = 64 33.0 / 5.0, 34.9 / 5.8);
+  //   - and where a wave has no second tile: tables of up to 64 tokens a split;
+  //   - eight x two for whole rows of 1 MiB or more of D = 128, one for every compute unit (append and attention of 256 rows x 2048
+  //     out of a pool of 8.6 GB 43.9, four x two and four x one 44.2; no faster with fewer rows); in the head-shared layout,
+  //     whose wave-loads are runs of 256 bytes, four x one there too (45.6; with two tiles 47.2, with eight waves 47.1);
+  //   - four x two else (136 whole rows x 2048 26.8, four x one 28.2; D = 64, 128 rows in 256 splits of 8192 82.7 and 98.2).
   const int64_t groups = (int64_t)desc->num_seqs * desc->num_kv_heads * splits;
-  const int64_t piece = row_bytes(desc) / splits;
+  const int64_t cus = compute_units();
   const bool shared = desc->layout == PE_LAYOUT_SHARED;
   const bool d128 = desc->head_dim == 128;
-  const bool large = d128 && groups >= compute_units() && piece >= (1 << 20);
-  const bool small = d128 && groups * 4 >= (int64_t)compute_units() * 3 && splits > 1 && piece < (512 << 10);
+  const bool large = d128 && splits == 1 && groups == cus && row_bytes(desc) >= (1 << 20);
+  const bool one_tile = (int64_t)desc->max_blocks * desc->block_size <= (int64_t)64 * splits;
   a.waves = large && !shared ? 8 : 4;
-  a.depth = (large && shared) || small ? 1 : 2;
+  a.depth = groups > cus || one_tile || (d128 && splits > 1 && groups * 4 >= cus * 3) || (large && shared) ? 1 : 2;
   if (desc->decode_shape == 424 || desc->decode_shape == 432) a.waves = 4, a.depth = 2;
   if (desc->decode_shape == 822) a.waves = 8;
   a.is_bf16 = desc->dtype == PE_BF16;

@@ -131,17 +131,21 @@ def test_workspace_checks():
 
 
 @pytest.mark.parametrize("kw,want", [
-    (dict(num_seqs=32, max_blocks=4096), 1), (dict(num_seqs=33, max_blocks=64), 4),    # a little more than one each
-    (dict(num_seqs=33, max_blocks=63), 1), (dict(num_seqs=41, max_blocks=128), 4), (dict(num_seqs=42, max_blocks=128), 1),
-    (dict(num_seqs=16, max_blocks=64), 1), (dict(num_seqs=16, max_blocks=65), 2),      # 512 KiB a row: whole
+    (dict(num_seqs=32, max_blocks=4096), 1), (dict(num_seqs=33, max_blocks=127), 1), (dict(num_seqs=33, max_blocks=128), 4),
+    (dict(num_seqs=41, max_blocks=4096), 4), (dict(num_seqs=42, max_blocks=4096), 1), (dict(num_seqs=33, head_dim=64, max_blocks=128), 4),
+    (dict(num_seqs=17, max_blocks=128), 1), (dict(num_seqs=17, max_blocks=129), 5), (dict(num_seqs=20, max_blocks=512), 4),
+    (dict(num_seqs=24, max_blocks=128), 1), (dict(num_seqs=24, max_blocks=129), 4), (dict(num_seqs=25, max_blocks=512), 4),
+    (dict(num_seqs=28, max_blocks=512), 4), (dict(num_seqs=29, max_blocks=512), 3), (dict(num_seqs=31, max_blocks=512), 3),
+    (dict(num_seqs=17, head_dim=64, max_blocks=64), 1), (dict(num_seqs=17, head_dim=64, max_blocks=65), 5),
+    (dict(num_seqs=16, max_blocks=64), 1), (dict(num_seqs=16, max_blocks=65), 2),      # up to 1024 tokens whole
     (dict(num_seqs=12, max_blocks=64), 2), (dict(num_seqs=14, max_blocks=64), 1),
-    (dict(num_seqs=16, max_blocks=255), 2), (dict(num_seqs=16, max_blocks=512), 4),    # pieces of 1 MiB: finer
-    (dict(num_seqs=24, max_blocks=511), 1), (dict(num_seqs=24, max_blocks=512), 4), (dict(num_seqs=31, max_blocks=512), 4),
-    (dict(num_seqs=17, max_blocks=128), 1), (dict(num_seqs=9, num_kv_heads=2, num_q_heads=2, max_blocks=372), 14),
+    (dict(num_seqs=16, max_blocks=511), 2), (dict(num_seqs=16, max_blocks=512), 4),    # rows of 4 MiB: finer
+    (dict(num_seqs=12, max_blocks=511), 2), (dict(num_seqs=12, max_blocks=512), 5), (dict(num_seqs=8, max_blocks=4096), 4),
+    (dict(num_seqs=9, num_kv_heads=2, num_q_heads=2, max_blocks=372), 14),
     (dict(num_seqs=4, max_blocks=256), 8), (dict(num_seqs=4, max_blocks=7), 1), (dict(num_seqs=4, max_blocks=31), 1),
-    (dict(num_seqs=4, max_blocks=32), 4), (dict(num_seqs=4, max_blocks=40), 5),
+    (dict(num_seqs=4, max_blocks=32), 4), (dict(num_seqs=4, max_blocks=40), 5), (dict(num_seqs=1, max_blocks=256), 16),
     (dict(num_seqs=1, num_kv_heads=1, num_q_heads=4, max_blocks=100000), 64),
-    (dict(num_seqs=16, head_dim=64, max_blocks=128), 1)] + [(dict(kw, dtype=pe.PE_F32), want) for kw, want in [
+    (dict(num_seqs=16, head_dim=64, max_blocks=128), 2)] + [(dict(kw, dtype=pe.PE_F32), want) for kw, want in [
         (dict(num_seqs=33, max_blocks=256), 1), (dict(num_seqs=32, max_blocks=256), 1), (dict(num_seqs=31, max_blocks=256), 2),
         (dict(num_seqs=25, max_blocks=32), 2), (dict(num_seqs=24, max_blocks=32), 4), (dict(num_seqs=17, max_blocks=512), 4),
         (dict(num_seqs=17, max_blocks=31), 1), (dict(num_seqs=16, max_blocks=64), 4), (dict(num_seqs=11, max_blocks=64), 4),
