@@ -612,6 +612,61 @@ def test_append_paged_decode_fused(dt, D, B, G):
         desc.decode_splits = 0
 
 
+@pytest.mark.parametrize("D,G", [(128, 1), (128, 4), (128, 5), (128, 8), (64, 4), (64, 8)])
+@pytest.mark.parametrize("fused", [False, True])
+def test_bf16_row_for_every_compute_unit(D, G, fused):
+    """As many rows as compute units in table rows of 2048 tokens, which the rows fill in part: whole rows of D = 128 run in
+    workgroups of eight waves (tiles in rounds of 128 tokens, 256 with two in flight); in two splits each, workgroups with one
+    tile in flight share a compute unit.  Lengths at the edges of tiles and rounds; attention alone, and with the append.  Tolerance: twice the
+    rounding of the bf16 result, 2^-9."""
+    print("case bf16_row_for_every_compute_unit", D, G, fused, flush=True)
+    B, Hk = 16, 8
+    S = torch.cuda.get_device_properties(0).multi_processor_count // Hk
+    edges = [1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 143, 144, 255, 256, 257, 383, 384, 511, 513, 1025]
+    lens = [edges[s % len(edges)] for s in range(S)]
+    k_pool, v_pool, table, sl = make_paged(1900 + G, lens, Hk, D, B, torch.bfloat16, extra=2048 // B - 65, pad_pages=S * Hk)
+    P, mb = k_pool.shape[0], table.shape[2]
+    assert mb * B == 2048
+    for s, L in enumerate(lens):   # junk behind the end of a tail page
+        if L % B:
+            for p in table[s, :, L // B].tolist():
+                k_pool[p, L % B:], v_pool[p, L % B:] = float("nan"), float("inf")
+    clean = lambda t: np.nan_to_num(f32(t), nan=0.0, posinf=0.0)
+    used = set(table[table >= 0].tolist())
+    spare = torch.tensor([p for p in range(P) if p not in used], dtype=torch.int32).reshape(S, Hk, 1)
+    o = dict(k=clean(k_pool), v=clean(v_pool), t=i32(table).copy(), l=i32(sl).copy(), f=np.full((S, Hk), -1, np.int32),
+             u=np.zeros((S, Hk), np.int32))
+    g = torch.Generator().manual_seed(1901)
+    kd, vd, td, ld, sd = (x.to(DEV) for x in (k_pool, v_pool, table, sl, spare))
+    fd, ud = torch.from_numpy(o["f"]).to(DEV), torch.from_numpy(o["u"]).to(DEV)
+    for splits in (1, 2):
+        desc = pe.make_desc(torch.bfloat16, S, Hk, Hk * G, D, B, mb, P)
+        desc.decode_splits = splits
+        ws = pe.alloc_workspace(pe.PE_OP_PAGED_DECODE, desc)
+        q = torch.randn((S, Hk * G, D), generator=g).to(torch.bfloat16)
+        out = torch.full(q.shape, 7.0, dtype=torch.bfloat16, device=DEV)
+        if fused:
+            nk, nv = (torch.randn((S, Hk, D), generator=g).to(torch.bfloat16) for _ in range(2))
+            oracle.append_kv(f32(nk), f32(nv), o["k"], o["v"], o["t"], o["l"], o["f"], i32(spare), o["u"])
+            ld_out = torch.full_like(ld, -3)
+            pe.pe_append_paged_decode(desc, nk.to(DEV), nv.to(DEV), q.to(DEV), kd, vd, td, ld, ld_out, fd, sd, ud, D ** -0.5,
+                                      out, ws)
+            ld = ld_out
+        else:
+            pe.pe_paged_decode(desc, q.to(DEV), kd, vd, td, ld, D ** -0.5, out, ws)
+        torch.cuda.synchronize()
+        want = oracle.paged_decode(f32(q), o["k"], o["v"], o["t"], o["l"])
+        e2, emax = rel_err(f32(out), want)
+        assert e2 <= 2 ** -8 and emax <= 2 ** -8, (splits, e2, emax)
+        assert np.array_equal(td.cpu().numpy(), o["t"]) and np.array_equal(ld.cpu().numpy(), o["l"])
+        assert np.array_equal(ud.cpu().numpy(), o["u"])
+        for s in range(S):   # the stored rows
+            n = int(o["l"][s])
+            p = o["t"][s, :, (n - 1) // B]
+            assert np.array_equal(f32(kd[p, (n - 1) % B]), o["k"][p, (n - 1) % B])
+            assert np.array_equal(f32(vd[p, (n - 1) % B]), o["v"][p, (n - 1) % B])
+
+
 @pytest.mark.parametrize("opts", [dict(policy=0, protect_first=2, protect_last=3), dict(policy=1, protect_first=4),
                                   dict(policy=0, share_heads=True), dict(policy=0, share_heads=True, protect_first=1),
                                   dict(policy=1), dict(policy=0, protect_first=500)])
