@@ -419,6 +419,8 @@ def test_paged_decode_with_a_smaller_workspace(dt):
     want = oracle.paged_decode(f32(q), f32(k_pool), f32(v_pool), i32(table), i32(sl))
     desc = pe.make_desc(DTYPES[dt], len(lens), Hk, Hk * G, D, B, table.shape[2], k_pool.shape[0])
     per_split = len(lens) * Hk * G * (D + 2) * 4
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("counts below are those of 256 compute units")
     assert pe.pe_decode_splits(desc) == 16
     args = [x.to(DEV) for x in (q, k_pool, v_pool, table, sl)]
     for splits in (16, 11, 8, 7):
