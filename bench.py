@@ -42,6 +42,8 @@ def parse_args():
     ap.add_argument("--seed", type=int, default=2509)
     ap.add_argument("--splits", type=int, default=None, help="override the split count of pe_paged_decode")
     ap.add_argument("--xcd-map", type=int, default=None, choices=(0, 1))
+    # a workgroup form of the bf16 attention kernel instead of the library's choice: four waves with two tiles in flight
+    # (--waves 4 or --loads 4), with three (--depth 3), eight waves with two (--waves 8)
     ap.add_argument("--waves", type=int, default=None)
     ap.add_argument("--depth", type=int, default=None)
     ap.add_argument("--loads", type=int, default=None)
@@ -419,7 +421,8 @@ def main():
     if args.xcd_map is not None:
         decode_opts["decode_flat_order"] = 1 - args.xcd_map
     if args.waves is not None or args.depth is not None or args.loads is not None:
-        decode_opts["decode_shape"] = (args.waves or 4) * 100 + (args.depth or 2) * 10 + (args.loads or 2)
+        waves, depth = args.waves or 4, args.depth or 2
+        decode_opts["decode_shape"] = waves * 100 + depth * 10 + (args.loads or (4 if (waves, depth) == (4, 2) else 2))
 
     shared = args.layout == "shared"
     # the committed counter summary covers the workload as defined, in the per-head layout; any override of the

@@ -87,10 +87,10 @@ typedef struct pe_cache_desc {
    * and the launch read the same fields and agree by construction. */
   int32_t decode_splits;   /* 0: chosen from the shape and the device's compute-unit count; 1..256: that many
                               splits of every row (1 = no partials, no workspace) */
-  int32_t decode_shape;    /* 0: default.  Others for tuning, only for bf16, D = 128, Hq/Hk = 4, per-head layout (422
-                              anywhere): 422 = the default; 424 and 432 = four waves per workgroup, 822 = eight, whatever
-                              the number of workgroups.  Anything else returns PE_ERR_UNSUPPORTED from the attention
-                              calls */
+  int32_t decode_shape;    /* 0: chosen by the library.  Others for tuning, only for bf16, D = 128, Hq/Hk = 4, per-head layout
+                              (422 anywhere): 422 = the library's choice; 424 = four waves per workgroup with two tiles (of
+                              four loads of K and four of V) in flight per wave; 432 = four waves with three; 822 = eight
+                              waves with two.  Anything else returns PE_ERR_UNSUPPORTED from the attention calls */
   int32_t decode_flat_order; /* 0: workgroup order that keeps the splits of a row on one XCD; 1: plain row-major */
 } pe_cache_desc;
 

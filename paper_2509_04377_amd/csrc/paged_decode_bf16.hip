@@ -485,8 +485,11 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(
   }
 }
 
+// (the forms that the head-shared layout never takes are not built for it)
 template <int D, int HG, int WAVES, int DEPTH>
 hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
+  constexpr bool kShared = WAVES == 4 && DEPTH <= 2;
+  if (a.shared && !kShared) return hipErrorInvalidValue;
   Params p;
   p.out = a.out;
   p.partials = a.partials;
@@ -506,8 +509,8 @@ hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
   if (grid <= 0 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
   const dim3 blocks((unsigned)grid), threads(WAVES * kWave);
   const bool fused = a.new_k != nullptr;
-  const auto kernel = a.shared ? (fused ? paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, true, true>
-                                        : paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, false, true>)
+  const auto kernel = a.shared ? (fused ? paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, true, kShared>
+                                        : paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, false, kShared>)
                                : (fused ? paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, true, false>
                                         : paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, false, false>);
   hipLaunchKernelGGL(kernel, blocks, threads, 0, stream, a.seq_lens, a.block_table, a.q, a.k_pool, a.v_pool,
@@ -515,7 +518,7 @@ hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// The workgroup forms that the rule in front of the launch chooses from.  Three and four tiles in flight were no faster than
+// The workgroup forms that the rule in front of the launch chooses from, and one (4 x 3) for tuning.  Three and four tiles in flight were no faster than
 // two (256 rows x 2048 tokens of D = 128 42.1 / 42.5 / 42.6 us, 128 rows x 1024 14.4 / 15.5 / 15.2).  The same rows through the
 // vector units (dot products, a cross-lane reduction per token, broadcast probabilities) took 43.7 us (256 x 2048, 4 query
 // heads per KV head) and 59.8 (8 heads; now 42.6).
@@ -524,6 +527,7 @@ hipError_t launch_shape(const DecodeArgs& a, hipStream_t stream) {
   const bool wide = a.num_q_heads / a.num_kv_heads > 4;
   if constexpr (D == 128) {
     if (a.waves == 8) return wide ? launch_one<D, 2, 8, 2>(a, stream) : launch_one<D, 1, 8, 2>(a, stream);
+    if (a.depth == 3) return wide ? hipErrorInvalidValue : launch_one<D, 1, 4, 3>(a, stream);
   }
   if (a.depth == 1) return wide ? launch_one<D, 2, 4, 1>(a, stream) : launch_one<D, 1, 4, 1>(a, stream);
   return wide ? launch_one<D, 2, 4, 2>(a, stream) : launch_one<D, 1, 4, 2>(a, stream);

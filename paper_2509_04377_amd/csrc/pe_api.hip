@@ -190,8 +190,9 @@ pe::DecodeArgs decode_args(const pe_cache_desc* desc, int splits) {
   const bool one_tile = (int64_t)desc->max_blocks * desc->block_size <= (int64_t)64 * splits;
   a.waves = large && !shared ? 8 : 4;
   a.depth = groups > cus || one_tile || (d128 && splits > 1 && groups * 4 >= cus * 3) || (large && shared) ? 1 : 2;
-  if (desc->decode_shape == 424 || desc->decode_shape == 432) a.waves = 4, a.depth = 2;
-  if (desc->decode_shape == 822) a.waves = 8;
+  if (desc->decode_shape == 424) a.waves = 4, a.depth = 2;
+  if (desc->decode_shape == 432) a.waves = 4, a.depth = 3;
+  if (desc->decode_shape == 822) a.waves = 8, a.depth = 2;
   a.is_bf16 = desc->dtype == PE_BF16;
   a.shared = shared;
   return a;

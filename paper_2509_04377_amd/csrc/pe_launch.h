@@ -77,7 +77,8 @@ struct DecodeArgs {
   int num_seqs, num_kv_heads, num_q_heads, head_dim, block_size, max_blocks;
   int splits;
   int xcd_map;
-  int waves, depth;  // bfloat16 kernel: workgroup size in waves, tiles in flight per wave: 4 x 2, 4 x 1; D = 128: 8 x 2 too
+  int waves, depth;  // bfloat16 kernel: workgroup size in waves, tiles in flight per wave: 4 x 2, 4 x 1; D = 128,
+                     // per-head layout: 8 x 2, and with up to four query heads per KV head 4 x 3 too
   bool is_bf16;
   // fused append: all null / 0 for plain attention
   const void* new_k = nullptr;

@@ -614,6 +614,42 @@ def test_append_paged_decode_fused(dt, D, B, G):
         desc.decode_splits = 0
 
 
+@pytest.mark.parametrize("shape", [422, 424, 432, 822])
+def test_bf16_named_shapes(shape):
+    """The workgroup forms that a descriptor can name, at the edges of their tiles and rounds: attention, and the append in
+    the same launch.  Tolerance: twice the rounding of the bf16 result, 2^-9."""
+    print("case bf16_named_shapes", shape, flush=True)
+    D, B, Hk, G = 128, 16, 2, 4
+    lens = [1, 15, 16, 17, 63, 64, 65, 127, 129, 191, 193, 255, 256, 257, 385, 513, 1025]
+    k_pool, v_pool, table, sl = make_paged(1950, lens, Hk, D, B, torch.bfloat16, pad_pages=len(lens) * Hk)
+    S, mb, P = len(lens), table.shape[2], k_pool.shape[0]
+    used = set(table[table >= 0].tolist())
+    spare = torch.tensor([p for p in range(P) if p not in used], dtype=torch.int32).reshape(S, Hk, 1)
+    g = torch.Generator().manual_seed(1951)
+    q = torch.randn((S, Hk * G, D), generator=g).to(torch.bfloat16)
+    nk, nv = (torch.randn((S, Hk, D), generator=g).to(torch.bfloat16) for _ in range(2))
+    o = dict(k=f32(k_pool).copy(), v=f32(v_pool).copy(), t=i32(table).copy(), l=i32(sl).copy())
+    want = [oracle.paged_decode(f32(q), o["k"], o["v"], o["t"], o["l"])]
+    oracle.append_kv(f32(nk), f32(nv), o["k"], o["v"], o["t"], o["l"], np.full((S, Hk), -1, np.int32), i32(spare),
+                     np.zeros((S, Hk), np.int32))
+    want.append(oracle.paged_decode(f32(q), o["k"], o["v"], o["t"], o["l"]))
+    for splits in (1, 3):
+        desc = pe.make_desc(torch.bfloat16, S, Hk, Hk * G, D, B, mb, P, decode_splits=splits, decode_shape=shape)
+        ws = pe.alloc_workspace(pe.PE_OP_PAGED_DECODE, desc)
+        qd, kd, vd, td, ld, sd, nkd, nvd = (x.to(DEV) for x in (q, k_pool, v_pool, table, sl, spare, nk, nv))
+        fd, ud = (torch.full((S, Hk), x, dtype=torch.int32, device=DEV) for x in (-1, 0))
+        outs = [torch.full(q.shape, 7.0, dtype=torch.bfloat16, device=DEV) for _ in range(2)]
+        ld_out = torch.full_like(ld, -3)
+        pe.pe_paged_decode(desc, qd, kd, vd, td, ld, D ** -0.5, outs[0], ws)
+        pe.pe_append_paged_decode(desc, nkd, nvd, qd, kd, vd, td, ld, ld_out, fd, sd, ud, D ** -0.5, outs[1], ws)
+        torch.cuda.synchronize()
+        for out, w in zip(outs, want):
+            e2, emax = rel_err(f32(out), w)
+            assert e2 <= 2 ** -8 and emax <= 2 ** -8, (splits, e2, emax)
+        assert np.array_equal(td.cpu().numpy(), o["t"]) and np.array_equal(ld_out.cpu().numpy(), o["l"])
+        assert np.array_equal(f32(kd), o["k"]) and np.array_equal(f32(vd), o["v"])
+
+
 @pytest.mark.parametrize("D,G", [(128, 1), (128, 4), (128, 5), (128, 8), (64, 4), (64, 8)])
 @pytest.mark.parametrize("fused", [False, True])
 def test_bf16_row_for_every_compute_unit(D, G, fused):

@@ -1,0 +1,77 @@
+"""Which form of the attention kernel a descriptor leads to: the host layer of the library, built here with recording stand-ins for
+the launches (no GPU needed)."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+import torch
+
+from paper_2509_04377_amd import binding as pe
+from paper_2509_04377_amd import build
+
+STANDINS = r"""
+#include "%s/pe_launch.h"
+namespace pe {
+static int seen[3];
+hipError_t launch_score_blocks(const ScoreArgs&, hipStream_t) { return hipSuccess; }
+hipError_t launch_score_evict(const ScoreEvictArgs&, hipStream_t) { return hipSuccess; }
+hipError_t launch_evict_blocks(const EvictArgs&, hipStream_t) { return hipSuccess; }
+hipError_t launch_append_kv(const AppendArgs&, hipStream_t) { return hipSuccess; }
+hipError_t launch_prefill_prune(const PruneArgs&, hipStream_t) { return hipSuccess; }
+size_t prune_workspace_bytes(int, int, int64_t, bool) { return 0; }
+size_t decode_partials_bytes(int, int, int, int splits) { return splits > 1 ? 256 : 0; }
+hipError_t launch_paged_decode(const DecodeArgs& a, hipStream_t) {
+  seen[0] = a.splits;
+  seen[1] = a.waves;
+  seen[2] = a.depth;
+  return hipSuccess;
+}
+}  // namespace pe
+extern "C" const int* seen_launch() { return pe::seen; }
+"""
+
+
+@pytest.fixture(scope="module")
+def host_layer(tmp_path_factory):
+    if torch.cuda.is_available() and torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the forms below are those of 256 compute units")
+    d = tmp_path_factory.mktemp("routes")
+    src, so = d / "standins.hip", d / "libroutes.so"
+    src.write_text(STANDINS % build.CSRC)
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    subprocess.run([hipcc] + build.FLAGS + ["-O1", "-shared", str(src), os.path.join(build.CSRC, "pe_api.hip"), "-o", str(so)],
+                   check=True, stderr=subprocess.DEVNULL)
+    lib = ctypes.CDLL(str(so))
+    lib.seen_launch.restype = ctypes.POINTER(ctypes.c_int)
+    return lib
+
+
+def _form(lib, **kw):
+    """(splits, waves, tiles in flight) of pe_paged_decode for a descriptor."""
+    d = dict(dtype=pe.PE_BF16, num_seqs=32, num_kv_heads=8, num_q_heads=32, head_dim=128, block_size=16, max_blocks=128,
+             num_phys_blocks=4096)
+    d.update(kw)
+    desc, p = pe.make_desc(**d), ctypes.c_void_p(0x1000)   # the pointer goes to the stand-in only
+    rc = lib.pe_paged_decode(ctypes.byref(desc), p, p, p, p, p, ctypes.c_float(0.1), p, p, ctypes.c_size_t(1 << 30), None)
+    assert rc == pe.PE_OK
+    return tuple(lib.seen_launch()[:3])
+
+
+def test_named_shapes_are_forms_of_their_own(host_layer):
+    named = [_form(host_layer, decode_shape=s, decode_splits=1) for s in (424, 432, 822)]
+    assert named == [(1, 4, 2), (1, 4, 3), (1, 8, 2)]
+    for kw in (dict(), dict(num_seqs=4, max_blocks=256), dict(num_seqs=48)):
+        assert _form(host_layer, decode_shape=422, **kw) == _form(host_layer, **kw)
+
+
+@pytest.mark.parametrize("kw,want", [
+    (dict(), (1, 8, 2)), (dict(max_blocks=127), (1, 4, 2)), (dict(head_dim=64, max_blocks=512), (1, 4, 2)),
+    (dict(layout=pe.PE_LAYOUT_SHARED), (1, 4, 1)), (dict(num_seqs=31), (1, 4, 2)), (dict(num_seqs=48), (1, 4, 1)),
+    (dict(num_seqs=48, head_dim=64), (1, 4, 1)), (dict(num_seqs=33), (4, 4, 1)), (dict(num_seqs=24, max_blocks=512), (4, 4, 1)),
+    (dict(num_seqs=4, max_blocks=256), (8, 4, 1)), (dict(num_seqs=4, head_dim=64, max_blocks=256), (8, 4, 2)),
+    (dict(num_seqs=1, max_blocks=100), (12, 4, 2)), (dict(max_blocks=4), (1, 4, 1)), (dict(num_seqs=4, max_blocks=4), (1, 4, 1)),
+    (dict(num_seqs=4, max_blocks=5), (1, 4, 2)), (dict(num_seqs=16, decode_splits=2), (2, 4, 1)),
+    (dict(num_seqs=8, decode_splits=2), (2, 4, 2))])
+def test_bf16_form(host_layer, kw, want):
+    assert _form(host_layer, **kw) == want
