@@ -164,11 +164,13 @@ __global__ __launch_bounds__(kThreads) void head_mean_kernel(const float* __rest
 // places in the candidate list are taken once per wave, two histograms share the atomics of the first digit.  Measured on
 // an MI355X, before (every pass from memory, three more barriers a pass) / now: 64 rows x 4096 scores 10.4 / 6.8 us, 128
 // ragged rows of up to 16384 13.7 / 11.3, 256 x 16384 17.7 / 14.4, 288 ragged rows of up to 6567 14.4 / 11.2 (15.2 with one
-// workgroup a compute unit), 2 x 44000 20.6 / 19.0, 32 x 65536 29.6 / 28.5.
+// workgroup a compute unit), 2 x 44000 20.7 / 18.8, 32 x 65536 30.0 / 28.7, 32 x 131072 46.6 / 43.4 (what lies beyond the held
+// scores comes in loads of 16 bytes, four in flight a thread: with loads of 4 bytes 19.9, 32.7 and 51.7; with eight of 16 bytes
+// the short ends of 36000 or 44000 scores take as long again as they save on 131072).
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / kWave;
 constexpr int kSelBins = 4096;
-constexpr int kSelUnroll = 8;
+constexpr int kSelUnroll = 4;  // 16-byte loads in flight per thread beyond the held scores
 constexpr int kSelCand = 8192;  // candidates kept in LDS after the first pass (32 KiB)
 constexpr int kSelMaxVecs = 8;
 constexpr int kSelCopies = 2;  // with the candidates 64 KiB: two workgroups fit a compute unit
@@ -220,19 +222,25 @@ struct RowScores {
       }
     }
   }
-  // ... and for the rest of the row, from memory
+  // ... and for the rest of the row, from memory: 16 bytes a load, past the end the row's last four again
   template <typename F>
   __device__ __forceinline__ void visit_rest(F f) const {
-    for (int i0 = kHeld + tid; i0 < L; i0 += kSelUnroll * kSelThreads) {
-      uint32_t r[kSelUnroll];
+    constexpr int kUnroll = NV == kSelMaxVecs ? kSelUnroll : 1;  // a smaller holding covers every row of its call
+    for (int i0 = kHeld + 4 * tid; i0 < L; i0 += kUnroll * 4 * kSelThreads) {
+      Unaligned4 r[kUnroll];
 #pragma unroll
-      for (int k = 0; k < kSelUnroll; ++k) {
-        const int i = i0 + k * kSelThreads;
-        r[k] = bits[i < L ? i : L - 1];
+      for (int k = 0; k < kUnroll; ++k) {
+        const int i = i0 + k * 4 * kSelThreads;
+        r[k] = *reinterpret_cast<const Unaligned4*>(bits + (i < L - 4 ? i : L - 4));
       }
 #pragma unroll
-      for (int k = 0; k < kSelUnroll; ++k)
-        if (i0 + k * kSelThreads < L) f(r[k]);
+      for (int k = 0; k < kUnroll; ++k) {
+        const int i = i0 + k * 4 * kSelThreads;
+        const int at = i < L - 4 ? i : L - 4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (at + e >= i) f(r[k].v[e]);
+      }
     }
   }
   template <typename F>

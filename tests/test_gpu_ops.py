@@ -501,7 +501,8 @@ def test_prefill_prune_ties():
 
 
 @pytest.mark.parametrize("lens", [[1, 4095, 3], [4096, 2, 4097], [6, 8191, 8193], [1, 16383, 16385], [2, 32768],
-                                  [32769, 5], [1, 33793, 32767], [3, 66000]])
+                                  [32769, 5], [1, 33793, 32767], [3, 66000], [32770, 1, 49151], [32771, 49153],
+                                  [2, 49155, 65541]])
 @pytest.mark.parametrize("crowded", [False, True])
 def test_prefill_prune_row_holding(lens, crowded):
     """Rows at the edges of what the selection holds in registers (4096 * 1, 2, 4, 8 scores) and beyond, starting
