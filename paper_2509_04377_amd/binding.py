@@ -141,17 +141,7 @@ def ptr(t, name, dtype=None, optional=False):
     return ctypes.c_void_p(t.data_ptr())
 
 
-def stream_arg():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-
-
-def ws_args(workspace):
-    if workspace is None:
-        return None, 0
-    return ctypes.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size()
-
-
-# What the calls below pass: the checks of ptr() and the values of stream_arg() and ws_args(), as plain numbers.  A small
+# What the calls below pass: the checks of ptr(), and the current stream and the workspace, as plain numbers.  A small
 # launch is over sooner than its arguments are put together (5 us against 13), and of those the stream object and a
 # ctypes object per pointer were the larger half; ctypes converts numbers by the declared argument types.
 def _addr(t, name, dtype=None):

@@ -153,43 +153,31 @@ struct Tile {
   static constexpr int GP = next_pow2(G);
   static_assert(GP <= LPR && GP <= 8, "query group too large");
 
-  // A tile touches at most NPT pages (two when a 32-token tile meets 16-token pages).
-  static constexpr int NPT = TT > 16 ? TT / 16 : 1;
+  static_assert(TT <= 16, "a tile lies in one page");
 
-  // Scalar loads of the physical page ids of tile `tile`.  The index is clamped to the table row, and an
+  // Physical page of tile `tile` (scalar load).  The index is clamped to the table row, and an
   // unused entry (-1, beyond the row's last page) is replaced by page 0: the tokens of such a page are
   // masked later, so any address inside the pool will do.  Nothing here depends on the row length, so
   // the first lookup can be issued before the length has arrived.
-  static __device__ __forceinline__ void lookup(int (&phys)[NPT], int tile, const int32_t* bt, int max_blocks,
-                                                int log2_block) {
-    const int p0 = (tile * TT) >> log2_block;
-#pragma unroll
-    for (int e = 0; e < NPT; ++e) {
-      int pi = p0 + e;
-      pi = pi < max_blocks ? pi : max_blocks - 1;
-      const int ph = __builtin_amdgcn_readfirstlane(bt[pi]);
-      phys[e] = ph < 0 ? 0 : ph;
-    }
+  static __device__ __forceinline__ int lookup(int tile, const int32_t* bt, int max_blocks, int log2_block) {
+    int pi = (tile * TT) >> log2_block;
+    pi = pi < max_blocks ? pi : max_blocks - 1;
+    const int ph = __builtin_amdgcn_readfirstlane(bt[pi]);
+    return ph < 0 ? 0 : ph;
   }
 
-  // Issue the 2*NLT wave-loads of tile `tile`, whose page ids were looked up one step earlier (the table
+  // Issue the 2*NLT wave-loads of tile `tile`, whose page was looked up one step earlier (the table
   // access is off the critical path of the loads).  `lane_off` is the lane id, or 0 in every lane for a
   // placeholder issue whose data is never used (all lanes then fetch the same 16 bytes): issues stay
   // unconditional, which keeps the order of outstanding loads known at compile time, so waiting for the
   // oldest tile leaves the younger ones in flight.
-  static __device__ __forceinline__ void issue(uint4 (&kb)[NLT], uint4 (&vb)[NLT], int tile, const int (&phys)[NPT],
-                                               const float* k_pool, const float* v_pool, int log2_block, int lane_off,
-                                               int row_vecs = LPR) {
+  static __device__ __forceinline__ void issue(uint4 (&kb)[NLT], uint4 (&vb)[NLT], int tile, int phys, const float* k_pool,
+                                               const float* v_pool, int log2_block, int lane_off, int row_vecs) {
     const int tok0 = tile * TT;
 #pragma unroll
     for (int i = 0; i < NLT; ++i) {
-      const int t = tok0 + i * TPL;
-      int ph = phys[0];
-#pragma unroll
-      for (int e = 1; e < NPT; ++e)
-        if (((i * TPL) >> log2_block) == e) ph = phys[e];
-      const int slot0 = t & ((1 << log2_block) - 1);
-      const int64_t vec = (((int64_t)ph << log2_block) + slot0) * row_vecs + lane_off;
+      const int slot0 = (tok0 + i * TPL) & ((1 << log2_block) - 1);
+      const int64_t vec = (((int64_t)phys << log2_block) + slot0) * row_vecs + lane_off;
       kb[i] = load_vec_stream(k_pool, vec);
       vb[i] = load_vec_stream(v_pool, vec);
     }
@@ -307,8 +295,7 @@ __global__ __launch_bounds__(kWaves * kWave) void paged_decode_kernel(const Deco
   // together with the length itself instead of waiting for it (one dependent round trip to memory less).
   const int stride = p.splits * WAVES;
   const int first = split * WAVES + wave;
-  int phys[TL::NPT];
-  TL::lookup(phys, first, bt, p.max_blocks, p.log2_block);
+  int phys = TL::lookup(first, bt, p.max_blocks, p.log2_block);
   const int len_pool = p.seq_lens[s];               // tokens that are read from the pool
   const int len = FUSED ? len_pool + 1 : len_pool;  // tokens attended to
 #pragma unroll
@@ -342,7 +329,7 @@ __global__ __launch_bounds__(kWaves * kWave) void paged_decode_kernel(const Deco
 #pragma unroll
     for (int d = 0; d < DEPTH - 1; ++d) {
       TL::issue(kb[d], vb[d], tile_at(d), phys, k_pool, v_pool, p.log2_block, d < n_mine ? lane_vec : 0, row_vecs);
-      TL::lookup(phys, tile_at(d + 1), bt, p.max_blocks, p.log2_block);
+      phys = TL::lookup(tile_at(d + 1), bt, p.max_blocks, p.log2_block);
     }
     for (int i = 0; i < n_mine; i += DEPTH) {
 #pragma unroll
@@ -350,7 +337,7 @@ __global__ __launch_bounds__(kWaves * kWave) void paged_decode_kernel(const Deco
         const int ahead = i + ph + DEPTH - 1;
         TL::issue(kb[(ph + DEPTH - 1) % DEPTH], vb[(ph + DEPTH - 1) % DEPTH], tile_at(ahead), phys, k_pool, v_pool,
                   p.log2_block, ahead < n_mine ? lane_vec : 0, row_vecs);
-        TL::lookup(phys, tile_at(ahead + 1), bt, p.max_blocks, p.log2_block);
+        phys = TL::lookup(tile_at(ahead + 1), bt, p.max_blocks, p.log2_block);
         if (i + ph < n_mine) {
           TL::template compute<NLT>(kb[ph], vb[ph], (first + (i + ph) * stride) * TT, len_pool, grp, p.scale_log2e, qs,
                                     m_run, l_run, acc);
