@@ -1,7 +1,8 @@
-// Paged decode attention (Eq. 1 for one new query per sequence; Alg. 3 "PagedAttention(Q,K,V)"): the kernel of fp32
-// caches, the merge of the splits, and the choice of the kernel (bfloat16 caches: paged_decode_bf16.hip).
+// Paged decode attention (Eq. 1 for one new query per sequence; Alg. 3 "PagedAttention(Q,K,V)") on the vector units, the merge
+// of the splits, and the choice of the kernel (on the matrix cores: paged_decode_bf16.hip).
 //
-// fp32: QK and PV run on the vector units (the fp32 matrix instructions have no higher rate).  A workgroup owns one
+// fp32 caches (the fp32 matrix instructions have no higher rate), and bfloat16 ones of one query head per KV head with short
+// rows, where the other kernel's longer way from the loads to the output shows and its products stay idle.  A workgroup owns one
 // split of one (sequence, KV head) row: every splits-th group of four consecutive tiles of the row's tokens.  Each of
 // its four waves walks tiles with a two-deep register pipeline.  Inside a tile every lane holds 16 bytes of two K rows
 // and two V rows (consecutive lanes = consecutive addresses, so each wave-load is 1 KiB of one page, found through the
@@ -38,8 +39,13 @@ constexpr float kNegInf = -__builtin_inff();
 
 constexpr int next_pow2(int x) { return x <= 1 ? 1 : 2 * next_pow2((x + 1) / 2); }
 
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+
 // The 16 bytes of one query head that face a lane's 16-byte K slice.
-struct QSlice {
+template <typename T>
+struct QSlice;
+template <>
+struct QSlice<float> {
   float v[4];
   __device__ __forceinline__ void load(const float* p) {
     const uint4 r = *reinterpret_cast<const uint4*>(p);
@@ -55,6 +61,25 @@ struct QSlice {
     a = fmaf(__uint_as_float(k.z), v[2], a);
     a = fmaf(__uint_as_float(k.w), v[3], a);
     return a;
+  }
+};
+
+template <>
+struct QSlice<bf16_t> {
+  uint32_t v[4];  // 8 bf16, packed as in memory
+  __device__ __forceinline__ void load(const bf16_t* p) {
+    const uint4 r = *reinterpret_cast<const uint4*>(p);
+    v[0] = r.x;
+    v[1] = r.y;
+    v[2] = r.z;
+    v[3] = r.w;
+  }
+  __device__ __forceinline__ void zero() { v[0] = v[1] = v[2] = v[3] = 0u; }
+  static __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c) {
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a), __builtin_bit_cast(bf16x2_t, b), c, false);
+  }
+  __device__ __forceinline__ float dot(const uint4& k) const {
+    return dot2(k.w, v[3], dot2(k.z, v[2], dot2(k.y, v[1], dot2(k.x, v[0], 0.f))));
   }
 };
 
@@ -142,9 +167,9 @@ struct DecodeParams {
 // while it waits): the stream runs fastest at about 8 MiB in flight over the chip.
 constexpr int kWaves = 4, kDepth = 2, kLoads = 2;
 
-template <int D, int G>
+template <typename T, int D, int G>
 struct Tile {
-  using Geo = RowGeom<float, D>;
+  using Geo = RowGeom<T, D>;
   static constexpr int EPL = Geo::kPerVec;
   static constexpr int LPR = Geo::kLanesPerRow;
   static constexpr int TPL = Geo::kTokensPerLoad;
@@ -171,8 +196,8 @@ struct Tile {
   // placeholder issue whose data is never used (all lanes then fetch the same 16 bytes): issues stay
   // unconditional, which keeps the order of outstanding loads known at compile time, so waiting for the
   // oldest tile leaves the younger ones in flight.
-  static __device__ __forceinline__ void issue(uint4 (&kb)[NLT], uint4 (&vb)[NLT], int tile, int phys, const float* k_pool,
-                                               const float* v_pool, int log2_block, int lane_off, int row_vecs) {
+  static __device__ __forceinline__ void issue(uint4 (&kb)[NLT], uint4 (&vb)[NLT], int tile, int phys, const T* k_pool,
+                                               const T* v_pool, int log2_block, int lane_off, int row_vecs) {
     const int tok0 = tile * TT;
 #pragma unroll
     for (int i = 0; i < NLT; ++i) {
@@ -186,7 +211,7 @@ struct Tile {
   // Consume NL wave-loads whose first token is tok0: logits, online softmax update, PV accumulation.
   template <int NL>
   static __device__ __forceinline__ void compute(uint4 (&kb)[NL], uint4 (&vb)[NL], int tok0, int len, int grp,
-                                                 float scale_log2e, const QSlice (&qs)[GP], float& m_run,
+                                                 float scale_log2e, const QSlice<T> (&qs)[GP], float& m_run,
                                                  float& l_run, float (&acc)[G][EPL]) {
     float x[NL];
 #pragma unroll
@@ -226,16 +251,16 @@ struct Tile {
     for (int i = 0; i < NL; ++i) {
       float ve[EPL];
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) ve[e] = vec_elem<float>(vb[i], e);
+      for (int e = 0; e < EPL; ++e) ve[e] = vec_elem<T>(vb[i], e);
       accumulate_pv<G, GP, EPL>(acc, pr[i], ve);
     }
   }
 };
 
-template <int D, int G, bool FUSED, bool SHARED>
+template <typename T, int D, int G, bool FUSED, bool SHARED>
 __global__ __launch_bounds__(kWaves * kWave) void paged_decode_kernel(const DecodeParams p) {
   static_assert(!(FUSED && SHARED), "the fused append is per-head only");
-  using TL = Tile<D, G>;
+  using TL = Tile<T, D, G>;
   constexpr int WAVES = kWaves, DEPTH = kDepth;
   constexpr int EPL = TL::EPL, LPR = TL::LPR, TPL = TL::TPL, NLT = TL::NLT, TT = TL::TT, GP = TL::GP;
   constexpr int GBITS = ilog2(GP);
@@ -272,17 +297,17 @@ __global__ __launch_bounds__(kWaves * kWave) void paged_decode_kernel(const Deco
   const int32_t* bt = p.block_table + (int64_t)(SHARED ? s : row) * p.max_blocks;
   const int row_vecs = SHARED ? LPR * p.num_kv_heads : LPR;
   const int lane_vec = SHARED ? (grp * p.num_kv_heads + hk) * LPR + u : lane;
-  const float* k_pool = static_cast<const float*>(p.k_pool);
-  const float* v_pool = static_cast<const float*>(p.v_pool);
+  const T* k_pool = static_cast<const T*>(p.k_pool);
+  const T* v_pool = static_cast<const T*>(p.v_pool);
 
   // ---- prologue: everything that does not depend on the row length is requested first --------------
   // query slices: slot i holds head (i ^ c_lane) of this KV head's group (heads past the group: zeros)
-  QSlice qs[GP];
+  QSlice<T> qs[GP];
 #pragma unroll
   for (int i = 0; i < GP; ++i) {
     const int head = i ^ c_lane;
     const int head_ld = head < p.g_real ? head : 0;
-    qs[i].load(static_cast<const float*>(p.q) + ((int64_t)s * p.num_q_heads + hk * p.g_real + head_ld) * D + u * EPL);
+    qs[i].load(static_cast<const T*>(p.q) + ((int64_t)s * p.num_q_heads + hk * p.g_real + head_ld) * D + u * EPL);
   }
   uint4 nk[1], nv[1];  // FUSED: the new token's K/V rows, held by the first lane group of every wave
   if constexpr (FUSED) {
@@ -430,7 +455,11 @@ __global__ __launch_bounds__(kWaves * kWave) void paged_decode_kernel(const Deco
       if (p.splits == 1) {
         const float r = ll > 0.f ? o / ll : 0.f;
         const int64_t off = ((int64_t)s * p.num_q_heads + hk * p.g_real + h) * D + d;
-        static_cast<float*>(p.out)[off] = r;
+        if constexpr (sizeof(T) == 4) {
+          static_cast<float*>(p.out)[off] = r;
+        } else {
+          static_cast<uint16_t*>(p.out)[off] = f32_to_bf16(r);
+        }
       } else {
         float* part = p.partials + (((int64_t)row * p.splits + split) * p.g_real + h) * (D + 2);
         part[d] = o;
@@ -479,7 +508,7 @@ __global__ __launch_bounds__(D) void paged_decode_reduce_kernel(const float* __r
   }
 }
 
-template <int D, int G>
+template <typename T, int D, int G>
 hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
   DecodeParams p;
   p.q = a.q;
@@ -510,11 +539,11 @@ hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
   const dim3 blocks((unsigned)grid), threads(kWaves * kWave);
   if (a.shared) {
     if (a.new_k != nullptr) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((paged_decode_kernel<D, G, false, true>), blocks, threads, 0, stream, p);
+    hipLaunchKernelGGL((paged_decode_kernel<T, D, G, false, true>), blocks, threads, 0, stream, p);
   } else if (a.new_k != nullptr) {
-    hipLaunchKernelGGL((paged_decode_kernel<D, G, true, false>), blocks, threads, 0, stream, p);
+    hipLaunchKernelGGL((paged_decode_kernel<T, D, G, true, false>), blocks, threads, 0, stream, p);
   } else {
-    hipLaunchKernelGGL((paged_decode_kernel<D, G, false, false>), blocks, threads, 0, stream, p);
+    hipLaunchKernelGGL((paged_decode_kernel<T, D, G, false, false>), blocks, threads, 0, stream, p);
   }
   return hipGetLastError();
 }
@@ -522,11 +551,11 @@ hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
 template <int D>
 hipError_t launch_group(const DecodeArgs& a, hipStream_t stream) {
   switch (a.num_q_heads / a.num_kv_heads) {
-    case 1: return launch_one<D, 1>(a, stream);
-    case 2: return launch_one<D, 2>(a, stream);
-    case 3: return launch_one<D, 3>(a, stream);
-    case 4: return launch_one<D, 4>(a, stream);
-    case 5: case 6: case 7: case 8: return launch_one<D, 8>(a, stream);
+    case 1: return launch_one<float, D, 1>(a, stream);
+    case 2: return launch_one<float, D, 2>(a, stream);
+    case 3: return launch_one<float, D, 3>(a, stream);
+    case 4: return launch_one<float, D, 4>(a, stream);
+    case 5: case 6: case 7: case 8: return launch_one<float, D, 8>(a, stream);
     default: return hipErrorInvalidValue;
   }
 }
@@ -547,9 +576,13 @@ size_t decode_partials_bytes(int num_seqs, int num_q_heads, int head_dim, int sp
 hipError_t launch_paged_decode(const DecodeArgs& a, hipStream_t stream) {
   if (a.head_dim != 64 && a.head_dim != 128) return hipErrorInvalidValue;
   const bool d64 = a.head_dim == 64;
-  const hipError_t e = a.is_bf16 ? launch_paged_decode_bf16(a, stream)
-                       : d64     ? launch_group<64>(a, stream)
-                                 : launch_group<128>(a, stream);
+  hipError_t e;
+  if (!a.is_bf16)
+    e = d64 ? launch_group<64>(a, stream) : launch_group<128>(a, stream);
+  else if (a.vector)
+    e = d64 ? launch_one<bf16_t, 64, 1>(a, stream) : launch_one<bf16_t, 128, 1>(a, stream);
+  else
+    e = launch_paged_decode_bf16(a, stream);
   if (e != hipSuccess || a.splits == 1) return e;
   if (a.is_bf16)
     d64 ? launch_reduce<bf16_t, 64>(a, stream) : launch_reduce<bf16_t, 128>(a, stream);

@@ -195,6 +195,16 @@ pe::DecodeArgs decode_args(const pe_cache_desc* desc, int splits) {
   if (desc->decode_shape == 822) a.waves = 8, a.depth = 2;
   a.is_bf16 = desc->dtype == PE_BF16;
   a.shared = shared;
+  // The vector units for bfloat16 rows that are short, of one query head per KV head (vector / matrix kernel, us a launch: D = 64,
+  // 32 rows x 64 / 256 / 448 / 1024 tokens 3.7 / 4.9 / 6.2 / 6.6 and 4.1 / 5.4 / 7.0 / 7.0, 256 rows 4.1 / 5.9 / 7.8 / 12.9 and 4.8
+  // / 6.1 / 8.2 / 12.9; D = 128, 128 rows x 64 / 128 / 192 / 256 3.9 / 4.8 / 5.6 / 6.5 and 4.7 / 5.2 / 6.1 / 6.4; with more rows than
+  // compute units the limits lie lower: 384 rows of D = 64 x 128 / 192 / 448 5.5 / 6.6 / 10.3 and 5.6 / 6.6 / 9.9, of D = 128 x 64
+  // / 128 5.2 / 7.2 and 5.8 / 7.1; in the head-shared layout the matrix kernel is ahead from 64 tokens on, 256 rows of D = 64 4.9
+  // and 4.2).
+  const int64_t tokens = (int64_t)desc->max_blocks * desc->block_size;
+  const bool few = (int64_t)desc->num_seqs * desc->num_kv_heads <= cus;
+  a.vector = a.is_bf16 && !shared && desc->num_q_heads == desc->num_kv_heads &&
+             tokens <= (few ? (d128 ? 192 : 1024) : (d128 ? 64 : 128));
   return a;
 }
 

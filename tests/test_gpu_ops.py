@@ -615,6 +615,50 @@ def test_append_paged_decode_fused(dt, D, B, G):
         desc.decode_splits = 0
 
 
+@pytest.mark.parametrize("D,B,lens", [(64, 16, [1, 15, 16, 17, 33, 63, 64, 65, 129, 300, 511, 513, 1000]),
+                                      (64, 64, [1, 63, 64, 65, 191, 575]), (128, 16, [1, 7, 8, 9, 16, 31, 33, 65, 127, 150]),
+                                      (128, 32, [1, 32, 33, 95, 128])])
+def test_bf16_short_rows_of_one_head(D, B, lens):
+    """Short rows of one query head per KV head, at the edges of tiles (8 and 16 tokens) and rounds, with non-finite junk behind
+    every row's end: attention, and the append in the same launch, whole and in splits.  Tolerance: twice the rounding of the
+    bf16 result, 2^-9."""
+    print("case bf16_short_rows_of_one_head", D, B, flush=True)
+    Hk = 3
+    k_pool, v_pool, table, sl = make_paged(1970 + D + B, lens, Hk, D, B, torch.bfloat16, pad_pages=len(lens) * Hk)
+    S, mb, P = len(lens), table.shape[2], k_pool.shape[0]
+    assert mb * B <= (1024 if D == 64 else 192)   # tables that lead to the vector units
+    for s, L in enumerate(lens):
+        if L % B:
+            for p in table[s, :, L // B].tolist():
+                k_pool[p, L % B:], v_pool[p, L % B:] = float("nan"), float("inf")
+    clean = lambda t: np.nan_to_num(f32(t), nan=0.0, posinf=0.0)
+    used = set(table[table >= 0].tolist())
+    spare = torch.tensor([p for p in range(P) if p not in used], dtype=torch.int32).reshape(S, Hk, 1)
+    g = torch.Generator().manual_seed(1971)
+    q = torch.randn((S, Hk, D), generator=g).to(torch.bfloat16)
+    nk, nv = (torch.randn((S, Hk, D), generator=g).to(torch.bfloat16) for _ in range(2))
+    o = dict(k=clean(k_pool), v=clean(v_pool), t=i32(table).copy(), l=i32(sl).copy())
+    want = [oracle.paged_decode(f32(q), o["k"], o["v"], o["t"], o["l"])]
+    oracle.append_kv(f32(nk), f32(nv), o["k"], o["v"], o["t"], o["l"], np.full((S, Hk), -1, np.int32), i32(spare),
+                     np.zeros((S, Hk), np.int32))
+    want.append(oracle.paged_decode(f32(q), o["k"], o["v"], o["t"], o["l"]))
+    for splits in (0, 1, 3):
+        desc = pe.make_desc(torch.bfloat16, S, Hk, Hk, D, B, mb, P, decode_splits=splits)
+        ws = pe.alloc_workspace(pe.PE_OP_PAGED_DECODE, desc)
+        qd, kd, vd, td, ld, sd, nkd, nvd = (x.to(DEV) for x in (q, k_pool, v_pool, table, sl, spare, nk, nv))
+        fd, ud = (torch.full((S, Hk), x, dtype=torch.int32, device=DEV) for x in (-1, 0))
+        outs = [torch.full(q.shape, 7.0, dtype=torch.bfloat16, device=DEV) for _ in range(2)]
+        ld_out = torch.full_like(ld, -3)
+        pe.pe_paged_decode(desc, qd, kd, vd, td, ld, D ** -0.5, outs[0], ws)
+        pe.pe_append_paged_decode(desc, nkd, nvd, qd, kd, vd, td, ld, ld_out, fd, sd, ud, D ** -0.5, outs[1], ws)
+        torch.cuda.synchronize()
+        for out, w in zip(outs, want):
+            e2, emax = rel_err(f32(out), w)
+            assert e2 <= 2 ** -8 and emax <= 2 ** -8, (splits, e2, emax)
+        assert np.array_equal(td.cpu().numpy(), o["t"]) and np.array_equal(ld_out.cpu().numpy(), o["l"])
+        assert np.array_equal(clean(kd), o["k"]) and np.array_equal(clean(vd), o["v"])
+
+
 @pytest.mark.parametrize("shape", [422, 424, 432, 822])
 def test_bf16_named_shapes(shape):
     """The workgroup forms that a descriptor can name, at the edges of their tiles and rounds: attention, and the append in

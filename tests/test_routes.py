@@ -13,7 +13,7 @@ from paper_2509_04377_amd import build
 STANDINS = r"""
 #include "%s/pe_launch.h"
 namespace pe {
-static int seen[3];
+static int seen[4];
 hipError_t launch_score_blocks(const ScoreArgs&, hipStream_t) { return hipSuccess; }
 hipError_t launch_score_evict(const ScoreEvictArgs&, hipStream_t) { return hipSuccess; }
 hipError_t launch_evict_blocks(const EvictArgs&, hipStream_t) { return hipSuccess; }
@@ -25,6 +25,7 @@ hipError_t launch_paged_decode(const DecodeArgs& a, hipStream_t) {
   seen[0] = a.splits;
   seen[1] = a.waves;
   seen[2] = a.depth;
+  seen[3] = a.vector;
   return hipSuccess;
 }
 }  // namespace pe
@@ -58,6 +59,11 @@ def _form(lib, **kw):
     return tuple(lib.seen_launch()[:3])
 
 
+def _vector(lib, **kw):
+    _form(lib, **kw)
+    return bool(lib.seen_launch()[3])
+
+
 def test_named_shapes_are_forms_of_their_own(host_layer):
     named = [_form(host_layer, decode_shape=s, decode_splits=1) for s in (424, 432, 822)]
     assert named == [(1, 4, 2), (1, 4, 3), (1, 8, 2)]
@@ -75,3 +81,12 @@ def test_named_shapes_are_forms_of_their_own(host_layer):
     (dict(num_seqs=8, decode_splits=2), (2, 4, 2))])
 def test_bf16_form(host_layer, kw, want):
     assert _form(host_layer, **kw) == want
+
+
+@pytest.mark.parametrize("kw,want", [
+    (dict(head_dim=64, max_blocks=64), True), (dict(head_dim=64, max_blocks=65), False), (dict(max_blocks=12), True),
+    (dict(max_blocks=13), False), (dict(num_seqs=33, head_dim=64, max_blocks=8), True), (dict(num_seqs=33, max_blocks=5), False),
+    (dict(num_seqs=33, head_dim=64, max_blocks=9), False), (dict(num_seqs=33, max_blocks=4), True),
+    (dict(num_q_heads=16, max_blocks=4), False), (dict(layout=pe.PE_LAYOUT_SHARED, max_blocks=4), False)])
+def test_bf16_vector_units(host_layer, kw, want):
+    assert _vector(host_layer, **dict(dict(num_q_heads=8), **kw)) is want
