@@ -73,14 +73,27 @@ def parse_args():
 
 
 def kernel_source_hash():
-    """sha256 over the sources that make up the attention kernel; a committed counter summary names the hash of
-    the sources it was measured on, and is only quoted while they are unchanged."""
+    """sha256 over what makes up an attention launch: the kernels' sources, the host layer that chooses their form, and the
+    flags they are built with.  A committed counter summary names the hash of what it was measured on, and is only quoted
+    while that is unchanged."""
     import hashlib
-    h = hashlib.sha256()
-    for name in ("paged_decode_bf16.hip", "paged_decode.hip", "pe_device.h", "pe_launch.h"):
+    from paper_2509_04377_amd import build
+    h = hashlib.sha256(" ".join(build.FLAGS).encode())
+    for name in ("paged_decode_bf16.hip", "paged_decode.hip", "pe_api.hip", "pe_device.h", "pe_launch.h"):
         with open(os.path.join(ROOT, "paper_2509_04377_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
+
+
+def attention_kernels(wl, splits):
+    """The kernels of one attention call, as a kernel trace names them."""
+    if wl.dtype == "f32":
+        name = "paged_decode_kernel"
+    elif wl.num_q_heads > wl.num_kv_heads:
+        name = "paged_decode_bf16_kernel"
+    else:   # the library's choice, by the length of the rows
+        name = "paged_decode_bf16_kernel or paged_decode_kernel"
+    return name + (" + paged_decode_reduce_kernel" if splits > 1 else "")
 
 
 def traffic_from_profiles(workload):
@@ -367,8 +380,7 @@ def run_workload(wl, args, dev, steps, warmup, shared=False, stagger=False, deco
         traffic, traffic_source = traffic_from_profiles(profile_key)
         r["roofline"] = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "traffic_source": traffic_source,
-                         "kernel": "paged_decode_kernel" + (" + paged_decode_reduce_kernel" if r["decode_splits"] > 1
-                                                            else ""),
+                         "kernel": attention_kernels(wl, r["decode_splits"]),
                          "launches_timed": n_launch, "avg_launch_us": avg_dur * 1e6,
                          "algorithmic_bytes_per_launch": avg_bytes}
         # whole-step algorithmic bytes: attention every step + the score sweep on trigger steps
