@@ -251,6 +251,10 @@ int pe_evict_blocks_ex(const pe_cache_desc* desc, const pe_evict_opts* opts, flo
  *     out[s][h][:] = sum_t softmax_t(softmax_scale * <q[s][h], K_t>) V_t over the seq_lens[s] tokens of
  *     row (s, h / (Hq/Hk)), token t being slot t % B of page block_table[s][hk][t / B].
  *     fp32 accumulation, output rounded to desc->dtype.  seq_lens[s] == 0 gives zeros.
+ *     q and the tokens attended to are finite (what lies behind a row's end may be anything).  bf16: an infinity or NaN in
+ *     one of them may reach every element of that row's outputs, not only those it takes part in (the products run over
+ *     several tokens and heads at once, with zeros for those that do not take part, and 0 * inf is NaN).  Finite values give
+ *     finite results as long as the sums over the tokens, relative to the largest weight, fit an fp32.
  *     q, out: [S][Hq][D].  workspace: pe_workspace_bytes(PE_OP_PAGED_DECODE, desc, 0) (split partials).
  *     shared: block_table [S][max_blocks]; query head h reads head h/(Hq/Hk) of the sequence's pages.
  */
