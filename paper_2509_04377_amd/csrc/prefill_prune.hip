@@ -165,8 +165,8 @@ __global__ __launch_bounds__(kThreads) void head_mean_kernel(const float* __rest
 // an MI355X, before (every pass from memory, three more barriers a pass) / now: 64 rows x 4096 scores 10.4 / 6.8 us, 128
 // ragged rows of up to 16384 13.7 / 11.3, 256 x 16384 17.7 / 14.4, 288 ragged rows of up to 6567 14.4 / 11.2 (15.2 with one
 // workgroup a compute unit), 2 x 44000 20.7 / 18.8, 32 x 65536 30.0 / 28.7, 32 x 131072 46.6 / 43.4 (what lies beyond the held
-// scores comes in loads of 16 bytes, four in flight a thread: with loads of 4 bytes 19.9, 32.7 and 51.7; with eight of 16 bytes
-// the short ends of 36000 or 44000 scores take as long again as they save on 131072).
+// scores comes in loads of 16 bytes, four in flight a thread: with loads of 4 bytes 19.9, 32.7 and 51.7; eight of 16 bytes in
+// flight save 0.6 on 131072 and cost 1.3 on rows of 36000 to 44000).
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / kWave;
 constexpr int kSelBins = 4096;
