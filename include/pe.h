@@ -109,7 +109,7 @@ int pe_version(void);
  * when that is set, else the library's choice from the type, the number of rows, the length of a TABLE row (not of the
  * sequences, which the host does not see) and the device's compute units: as many as there is room for with one workgroup per
  * compute unit, fewer for short rows, more for long ones, at most 64, none shorter than 128 tokens nor of rows under 512.  A
- * table that holds little pays for splits without tokens and their merge (measured: up to 4.5 us a call for rows of 64 tokens
+ * table that holds little pays for splits without tokens and their merge (measured: up to 5.2 us a call for rows of 64 tokens
  * in tables of 2048 and more, 2 to 3 us for most shapes): a caller who knows that its rows are short may set 1.
  * (A call that is given a smaller workspace than pe_workspace_bytes() asks for uses fewer, down to one workgroup per
  * compute unit; below that it is refused.)  0 for an invalid desc.  (The compute-unit count is read from the HIP runtime

@@ -83,21 +83,27 @@ int64_t splits_by_length(const pe_cache_desc* d) {
 // KV head), several of its workgroups fit a compute unit, and one without tokens is through early; so the rule asks for an
 // even deal, also of rows of unequal length.  Measured on an MI355X with full tables / ragged ones (37 tokens to all), D = 128,
 // 4 query heads a KV head (8 in brackets), us:
-//   - more rows than compute units stay whole: in four, 264 rows x 1024 take 50.7 and not 55.9, but rows of 64 tokens in the
-//     same table 10.4 and not 7.1, and 320 rows (63.0) and not (60.1);
+//   - somewhat more rows than compute units, of 2048 tokens or more, in four (264 rows x 2048 94 / 72, whole 109 / 95; rows of 64
+//     tokens in that table 10.3 and 7.0), shorter ones whole (320 rows x 1024 56.7 (63.0) in four, 60.9 (60.1) whole);
 //   - from half to three quarters of the compute units, four: 136 rows x 4096 104 / 56 (110 / 60), in two 113 / 69 (110 / 85),
 //     whole 122 / 114 (156 / 152); beyond that, two: 224 rows x 4096 146 / 94 (150 / 98), in four 152 / 83 (160 / 88), whole
 //     142 / 119 (162 / 153);
 //   - from a quarter to half, four or six, two workgroups a compute unit: 88 rows x 2048 35 / 25 (37 / 29), in three 41 / 30
 //     (41 / 35), in two 37 / 35 (48 / 47);
-//   - below, as many as leave no compute unit two workgroups: 40 rows x 2048 in six 18.6 / 17.0, in seven 22.0 / 18.4; with more
+//   - up to an eighth of them, two a compute unit too where pieces of 1 MiB remain (64 rows x 8192 84 / 55 (86 / 59), in four 82 /
+//     67 (92 / 84); rows of 64 tokens in that table 7.6 and 6.6);
+//   - else as many as leave no compute unit two workgroups: 40 rows x 2048 in six 18.6 / 17.0, in seven 22.0 / 18.4; with more
 //     than four query heads as many as leave none without: 48 rows x 4096 in six (42.6 / 37.4), in five (42.3 / 40.0).
 int decode_splits_f32(const pe_cache_desc* d, int64_t rows, int64_t cus) {
-  if (rows >= cus) return 1;
+  if (rows >= cus) return rows > cus && rows * 10 <= cus * 13 && (int64_t)d->max_blocks * d->block_size >= 2048 ? 4 : 1;
   const int64_t fit = cus / rows;
-  int64_t splits = fit >= 4   ? (d->num_q_heads / d->num_kv_heads > 4 ? (cus + rows - 1) / rows : fit)
-                   : fit >= 2 ? 2 * fit
-                              : (rows * 4 <= cus * 3 ? 4 : 2);
+  int64_t splits;
+  if (fit == 1)
+    splits = rows * 4 <= cus * 3 ? 4 : 2;
+  else if (fit < 4 || (fit <= 8 && row_bytes(d) / (2 * fit) >= (1 << 20)))
+    splits = 2 * fit;
+  else
+    splits = d->num_q_heads / d->num_kv_heads > 4 ? (cus + rows - 1) / rows : fit;
   const int64_t by_len = splits_by_length(d);
   if (splits > by_len) splits = by_len;
   return splits > 64 ? 64 : (int)splits;

@@ -148,7 +148,9 @@ def test_workspace_checks():
     (dict(num_seqs=1, num_kv_heads=1, num_q_heads=4, max_blocks=100000), 64),
     (dict(num_seqs=1, num_kv_heads=1, num_q_heads=1, max_blocks=1 << 20), 64),
     (dict(num_seqs=16, head_dim=64, max_blocks=128), 2)] + [(dict(kw, dtype=pe.PE_F32), want) for kw, want in [
-        (dict(num_seqs=33, max_blocks=256), 1), (dict(num_seqs=32, max_blocks=256), 1), (dict(num_seqs=31, max_blocks=256), 2),
+        (dict(num_seqs=33, max_blocks=127), 1), (dict(num_seqs=33, max_blocks=128), 4), (dict(num_seqs=42, max_blocks=256), 1),
+        (dict(num_seqs=8, max_blocks=511), 4), (dict(num_seqs=8, max_blocks=512), 8), (dict(num_seqs=4, max_blocks=1024), 16),
+        (dict(num_seqs=3, max_blocks=4096), 10), (dict(num_seqs=32, max_blocks=256), 1), (dict(num_seqs=31, max_blocks=256), 2),
         (dict(num_seqs=25, max_blocks=32), 2), (dict(num_seqs=24, max_blocks=32), 4), (dict(num_seqs=17, max_blocks=512), 4),
         (dict(num_seqs=17, max_blocks=31), 1), (dict(num_seqs=16, max_blocks=64), 4), (dict(num_seqs=11, max_blocks=64), 4),
         (dict(num_seqs=9, max_blocks=64), 6), (dict(num_seqs=9, max_blocks=32), 4), (dict(num_seqs=8, max_blocks=64), 4),
