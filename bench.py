@@ -79,7 +79,8 @@ def kernel_source_hash():
     import hashlib
     from paper_2509_04377_amd import build
     h = hashlib.sha256(" ".join(build.FLAGS).encode())
-    for name in ("paged_decode_bf16.hip", "paged_decode.hip", "pe_api.hip", "pe_device.h", "pe_launch.h"):
+    for name in ("paged_decode_bf16.hip", "paged_decode.hip", "pe_api.hip", "pe_decode_common.h", "pe_device.h", "pe_launch.h",
+                 "pe_place.h"):
         with open(os.path.join(ROOT, "paper_2509_04377_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]

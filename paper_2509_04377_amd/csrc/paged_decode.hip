@@ -29,8 +29,7 @@
 // The SHARED variant reads the head-shared cache layout: one table row per sequence and pages of
 // [B][Hk][D], so the token rows of this workgroup's head are Hk rows apart (a wave-load is then TPL runs
 // of one row each instead of one contiguous KiB).  Everything after the loads is the same.
-#include "pe_device.h"
-#include "pe_launch.h"
+#include "pe_decode_common.h"
 
 namespace pe {
 namespace {
@@ -54,7 +53,6 @@ struct QSlice<float> {
     v[2] = __uint_as_float(r.z);
     v[3] = __uint_as_float(r.w);
   }
-  __device__ __forceinline__ void zero() { v[0] = v[1] = v[2] = v[3] = 0.f; }
   __device__ __forceinline__ float dot(const uint4& k) const {
     float a = __uint_as_float(k.x) * v[0];
     a = fmaf(__uint_as_float(k.y), v[1], a);
@@ -74,7 +72,6 @@ struct QSlice<bf16_t> {
     v[2] = r.z;
     v[3] = r.w;
   }
-  __device__ __forceinline__ void zero() { v[0] = v[1] = v[2] = v[3] = 0u; }
   static __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c) {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a), __builtin_bit_cast(bf16x2_t, b), c, false);
   }
@@ -121,6 +118,20 @@ __device__ __forceinline__ float row_all_reduce(float v) {
   }
 }
 
+// Over the lanes of a wave that hold the same slice of a token row (every lane gets the total).
+template <int LPR>
+__device__ __forceinline__ float streams_sum(float v) {
+  if constexpr (LPR == 8) v += dpp_f32<0x128>(v);  // row_ror:8
+  if constexpr (LPR == 32) return halves_sum(v);
+  return rows_sum(v);
+}
+template <int LPR>
+__device__ __forceinline__ float streams_max(float v) {
+  if constexpr (LPR == 8) v = fmaxf(v, dpp_f32<0x128>(v));
+  if constexpr (LPR == 32) return halves_max(v);
+  return rows_max(v);
+}
+
 // acc[h][:] *= alpha of head h, which lives on lane position bit_reverse(h) of each GP-lane group.
 template <int G, int GP, int EPL, int H = 0>
 __device__ __forceinline__ void rescale_acc(float (&acc)[G][EPL], float alpha) {
@@ -143,26 +154,6 @@ __device__ __forceinline__ void accumulate_pv(float (&acc)[G][EPL], float prob, 
   }
 }
 
-struct DecodeParams {
-  const void* q;
-  const void* k_pool;
-  const void* v_pool;
-  const int32_t* block_table;
-  const int32_t* seq_lens;
-  void* out;
-  float* partials;
-  float scale_log2e;
-  int num_kv_heads, num_q_heads, max_blocks, log2_block, splits, xcd_map, g_real;
-  // fused append (FUSED kernels only)
-  const void* new_k;
-  const void* new_v;
-  int32_t* freed_phys;
-  const int32_t* spare;
-  int32_t* spare_used;
-  int32_t* seq_lens_out;  // [S], must not alias seq_lens
-  int n_spare;
-};
-
 // Four waves, two register buffers, two wave-loads of K and of V per tile (4 KiB per tile, 8 KiB per wave in flight
 // while it waits): the stream runs fastest at about 8 MiB in flight over the chip.
 constexpr int kWaves = 4, kDepth = 2, kLoads = 2;
@@ -180,29 +171,21 @@ struct Tile {
 
   static_assert(TT <= 16, "a tile lies in one page");
 
-  // Physical page of tile `tile` (scalar load).  The index is clamped to the table row, and an
-  // unused entry (-1, beyond the row's last page) is replaced by page 0: the tokens of such a page are
-  // masked later, so any address inside the pool will do.  Nothing here depends on the row length, so
-  // the first lookup can be issued before the length has arrived.
+  // Table entry of the page of tile `tile` (scalar load).  The index is clamped to the table row; nothing here depends on the
+  // row length, so that the first lookup can be issued before the length has arrived.
   static __device__ __forceinline__ int lookup(int tile, const int32_t* bt, int max_blocks, int log2_block) {
     int pi = (tile * TT) >> log2_block;
     pi = pi < max_blocks ? pi : max_blocks - 1;
-    const int ph = __builtin_amdgcn_readfirstlane(bt[pi]);
-    return ph < 0 ? 0 : ph;
+    return __builtin_amdgcn_readfirstlane(bt[pi]);
   }
 
-  // Issue the 2*NLT wave-loads of tile `tile`, whose page was looked up one step earlier (the table
-  // access is off the critical path of the loads).  `lane_off` is the lane id, or 0 in every lane for a
-  // placeholder issue whose data is never used (all lanes then fetch the same 16 bytes): issues stay
-  // unconditional, which keeps the order of outstanding loads known at compile time, so waiting for the
-  // oldest tile leaves the younger ones in flight.
-  static __device__ __forceinline__ void issue(uint4 (&kb)[NLT], uint4 (&vb)[NLT], int tile, int phys, const T* k_pool,
-                                               const T* v_pool, int log2_block, int lane_off, int row_vecs) {
-    const int tok0 = tile * TT;
+  // Issue the 2*NLT wave-loads of the tile whose first row lies at 16-byte vector `base`; its page was looked up one step
+  // earlier (the table access is off the critical path of the loads).  `lane_off` is the lane's place inside a wave-load.
+  static __device__ __forceinline__ void issue(uint4 (&kb)[NLT], uint4 (&vb)[NLT], int64_t base, const T* k_pool,
+                                               const T* v_pool, int lane_off, int row_vecs) {
 #pragma unroll
     for (int i = 0; i < NLT; ++i) {
-      const int slot0 = (tok0 + i * TPL) & ((1 << log2_block) - 1);
-      const int64_t vec = (((int64_t)phys << log2_block) + slot0) * row_vecs + lane_off;
+      const int64_t vec = base + i * TPL * row_vecs + lane_off;
       kb[i] = load_vec_stream(k_pool, vec);
       vb[i] = load_vec_stream(v_pool, vec);
     }
@@ -258,19 +241,16 @@ struct Tile {
 };
 
 template <typename T, int D, int G, bool FUSED, bool SHARED>
-__global__ __launch_bounds__(kWaves * kWave) void paged_decode_kernel(const DecodeParams p) {
+__global__ __launch_bounds__(kWaves * kWave) void paged_decode_kernel(
+    const int32_t* seq_lens, const int32_t* block_table, const void* q, const void* k_pool_p, const void* v_pool_p,
+    const int num_kv_heads, const int max_blocks, const uint32_t inv_heads, const uint32_t shape, const DecodeParams) {
   static_assert(!(FUSED && SHARED), "the fused append is per-head only");
   using TL = Tile<T, D, G>;
   constexpr int WAVES = kWaves, DEPTH = kDepth;
-  constexpr int EPL = TL::EPL, LPR = TL::LPR, TPL = TL::TPL, NLT = TL::NLT, TT = TL::TT, GP = TL::GP;
+  constexpr int EPL = TL::EPL, LPR = TL::LPR, NLT = TL::NLT, TT = TL::TT, GP = TL::GP;
   constexpr int GBITS = ilog2(GP);
-  constexpr int NCONTRIB = WAVES * TPL;
 
-  constexpr int HC = G < 4 ? G : 4;  // heads merged per LDS pass
-  __shared__ float sm_m[NCONTRIB][GP];
-  __shared__ float sm_l[NCONTRIB][GP];
-  __shared__ float sm_ML[G][2];
-  __shared__ __attribute__((aligned(16))) float sm_acc[NCONTRIB][HC][D];
+  __shared__ WaveStates<WAVES, GP, D> sm;
 
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
@@ -278,64 +258,69 @@ __global__ __launch_bounds__(kWaves * kWave) void paged_decode_kernel(const Deco
   const int grp = lane / LPR;  // which token row of a wave-load
   const int c_lane = bit_reverse<GBITS>(lane & (GP - 1));
 
-  int row, split;
-  {
-    const int b = (int)blockIdx.x;
-    if (p.xcd_map) {  // workgroup b runs on XCD b % 8: keep all splits of a row on one XCD
-      const int xcd = b & 7, k = b >> 3;
-      row = (k / p.splits) * 8 + xcd;
-      split = k % p.splits;
-    } else {
-      row = b / p.splits;
-      split = b % p.splits;
-    }
-  }
-  const int s = row / p.num_kv_heads;
-  const int hk = row % p.num_kv_heads;
+  const int log2_block = shape_log2_block(shape), g_real = shape_group(shape), splits = shape_splits(shape);
+  const int num_q_heads = num_kv_heads * g_real;
+  const Place at = decode_place(shape, num_kv_heads, inv_heads);
+  const int row = at.row, split = at.split, s = at.seq, hk = at.head;
   // SHARED: one table row per sequence; a page holds [B][Hk][D], so consecutive tokens of this head are
   // Hk rows apart and a lane's offset inside a wave-load carries the head
-  const int32_t* bt = p.block_table + (int64_t)(SHARED ? s : row) * p.max_blocks;
-  const int row_vecs = SHARED ? LPR * p.num_kv_heads : LPR;
-  const int lane_vec = SHARED ? (grp * p.num_kv_heads + hk) * LPR + u : lane;
-  const T* k_pool = static_cast<const T*>(p.k_pool);
-  const T* v_pool = static_cast<const T*>(p.v_pool);
+  const int32_t* bt = block_table + (int64_t)(SHARED ? s : row) * max_blocks;
 
-  // ---- prologue: everything that does not depend on the row length is requested first --------------
-  // query slices: slot i holds head (i ^ c_lane) of this KV head's group (heads past the group: zeros)
+  // ---- prologue: page lookups and the length first, then K and V, and everything else behind them ----
+  // The row's tiles are dealt out round-robin: tile t belongs to split (t / WAVES) % splits, wave t % WAVES.  A
+  // wave's first tile is therefore the same whatever the row length, and the lookup of its page travels
+  // together with the length itself instead of waiting for it (one dependent round trip to memory less).
+  const int stride = splits * WAVES;
+  const int first = split * WAVES + wave;
+  int phys[DEPTH];
+#pragma unroll
+  for (int d = 0; d < DEPTH; ++d) phys[d] = TL::lookup(first + d * stride, bt, max_blocks, log2_block);
+  const int len_pool = seq_lens[s];  // tokens that are read from the pool
+  __builtin_amdgcn_sched_barrier(0);
+
+  const int row_vecs = SHARED ? LPR * num_kv_heads : LPR;
+  const int lane_vec = SHARED ? (grp * num_kv_heads + hk) * LPR + u : lane;
+  const T* k_pool = static_cast<const T*>(k_pool_p);
+  const T* v_pool = static_cast<const T*>(v_pool_p);
+  const int ntiles = (len_pool + TT - 1) >> ilog2(TT);
+  // Loads are issued unconditionally, past the row's end all lanes fetch the pool's first 16 bytes: the order of outstanding
+  // loads is known at compile time, so that waiting for the oldest tile leaves the younger ones in flight.
+  const auto issue = [&](uint4(&kb)[NLT], uint4(&vb)[NLT], int tile, int ph) {
+    // (an unused entry, -1, is replaced by page 0: its tokens are masked, so any address inside the pool will do)
+    const int64_t there = (((int64_t)(ph < 0 ? 0 : ph) << log2_block) + ((tile * TT) & ((1 << log2_block) - 1))) * row_vecs;
+    const bool in = tile < ntiles;
+    TL::issue(kb, vb, in ? there : 0, k_pool, v_pool, in ? lane_vec : 0, in ? row_vecs : 0);
+  };
+  uint4 kb[DEPTH][NLT], vb[DEPTH][NLT];
+#pragma unroll
+  for (int d = 0; d < DEPTH - 1; ++d) issue(kb[d], vb[d], first + d * stride, phys[d]);
+  __builtin_amdgcn_sched_barrier(0);
+  // query slices: slot i holds head (i ^ c_lane) of this KV head's group (heads past the group: head 0 again, never written)
   QSlice<T> qs[GP];
 #pragma unroll
   for (int i = 0; i < GP; ++i) {
     const int head = i ^ c_lane;
-    const int head_ld = head < p.g_real ? head : 0;
-    qs[i].load(static_cast<const T*>(p.q) + ((int64_t)s * p.num_q_heads + hk * p.g_real + head_ld) * D + u * EPL);
+    const int head_ld = head < g_real ? head : 0;
+    qs[i].load(static_cast<const T*>(q) + ((int64_t)s * num_q_heads + hk * g_real + head_ld) * D + u * EPL);
   }
+  const DecodeParams p = decode_params(phys[0] ^ ntiles);
   uint4 nk[1], nv[1];  // FUSED: the new token's K/V rows, held by the first lane group of every wave
   if constexpr (FUSED) {
     const int64_t vec = (int64_t)row * LPR + u;
     nk[0] = load_vec(p.new_k, vec);
     nv[0] = load_vec(p.new_v, vec);
   }
-  // The row's tiles are dealt out round-robin: tile t belongs to split (t / WAVES) % splits, wave t % WAVES.  A
-  // wave's first tile is therefore the same whatever the row length, and the lookup of its page travels
-  // together with the length itself instead of waiting for it (one dependent round trip to memory less).
-  const int stride = p.splits * WAVES;
-  const int first = split * WAVES + wave;
-  int phys = TL::lookup(first, bt, p.max_blocks, p.log2_block);
-  const int len_pool = p.seq_lens[s];               // tokens that are read from the pool
-  const int len = FUSED ? len_pool + 1 : len_pool;  // tokens attended to
-#pragma unroll
-  for (int i = 0; i < GP; ++i)
-    if ((i ^ c_lane) >= p.g_real) qs[i].zero();
-  // FUSED: requests for what the append needs, issued now and used after the main loop
-  const bool appender = FUSED && split == p.splits - 1 && wave == WAVES - 1;  // wave-uniform
-  int ap_freed = -1, ap_used = 0;
+  // FUSED: requests for what the append needs, issued now and used at the end
+  const bool appender = FUSED && split == splits - 1 && wave == WAVES - 1;  // wave-uniform
+  const int jb = len_pool >> log2_block;
+  int ap_freed = -1, ap_used = 0, ap_page = -1;
   if constexpr (FUSED) {
     if (appender) {
       ap_freed = p.freed_phys[row];
       ap_used = p.spare_used[row];
+      ap_page = bt[jb < 0 ? 0 : jb < max_blocks ? jb : max_blocks - 1];
     }
   }
-  const int ntiles = (len_pool + TT - 1) / TT;
 
   float m_run = kNegInf;  // running max of head c_lane over this lane's stream of tokens
   float l_run = 0.f;
@@ -345,146 +330,81 @@ __global__ __launch_bounds__(kWaves * kWave) void paged_decode_kernel(const Deco
 #pragma unroll
     for (int e = 0; e < EPL; ++e) acc[h][e] = 0.f;
 
-  // This wave's tiles are first + i*stride, i = 0 .. n_mine-1.  DEPTH register buffers: while tile i is
-  // consumed, tiles i+1 .. i+DEPTH-1 are in flight.
-  const int n_mine = first < ntiles ? (ntiles - first + stride - 1) / stride : 0;
-  if (n_mine > 0) {
-    uint4 kb[DEPTH][NLT], vb[DEPTH][NLT];
-    const auto tile_at = [&](int i) { return first + (i < n_mine ? i : n_mine - 1) * stride; };
+  // This wave's tiles are first, first + stride, ... < ntiles.  DEPTH register buffers: while a tile is consumed, the next
+  // DEPTH - 1 are in flight.
+  int ph_next = phys[DEPTH - 1];
+  for (int tile0 = first; tile0 < ntiles; tile0 += DEPTH * stride) {
 #pragma unroll
-    for (int d = 0; d < DEPTH - 1; ++d) {
-      TL::issue(kb[d], vb[d], tile_at(d), phys, k_pool, v_pool, p.log2_block, d < n_mine ? lane_vec : 0, row_vecs);
-      phys = TL::lookup(tile_at(d + 1), bt, p.max_blocks, p.log2_block);
-    }
-    for (int i = 0; i < n_mine; i += DEPTH) {
-#pragma unroll
-      for (int ph = 0; ph < DEPTH; ++ph) {
-        const int ahead = i + ph + DEPTH - 1;
-        TL::issue(kb[(ph + DEPTH - 1) % DEPTH], vb[(ph + DEPTH - 1) % DEPTH], tile_at(ahead), phys, k_pool, v_pool,
-                  p.log2_block, ahead < n_mine ? lane_vec : 0, row_vecs);
-        phys = TL::lookup(tile_at(ahead + 1), bt, p.max_blocks, p.log2_block);
-        if (i + ph < n_mine) {
-          TL::template compute<NLT>(kb[ph], vb[ph], (first + (i + ph) * stride) * TT, len_pool, grp, p.scale_log2e, qs,
-                                    m_run, l_run, acc);
-        }
-      }
+    for (int d = 0; d < DEPTH; ++d) {
+      const int tile = tile0 + d * stride, ahead = tile + (DEPTH - 1) * stride;
+      issue(kb[(d + DEPTH - 1) % DEPTH], vb[(d + DEPTH - 1) % DEPTH], ahead, ph_next);
+      ph_next = TL::lookup(ahead + stride, bt, max_blocks, log2_block);
+      if (tile < ntiles)
+        TL::template compute<NLT>(kb[d], vb[d], tile * TT, len_pool, grp, p.scale_log2e, qs, m_run, l_run, acc);
     }
   }
 
-  if constexpr (FUSED) {
-    // the new token is token number len_pool of the row: wave 0 of the last split attends to it from
-    // registers ...
-    if (split == p.splits - 1 && wave == 0)
+  if constexpr (FUSED) {  // the new token is token number len_pool of the row: wave 0 of the last split attends to it
+    if (split == splits - 1 && wave == 0)
       TL::template compute<1>(nk, nv, len_pool, len_pool + (grp == 0 ? 1 : 0), 0, p.scale_log2e, qs, m_run, l_run, acc);
-    // ... and the first lane group of its last wave stores it into the pool, linking a new page first when
-    // the tail page is full (the page freed by the eviction just before, else the next spare)
+  }
+
+  // ---- merge: the token streams of a wave (lanes that hold the same slice) in registers, then the waves through LDS -----
+  const float m_wave = streams_max<LPR>(m_run);
+  const float f = __builtin_amdgcn_exp2f(m_run - (m_wave == kNegInf ? 0.f : m_wave));
+  const float l_wave = streams_sum<LPR>(l_run * f);
+  rescale_acc<G, GP, EPL>(acc, f);
+#pragma unroll
+  for (int h = 0; h < G; ++h)
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) acc[h][e] = streams_sum<LPR>(acc[h][e]);
+  if (grp == 0) {
+    if (u < GP) sm.ml[wave][c_lane] = make_float2(m_wave, l_wave);
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      float4* dst = reinterpret_cast<float4*>(&sm.acc[wave][h][u * EPL]);
+#pragma unroll
+      for (int e = 0; e < EPL; e += 4) dst[e / 4] = make_float4(acc[h][e], acc[h][e + 1], acc[h][e + 2], acc[h][e + 3]);
+    }
+  }
+  __syncthreads();
+  merge_waves<T>(sm, p, row, split, splits, g_real);
+
+  // FUSED: the first lane group of the last split's last wave stores the new token into the pool, linking a new page first when
+  // the tail page is full.  Last of all, so that nothing of this launch waits for a store.
+  if constexpr (FUSED) {
     if (appender) {
-      const int B = 1 << p.log2_block;
-      const int slot = len_pool & (B - 1);
-      const int jb = len_pool >> p.log2_block;
-      if (len_pool >= 0 && jb < p.max_blocks) {  // a length outside the table row is a caller error: touch nothing
-        int page;
-        if (slot == 0) {
-          page = ap_freed;
-          if (page < 0) {
-            page = ap_used < p.n_spare ? p.spare[(int64_t)row * p.n_spare + ap_used] : -1;
-            if (lane == 0) p.spare_used[row] = ap_used + 1;
-          } else if (lane == 0) {
-            p.freed_phys[row] = -1;
-          }
-          if (lane == 0) const_cast<int32_t*>(bt)[jb] = page;
-        } else {
-          page = bt[jb];
-        }
+      const int slot = len_pool & ((1 << log2_block) - 1);
+      if (len_pool >= 0 && jb < max_blocks) {  // a length outside the table row is a caller error: touch nothing
+        const int page = slot == 0 ? link_page(p, const_cast<int32_t*>(bt), jb, row, ap_freed, ap_used, lane) : ap_page;
         if (page >= 0 && grp == 0) {
-          const int64_t vec = (((int64_t)page << p.log2_block) + slot) * LPR + u;
-          reinterpret_cast<uint4*>(const_cast<void*>(p.k_pool))[vec] = nk[0];
-          reinterpret_cast<uint4*>(const_cast<void*>(p.v_pool))[vec] = nv[0];
+          const int64_t vec = (((int64_t)page << log2_block) + slot) * LPR + u;
+          reinterpret_cast<uint4*>(const_cast<void*>(k_pool_p))[vec] = nk[0];
+          reinterpret_cast<uint4*>(const_cast<void*>(v_pool_p))[vec] = nv[0];
         }
       }
       if (hk == 0 && lane == 0) p.seq_lens_out[s] = len_pool + 1;
     }
   }
-
-  // ---- merge the WAVES x TPL token streams of this workgroup through LDS ------------------------------
-  // (1) every stream publishes its (m, l) per head; (2) one thread per head folds them into the row's
-  // (M, L); (3) every lane rescales its accumulators to M and publishes them, up to four heads per pass;
-  // (4) all threads sum the streams and write the output (or the split partial).
-  const int contrib = wave * TPL + grp;
-  if (u < GP) {
-    sm_m[contrib][c_lane] = m_run;
-    sm_l[contrib][c_lane] = l_run;
-  }
-  __syncthreads();
-  if ((int)threadIdx.x < G) {
-    const int h = (int)threadIdx.x;
-    float mm = kNegInf;
-    for (int c = 0; c < NCONTRIB; ++c) mm = fmaxf(mm, sm_m[c][h]);
-    const float ms = mm == kNegInf ? 0.f : mm;
-    float ll = 0.f;
-    for (int c = 0; c < NCONTRIB; ++c) ll = fmaf(sm_l[c][h], __builtin_amdgcn_exp2f(sm_m[c][h] - ms), ll);
-    sm_ML[h][0] = mm;
-    sm_ML[h][1] = ll;
-  }
-  __syncthreads();
+  // The placeholder loads behind a wave's last tile are still on their way during the merge; their registers are in use until
+  // here, so that nothing there waits for them.
 #pragma unroll
-  for (int h0 = 0; h0 < G; h0 += HC) {
-    if (h0 > 0) __syncthreads();  // the previous pass has been read
+  for (int d = 0; d < DEPTH; ++d)
 #pragma unroll
-    for (int hh = 0; hh < HC; ++hh) {
-      const int h = h0 + hh;
-      if (h < G) {
-        const float mm = sm_ML[h][0];
-        const float ms = mm == kNegInf ? 0.f : mm;
-        const float f = __builtin_amdgcn_exp2f(sm_m[contrib][h] - ms);
-        float4* dst = reinterpret_cast<float4*>(&sm_acc[contrib][hh][u * EPL]);
-#pragma unroll
-        for (int e = 0; e < EPL; e += 4)
-          dst[e / 4] = make_float4(acc[h][e] * f, acc[h][e + 1] * f, acc[h][e + 2] * f, acc[h][e + 3] * f);
-      }
+    for (int i = 0; i < NLT; ++i) {
+      asm volatile("" : : "v"(kb[d][i].x), "v"(kb[d][i].y), "v"(kb[d][i].z), "v"(kb[d][i].w));
+      asm volatile("" : : "v"(vb[d][i].x), "v"(vb[d][i].y), "v"(vb[d][i].z), "v"(vb[d][i].w));
     }
-    __syncthreads();
-    for (int idx = (int)threadIdx.x; idx < HC * D; idx += WAVES * kWave) {
-      const int hh = idx / D, d = idx % D;
-      const int h = h0 + hh;
-      if (h >= p.g_real) continue;
-      const float mm = sm_ML[h][0], ll = sm_ML[h][1];
-      float o = 0.f;
-#pragma unroll 8
-      for (int c = 0; c < NCONTRIB; ++c) o += sm_acc[c][hh][d];
-      if (p.splits == 1) {
-        const float r = ll > 0.f ? o / ll : 0.f;
-        const int64_t off = ((int64_t)s * p.num_q_heads + hk * p.g_real + h) * D + d;
-        if constexpr (sizeof(T) == 4) {
-          static_cast<float*>(p.out)[off] = r;
-        } else {
-          static_cast<uint16_t*>(p.out)[off] = f32_to_bf16(r);
-        }
-      } else {
-        float* part = p.partials + (((int64_t)row * p.splits + split) * p.g_real + h) * (D + 2);
-        part[d] = o;
-        if (d == 0) {
-          part[D] = mm;
-          part[D + 1] = ll;
-        }
-      }
-    }
-  }
 }
 
 // Merge the split partials of one (sequence, query head): one workgroup of D threads.
 template <typename T, int D>
 __global__ __launch_bounds__(D) void paged_decode_reduce_kernel(const float* __restrict__ partials,
-                                                                void* __restrict__ out, int num_kv_heads, int g_real,
-                                                                int splits) {
+                                                                void* __restrict__ out, int total_heads, int splits) {
   const int sh = (int)blockIdx.x;  // s * Hq + hq
-  const int num_q_heads = num_kv_heads * g_real;
-  const int s = sh / num_q_heads, hq = sh % num_q_heads;
-  const int row = s * num_kv_heads + hq / g_real;
-  const int h = hq % g_real;
   const int d = (int)threadIdx.x;
-  const float* base = partials + (((int64_t)row * splits) * g_real + h) * (D + 2);
-  const int64_t stride = (int64_t)g_real * (D + 2);
+  const float* base = partials + (int64_t)sh * (D + 2);
+  const int64_t stride = (int64_t)total_heads * (D + 2);
   // one pass, online: all loads are independent of the running state, so they overlap
   float mm = kNegInf, o = 0.f, l = 0.f;
 #pragma unroll 4
@@ -510,41 +430,16 @@ __global__ __launch_bounds__(D) void paged_decode_reduce_kernel(const float* __r
 
 template <typename T, int D, int G>
 hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
-  DecodeParams p;
-  p.q = a.q;
-  p.k_pool = a.k_pool;
-  p.v_pool = a.v_pool;
-  p.block_table = a.block_table;
-  p.seq_lens = a.seq_lens;
-  p.out = a.out;
-  p.partials = a.partials;
-  p.scale_log2e = a.scale * 1.4426950408889634f;
-  p.num_kv_heads = a.num_kv_heads;
-  p.num_q_heads = a.num_q_heads;
-  p.max_blocks = a.max_blocks;
-  p.log2_block = ilog2(a.block_size);
-  p.splits = a.splits;
-  p.g_real = a.num_q_heads / a.num_kv_heads;
-  p.new_k = a.new_k;
-  p.new_v = a.new_v;
-  p.freed_phys = a.freed_phys;
-  p.spare = a.spare;
-  p.spare_used = a.spare_used;
-  p.seq_lens_out = a.seq_lens_out;
-  p.n_spare = a.n_spare;
-  const int64_t rows = (int64_t)a.num_seqs * a.num_kv_heads;
-  p.xcd_map = (a.xcd_map && rows % 8 == 0) ? 1 : 0;
-  const int64_t grid = rows * a.splits;
-  if (grid <= 0 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
-  const dim3 blocks((unsigned)grid), threads(kWaves * kWave);
-  if (a.shared) {
-    if (a.new_k != nullptr) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((paged_decode_kernel<T, D, G, false, true>), blocks, threads, 0, stream, p);
-  } else if (a.new_k != nullptr) {
-    hipLaunchKernelGGL((paged_decode_kernel<T, D, G, true, false>), blocks, threads, 0, stream, p);
-  } else {
-    hipLaunchKernelGGL((paged_decode_kernel<T, D, G, false, false>), blocks, threads, 0, stream, p);
-  }
+  DecodeKernelArgs k;
+  dim3 blocks;
+  if (!decode_kernel_args(a, &k, &blocks)) return hipErrorInvalidValue;
+  const dim3 threads(kWaves * kWave);
+  if (a.shared && a.new_k != nullptr) return hipErrorInvalidValue;
+  const auto kernel = a.shared             ? paged_decode_kernel<T, D, G, false, true>
+                      : a.new_k != nullptr ? paged_decode_kernel<T, D, G, true, false>
+                                           : paged_decode_kernel<T, D, G, false, false>;
+  hipLaunchKernelGGL(kernel, blocks, threads, 0, stream, k.seq_lens, k.block_table, k.q, k.k_pool, k.v_pool, k.num_kv_heads,
+                     k.max_blocks, k.inv_heads, k.shape, k.p);
   return hipGetLastError();
 }
 
@@ -563,7 +458,7 @@ hipError_t launch_group(const DecodeArgs& a, hipStream_t stream) {
 template <typename T, int D>
 void launch_reduce(const DecodeArgs& a, hipStream_t stream) {
   hipLaunchKernelGGL((paged_decode_reduce_kernel<T, D>), dim3((unsigned)(a.num_seqs * a.num_q_heads)), dim3(D), 0, stream,
-                     a.partials, a.out, a.num_kv_heads, a.num_q_heads / a.num_kv_heads, a.splits);
+                     a.partials, a.out, a.num_seqs * a.num_q_heads, a.splits);
 }
 
 }  // namespace

@@ -45,8 +45,7 @@
 // SHARED reads the head-shared cache layout: one table row per sequence and pages of [B][Hk][D], so the token rows of
 // this workgroup's head are Hk rows apart.  (FUSED there took the place of an append launch in front of the attention:
 // 32 sequences x 8 heads x 2048 tokens 45.7 us a layer in two launches, 43.6 in one; 8 x 4 x 2304 13.9 and 11.1.)
-#include "pe_device.h"
-#include "pe_launch.h"
+#include "pe_decode_common.h"
 
 namespace pe {
 namespace {
@@ -59,10 +58,6 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-
-struct __attribute__((packed, aligned(2))) Pair {  // two bf16 at any 2-byte boundary, in one store
-  uint32_t v;
-};
 
 template <int CTRL>
 __device__ __forceinline__ float quad_perm_add(float v) {
@@ -77,23 +72,6 @@ __device__ __forceinline__ float pick4(const f32x4_t& v, bool b0, bool b1) {
   const float hi = b0 ? v[3] : v[2];
   return b1 ? hi : lo;
 }
-
-// Kernel arguments besides the leading ones, which are what a wave needs before its first K/V load (14 registers' worth: the
-// compiler's kernel-argument preloading puts them into scalar registers before the wave starts, and the page lookup does
-// not wait for a load of them.  Layer launches of the 1B shape 8.70 / 8.52 us, 8B long context 17.9 / 17.4, 8B 44.9 / 44.7).
-struct Params {
-  void* out;
-  float* partials;
-  float scale_log2e;
-  // fused append (FUSED kernels only)
-  int n_spare;
-  const void* new_k;
-  const void* new_v;
-  int32_t* freed_phys;
-  const int32_t* spare;
-  int32_t* spare_used;
-  int32_t* seq_lens_out;  // [S], must not alias seq_lens
-};
 
 // One wave's view of a tile.  HG: groups of four query heads (G <= 4: 1, G <= 8: 2).
 template <int D, int HG>
@@ -141,8 +119,7 @@ struct Tile {
   // Move the reference m_run of a head group above the logits of this tile, where one of them exceeds it.  m_ref is the
   // same, but finite before the first logit (-inf - -inf is no number).
   static __device__ __forceinline__ void regrow(float mx, float& m_run, float& m_ref, float& l_run, f32x4_t (&acc)[8]) {
-    mx = fmaxf(mx, lane_xor_f32<16>(mx));
-    mx = fmaxf(mx, lane_xor_f32<32>(mx));
+    mx = rows_max(mx);
     const float m_new = mx > m_run ? mx + kGrow : m_run;
     const float ref = m_new == kNegInf ? 0.f : m_new;
     const float alpha = __builtin_amdgcn_exp2f(m_run - ref);
@@ -197,14 +174,12 @@ struct Tile {
   }
 };
 
-// Physical page of tile `tile` of a table row (scalar load).  The index is clamped to the row and an unused entry (-1,
-// beyond the row's last page) is replaced by page 0: its tokens are masked later, so any address inside the pool
-// will do, and nothing here depends on the row length.
+// Table entry of the page of tile `tile` of a row (scalar load).  The index is clamped to the row; nothing here depends on
+// the row length.
 __device__ __forceinline__ int lookup(const int32_t* bt, int tile, int max_blocks, int log2_block) {
   int pi = (tile * kTile) >> log2_block;
   pi = pi < max_blocks ? pi : max_blocks - 1;
-  const int ph = __builtin_amdgcn_readfirstlane(bt[pi]);
-  return ph < 0 ? 0 : ph;
+  return __builtin_amdgcn_readfirstlane(bt[pi]);
 }
 
 template <int D, int HG, int WAVES, int DEPTH, bool FUSED, bool SHARED>
@@ -212,35 +187,33 @@ template <int D, int HG, int WAVES, int DEPTH, bool FUSED, bool SHARED>
 // vector registers instead of moving them to and from accumulation registers in every step)
 __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(
     const int32_t* seq_lens, const int32_t* block_table, const void* q, const void* k_pool, const void* v_pool,
-    const int num_kv_heads, const int max_blocks, const int splits, const uint32_t shape, const Params p) {
+    const int num_kv_heads, const int max_blocks, const uint32_t inv_heads, const uint32_t shape, const DecodeParams) {
   using TL = Tile<D, HG>;
   constexpr int LPR = TL::LPR, TPL = TL::TPL, NL = TL::NL, NT = TL::NT;
   constexpr int GH = 4 * HG;  // heads computed; g_real of them exist
 
-  __shared__ float sm_ml[WAVES][GH][2];
-  __shared__ __attribute__((aligned(16))) float sm_acc[WAVES][GH][D];
+  __shared__ WaveStates<WAVES, GH, D> sm;
 
-  const int log2_block = (int)(shape & 0xffu), g_real = (int)(shape >> 8 & 0xffu), num_q_heads = num_kv_heads * g_real;
+  const int log2_block = shape_log2_block(shape), g_real = shape_group(shape), splits = shape_splits(shape);
+  const int num_q_heads = num_kv_heads * g_real;
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int g = lane >> 4, m = lane & 15, c = lane & 3;
 
-  int row, split;
-  {
-    const int b = (int)blockIdx.x;
-    if (shape >> 16) {  // workgroup b runs on XCD b % 8: keep all splits of a row on one XCD
-      const int xcd = b & 7, k = b >> 3;
-      row = (k / splits) * 8 + xcd;
-      split = k % splits;
-    } else {
-      row = b / splits;
-      split = b % splits;
-    }
-  }
-  const int s = row / num_kv_heads;
-  const int hk = row % num_kv_heads;
+  const Place at = decode_place(shape, num_kv_heads, inv_heads);
+  const int row = at.row, split = at.split, s = at.seq, hk = at.head;
   const int table_row = SHARED ? s : row;
   const int32_t* bt = block_table + (int64_t)table_row * max_blocks;
+
+  // ---- prologue: everything that does not depend on the row length is requested first --------------
+  const int stride = splits * WAVES;
+  const int first = split * WAVES + wave;
+  int phys[DEPTH + 1];
+#pragma unroll
+  for (int d = 0; d <= DEPTH; ++d) phys[d] = lookup(bt, first + d * stride, max_blocks, log2_block);
+  const int len_pool = seq_lens[s];                                // tokens that are read from the pool
+  const int len = FUSED ? len_pool + 1 : len_pool;  // tokens attended to
+  __builtin_amdgcn_sched_barrier(0);  // (what follows, some sixty instructions, runs while they travel)
 
   TL tl;
   tl.k_pool = static_cast<const u32x4_t*>(k_pool);
@@ -263,45 +236,22 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(
   tl.k_off = tl.k_tok * tl.row_vecs + (SHARED ? hk * LPR : 0) + k_slice;
   tl.v_off = tl.v_tok * tl.row_vecs + (SHARED ? hk * LPR : 0) + v_slice;
 
-  // ---- prologue: everything that does not depend on the row length is requested first --------------
-  const int stride = splits * WAVES;
-  const int first = split * WAVES + wave;
-  int phys[DEPTH + 1];
-#pragma unroll
-  for (int d = 0; d <= DEPTH; ++d) phys[d] = lookup(bt, first + d * stride, max_blocks, log2_block);
-  const int len_pool = seq_lens[s];                 // tokens that are read from the pool
-  const int len = FUSED ? len_pool + 1 : len_pool;  // tokens attended to
-  // query operand: column n = 4*h + c holds the class-c slices of head h (heads past the group: zeros)
-  bf16x8_t qop[HG][NT];
-#pragma unroll
-  for (int hg = 0; hg < HG; ++hg) {
-    const int h = 4 * hg + (m >> 2);
-    const int64_t head = (int64_t)s * num_q_heads + hk * g_real + (h < g_real ? h : 0);
-    const u32x4_t raw = static_cast<const u32x4_t*>(q)[head * LPR + k_slice];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const u32x4_t zero = {0u, 0u, 0u, 0u};
-      const bool in = h < g_real && (NT == 1 || (g >> 1) == t);
-      qop[hg][t] = __builtin_bit_cast(bf16x8_t, in ? raw : zero);
-    }
-  }
-  u32x4_t nk = {0u, 0u, 0u, 0u}, nv = {0u, 0u, 0u, 0u};  // FUSED: the new token's K/V rows
-  int ap_freed = -1, ap_used = 0;
-  if constexpr (FUSED) {
-    nk = static_cast<const u32x4_t*>(p.new_k)[(int64_t)row * LPR + k_slice];
-    nv = static_cast<const u32x4_t*>(p.new_v)[(int64_t)row * LPR + v_slice];
-    ap_freed = p.freed_phys[table_row];
-    ap_used = p.spare_used[table_row];
-  }
-  int ap_page = -1;  // the tail page, where it is not full
-  if constexpr (FUSED) {
-    const int jb = len_pool >> log2_block;
-    ap_page = bt[jb < 0 ? 0 : jb < max_blocks ? jb : max_blocks - 1];
-  }
-  const int ntiles = (len + kTile - 1) / kTile;
-  const int n_mine = first < ntiles ? (ntiles - first + stride - 1) / stride : 0;
+  const int ntiles = (len + kTile - 1) >> ilog2(kTile);
   const int block_mask = (1 << log2_block) - 1;
 
+  // This wave's tiles are first, first + stride, ... < ntiles.  DEPTH tiles are in flight: as soon as the K (V) registers of
+  // a tile have been used, the K (V) loads of the tile DEPTH further on go out into them.  Loads are issued
+  // unconditionally, past the end all lanes fetch the same 16 bytes: the order of outstanding loads is known at
+  // compile time, so that waiting for the oldest leaves the younger ones in flight.
+  // (an unused entry, -1, is replaced by page 0: its tokens are masked, so any address inside the pool will do)
+  const auto base_of = [&](int tile, int ph) {
+    return (((int64_t)(ph < 0 ? 0 : ph) << log2_block) + ((tile * kTile) & block_mask)) * tl.row_vecs;
+  };
+  DecodeParams p;
+  u32x4_t nk = {0u, 0u, 0u, 0u}, nv = {0u, 0u, 0u, 0u};  // FUSED: the new token's K/V rows
+  int ap_freed = -1, ap_used = 0;
+  int ap_page = -1;  // the tail page, where it is not full
+  bool owner = len_pool < 0 && first == 0;  // FUSED: this wave has the new token's tile (or the length is no length)
   float m_run[HG], m_ref[HG], l_run[HG];
   f32x4_t acc[HG][8];
 #pragma unroll
@@ -312,30 +262,56 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[hg][e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   }
-
-  // This wave's tiles are first + i*stride, i < n_mine.  DEPTH tiles are in flight: as soon as the K (V) registers of
-  // a tile have been used, the K (V) loads of the tile DEPTH further on go out into them.  Loads are issued
-  // unconditionally, past the end all lanes fetch the same 16 bytes: the order of outstanding loads is known at
-  // compile time, so that waiting for the oldest leaves the younger ones in flight.
-  const auto base_of = [&](int tile, int ph) {
-    return (((int64_t)ph << log2_block) + ((tile * kTile) & block_mask)) * tl.row_vecs;
-  };
-  if (n_mine > 0) {
-    u32x4_t kb[DEPTH][NL], vb[DEPTH][NL];
+  u32x4_t kb[DEPTH][NL], vb[DEPTH][NL];
+  if (__builtin_expect(first < ntiles, 1)) {
+    u32x4_t q_raw[HG];
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) {
-      const int64_t base = d < n_mine ? base_of(first + d * stride, phys[d]) : 0;
-      tl.issue(kb[d], tl.k_pool, base, d < n_mine ? tl.k_off : 0);
-      tl.issue(vb[d], tl.v_pool, base, d < n_mine ? tl.v_off : 0);
+      const bool more = first + d * stride < ntiles;
+      const int64_t there = base_of(first + d * stride, phys[d]), base = more ? there : 0;
+      tl.issue(kb[d], tl.k_pool, base, more ? tl.k_off : 0);
+      if (d == 0) {
+        // queries, needed together with the first K: column n = 4*h + c of the operand holds the class-c slices of head h
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int hg = 0; hg < HG; ++hg) {
+          const int h = 4 * hg + (m >> 2);
+          const int64_t head = (int64_t)s * num_q_heads + hk * g_real + (h < g_real ? h : 0);
+          q_raw[hg] = static_cast<const u32x4_t*>(q)[head * LPR + k_slice];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      tl.issue(vb[d], tl.v_pool, base, more ? tl.v_off : 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    p = decode_params(phys[0]);
+    if constexpr (FUSED) {
+      nk = static_cast<const u32x4_t*>(p.new_k)[(int64_t)row * LPR + k_slice];
+      nv = static_cast<const u32x4_t*>(p.new_v)[(int64_t)row * LPR + v_slice];
+      ap_freed = p.freed_phys[table_row];
+      ap_used = p.spare_used[table_row];
+      const int jb = len_pool >> log2_block;
+      ap_page = bt[jb < 0 ? 0 : jb < max_blocks ? jb : max_blocks - 1];
+    }
+    bf16x8_t qop[HG][NT];
+#pragma unroll
+    for (int hg = 0; hg < HG; ++hg) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const u32x4_t zero = {0u, 0u, 0u, 0u};
+        const bool in = 4 * hg + (m >> 2) < g_real && (NT == 1 || (g >> 1) == t);
+        qop[hg][t] = __builtin_bit_cast(bf16x8_t, in ? q_raw[hg] : zero);
+      }
     }
     int ph_next = phys[DEPTH];
-    for (int i = 0; i < n_mine; i += DEPTH) {
+    for (int tile0 = first; tile0 < ntiles; tile0 += DEPTH * stride) {
 #pragma unroll
       for (int d = 0; d < DEPTH; ++d) {
-        const int tile = first + (i + d) * stride;   // past the end (an odd last one): every token is masked
+        const int tile = tile0 + d * stride;   // past the end (an odd last one): every token is masked
         const int tok0 = tile * kTile;
         const bool tail = tok0 + kTile > len_pool;
         if (tail) {
+          owner = owner || tok0 <= len_pool;
 #pragma unroll
           for (int w = 0; w < NL; ++w) {
             if constexpr (FUSED) {  // the new token takes its place among the loaded ones
@@ -349,9 +325,9 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(
         }
         float x[HG][4];
         tl.logits(kb[d], qop, p.scale_log2e, x);
-        const bool more = i + d + DEPTH < n_mine;
         const int ahead = tile + DEPTH * stride;
-        const int64_t base = more ? base_of(ahead, ph_next) : 0;
+        const bool more = ahead < ntiles;
+        const int64_t there = base_of(ahead, ph_next), base = more ? there : 0;
         ph_next = lookup(bt, ahead + stride, max_blocks, log2_block);
         tl.issue(kb[d], tl.k_pool, base, more ? tl.k_off : 0);
         if (tail) {  // mask logits past the row's end, keep junk V out of the sum
@@ -381,18 +357,17 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(
         tl.issue(vb[d], tl.v_pool, base, more ? tl.v_off : 0);
       }
     }
+  } else {
+    p = decode_params(ntiles);
   }
 
   // ---- merge: columns of a quad, lane groups, then the waves through LDS -------------------------------
 #pragma unroll
   for (int hg = 0; hg < HG; ++hg) {
-    float l = l_run[hg];
-    l += lane_xor_f32<16>(l);
-    l += lane_xor_f32<32>(l);
+    const float l = rows_sum(l_run[hg]);
     const int h = 4 * hg + (m >> 2);
     if (g == 0 && c == 0) {
-      sm_ml[wave][h][0] = m_run[hg];
-      sm_ml[wave][h][1] = l;
+      sm.ml[wave][h] = make_float2(m_run[hg], l);
     }
     // lane (g, 4*h + c) keeps row 4*g + c of C: elements 8*slice .. 8*slice + 7 of head h
     float o[8];
@@ -402,47 +377,21 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(
 #pragma unroll
       for (int r = 0; r < 4; ++r) a[r] = quad_sum(a[r]);
       o[e] = pick4(a, tl.b0, tl.b1);
-      if constexpr (D == 64) o[e] += lane_xor_f32<32>(o[e]);  // the two token parities
+      if constexpr (D == 64) o[e] = halves_sum(o[e]);  // the two token parities
     }
     if (D == 128 || g < 2) {
-      float4* dst = reinterpret_cast<float4*>(&sm_acc[wave][h][(4 * g + c) * 8]);
+      float4* dst = reinterpret_cast<float4*>(&sm.acc[wave][h][(4 * g + c) * 8]);
       dst[0] = make_float4(o[0], o[1], o[2], o[3]);
       dst[1] = make_float4(o[4], o[5], o[6], o[7]);
     }
   }
   __syncthreads();
-  for (int idx = (int)threadIdx.x; idx < g_real * (D / 2); idx += WAVES * kWave) {
-    const int h = idx / (D / 2), d = idx % (D / 2) * 2;
-    float mm = kNegInf;
-#pragma unroll
-    for (int w = 0; w < WAVES; ++w) mm = fmaxf(mm, sm_ml[w][h][0]);
-    const float ms = mm == kNegInf ? 0.f : mm;
-    float ll = 0.f, o0 = 0.f, o1 = 0.f;
-#pragma unroll
-    for (int w = 0; w < WAVES; ++w) {
-      const float f = __builtin_amdgcn_exp2f(sm_ml[w][h][0] - ms);
-      const float2 a = *reinterpret_cast<const float2*>(&sm_acc[w][h][d]);
-      ll = fmaf(sm_ml[w][h][1], f, ll);
-      o0 = fmaf(a.x, f, o0);
-      o1 = fmaf(a.y, f, o1);
-    }
-    if (splits == 1) {
-      const float r0 = ll > 0.f ? o0 / ll : 0.f, r1 = ll > 0.f ? o1 / ll : 0.f;
-      const int64_t off = ((int64_t)s * num_q_heads + hk * g_real + h) * D + d;
-      static_cast<Pair*>(p.out)[off / 2].v = (uint32_t)f32_to_bf16(r0) | ((uint32_t)f32_to_bf16(r1) << 16);
-    } else {
-      float* part = p.partials + (((int64_t)row * splits + split) * g_real + h) * (D + 2);
-      *reinterpret_cast<float2*>(part + d) = make_float2(o0, o1);
-      if (d == 0) *reinterpret_cast<float2*>(part + D) = make_float2(mm, ll);
-    }
-  }
+  merge_waves<bf16_t>(sm, p, row, split, splits, g_real);
 
   if constexpr (FUSED) {
     // the wave whose tile holds the new token stores it into the pool; when the tail page is full it links a new page
-    // first (the page freed by the eviction just before, else the next spare).  Last of all, so that nothing of this
-    // launch waits for a store.
-    const int owner = len_pool >= 0 ? (len_pool / kTile) % stride : 0;
-    if (owner == first) {
+    // first.  Last of all, so that nothing of this launch waits for a store.
+    if (owner) {
       const int B = 1 << log2_block;
       const int slot = len_pool & (B - 1);
       const int jb = len_pool >> log2_block;
@@ -453,15 +402,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(
         int page = ap_page;
         if (link) {
           page = ap_freed;
-          if (!SHARED || hk == 0) {
-            if (page < 0) {
-              page = ap_used < p.n_spare ? p.spare[(int64_t)table_row * p.n_spare + ap_used] : -1;
-              if (lane == 0) p.spare_used[table_row] = ap_used + 1;
-            } else if (lane == 0) {
-              p.freed_phys[table_row] = -1;
-            }
-            if (lane == 0) const_cast<int32_t*>(bt)[jb] = page;
-          }
+          if (!SHARED || hk == 0) page = link_page(p, const_cast<int32_t*>(bt), jb, table_row, ap_freed, ap_used, lane);
         }
         u32x4_t* k_to = static_cast<u32x4_t*>(const_cast<void*>(k_pool));
         u32x4_t* v_to = static_cast<u32x4_t*>(const_cast<void*>(v_pool));
@@ -483,6 +424,14 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void paged_decode_bf16_kernel(
       if (hk == 0 && lane == 0) p.seq_lens_out[s] = len_pool + 1;
     }
   }
+  // The loads behind a wave's last tiles are still on their way while the rows are merged.  Their registers are not to be given
+  // to anything before (whatever is written to a register waits for the load into it): they are in use until here.
+  if (first < ntiles) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d)
+#pragma unroll
+      for (int i = 0; i < NL; ++i) asm volatile("" : : "v"(kb[d][i]), "v"(vb[d][i]));
+  }
 }
 
 // (the forms that the head-shared layout never takes are not built for it)
@@ -490,31 +439,17 @@ template <int D, int HG, int WAVES, int DEPTH>
 hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
   constexpr bool kShared = WAVES == 4 && DEPTH <= 2;
   if (a.shared && !kShared) return hipErrorInvalidValue;
-  Params p;
-  p.out = a.out;
-  p.partials = a.partials;
-  p.scale_log2e = a.scale * 1.4426950408889634f;
-  p.new_k = a.new_k;
-  p.new_v = a.new_v;
-  p.freed_phys = a.freed_phys;
-  p.spare = a.spare;
-  p.spare_used = a.spare_used;
-  p.seq_lens_out = a.seq_lens_out;
-  p.n_spare = a.n_spare;
-  const int64_t rows = (int64_t)a.num_seqs * a.num_kv_heads;
-  const uint32_t xcd_map = (a.xcd_map && rows % 8 == 0) ? 1u : 0u;
-  const uint32_t shape =
-      (uint32_t)ilog2(a.block_size) | (uint32_t)(a.num_q_heads / a.num_kv_heads) << 8 | xcd_map << 16;
-  const int64_t grid = rows * a.splits;
-  if (grid <= 0 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
-  const dim3 blocks((unsigned)grid), threads(WAVES * kWave);
+  DecodeKernelArgs k;
+  dim3 blocks;
+  if (!decode_kernel_args(a, &k, &blocks)) return hipErrorInvalidValue;
+  const dim3 threads(WAVES * kWave);
   const bool fused = a.new_k != nullptr;
   const auto kernel = a.shared ? (fused ? paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, true, kShared>
                                         : paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, false, kShared>)
                                : (fused ? paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, true, false>
                                         : paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, false, false>);
-  hipLaunchKernelGGL(kernel, blocks, threads, 0, stream, a.seq_lens, a.block_table, a.q, a.k_pool, a.v_pool,
-                     a.num_kv_heads, a.max_blocks, a.splits, shape, p);
+  hipLaunchKernelGGL(kernel, blocks, threads, 0, stream, k.seq_lens, k.block_table, k.q, k.k_pool, k.v_pool, k.num_kv_heads,
+                     k.max_blocks, k.inv_heads, k.shape, k.p);
   return hipGetLastError();
 }
 

@@ -89,6 +89,37 @@ __device__ __forceinline__ double lane_xor_f64(double v) {
   return __hiloint2double(hi, lo);
 }
 
+// Reductions over the two halves of a wave and over its four rows of 16 lanes (every lane gets the total of the lanes that
+// are 32, or 16, apart), on the vector units: a half (row) swap of a value with itself leaves one operand of each pair in each
+// result.
+struct Swapped {
+  float a, b;
+};
+__device__ __forceinline__ Swapped swap_halves(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ __forceinline__ Swapped swap_rows(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ __forceinline__ float halves_sum(float v) {
+  const Swapped r = swap_halves(v);
+  return r.a + r.b;
+}
+__device__ __forceinline__ float halves_max(float v) {
+  const Swapped r = swap_halves(v);
+  return fmaxf(r.a, r.b);
+}
+__device__ __forceinline__ float rows_sum(float v) {
+  const Swapped r = swap_rows(v);
+  return halves_sum(r.a + r.b);
+}
+__device__ __forceinline__ float rows_max(float v) {
+  const Swapped r = swap_rows(v);
+  return halves_max(fmaxf(r.a, r.b));
+}
+
 // Inclusive prefix sum over the 64 lanes (DPP row shifts, then row broadcasts: no LDS traffic).
 __device__ __forceinline__ uint32_t wave_prefix_sum_u32(uint32_t v) {
   v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111 /* row_shr:1 */, 0xf, 0xf, false);
