@@ -62,7 +62,9 @@ __device__ __forceinline__ int64_t chunk_slot(int cu_s, int s, int c) { return (
 // ---- 1. token scores -------------------------------------------------------------------------------
 // The packed prompt is a flat array of (token, head) rows of D elements.  A wave-load covers TPL rows;
 // a wave handles kIters groups of NL wave-loads for K and for V, software-pipelined.
-template <typename T, int D>
+// STREAM: K and V with the non-temporal hint.  Without it a prompt stays in the Infinity Cache for the gather, and one that
+// was written a moment ago is found there; one that is too large for that is read more slowly (see the rule at the launch).
+template <typename T, int D, bool STREAM>
 __global__ __launch_bounds__(kThreads) void token_scores_kernel(const T* __restrict__ k_in,
                                                                 const T* __restrict__ v_in,
                                                                 float* __restrict__ scores, int64_t total_rows,
@@ -92,8 +94,8 @@ __global__ __launch_bounds__(kThreads) void token_scores_kernel(const T* __restr
     for (int i = 0; i < NL; ++i) {
       const int64_t r = base_row + i * TPL + grp;
       const int64_t vec = (r < last_row ? r : last_row) * LPR + u;
-      kb[buf][i] = load_vec_stream(k_in, vec);
-      vb[buf][i] = load_vec_stream(v_in, vec);
+      kb[buf][i] = STREAM ? load_vec_stream(k_in, vec) : load_vec(k_in, vec);
+      vb[buf][i] = STREAM ? load_vec_stream(v_in, vec) : load_vec(v_in, vec);
     }
   };
   issue(0, row0);
@@ -129,10 +131,12 @@ __global__ __launch_bounds__(kThreads) void token_scores_kernel(const T* __restr
     const int h = p / ntok;
     const int64_t tok = tok_lo + (p - h * ntok);
     const int64_t r = tok * num_kv_heads + h;
-    // non-temporal: the scores are written once and read by another kernel (measured 330 us against 344 us per
-    // 2.1 GB swept with plain stores; with no stores at all the sweep takes 316 us)
+    // written through to memory, where the selection's workgroups find them whichever L2 they have: lines left in the L2s are
+    // written back when the kernel ends (whole prunes, plain / non-temporal / this: 2.1 GB of prompt 493 / 464 / 465 us,
+    // 0.6 GB ragged 139 / 142 / 137, 1.1 GB of four prompts 222 / 221 / 215)
     if (r >= group_row0 && r < group_end)
-      __builtin_nontemporal_store(sm_score[(int)(r - group_row0)], &scores[(int64_t)h * total_tokens + tok]);
+      __hip_atomic_store(&scores[(int64_t)h * total_tokens + tok], sm_score[(int)(r - group_row0)], __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -443,8 +447,8 @@ SelectKernel select_kernel_for(int max_seqlen) {
 
 // ---- 3. gather ----------------------------------------------------------------------------------------
 // VPR_T > 0: vectors per token row known at compile time; 0: taken from vpr_rt (head-shared mode, where a
-// row is the K (or V) of all heads of a token).
-template <int VPR_T>
+// row is the K (or V) of all heads of a token).  STREAM: stores with the non-temporal hint.
+template <int VPR_T, bool STREAM>
 __global__ __launch_bounds__(kThreads) void gather_kernel(const uint4* __restrict__ k_in, const uint4* __restrict__ v_in,
                                                           const float* __restrict__ scores,
                                                           const int32_t* __restrict__ cu_seqlens,
@@ -531,8 +535,8 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(const uint4* __restric
       const int pos = kept_before_chunk + e;
       const int64_t src = ((int64_t)(t0 + src_tok[e]) * num_kv_heads + h) * VEC_PER_ROW + u;
       const int64_t dst = (((int64_t)bt[pos >> log2_block] << log2_block) + (pos & block_mask)) * VEC_PER_ROW + u;
-      k_pool[dst] = k_in[src];
-      v_pool[dst] = v_in[src];
+      store_vec<STREAM>(k_pool, dst, k_in[src]);
+      store_vec<STREAM>(v_pool, dst, v_in[src]);
     }
   } else {
     const int total_vecs = n_kept * vpr_rt;
@@ -541,8 +545,8 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(const uint4* __restric
       const int tok = src_tok[e], pos = kept_before_chunk + e;
       const int64_t src = ((int64_t)(t0 + tok) * num_kv_heads + h) * vpr_rt + u;
       const int64_t dst = (((int64_t)bt[pos >> log2_block] << log2_block) + (pos & block_mask)) * vpr_rt + u;
-      k_pool[dst] = k_in[src];
-      v_pool[dst] = v_in[src];
+      store_vec<STREAM>(k_pool, dst, k_in[src]);
+      store_vec<STREAM>(v_pool, dst, v_in[src]);
     }
   }
 }
@@ -553,12 +557,19 @@ hipError_t launch(const PruneArgs& a, hipStream_t stream) {
   const Workspace w = carve(a.workspace, a.num_seqs, a.num_kv_heads, a.total_tokens, a.shared);
   const int64_t total_rows = a.total_tokens * a.num_kv_heads;
   hipError_t e;
+  const int64_t row_bytes = 2 * (int64_t)a.num_kv_heads * D * (int64_t)sizeof(T);  // K and V of a token
   if (total_rows > 0) {
     const int64_t rows_per_group = (int64_t)kWaves * kSweepIters * kSweepLoads * G::kTokensPerLoad;
     const int64_t grid = (total_rows + rows_per_group - 1) / rows_per_group;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((token_scores_kernel<T, D>), dim3((unsigned)grid), dim3(kThreads), 0, stream,
-                       (const T*)a.k_in, (const T*)a.v_in, w.scores, total_rows, a.total_tokens, a.num_kv_heads);
+    // Prompts of 96 MiB are swept without the hint: they then lie in the Infinity Cache (256 MB) when the gather comes, and what
+    // the model has just written is found there (whole prunes of D = 64, 1024 of 4096 kept, with / without the hint, K and V
+    // written right before: 17 MB 27.3 / 25.2 us, 34 MB 30.2 / 27.8, 67 MB 33.8 / 29.5, 134 MB 50.6 / 45.7, 268 MB 83.8 / 83.8, 537 MB
+    // 133 / 165; out of memory: 67 MB 31.5 / 31.7, 134 MB 49.6 / 51.3, 268 MB 85.4 / 94.8)
+    const bool streamed = a.total_tokens * row_bytes > (int64_t)96 << 20;
+    const auto sweep = streamed ? token_scores_kernel<T, D, true> : token_scores_kernel<T, D, false>;
+    hipLaunchKernelGGL(sweep, dim3((unsigned)grid), dim3(kThreads), 0, stream, (const T*)a.k_in, (const T*)a.v_in, w.scores,
+                       total_rows, a.total_tokens, a.num_kv_heads);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   // what kernels 2-3 see: per-head rows, or (shared) one row per sequence whose score is the head mean and
@@ -584,17 +595,17 @@ hipError_t launch(const PruneArgs& a, hipStream_t stream) {
   const int64_t grid2 = (int64_t)rows * chunks_per_row;
   if (grid2 > 0x7fffffffLL) return hipErrorInvalidValue;
   constexpr int VPR = G::kLanesPerRow;
-  if (a.shared) {
-    hipLaunchKernelGGL((gather_kernel<0>), dim3((unsigned)grid2), dim3(kThreads), 0, stream, (const uint4*)a.k_in,
-                       (const uint4*)a.v_in, sel_scores, a.cu_seqlens, w.sel, w.before, a.block_table, (uint4*)a.k_pool,
-                       (uint4*)a.v_pool, a.kept_idx_out, a.total_tokens, w.chunk_slots, heads, rows,
-                       ilog2(a.block_size), a.max_blocks, a.budget, VPR * a.num_kv_heads);
-  } else {
-    hipLaunchKernelGGL((gather_kernel<VPR>), dim3((unsigned)grid2), dim3(kThreads), 0, stream, (const uint4*)a.k_in,
-                       (const uint4*)a.v_in, sel_scores, a.cu_seqlens, w.sel, w.before, a.block_table, (uint4*)a.k_pool,
-                       (uint4*)a.v_pool, a.kept_idx_out, a.total_tokens, w.chunk_slots, heads, rows,
-                       ilog2(a.block_size), a.max_blocks, a.budget, VPR);
-  }
+  // Kept rows of a prompt that is larger than the Infinity Cache go past the caches: what the gather reads is not there either, and
+  // what it writes need not push it out (whole prunes, plain stores / with the hint: 2.1 GB of prompt, 268 MB kept 465 / 453 us,
+  // 134 MB kept 418 / 409; 0.6 GB, 67 MB kept 141 / 137, fp32 110 / 106; 0.5 GB, 67 MB kept 127 / 122, written right before 133 / 136; smaller
+  // ones, written right before, 268 MB 84 / 87, 67 MB 33.8 / 34.9).
+  const bool streamed = a.total_tokens * row_bytes > (int64_t)256 << 20;
+  const auto gather = a.shared ? (streamed ? gather_kernel<0, true> : gather_kernel<0, false>)
+                               : (streamed ? gather_kernel<VPR, true> : gather_kernel<VPR, false>);
+  hipLaunchKernelGGL(gather, dim3((unsigned)grid2), dim3(kThreads), 0, stream, (const uint4*)a.k_in, (const uint4*)a.v_in,
+                     sel_scores, a.cu_seqlens, w.sel, w.before, a.block_table, (uint4*)a.k_pool, (uint4*)a.v_pool,
+                     a.kept_idx_out, a.total_tokens, w.chunk_slots, heads, rows, ilog2(a.block_size), a.max_blocks, a.budget,
+                     a.shared ? VPR * a.num_kv_heads : VPR);
   return hipGetLastError();
 }
 
