@@ -5,10 +5,10 @@
 // Three kernels on one stream:
 //   1. token_scores:  sweep of the packed K/V prompt; S_i = ||V_i||/||K_i|| in fp64, rounded once to
 //                     fp32, stored per KV head as a contiguous run  scores[hk][token].
-//   2. select:        per row, radix select (digits of 12, 10 and 10 bits, most significant first) on the
-//                     fp32 bit patterns (scores are >= +0, so they order like unsigned integers) for the
-//                     E-th smallest score T and the number q of tokens equal to T that must go; then, per
-//                     chunk of 1024 tokens of the row, how many scores are > T and how many == T.
+//   2. select:        per row, on the fp32 bit patterns (scores are >= +0, so they order like unsigned integers): a
+//                     histogram, then the few scores of one bin settled bit by bit, give the E-th smallest score T and
+//                     the number q of tokens equal to T that must go; then, per chunk of 1024 tokens of the row, how
+//                     many scores are > T and how many == T (none counted, and q = the largest number, where all go).
 //   3. gather:        per row and chunk, an index-ordered scan turns those counts into the destination
 //                     of every kept token; token rows are then copied with 16-byte lane accesses.
 // A token is kept iff score > T, or score == T and at least q equal-score tokens precede it.
@@ -151,85 +151,111 @@ __global__ __launch_bounds__(kThreads) void head_mean_kernel(const float* __rest
   mean_out[t] = (float)(sum / (double)num_kv_heads);
 }
 
-// ---- 2. per-row radix select + per-chunk counts ------------------------------------------------------
-// One workgroup of 1024 threads per row.  Radix select on the row's fp32 bit patterns, most significant digit
-// first: 12 bits (sign, exponent, top three mantissa bits: scores of one row cluster in a few exponents, and a
-// narrower first digit would pile every LDS atomic onto three or four bins), then 10 + 10 bits.  After a pass
-// the digit that holds rank k is found with a workgroup-wide scan.  The tokens that fall into the first digit's bin
-// are collected in LDS (a few percent of the row for any spread-out score distribution), so the second and third
-// pass see only them; a row with more candidates than the LDS buffer holds (e.g. all scores equal) goes over all of
-// its scores again.  With the threshold known the same workgroup counts, per chunk of 1024 tokens, how many scores are
-// > T and how many == T: the gather turns these into destinations.
+// ---- 2. per-row select + per-chunk counts ------------------------------------------------------------
+// One workgroup of 1024 threads per row finds the threshold on the row's fp32 bit patterns, which order like unsigned integers.
+// A histogram of 4096 equal bins is laid over the range of a sample (one score a thread; what lies outside falls into the
+// first or the last bin), so that few scores share a bin whatever their magnitude and spread.
+// The bin that holds rank k is found with a workgroup-wide scan; a row of some ten thousand scores leaves some ten candidates
+// in it.  They are collected in LDS, and one wave settles the remaining bits of the threshold, bit by bit, with ballots over
+// the candidates in its registers: no barriers in between.  More than 256 candidates go through further digits of up to 12
+// bits, with a histogram each; more than LDS holds (e.g. many equal scores) go over all scores of the row again for each, and
+// once before for their range.
+// With the threshold known the same workgroup counts, per chunk of 1024 tokens, how many scores are > T and how many == T: the
+// gather turns these into destinations.
 // A row is worked on by one compute unit, and one compute unit pulls about 45 GB/s from L2 however many loads it keeps
-// in flight: that, not the histogram atomics, bounds the reading of a long row.  So up to 32768 scores of it are read once,
-// into registers (4*NV a thread, NV by the longest row of the call), and every pass works from there; only what a row has
-// beyond is read from memory in each pass (all 65536 in registers, 64 a thread, leave too few for the rest: 56 us).  Also
-// kept out of the serial chain of a short row: cross-lane sums go through DPP, the wave totals of a scan are read at once,
-// places in the candidate list are taken once per wave, two histograms share the atomics of the first digit.  Measured on
-// an MI355X, before (every pass from memory, three more barriers a pass) / now: 64 rows x 4096 scores 10.4 / 6.8 us, 128
-// ragged rows of up to 16384 13.7 / 11.3, 256 x 16384 17.7 / 14.4, 288 ragged rows of up to 6567 14.4 / 11.2 (15.2 with one
-// workgroup a compute unit), 2 x 44000 20.7 / 18.8, 32 x 65536 30.0 / 28.7, 32 x 131072 46.6 / 43.4 (what lies beyond the held
-// scores comes in loads of 16 bytes, four in flight a thread: with loads of 4 bytes 19.9, 32.7 and 51.7; eight of 16 bytes in
-// flight save 0.6 on 131072 and cost 1.3 on rows of 36000 to 44000).
+// in flight: that, not the histogram atomics, bounds the reading of a long row.  So up to 65536 scores of it are read once and
+// held, 32768 in registers (32 a thread: 64 would leave too few for the rest) and as many in LDS, and every pass works from
+// there; only what a row has beyond is read from memory in each pass.
+// Measured on an MI355X (kernel trace), digits of 12, 10 and 10 plain bits with a histogram each and 32768 scores held / this: 64
+// rows x 4096 scores 7.3 / 6.6 us, 128 ragged rows of up to 16384 10.4 / 9.0, 256 x 16384 13.4 / 11.1, 32 x 65536 25.9 / 20.5; whole
+// prunes of 4 x 131072 tokens 444 / 430, with all scores equal 686 / 527, with zeros and infinities among them 422 / 429.  (What
+// bounds a long row is the vector issue of its one compute unit, 0.43 us per operation on each of 65536 scores: so equal scores
+// are counted only where some of them stay, a wave's scores are consecutive, and candidates are looked for four at a time.)
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / kWave;
 constexpr int kSelBins = 4096;
-constexpr int kSelUnroll = 4;  // 16-byte loads in flight per thread beyond the held scores
-constexpr int kSelCand = 8192;  // candidates kept in LDS after the first pass (32 KiB)
+constexpr int kSelDigit = ilog2(kSelBins);
+constexpr int kSelUnroll = 4;   // 16-byte loads in flight per thread beyond the held scores
+constexpr int kSelCand = 2048;  // candidates kept in LDS after the first digit
+constexpr int kSelFew = 256;    // candidates that a wave settles in its registers
 constexpr int kSelMaxVecs = 8;
-constexpr int kSelCopies = 2;  // with the candidates 64 KiB: two workgroups fit a compute unit
+constexpr int kSelMaxHeldChunks = 2 * kSelMaxVecs * 4;
 
 struct __attribute__((packed, aligned(4))) Unaligned4 {  // 16 bytes at any 4-byte boundary, in one load
   uint32_t v[4];
 };
 
-// The scores of a row as its workgroup holds them: score 4*(j*1024 + tid) + e is reg[j].v[e] of thread tid.
-template <int NV>
+// The scores of a row as its workgroup holds them, (NV + LV) * 256 consecutive ones a wave (so that a chunk of 1024 is counted
+// by as few waves as possible): score 256*j + 4*lane + e of a wave is element e of vector j of a lane, the first NV vectors in
+// registers, the next LV in LDS (a thread reads back only what it has written).
+template <int NV, int LV>
 struct RowScores {
-  static constexpr int kHeld = 4 * NV * kSelThreads;
+  static constexpr int kHeld = 4 * (NV + LV) * kSelThreads;
+  static constexpr int kVector = 4 * kWave;  // scores of a vector of a wave
   const uint32_t* bits;
+  uint4* lds;
   int L, tid;
+  int wave0;  // first score of the wave
   Unaligned4 reg[NV];
 
-  __device__ __forceinline__ int index(int j) const { return 4 * (j * kSelThreads + tid); }
+  __device__ __forceinline__ int index(int j) const { return wave0 + j * kVector + 4 * (tid & (kWave - 1)); }
 
+  __device__ __forceinline__ Unaligned4 request(int j) const {  // past the end the row's last four again
+    const int i = index(j);
+    const int last = L >= 4 ? L - 4 : 0;
+    return L >= 4 ? *reinterpret_cast<const Unaligned4*>(bits + (i < last ? i : last)) : Unaligned4{{0u, 0u, 0u, 0u}};
+  }
+  __device__ __forceinline__ void mend(int j, Unaligned4& r) const {  // the one vector that the row's end cuts
+    const int i = index(j);
+    if (i < L && i + 4 > L) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) r.v[e] = i + e < L ? bits[i + e] : 0u;
+    }
+  }
   __device__ __forceinline__ void load() {
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {  // unconditional, so that all are in flight: past the end the row's last four again
-      const int i = index(j);
-      const int last = L >= 4 ? L - 4 : 0;
-      reg[j] = L >= 4 ? *reinterpret_cast<const Unaligned4*>(bits + (i < last ? i : last)) : Unaligned4{{0u, 0u, 0u, 0u}};
-    }
+    for (int j = 0; j < NV; ++j) reg[j] = request(j);  // unconditional, so that all are in flight
+    constexpr int kStep = 4;
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {  // the one vector that the row's end cuts
-      const int i = index(j);
-      if (i < L && i + 4 > L) {
+    for (int j0 = 0; j0 < LV; j0 += kStep) {
+      Unaligned4 r[kStep];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) reg[j].v[e] = i + e < L ? bits[i + e] : 0u;
+      for (int j = 0; j < kStep; ++j) r[j] = request(NV + j0 + j);
+#pragma unroll
+      for (int j = 0; j < kStep; ++j) {
+        mend(NV + j0 + j, r[j]);
+        lds[(j0 + j) * kSelThreads + tid] = make_uint4(r[j].v[0], r[j].v[1], r[j].v[2], r[j].v[3]);
       }
     }
+#pragma unroll
+    for (int j = 0; j < NV; ++j) mend(j, reg[j]);
   }
 
-  // f(score) for every score that the registers hold ...
-  template <typename F>
-  __device__ __forceinline__ void visit_held(F f) const {
+  __device__ __forceinline__ Unaligned4 in_lds(int j) const {
+    const uint4 r = lds[(j - NV) * kSelThreads + tid];
+    return Unaligned4{{r.x, r.y, r.z, r.w}};
+  }
+  // Every score of the row: four(vector) for whole vectors, one(score) for those of a vector that the row's end cuts.  The
+  // held ones ...
+  template <typename F4, typename F1>
+  __device__ __forceinline__ void visit_vector(int j, const Unaligned4& r, F4 four, F1 one) const {
+    if (wave0 + (j + 1) * kVector <= L) {  // the same for all lanes
+      four(r);
+    } else if (wave0 + j * kVector < L) {
+      const int left = L - index(j);
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      if (4 * (j + 1) * kSelThreads <= L) {  // the same for all threads
-#pragma unroll
-        for (int e = 0; e < 4; ++e) f(reg[j].v[e]);
-      } else if (4 * j * kSelThreads < L) {
-        const int left = L - index(j);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (e < left) f(reg[j].v[e]);
-      }
+      for (int e = 0; e < 4; ++e)
+        if (e < left) one(r.v[e]);
     }
   }
-  // ... and for the rest of the row, from memory: 16 bytes a load, past the end the row's last four again
-  template <typename F>
-  __device__ __forceinline__ void visit_rest(F f) const {
-    constexpr int kUnroll = NV == kSelMaxVecs ? kSelUnroll : 1;  // a smaller holding covers every row of its call
+  template <typename F4, typename F1>
+  __device__ __forceinline__ void visit(F4 four, F1 one) const {
+#pragma unroll
+    for (int j = 0; j < NV; ++j) visit_vector(j, reg[j], four, one);
+#pragma unroll 1
+    for (int j = NV; j < NV + LV; ++j) visit_vector(j, in_lds(j), four, one);
+    // ... and the rest, from memory: 16 bytes a load, past the end the row's last four again
+    constexpr int kUnroll = LV > 0 ? kSelUnroll : 1;  // a smaller holding covers every row of its call
     for (int i0 = kHeld + 4 * tid; i0 < L; i0 += kUnroll * 4 * kSelThreads) {
       Unaligned4 r[kUnroll];
 #pragma unroll
@@ -240,37 +266,90 @@ struct RowScores {
 #pragma unroll
       for (int k = 0; k < kUnroll; ++k) {
         const int i = i0 + k * 4 * kSelThreads;
-        const int at = i < L - 4 ? i : L - 4;
+        if (i + 4 <= L) {
+          four(r[k]);
+        } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (at + e >= i) f(r[k].v[e]);
+          for (int e = 0; e < 4; ++e)
+            if (L - 4 + e >= i) one(r[k].v[e]);
+        }
       }
     }
   }
-  template <typename F>
-  __device__ __forceinline__ void visit(F f) const {
-    visit_held(f);
-    visit_rest(f);
-  }
 };
+
+// Largest value of a wave's lanes.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  const auto step = [&v](uint32_t o) { v = v > o ? v : o; };
+  step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111 /* row_shr:1 */, 0xf, 0xf, false));
+  step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112 /* row_shr:2 */, 0xf, 0xf, false));
+  step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114 /* row_shr:4 */, 0xf, 0xf, false));
+  step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118 /* row_shr:8 */, 0xf, 0xf, false));
+  step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142 /* row_bcast:15 */, 0xa, 0xf, false));
+  step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143 /* row_bcast:31 */, 0xc, 0xf, false));
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
+}
+
+// The highest bit in which two numbers differ (-1: none), and what they share above it.
+__device__ __forceinline__ int top_bit(uint32_t lo, uint32_t hi) { return lo == hi ? -1 : 31 - __builtin_clz(lo ^ hi); }
+__device__ __forceinline__ uint32_t above(uint32_t v, int bit) { return bit < 31 ? v >> (bit + 1) << (bit + 1) : 0u; }
+
+// The value of rank k among n <= 64 * R candidates between lo and hi, bit by bit; k becomes the rank among those equal to it,
+// `same` their number.  One wave.
+template <int R>
+__device__ __forceinline__ uint32_t settle(const uint32_t* cand, uint32_t n, uint32_t lo, uint32_t hi, uint32_t& k, uint32_t& same,
+                                            int lane) {
+  int bit = top_bit(lo, hi);
+  uint32_t T = above(lo, bit);
+  uint32_t x[R];
+  uint64_t left[R];  // lanes whose candidate agrees with the bits settled so far
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const bool is = (uint32_t)(r * kWave + lane) < n;
+    x[r] = is ? cand[r * kWave + lane] : 0u;
+    left[r] = __builtin_amdgcn_ballot_w64(is);
+  }
+  for (; bit >= 0; --bit) {
+    uint64_t ones[R];
+    uint32_t zeros = 0u;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      ones[r] = __builtin_amdgcn_ballot_w64((x[r] >> bit & 1u) != 0u);
+      zeros += (uint32_t)__popcll(left[r] & ~ones[r]);
+    }
+    const bool up = k >= zeros;
+    k -= up ? zeros : 0u;
+    T |= up ? 1u << bit : 0u;
+#pragma unroll
+    for (int r = 0; r < R; ++r) left[r] &= up ? ones[r] : ~ones[r];
+  }
+  same = 0u;
+#pragma unroll
+  for (int r = 0; r < R; ++r) same += (uint32_t)__popcll(left[r]);
+  return T;
+}
 
 // Two workgroups a compute unit (eight waves per SIMD, 64 registers) as long as the row leaves the registers for it: more
 // rows than compute units then still run at once.
-template <int NV>
+template <int NV, int LV>
 __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(const float* __restrict__ scores,
                                                              const int32_t* __restrict__ cu_seqlens,
                                                              uint32_t* __restrict__ sel, int32_t* __restrict__ before,
                                                              int32_t* __restrict__ seq_lens_out,
                                                              int32_t* __restrict__ kept_idx_out, int64_t total_tokens,
                                                              int64_t chunk_slots, int num_kv_heads, int budget) {
-  constexpr int kHeldChunks = RowScores<NV>::kHeld / kChunk;
+  using Row = RowScores<NV, LV>;
+  constexpr int kHeldChunks = Row::kHeld / kChunk;
+  static_assert(kHeldChunks <= kSelMaxHeldChunks, "chunk counters");
   constexpr int kBinsPerThread = kSelBins / kSelThreads;
-  // First digit: kSelCopies histograms side by side (bin * kSelCopies + lane % kSelCopies), so that fewer lanes of a
-  // wave meet in one word.  The 1024 bins of a later digit use the front of it.
-  __shared__ __attribute__((aligned(16))) uint32_t hist[kSelBins * kSelCopies];
-  __shared__ uint32_t cand[kSelCand];  // candidates; at the end, the counts of up to kSelCand chunks at a time
+  static_assert(kBinsPerThread == 4, "a thread reads its bins as one vector");
+  __shared__ __attribute__((aligned(16))) uint32_t hist[kSelBins];  // at the end, counts of chunks beyond the held ones
+  __shared__ uint32_t cand[kSelCand];
+  __shared__ uint4 held_lds[LV > 0 ? LV * kSelThreads : 1];
+  __shared__ uint32_t held_count[kSelMaxHeldChunks];
   __shared__ __attribute__((aligned(16))) uint32_t wave_tot[kSelWaves];
-  __shared__ uint32_t sh_prefix, sh_k, sh_in_bin, sh_ncand;
+  __shared__ uint2 wave_range[kSelWaves];
+  __shared__ uint32_t sh_bin, sh_k, sh_in_bin, sh_ncand;
   const int row = (int)blockIdx.x;
   const int s = row / num_kv_heads, h = row % num_kv_heads;
   const int t0 = cu_seqlens[s];
@@ -279,21 +358,24 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
   const int E = L - keep;
   const int tid = (int)threadIdx.x;
   const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  RowScores<NV> rs;
+  Row rs;
   rs.bits = reinterpret_cast<const uint32_t*>(scores) + (int64_t)h * total_tokens + t0;
+  rs.lds = held_lds;
   rs.L = L;
   rs.tid = tid;
+  rs.wave0 = wave * (NV + LV) * Row::kVector;
   rs.load();
 
   if (h == 0 && tid == 0) seq_lens_out[s] = keep;
   if (kept_idx_out != nullptr)
     for (int i = keep + tid; i < budget; i += kSelThreads) kept_idx_out[(int64_t)row * budget + i] = -1;
 
-  // The bin that rank k falls into: c[j] elements in the calling thread's bin number bin0 + j.
-  const auto find_bin = [&](const uint32_t (&c)[kBinsPerThread], uint32_t bin0, uint32_t k) {
-    uint32_t tot = 0u;
-#pragma unroll
-    for (int j = 0; j < kBinsPerThread; ++j) tot += c[j];
+  const auto clear_hist = [&] { reinterpret_cast<uint4*>(hist)[tid] = make_uint4(0u, 0u, 0u, 0u); };
+  // The bin of the histogram that rank k falls into (sh_bin), the rank inside it (sh_k) and what it holds (sh_in_bin).
+  const auto find_bin = [&](uint32_t k) {
+    const uint4 c4 = reinterpret_cast<const uint4*>(hist)[tid];
+    const uint32_t c[kBinsPerThread] = {c4.x, c4.y, c4.z, c4.w};
+    const uint32_t tot = c[0] + c[1] + c[2] + c[3];
     const uint32_t incl = wave_prefix_sum_u32(tot);
     if (lane == kWave - 1) wave_tot[wave] = incl;
     __syncthreads();
@@ -304,7 +386,7 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
 #pragma unroll
       for (int j = 0; j < kBinsPerThread; ++j) {
         if (k >= first && k < first + c[j]) {
-          sh_prefix = bin0 + j;
+          sh_bin = (uint32_t)(tid * kBinsPerThread + j);
           sh_k = k - first;
           sh_in_bin = c[j];
         }
@@ -314,97 +396,163 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
     __syncthreads();
   };
 
+  // The least and the largest of all threads' (lo, hi); nothing (lo > hi) counts as the largest, or the least, number.
+  const auto publish_range = [&](uint32_t lo, uint32_t hi) {
+    const uint2 r = make_uint2(wave_max_u32(~lo), wave_max_u32(hi));
+    if (lane == 0) wave_range[wave] = r;
+  };
+  const auto read_range = [&](uint32_t& lo, uint32_t& hi) {  // behind a barrier
+    const uint2 r = wave_range[lane % kSelWaves];
+    lo = ~wave_max_u32(r.x);
+    hi = wave_max_u32(r.y);
+  };
+
+  clear_hist();
+  if (tid < kSelMaxHeldChunks) held_count[tid] = 0u;
+  if (tid == 0) sh_ncand = 0u;
+  {
+    const bool in = rs.index(0) < L;
+    publish_range(in ? rs.reg[0].v[0] : 0xffffffffu, in ? rs.reg[0].v[0] : 0u);
+  }
+  __syncthreads();
   // E == 0, nothing to evict: T = +0.0, q = 0 keeps every token (scores are >= +0)
   uint32_t T = 0u, k = (uint32_t)(E > 0 ? E - 1 : 0);  // k: 0-based rank of the threshold among the remaining ones
   if (E > 0) {
-    for (int i = tid; i < kSelBins * kSelCopies / 4; i += kSelThreads)
-      reinterpret_cast<uint4*>(hist)[i] = make_uint4(0u, 0u, 0u, 0u);
-    if (tid == 0) sh_ncand = 0u;
-    __syncthreads();
-    const uint32_t copy = (uint32_t)lane % kSelCopies;
-    rs.visit([&](uint32_t b) { atomicAdd(&hist[(b >> 20) * kSelCopies + copy], 1u); });
-    __syncthreads();
-    uint32_t c[kBinsPerThread];
+    uint32_t low, top;
+    read_range(low, top);
+    const int shift0 = top_bit(top - low, 0u) < kSelDigit ? 0 : top_bit(top - low, 0u) + 1 - kSelDigit;
+    const auto count_one = [&](uint32_t b) {
+      const uint32_t up = __builtin_elementwise_sub_sat(b, low) >> shift0;
+      atomicAdd(&hist[up < (uint32_t)kSelBins - 1u ? up : (uint32_t)kSelBins - 1u], 1u);
+    };
+    rs.visit([&](const Unaligned4& r) {
 #pragma unroll
-    for (int j = 0; j < kBinsPerThread; ++j) {
-      c[j] = 0u;
-#pragma unroll
-      for (int i = 0; i < kSelCopies; ++i) c[j] += hist[(tid * kBinsPerThread + j) * kSelCopies + i];
-    }
-    find_bin(c, (uint32_t)(tid * kBinsPerThread), k);
-    uint32_t prefix = sh_prefix << 20, mask = 0xfff00000u;
+      for (int e = 0; e < 4; ++e) count_one(r.v[e]);
+    }, count_one);
+    __syncthreads();
+    find_bin(k);
+    const uint32_t bin = sh_bin, n = sh_in_bin;
     k = sh_k;
-    const bool in_lds = sh_in_bin <= (uint32_t)kSelCand;
-    const uint32_t ncand = sh_in_bin;
-    hist[tid] = 0u;  // the next digit's bins
-    if (in_lds) {  // collect the bin's tokens (their order does not matter: only values are counted)
-      // places for what the registers hold are taken once per wave: an atomic per score would be waited for each time
-      uint32_t mine = 0u;
-      rs.visit_held([&](uint32_t b) { mine += (b & mask) == prefix ? 1u : 0u; });
-      const uint32_t upto = wave_prefix_sum_u32(mine);
-      uint32_t at = 0u;
-      if (lane == kWave - 1) at = atomicAdd(&sh_ncand, upto);
-      at = (uint32_t)__builtin_amdgcn_readlane((int)at, kWave - 1) + upto - mine;
-      rs.visit_held([&](uint32_t b) {
-        if ((b & mask) == prefix) cand[at++] = b;
-      });
-      rs.visit_rest([&](uint32_t b) {
-        if ((b & mask) == prefix) cand[atomicAdd(&sh_ncand, 1u)] = b;
-      });
-    }
-    __syncthreads();
-#pragma unroll 1
-    for (int shift = 10; shift >= 0; shift -= 10) {
-      const auto count = [&](uint32_t b) {
-        if ((b & mask) == prefix) atomicAdd(&hist[(b >> shift) & 1023u], 1u);
+    uint32_t lo = bin == 0u ? 0u : low + (bin << shift0);
+    uint32_t hi = bin == (uint32_t)kSelBins - 1u ? 0xffffffffu : low + ((bin + 1u) << shift0) - 1u;
+    const uint32_t span = hi - lo;
+    if (n <= (uint32_t)kSelCand) {  // collect the bin's scores (their order does not matter: only values are counted)
+      const auto keep_one = [&](uint32_t b) {
+        if (b - lo <= span) cand[atomicAdd(&sh_ncand, 1u)] = b;
       };
-      if (in_lds) {
-        for (uint32_t i = (uint32_t)tid; i < ncand; i += kSelThreads) count(cand[i]);
-      } else {
-        rs.visit(count);
+      rs.visit([&](const Unaligned4& r) {
+        const uint32_t d0 = r.v[0] - lo, d1 = r.v[1] - lo, d2 = r.v[2] - lo, d3 = r.v[3] - lo;
+        const uint32_t d01 = d0 < d1 ? d0 : d1, d23 = d2 < d3 ? d2 : d3;
+        if (__builtin_amdgcn_ballot_w64((d01 < d23 ? d01 : d23) <= span) != 0ull) {  // one vector of a wave in some ten
+          const uint32_t d[4] = {d0, d1, d2, d3};
+          uint64_t who[4];
+          uint32_t all = 0u, at = 0u;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) all += (uint32_t)__popcll(who[e] = __builtin_amdgcn_ballot_w64(d[e] <= span));
+          if (lane == 0) at = atomicAdd(&sh_ncand, all);
+          at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if (d[e] <= span)
+              cand[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(who[e] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)who[e], 0u))] = r.v[e];
+            at += (uint32_t)__popcll(who[e]);
+          }
+        }
+      }, keep_one);
+      __syncthreads();
+    }
+    if (n <= (uint32_t)kSelFew) {
+      if (wave == 0) {  // (all sixteen at once would be in one another's way)
+        uint32_t same;
+        T = n <= (uint32_t)kWave ? settle<1>(cand, n, lo, hi, k, same, lane)
+                                 : settle<kSelFew / kWave>(cand, n, lo, hi, k, same, lane);
+        if (lane == 0) {
+          sh_bin = T;
+          sh_k = k;
+          sh_in_bin = same;
+        }
       }
       __syncthreads();
-      c[0] = hist[tid];
-#pragma unroll
-      for (int j = 1; j < kBinsPerThread; ++j) c[j] = 0u;
-      find_bin(c, (uint32_t)tid, k);
-      prefix |= sh_prefix << shift;
-      mask |= 1023u << shift;
+      T = sh_bin;
       k = sh_k;
-      hist[tid] = 0u;
-      __syncthreads();
+    } else {
+      if (n > (uint32_t)kSelCand) {
+        uint32_t mn = 0xffffffffu, mx = 0u;
+        const auto widen = [&](uint32_t b) {
+          const bool in = b - lo <= span;
+          mn = in && b < mn ? b : mn;
+          mx = in && b > mx ? b : mx;
+        };
+        rs.visit([&](const Unaligned4& r) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) widen(r.v[e]);
+        }, widen);
+        publish_range(mn, mx);
+        __syncthreads();
+        read_range(lo, hi);
+      }
+      int bits = top_bit(lo, hi) + 1;  // not settled yet
+      T = above(lo, bits - 1);
+#pragma unroll 1
+      while (bits > 0) {
+        const int shift = bits > kSelDigit ? bits - kSelDigit : 0;
+        const uint32_t digit = (1u << (bits - shift)) - 1u, settled = bits < 32 ? ~0u << bits : 0u;
+        clear_hist();
+        __syncthreads();
+        const auto count = [&](uint32_t b) {
+          if (b - lo <= hi - lo && ((b ^ T) & settled) == 0u) atomicAdd(&hist[(b >> shift) & digit], 1u);
+        };
+        if (n <= (uint32_t)kSelCand) {
+          for (uint32_t i = (uint32_t)tid; i < n; i += kSelThreads) count(cand[i]);
+        } else {
+          rs.visit([&](const Unaligned4& r) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) count(r.v[e]);
+          }, count);
+        }
+        __syncthreads();
+        find_bin(k);
+        T |= sh_bin << shift;
+        k = sh_k;
+        bits = shift;
+      }
     }
-    T = prefix;  // threshold score (bit pattern)
   }
+  // The first k + 1 tokens (index order) with score == T go.  Where that is all there are, as almost always, nobody has to count
+  // them: q = the largest number, none before any token.
+  const bool all_go = E > 0 && k + 1u == sh_in_bin;
   if (tid == 0) {
-    sel[2 * row] = T;
-    sel[2 * row + 1] = E > 0 ? k + 1 : 0u;           // q: the first q tokens (index order) with score == T go
+    sel[2 * row] = T;  // threshold score (bit pattern)
+    sel[2 * row + 1] = all_go ? 0x7fffffffu : E > 0 ? k + 1u : 0u;
   }
 
   // Scores > T (lower half) and == T (upper half) per chunk, then how many there are before each chunk of the row.
   const int nchunks = (L + kChunk - 1) / kChunk;
   int32_t* brow = before + ((int64_t)h * chunk_slots + chunk_slot(t0, s, 0)) * 2;
-  int gt_total = 0, eq_total = 0;  // of the pieces done
-  for (int c0 = 0; c0 < nchunks; c0 += kSelCand) {
-    const int nc = nchunks - c0 < kSelCand ? nchunks - c0 : kSelCand;
-    __syncthreads();
-    if (c0 == 0) {  // what the registers hold: a chunk is one vector of four waves
-      if (tid < kHeldChunks) cand[tid] = 0u;
-      __syncthreads();
+  constexpr int kVectorsPerChunk = kChunk / Row::kVector;
+  uint32_t n = 0u;  // of this lane, of the chunk at hand
+  const auto count_vector = [&](int j, const Unaligned4& r) {
+    const int left = rs.wave0 + (j + 1) * Row::kVector <= L ? 4 : L - rs.index(j);
 #pragma unroll
-      for (int j = 0; j < NV; ++j) {
-        if (4 * j * kSelThreads >= L) break;
-        const int left = L - rs.index(j);
-        uint32_t n = 0u;
+    for (int e = 0; e < 4; ++e) n += e < left && r.v[e] > T ? 1u : 0u;
+    if (!all_go) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const uint32_t b = rs.reg[j].v[e];
-          n += e < left ? (b > T ? 1u : 0u) + (b == T ? 0x10000u : 0u) : 0u;
-        }
-        n = wave_prefix_sum_u32(n);
-        if (lane == kWave - 1) atomicAdd(&cand[(j * kSelThreads + wave * kWave) * 4 / kChunk], n);
-      }
+      for (int e = 0; e < 4; ++e) n += e < left && r.v[e] == T ? 0x10000u : 0u;
     }
+    const int v = rs.wave0 / Row::kVector + j;  // number of the vector in the row
+    if (v % kVectorsPerChunk == kVectorsPerChunk - 1 || j == NV + LV - 1) {
+      n = wave_prefix_sum_u32(n);
+      if (lane == kWave - 1) atomicAdd(&held_count[v / kVectorsPerChunk], n);
+      n = 0u;
+    }
+  };
+#pragma unroll
+  for (int j = 0; j < NV; ++j) count_vector(j, rs.reg[j]);
+#pragma unroll 1
+  for (int j = NV; j < NV + LV; ++j) count_vector(j, rs.in_lds(j));
+  int gt_total = 0, eq_total = 0;  // of the pieces done
+  for (int c0 = 0; c0 < nchunks; c0 += kSelBins) {
+    const int nc = nchunks - c0 < kSelBins ? nchunks - c0 : kSelBins;
     // beyond them, one wave per chunk: 16 tokens per lane, all loads issued before the first compare
     for (int cc = (c0 == 0 ? kHeldChunks : 0) + wave; cc < nc; cc += kSelWaves) {
       constexpr int kPerLane = kChunk / kWave;
@@ -414,14 +562,14 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
       for (int j = 0; j < kPerLane; ++j) b[j] = rs.bits[i0 + j * kWave < L ? i0 + j * kWave : L - 1];
 #pragma unroll
       for (int j = 0; j < kPerLane; ++j)
-        n += i0 + j * kWave < L ? (b[j] > T ? 1u : 0u) + (b[j] == T ? 0x10000u : 0u) : 0u;
+        n += i0 + j * kWave < L ? (b[j] > T ? 1u : 0u) + (!all_go && b[j] == T ? 0x10000u : 0u) : 0u;
       n = wave_prefix_sum_u32(n);
-      if (lane == kWave - 1) cand[cc] = n;
+      if (lane == kWave - 1) hist[cc] = n;
     }
     __syncthreads();
     if (wave == 0) {
       for (int cc = 0; cc < nc; cc += kWave) {
-        const uint32_t n = cc + lane < nc ? cand[cc + lane] : 0u;
+        const uint32_t n = cc + lane >= nc ? 0u : c0 + cc + lane < kHeldChunks ? held_count[cc + lane] : hist[cc + lane];
         const int gt = (int)wave_prefix_sum_u32(n & 0xffffu), eq = (int)wave_prefix_sum_u32(n >> 16);
         if (cc + lane < nc) {
           const int2 v = make_int2(gt_total + gt - (int)(n & 0xffffu), eq_total + eq - (int)(n >> 16));
@@ -431,18 +579,20 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
         eq_total += __builtin_amdgcn_readlane(eq, kWave - 1);
       }
     }
+    __syncthreads();
   }
 }
 
-// The smallest register holding that covers rows of max_seqlen tokens (or the largest there is): a larger one than needed
-// costs loads, branches and, beyond 16 scores a thread, the second workgroup of a compute unit.
+// The smallest holding that covers rows of max_seqlen tokens (or the largest there is): a larger one than needed costs loads,
+// branches and, beyond 16 scores a thread, the second workgroup of a compute unit.
 using SelectKernel = void (*)(const float*, const int32_t*, uint32_t*, int32_t*, int32_t*, int32_t*, int64_t, int64_t, int, int);
 SelectKernel select_kernel_for(int max_seqlen) {
   const int vecs = (max_seqlen + 4 * kSelThreads - 1) / (4 * kSelThreads);
-  if (vecs <= 1) return select_kernel<1>;
-  if (vecs <= 2) return select_kernel<2>;
-  if (vecs <= 4) return select_kernel<4>;
-  return select_kernel<kSelMaxVecs>;
+  if (vecs <= 1) return select_kernel<1, 0>;
+  if (vecs <= 2) return select_kernel<2, 0>;
+  if (vecs <= 4) return select_kernel<4, 0>;
+  if (vecs <= kSelMaxVecs) return select_kernel<kSelMaxVecs, 0>;
+  return select_kernel<kSelMaxVecs, kSelMaxVecs>;
 }
 
 // ---- 3. gather ----------------------------------------------------------------------------------------
