@@ -12,6 +12,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libpe.so")
+HOST_PATH = os.path.join(_HERE, "_pe_host.so")
 
 PE_OK = 0
 PE_ERR_INVALID_ARG, PE_ERR_UNSUPPORTED, PE_ERR_WORKSPACE, PE_ERR_HIP = -1, -2, -3, -4
@@ -50,6 +51,7 @@ class PeError(RuntimeError):
 
 
 _lib = None
+_host = None   # the native marshalling of the calls that come once a layer (csrc/pe_host.cpp), loaded with the library
 
 
 def lib():
@@ -59,6 +61,10 @@ def lib():
         if not os.path.exists(LIB_PATH):
             raise RuntimeError("libpe.so is not built (%s): run `python -c 'import __graft_entry__ as g; g.build()'` "
                                "or `python paper_2509_04377_amd/build.py`" % LIB_PATH)
+        if not os.path.exists(HOST_PATH):
+            raise RuntimeError("_pe_host.so is not built (%s): build as for libpe.so" % HOST_PATH)
+        global _host
+        from . import _pe_host as _host
         L = ctypes.CDLL(LIB_PATH)
         vp, i32, i64, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_size_t
         dp = ctypes.POINTER(pe_cache_desc)
@@ -98,6 +104,9 @@ def lib():
         L.pe_score_recent_blocks.argtypes = [dp, vp, vp, vp, vp, i32, vp, vp]
         L.pe_evict_blocks_cached.restype = ctypes.c_int
         L.pe_evict_blocks_cached.argtypes = [dp, vp, vp, vp, i32, vp, vp, vp]
+        # addresses of the functions that are called through _pe_host
+        for name in ("paged_decode", "append_paged_decode", "append_paged_decode_layers", "prefill_prune"):
+            setattr(L, "addr_" + name, ctypes.cast(getattr(L, "pe_" + name), vp).value)
         _lib = L
     return _lib
 
@@ -141,9 +150,10 @@ def ptr(t, name, dtype=None, optional=False):
     return ctypes.c_void_p(t.data_ptr())
 
 
-# What the calls below pass: the checks of ptr(), and the current stream and the workspace, as plain numbers.  A small
-# launch is over sooner than its arguments are put together (5 us against 13), and of those the stream object and a
-# ctypes object per pointer were the larger half; ctypes converts numbers by the declared argument types.
+# What the calls below pass: the checks of ptr(), and the current stream and the workspace, as plain numbers (ctypes converts
+# them by the declared argument types).  The calls that come once a layer try _pe_host first, which does the same in native code:
+# a small launch is over sooner than its arguments are put together here.  It returns None for anything out of the ordinary;
+# the way through ctypes then accepts it or raises what is wrong.
 def _addr(t, name, dtype=None):
     if t is not None and t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype is dtype):
         return t.data_ptr()
@@ -188,14 +198,18 @@ def pe_score_blocks(desc, k_pool, v_pool, block_table, seq_lens, scores_out, wor
 
 def pe_prefill_prune(desc, k_in, v_in, cu_seqlens, total_tokens, max_seqlen, budget_tokens, k_pool, v_pool,
                      block_table, seq_lens_out, kept_idx_out, workspace):
-    wp, wn = _ws(workspace)
-    check(lib().pe_prefill_prune(ctypes.byref(desc), _addr(k_in, "k_in"), _addr(v_in, "v_in"),
-                                  _addr(cu_seqlens, "cu_seqlens", torch.int32), int(total_tokens), int(max_seqlen),
-                                  int(budget_tokens), _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
-                                  _addr(block_table, "block_table", torch.int32),
-                                  _addr(seq_lens_out, "seq_lens_out", torch.int32),
-                                  _addr_opt(kept_idx_out, "kept_idx_out", torch.int32), wp, wn, _stream()),
-           "pe_prefill_prune")
+    L = lib()
+    status = _host.prefill_prune(L.addr_prefill_prune, desc, k_in, v_in, cu_seqlens, total_tokens, max_seqlen, budget_tokens,
+                                 k_pool, v_pool, block_table, seq_lens_out, kept_idx_out, workspace)
+    if status is None:
+        wp, wn = _ws(workspace)
+        status = L.pe_prefill_prune(ctypes.byref(desc), _addr(k_in, "k_in"), _addr(v_in, "v_in"),
+                                    _addr(cu_seqlens, "cu_seqlens", torch.int32), int(total_tokens), int(max_seqlen),
+                                    int(budget_tokens), _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
+                                    _addr(block_table, "block_table", torch.int32),
+                                    _addr(seq_lens_out, "seq_lens_out", torch.int32),
+                                    _addr_opt(kept_idx_out, "kept_idx_out", torch.int32), wp, wn, _stream())
+    check(status, "pe_prefill_prune")
 
 
 def pe_evict_blocks(desc, scores, block_table, seq_lens, budget_tokens, evicted_logical_out, freed_phys_out):
@@ -251,10 +265,15 @@ def pe_evict_blocks_ex(desc, opts, scores, block_table, seq_lens, budget_tokens,
 
 
 def pe_paged_decode(desc, q, k_pool, v_pool, block_table, seq_lens, softmax_scale, out, workspace=None):
-    wp, wn = _ws(workspace)
-    check(lib().pe_paged_decode(ctypes.byref(desc), _addr(q, "q"), _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
-                                 _addr(block_table, "block_table", torch.int32), _addr(seq_lens, "seq_lens", torch.int32),
-                                 float(softmax_scale), _addr(out, "out"), wp, wn, _stream()), "pe_paged_decode")
+    L = lib()
+    status = _host.paged_decode(L.addr_paged_decode, desc, q, k_pool, v_pool, block_table, seq_lens, softmax_scale, out,
+                                workspace)
+    if status is None:
+        wp, wn = _ws(workspace)
+        status = L.pe_paged_decode(ctypes.byref(desc), _addr(q, "q"), _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
+                                   _addr(block_table, "block_table", torch.int32), _addr(seq_lens, "seq_lens", torch.int32),
+                                   float(softmax_scale), _addr(out, "out"), wp, wn, _stream())
+    check(status, "pe_paged_decode")
 
 
 def pe_paged_decode_static(desc, q, k_pool, v_pool, block_table, seq_lens, softmax_scale, out):
@@ -274,27 +293,36 @@ def pe_append_kv(desc, new_k, new_v, k_pool, v_pool, block_table, seq_lens, free
 
 def pe_append_paged_decode(desc, new_k, new_v, q, k_pool, v_pool, block_table, seq_lens, seq_lens_out, freed_phys, spare,
                            spare_used, softmax_scale, out, workspace=None):
-    wp, wn = _ws(workspace)
-    check(lib().pe_append_paged_decode(ctypes.byref(desc), _addr(new_k, "new_k"), _addr(new_v, "new_v"), _addr(q, "q"),
-                                        _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
-                                        _addr(block_table, "block_table", torch.int32),
-                                        _addr(seq_lens, "seq_lens", torch.int32),
-                                        _addr(seq_lens_out, "seq_lens_out", torch.int32),
-                                        _addr(freed_phys, "freed_phys", torch.int32), _addr(spare, "spare", torch.int32),
-                                        _addr(spare_used, "spare_used", torch.int32), int(spare.shape[-1]),
-                                        float(softmax_scale), _addr(out, "out"), wp, wn, _stream()),
-           "pe_append_paged_decode")
+    L = lib()
+    status = _host.append_paged_decode(L.addr_append_paged_decode, desc, new_k, new_v, q, k_pool, v_pool, block_table, seq_lens,
+                                       seq_lens_out, freed_phys, spare, spare_used, spare, softmax_scale, out, workspace)
+    if status is None:
+        wp, wn = _ws(workspace)
+        status = L.pe_append_paged_decode(ctypes.byref(desc), _addr(new_k, "new_k"), _addr(new_v, "new_v"), _addr(q, "q"),
+                                          _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
+                                          _addr(block_table, "block_table", torch.int32),
+                                          _addr(seq_lens, "seq_lens", torch.int32),
+                                          _addr(seq_lens_out, "seq_lens_out", torch.int32),
+                                          _addr(freed_phys, "freed_phys", torch.int32), _addr(spare, "spare", torch.int32),
+                                          _addr(spare_used, "spare_used", torch.int32), int(spare.shape[-1]),
+                                          float(softmax_scale), _addr(out, "out"), wp, wn, _stream())
+    check(status, "pe_append_paged_decode")
 
 
 def pe_append_paged_decode_layers(desc, num_layers, new_k, new_v, q, k_pool, v_pool, block_table, seq_lens, seq_lens_out,
                                   freed_phys, spare, spare_used, softmax_scale, out, workspace=None):
-    wp, wn = _ws(workspace)
-    check(lib().pe_append_paged_decode_layers(ctypes.byref(desc), int(num_layers), _addr(new_k, "new_k"), _addr(new_v, "new_v"),
-                                              _addr(q, "q"), _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
-                                              _addr(block_table, "block_table", torch.int32),
-                                              _addr(seq_lens, "seq_lens", torch.int32),
-                                              _addr(seq_lens_out, "seq_lens_out", torch.int32),
-                                              _addr(freed_phys, "freed_phys", torch.int32), _addr(spare, "spare", torch.int32),
-                                              _addr(spare_used, "spare_used", torch.int32), int(spare.shape[-1]),
-                                              float(softmax_scale), _addr(out, "out"), wp, wn, _stream()),
-          "pe_append_paged_decode_layers")
+    L = lib()
+    status = _host.append_paged_decode_layers(L.addr_append_paged_decode_layers, desc, num_layers, new_k, new_v, q, k_pool,
+                                              v_pool, block_table, seq_lens, seq_lens_out, freed_phys, spare, spare_used, spare,
+                                              softmax_scale, out, workspace)
+    if status is None:
+        wp, wn = _ws(workspace)
+        status = L.pe_append_paged_decode_layers(ctypes.byref(desc), int(num_layers), _addr(new_k, "new_k"), _addr(new_v, "new_v"),
+                                                 _addr(q, "q"), _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
+                                                 _addr(block_table, "block_table", torch.int32),
+                                                 _addr(seq_lens, "seq_lens", torch.int32),
+                                                 _addr(seq_lens_out, "seq_lens_out", torch.int32),
+                                                 _addr(freed_phys, "freed_phys", torch.int32), _addr(spare, "spare", torch.int32),
+                                                 _addr(spare_used, "spare_used", torch.int32), int(spare.shape[-1]),
+                                                 float(softmax_scale), _addr(out, "out"), wp, wn, _stream())
+    check(status, "pe_append_paged_decode_layers")

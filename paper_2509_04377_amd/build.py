@@ -1,4 +1,5 @@
-"""Build libpe.so (the C-ABI library of HIP kernels) for gfx950 with hipcc, in-tree."""
+"""Build libpe.so (the C-ABI library of HIP kernels) for gfx950 with hipcc, and _pe_host.so (argument marshalling of its Python
+front end) with g++, in-tree."""
 import os
 import subprocess
 import sys
@@ -7,6 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libpe.so")
+HOST_LIB = os.path.join(HERE, "_pe_host.so")
 SOURCES = ["pe_api.hip", "score_blocks.hip", "evict_blocks.hip", "paged_decode.hip", "paged_decode_bf16.hip",
            "prefill_prune.hip"]
 # Packed fp32 VALU ops are switched off for all device code.  The leading kernel arguments (up to 14 dwords) are preloaded
@@ -25,6 +27,7 @@ def build(verbose: bool = False, extra_flags=()) -> str:
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, obj, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    host_tmp, host = start_host_build(verbose)
     objs, failed = [], []
     for src, obj, p in procs:
         out, _ = p.communicate()
@@ -34,13 +37,34 @@ def build(verbose: bool = False, extra_flags=()) -> str:
         elif out and verbose:
             print(out)
         objs.append(obj)
+    out, _ = host.communicate()
+    if host.returncode != 0:
+        failed.append(("pe_host.cpp", out))
     if failed:
         raise RuntimeError("hipcc failed:\n" + "\n".join("%s:\n%s" % f for f in failed))
     tmp = LIB + ".tmp.%d" % os.getpid()
     subprocess.run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs, check=True)
     os.replace(tmp, LIB)
+    os.replace(host_tmp, HOST_LIB)
     build_c_smoke()
     return LIB
+
+
+def start_host_build(verbose: bool = False):
+    """Start the compiler on the Python extension (host code only).  Returns where it writes to, and the process."""
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    tmp = HOST_LIB + ".tmp.%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unused-function", "-Wno-attributes",
+           "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I" + sysconfig.get_paths()["include"]]
+    cmd += ["-isystem" + d for d in cpp_extension.include_paths("cuda")]
+    cmd += [os.path.join(CSRC, "pe_host.cpp"), "-o", tmp] + ["-L" + d for d in cpp_extension.library_paths("cuda")]
+    cmd += ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    return tmp, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
 
 
 C_SMOKE_SRC = os.path.join(os.path.dirname(HERE), "tests", "c_abi", "pe_c_smoke.c")

@@ -1,0 +1,84 @@
+"""The native argument marshalling: what it takes, what it leaves to the way through ctypes (which accepts it or says what is
+wrong), and that both make the same call."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2509_04377_amd import binding as pe
+
+S, Hk, Hq, D, B, PAGES = 3, 2, 4, 64, 16, 4
+
+
+def _args(dev):
+    g = torch.Generator().manual_seed(3)
+    P = S * Hk * PAGES
+    k, v = (torch.randn((P, B, D), generator=g).to(dev) for _ in range(2))
+    table = torch.arange(P, dtype=torch.int32).view(S, Hk, PAGES).to(dev)
+    lens = torch.tensor([1, 40, 63], dtype=torch.int32).to(dev)
+    q = torch.randn((S, Hq, D), generator=g).to(dev)
+    return pe.make_desc(torch.float32, S, Hk, Hq, D, B, PAGES, P), q, k, v, table, lens
+
+
+def test_what_is_not_a_dense_gpu_tensor_is_left_to_ctypes():
+    L = pe.lib()
+    desc, q, k, v, table, lens = _args("cpu")
+    assert pe._host.paged_decode(L.addr_paged_decode, desc, q, k, v, table, lens, 0.1, q, None) is None
+    assert pe._host.paged_decode(L.addr_paged_decode, b"short", q, k, v, table, lens, 0.1, q, None) is None
+    with pytest.raises(ValueError, match="q must be a GPU tensor"):
+        pe.pe_paged_decode(desc, q, k, v, table, lens, 0.1, torch.empty_like(q))
+    with pytest.raises(TypeError):
+        pe._host.paged_decode(L.addr_paged_decode, desc)
+    with pytest.raises(ValueError):
+        pe._host.paged_decode(0, desc, q, k, v, table, lens, 0.1, q, None)
+
+
+def test_descriptor_is_the_structure_of_the_header():
+    assert ctypes.sizeof(pe.pe_cache_desc) == 56
+
+
+@pytest.mark.gpu
+def test_native_call_and_ctypes_call_are_the_same():
+    L = pe.lib()
+    desc, q, k, v, table, lens = _args("cuda")
+    outs = [torch.empty_like(q) for _ in range(3)]
+    assert pe._host.paged_decode(L.addr_paged_decode, desc, q, k, v, table, lens, 0.125, outs[0], None) == pe.PE_OK
+    pe.pe_paged_decode(desc, q, k, v, table, lens, 0.125, outs[1])
+    pe.pe_paged_decode(desc, q, k, v, table, lens, torch.tensor(0.125), outs[2])   # a scale that only float() understands
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+
+
+@pytest.mark.gpu
+def test_gpu_arguments_that_are_refused():
+    L = pe.lib()
+    desc, q, k, v, table, lens = _args("cuda")
+    out = torch.empty_like(q)
+    bad = {"q": q.transpose(0, 1), "table": table.long(), "lens": lens.float()}
+    assert pe._host.paged_decode(L.addr_paged_decode, desc, bad["q"], k, v, table, lens, 0.1, out, None) is None
+    with pytest.raises(ValueError, match="q must be contiguous"):
+        pe.pe_paged_decode(desc, bad["q"], k, v, table, lens, 0.1, out)
+    with pytest.raises(ValueError, match="block_table must be torch.int32"):
+        pe.pe_paged_decode(desc, q, k, v, bad["table"], lens, 0.1, out)
+    with pytest.raises(ValueError, match="seq_lens must be torch.int32"):
+        pe.pe_paged_decode(desc, q, k, v, table, bad["lens"], 0.1, out)
+    with pytest.raises(pe.PeError):   # a status that the library gives
+        pe.pe_paged_decode(pe.make_desc(torch.float32, S, Hk, Hq, 96, B, PAGES, S * Hk * PAGES), q, k, v, table, lens, 0.1, out)
+    with pytest.raises(pe.PeError):
+        pe.pe_paged_decode(desc, None, k, v, table, lens, 0.1, out)
+
+
+@pytest.mark.gpu
+def test_native_call_runs_on_the_current_stream():
+    desc, q, k, v, table, lens = _args("cuda")
+    want, got = torch.empty_like(q), torch.zeros_like(q)
+    pe.pe_paged_decode(desc, q, k, v, table, lens, 0.125, want)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        scratch = torch.randn((2048, 2048), device="cuda")
+        for _ in range(20):
+            scratch = scratch @ scratch / 2048
+        late = q + 0 * scratch[0, 0]
+        pe.pe_paged_decode(desc, late, k, v, table, lens, 0.125, got)   # behind `late` only on this stream
+    side.synchronize()
+    assert torch.equal(got, want)
