@@ -596,9 +596,11 @@ SelectKernel select_kernel_for(int max_seqlen) {
 }
 
 // ---- 3. gather ----------------------------------------------------------------------------------------
-// VPR_T > 0: vectors per token row known at compile time; 0: taken from vpr_rt (head-shared mode, where a
-// row is the K (or V) of all heads of a token).  STREAM: stores with the non-temporal hint.
-template <int VPR_T, bool STREAM>
+// One workgroup per (row, chunk) copies the kept token rows of one head.  SHARED: the heads of a sequence share its selection and its
+// table row, their token rows lie num_kv_heads apart in the pages (whole records by one workgroup were a division per
+// 16 bytes and an eighth of the workgroups: 16 prompts of 2048 to 8192 tokens, 8 heads, 1024 kept 204 us a prune, now 98; 8 x 4096 of
+// D = 64 54.8, now 31.1).  STREAM: stores with the non-temporal hint.
+template <int VEC_PER_ROW, bool SHARED, bool STREAM>
 __global__ __launch_bounds__(kThreads) void gather_kernel(const uint4* __restrict__ k_in, const uint4* __restrict__ v_in,
                                                           const float* __restrict__ scores,
                                                           const int32_t* __restrict__ cu_seqlens,
@@ -608,7 +610,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(const uint4* __restric
                                                           uint4* __restrict__ k_pool, uint4* __restrict__ v_pool,
                                                           int32_t* __restrict__ kept_idx_out, int64_t total_tokens,
                                                           int64_t chunk_slots, int num_kv_heads, int rows,
-                                                          int log2_block, int max_blocks, int budget, int vpr_rt) {
+                                                          int log2_block, int max_blocks, int budget) {
   __shared__ uint32_t wave_sum[kWaves];
   __shared__ int32_t src_tok[kChunk];  // kept tokens of this chunk, in order: in-sequence index
   __shared__ int n_kept_sh;
@@ -618,21 +620,22 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(const uint4* __restric
   const int row = (int)(blockIdx.x % (unsigned)rows);
   const int chunk = (int)(blockIdx.x / (unsigned)rows);
   const int s = row / num_kv_heads, h = row % num_kv_heads;
+  const int sel_row = SHARED ? s : row, sel_h = SHARED ? 0 : h;  // whose scores decide
   const int t0 = cu_seqlens[s];
   const int L = cu_seqlens[s + 1] - t0;
   if (chunk * kChunk >= L) return;
   const int tid = (int)threadIdx.x;
   const int lane = lane_id();
   const int wave = tid / kWave;
-  const uint32_t T = sel[2 * row];
-  const int q = (int)sel[2 * row + 1];
+  const uint32_t T = sel[2 * sel_row];
+  const int q = (int)sel[2 * sel_row + 1];
 
   // counts over all earlier chunks of this row
-  const int2 earlier = reinterpret_cast<const int2*>(before)[(int64_t)h * chunk_slots + chunk_slot(t0, s, chunk)];
+  const int2 earlier = reinterpret_cast<const int2*>(before)[(int64_t)sel_h * chunk_slots + chunk_slot(t0, s, chunk)];
   const int gt_before = earlier.x, eq_before = earlier.y;
 
   // this thread's kTokPerThread consecutive tokens
-  const uint32_t* bits = reinterpret_cast<const uint32_t*>(scores) + (int64_t)h * total_tokens + t0;
+  const uint32_t* bits = reinterpret_cast<const uint32_t*>(scores) + (int64_t)sel_h * total_tokens + t0;
   const int i0 = chunk * kChunk + tid * kTokPerThread;
   uint32_t b[kTokPerThread];
   int n_gt = 0, n_eq = 0;
@@ -671,33 +674,22 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(const uint4* __restric
   __syncthreads();
   const int n_kept = n_kept_sh;
 
-  if (kept_idx_out != nullptr)  // consecutive positions: whole lines
-    for (int e = tid; e < n_kept; e += kThreads) kept_idx_out[(int64_t)row * budget + kept_before_chunk + e] = src_tok[e];
+  if (kept_idx_out != nullptr && (!SHARED || h == 0))  // consecutive positions: whole lines
+    for (int e = tid; e < n_kept; e += kThreads) kept_idx_out[(int64_t)sel_row * budget + kept_before_chunk + e] = src_tok[e];
 
-  // copy the kept rows: VEC_PER_ROW lanes per token row, K and V (two or four rows of a thread in flight: no faster)
-  const int32_t* bt = block_table + (int64_t)row * max_blocks;
+  // copy the kept rows: VEC_PER_ROW lanes per token row, K and V (two or four rows of a thread in flight, or the pages looked up
+  // beforehand: no faster)
+  const int32_t* bt = block_table + (int64_t)sel_row * max_blocks;
   const int block_mask = (1 << log2_block) - 1;
-  if constexpr (VPR_T > 0) {
-    constexpr int VEC_PER_ROW = VPR_T;
-    constexpr int kRowsPerPass = kThreads / VEC_PER_ROW;
-    const int u = tid % VEC_PER_ROW, r = tid / VEC_PER_ROW;
-    for (int e = r; e < n_kept; e += kRowsPerPass) {
-      const int pos = kept_before_chunk + e;
-      const int64_t src = ((int64_t)(t0 + src_tok[e]) * num_kv_heads + h) * VEC_PER_ROW + u;
-      const int64_t dst = (((int64_t)bt[pos >> log2_block] << log2_block) + (pos & block_mask)) * VEC_PER_ROW + u;
-      store_vec<STREAM>(k_pool, dst, k_in[src]);
-      store_vec<STREAM>(v_pool, dst, v_in[src]);
-    }
-  } else {
-    const int total_vecs = n_kept * vpr_rt;
-    for (int f = tid; f < total_vecs; f += kThreads) {
-      const int e = f / vpr_rt, u = f - e * vpr_rt;
-      const int tok = src_tok[e], pos = kept_before_chunk + e;
-      const int64_t src = ((int64_t)(t0 + tok) * num_kv_heads + h) * vpr_rt + u;
-      const int64_t dst = (((int64_t)bt[pos >> log2_block] << log2_block) + (pos & block_mask)) * vpr_rt + u;
-      store_vec<STREAM>(k_pool, dst, k_in[src]);
-      store_vec<STREAM>(v_pool, dst, v_in[src]);
-    }
+  constexpr int kRowsPerPass = kThreads / VEC_PER_ROW;
+  const int u = tid % VEC_PER_ROW, r = tid / VEC_PER_ROW;
+  for (int e = r; e < n_kept; e += kRowsPerPass) {
+    const int pos = kept_before_chunk + e;
+    const int64_t src = ((int64_t)(t0 + src_tok[e]) * num_kv_heads + h) * VEC_PER_ROW + u;
+    const int64_t slot = ((int64_t)bt[pos >> log2_block] << log2_block) + (pos & block_mask);
+    const int64_t dst = (SHARED ? slot * num_kv_heads + h : slot) * VEC_PER_ROW + u;
+    store_vec<STREAM>(k_pool, dst, k_in[src]);
+    store_vec<STREAM>(v_pool, dst, v_in[src]);
   }
 }
 
@@ -742,7 +734,8 @@ hipError_t launch(const PruneArgs& a, hipStream_t stream) {
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const int chunks_per_row = (a.max_seqlen + kChunk - 1) / kChunk;
   if (chunks_per_row == 0) return hipSuccess;
-  const int64_t grid2 = (int64_t)rows * chunks_per_row;
+  const int copied = a.num_seqs * a.num_kv_heads;  // (row, head) pairs that the gather copies
+  const int64_t grid2 = (int64_t)copied * chunks_per_row;
   if (grid2 > 0x7fffffffLL) return hipErrorInvalidValue;
   constexpr int VPR = G::kLanesPerRow;
   // Kept rows of a prompt that is larger than the Infinity Cache go past the caches: what the gather reads is not there either, and
@@ -750,12 +743,12 @@ hipError_t launch(const PruneArgs& a, hipStream_t stream) {
   // 134 MB kept 418 / 409; 0.6 GB, 67 MB kept 141 / 137, fp32 110 / 106; 0.5 GB, 67 MB kept 127 / 122, written right before 133 / 136; smaller
   // ones, written right before, 268 MB 84 / 87, 67 MB 33.8 / 34.9).
   const bool streamed = a.total_tokens * row_bytes > (int64_t)256 << 20;
-  const auto gather = a.shared ? (streamed ? gather_kernel<0, true> : gather_kernel<0, false>)
-                               : (streamed ? gather_kernel<VPR, true> : gather_kernel<VPR, false>);
+  const auto gather = a.shared ? (streamed ? gather_kernel<VPR, true, true> : gather_kernel<VPR, true, false>)
+                               : (streamed ? gather_kernel<VPR, false, true> : gather_kernel<VPR, false, false>);
   hipLaunchKernelGGL(gather, dim3((unsigned)grid2), dim3(kThreads), 0, stream, (const uint4*)a.k_in, (const uint4*)a.v_in,
                      sel_scores, a.cu_seqlens, w.sel, w.before, a.block_table, (uint4*)a.k_pool, (uint4*)a.v_pool,
-                     a.kept_idx_out, a.total_tokens, w.chunk_slots, heads, rows, ilog2(a.block_size), a.max_blocks, a.budget,
-                     a.shared ? VPR * a.num_kv_heads : VPR);
+                     a.kept_idx_out, a.total_tokens, w.chunk_slots, a.num_kv_heads, copied, ilog2(a.block_size), a.max_blocks,
+                     a.budget);
   return hipGetLastError();
 }
 
