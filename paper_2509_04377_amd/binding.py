@@ -105,7 +105,8 @@ def lib():
         L.pe_evict_blocks_cached.restype = ctypes.c_int
         L.pe_evict_blocks_cached.argtypes = [dp, vp, vp, vp, i32, vp, vp, vp]
         # addresses of the functions that are called through _pe_host
-        for name in ("paged_decode", "append_paged_decode", "append_paged_decode_layers", "prefill_prune"):
+        for name in ("paged_decode", "append_paged_decode", "append_paged_decode_layers", "prefill_prune",
+                     "score_triggered_blocks", "score_recent_blocks", "evict_blocks", "evict_blocks_cached"):
             setattr(L, "addr_" + name, ctypes.cast(getattr(L, "pe_" + name), vp).value)
         _lib = L
     return _lib
@@ -151,9 +152,9 @@ def ptr(t, name, dtype=None, optional=False):
 
 
 # What the calls below pass: the checks of ptr(), and the current stream and the workspace, as plain numbers (ctypes converts
-# them by the declared argument types).  The calls that come once a layer try _pe_host first, which does the same in native code:
-# a small launch is over sooner than its arguments are put together here.  It returns None for anything out of the ordinary;
-# the way through ctypes then accepts it or raises what is wrong.
+# them by the declared argument types).  The calls of prompts and decode steps try _pe_host first, which does the same in native
+# code: a small launch is over sooner than its arguments are put together here.  It returns None for anything out of the
+# ordinary; the way through ctypes then accepts it or raises what is wrong.
 def _addr(t, name, dtype=None):
     if t is not None and t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype is dtype):
         return t.data_ptr()
@@ -213,18 +214,27 @@ def pe_prefill_prune(desc, k_in, v_in, cu_seqlens, total_tokens, max_seqlen, bud
 
 
 def pe_evict_blocks(desc, scores, block_table, seq_lens, budget_tokens, evicted_logical_out, freed_phys_out):
-    check(lib().pe_evict_blocks(ctypes.byref(desc), _addr(scores, "scores", torch.float32),
-                                 _addr(block_table, "block_table", torch.int32), _addr(seq_lens, "seq_lens", torch.int32),
-                                 int(budget_tokens), _addr(evicted_logical_out, "evicted_logical_out", torch.int32),
-                                 _addr(freed_phys_out, "freed_phys_out", torch.int32), _stream()), "pe_evict_blocks")
+    L = lib()
+    status = _host.evict_blocks(L.addr_evict_blocks, desc, scores, block_table, seq_lens, budget_tokens, evicted_logical_out,
+                                freed_phys_out)
+    if status is None:
+        status = L.pe_evict_blocks(ctypes.byref(desc), _addr(scores, "scores", torch.float32),
+                                   _addr(block_table, "block_table", torch.int32), _addr(seq_lens, "seq_lens", torch.int32),
+                                   int(budget_tokens), _addr(evicted_logical_out, "evicted_logical_out", torch.int32),
+                                   _addr(freed_phys_out, "freed_phys_out", torch.int32), _stream())
+    check(status, "pe_evict_blocks")
 
 
 def pe_score_triggered_blocks(desc, k_pool, v_pool, block_table, seq_lens, budget_tokens, scores_inout):
-    check(lib().pe_score_triggered_blocks(ctypes.byref(desc), _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
-                                           _addr(block_table, "block_table", torch.int32),
-                                           _addr(seq_lens, "seq_lens", torch.int32), int(budget_tokens),
-                                           _addr(scores_inout, "scores_inout", torch.float32), _stream()),
-           "pe_score_triggered_blocks")
+    L = lib()
+    status = _host.score_triggered_blocks(L.addr_score_triggered_blocks, desc, k_pool, v_pool, block_table, seq_lens,
+                                          budget_tokens, scores_inout)
+    if status is None:
+        status = L.pe_score_triggered_blocks(ctypes.byref(desc), _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
+                                             _addr(block_table, "block_table", torch.int32),
+                                             _addr(seq_lens, "seq_lens", torch.int32), int(budget_tokens),
+                                             _addr(scores_inout, "scores_inout", torch.float32), _stream())
+    check(status, "pe_score_triggered_blocks")
 
 
 def pe_score_evict(desc, k_pool, v_pool, block_table, seq_lens, budget_tokens, scores_out, evicted_logical_out,
@@ -237,21 +247,29 @@ def pe_score_evict(desc, k_pool, v_pool, block_table, seq_lens, budget_tokens, s
 
 
 def pe_score_recent_blocks(desc, k_pool, v_pool, block_table, seq_lens, recent, scores_inout):
-    check(lib().pe_score_recent_blocks(ctypes.byref(desc), _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
-                                        _addr(block_table, "block_table", torch.int32),
-                                        _addr(seq_lens, "seq_lens", torch.int32), int(recent),
-                                        _addr(scores_inout, "scores_inout", torch.float32), _stream()),
-           "pe_score_recent_blocks")
+    L = lib()
+    status = _host.score_recent_blocks(L.addr_score_recent_blocks, desc, k_pool, v_pool, block_table, seq_lens, recent,
+                                       scores_inout)
+    if status is None:
+        status = L.pe_score_recent_blocks(ctypes.byref(desc), _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
+                                          _addr(block_table, "block_table", torch.int32),
+                                          _addr(seq_lens, "seq_lens", torch.int32), int(recent),
+                                          _addr(scores_inout, "scores_inout", torch.float32), _stream())
+    check(status, "pe_score_recent_blocks")
 
 
 def pe_evict_blocks_cached(desc, scores_inout, block_table, seq_lens, budget_tokens, evicted_logical_out,
                            freed_phys_out):
-    check(lib().pe_evict_blocks_cached(ctypes.byref(desc), _addr(scores_inout, "scores_inout", torch.float32),
-                                        _addr(block_table, "block_table", torch.int32),
-                                        _addr(seq_lens, "seq_lens", torch.int32), int(budget_tokens),
-                                        _addr(evicted_logical_out, "evicted_logical_out", torch.int32),
-                                        _addr(freed_phys_out, "freed_phys_out", torch.int32), _stream()),
-           "pe_evict_blocks_cached")
+    L = lib()
+    status = _host.evict_blocks_cached(L.addr_evict_blocks_cached, desc, scores_inout, block_table, seq_lens, budget_tokens,
+                                       evicted_logical_out, freed_phys_out)
+    if status is None:
+        status = L.pe_evict_blocks_cached(ctypes.byref(desc), _addr(scores_inout, "scores_inout", torch.float32),
+                                          _addr(block_table, "block_table", torch.int32),
+                                          _addr(seq_lens, "seq_lens", torch.int32), int(budget_tokens),
+                                          _addr(evicted_logical_out, "evicted_logical_out", torch.int32),
+                                          _addr(freed_phys_out, "freed_phys_out", torch.int32), _stream())
+    check(status, "pe_evict_blocks_cached")
 
 
 def pe_evict_blocks_ex(desc, opts, scores, block_table, seq_lens, budget_tokens, evicted_logical_out, freed_phys_out):

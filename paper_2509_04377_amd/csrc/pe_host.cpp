@@ -1,5 +1,5 @@
-// Argument marshalling of the library's calls that come once a layer, for binding.py: tensors are checked (on a GPU, dense, of the
-// type asked for) and turned into addresses, the current stream is added, and the C function is called with the interpreter's
+// Argument marshalling of the library's calls for prompts and decode steps, for binding.py: tensors are checked (on a GPU, dense,
+// of the type asked for) and turned into addresses, the current stream is added, and the C function is called with the interpreter's
 // lock released.  A small launch is over sooner than the same checks take from Python (one layer of one sequence: 10.5 us a
 // step with them in Python, 7.8 with these; the kernel takes 5).
 //
@@ -41,6 +41,10 @@ struct Tensor {
 struct Ints {
   std::tuple<Address> c;
   bool get(PyObject* o) { return address_of(o, true, at::kInt, &std::get<0>(c)); }
+};
+struct Floats {
+  std::tuple<Address> c;
+  bool get(PyObject* o) { return address_of(o, true, at::kFloat, &std::get<0>(c)); }
 };
 struct IntsOrNone {
   std::tuple<Address> c;
@@ -159,6 +163,14 @@ PyMethodDef methods[] = {
     // workspace
     method<call<decltype(&pe_prefill_prune), Tensor, Tensor, Ints, Number<int64_t>, Number<int32_t>, Number<int32_t>, Tensor, Tensor,
                 Ints, Ints, IntsOrNone, Workspace>>("prefill_prune"),
+    // k_pool, v_pool, block_table, seq_lens, budget_tokens, scores_inout
+    method<call<decltype(&pe_score_triggered_blocks), Tensor, Tensor, Ints, Ints, Number<int32_t>, Floats>>(
+        "score_triggered_blocks"),
+    // the same with `recent`
+    method<call<decltype(&pe_score_recent_blocks), Tensor, Tensor, Ints, Ints, Number<int32_t>, Floats>>("score_recent_blocks"),
+    // scores, block_table, seq_lens, budget_tokens, evicted_logical_out, freed_phys_out
+    method<call<decltype(&pe_evict_blocks), Floats, Ints, Ints, Number<int32_t>, Ints, Ints>>("evict_blocks"),
+    method<call<decltype(&pe_evict_blocks_cached), Floats, Ints, Ints, Number<int32_t>, Ints, Ints>>("evict_blocks_cached"),
     {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_pe_host", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

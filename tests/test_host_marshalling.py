@@ -82,3 +82,28 @@ def test_native_call_runs_on_the_current_stream():
         pe.pe_paged_decode(desc, late, k, v, table, lens, 0.125, got)   # behind `late` only on this stream
     side.synchronize()
     assert torch.equal(got, want)
+
+
+@pytest.mark.gpu
+def test_score_and_evict_marshalling():
+    L = pe.lib()
+    desc, q, k, v, table, lens = _args("cuda")
+    lens = torch.tensor([16, 64, 48], dtype=torch.int32, device="cuda")
+    outs = []
+    for native in (True, False):
+        t, n = table.clone(), lens.clone()
+        scores = torch.zeros((S, Hk, PAGES), device="cuda")
+        gone, freed = (torch.full((S, Hk), -7, dtype=torch.int32, device="cuda") for _ in range(2))
+        budget = 48 if native else torch.tensor(48)   # only int() understands the second
+        if native:
+            assert pe._host.score_triggered_blocks(L.addr_score_triggered_blocks, desc, k, v, t, n, budget, scores) == pe.PE_OK
+            assert pe._host.evict_blocks(L.addr_evict_blocks, desc, scores, t, n, budget, gone, freed) == pe.PE_OK
+        else:
+            pe.pe_score_triggered_blocks(desc, k, v, t, n, budget, scores)
+            pe.pe_evict_blocks(desc, scores, t, n, budget, gone, freed)
+        outs.append((t, n, scores, gone, freed))
+    assert all(torch.equal(a, b) for a, b in zip(*outs)) and outs[0][1].tolist() == [16, 48, 32]
+    with pytest.raises(ValueError, match="scores must be torch.float32"):
+        pe.pe_evict_blocks(desc, outs[0][2].double(), *outs[0][:2], 48, *outs[0][3:])
+    with pytest.raises(pe.PeError):   # no multiple of the page
+        pe.pe_evict_blocks(desc, outs[0][2], *outs[0][:2], 40, *outs[0][3:])
