@@ -397,34 +397,51 @@ __global__ __launch_bounds__(kWaves * kWave) void paged_decode_kernel(
     }
 }
 
-// Merge the split partials of one (sequence, query head): one workgroup of D threads.
+// Merge the split partials of one (sequence, query head): one wave, D / 64 elements a lane.  What a launch of it costs is the
+// launch and one round trip to the records.  `group` > 0: eight rows of so many heads a grid row, so that a row's records are read
+// on the XCD that wrote them (D = 128, 32 rows x 4096 in eight splits 16.4 us a layer, with this and 8-byte loads 16.2; 192 ragged
+// rows with eight query heads 78.4 and 77.6; D = 64 40.8 and 41.0: there without).
 template <typename T, int D>
-__global__ __launch_bounds__(D) void paged_decode_reduce_kernel(const float* __restrict__ partials,
-                                                                void* __restrict__ out, int total_heads, int splits) {
-  const int sh = (int)blockIdx.x;  // s * Hq + hq
-  const int d = (int)threadIdx.x;
-  const float* base = partials + (int64_t)sh * (D + 2);
+__global__ __launch_bounds__(kWave) void paged_decode_reduce_kernel(const float* __restrict__ partials, void* __restrict__ out,
+                                                                    int total_heads, int splits, int group) {
+  constexpr int E = D / kWave;
+  const int sh = group > 0 ? ((int)blockIdx.y * 8 + ((int)blockIdx.x & 7)) * group + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
+  const int d = (int)threadIdx.x * E;
+  const float* base = partials + (int64_t)sh * (D + 2);  // sh = s * Hq + hq
   const int64_t stride = (int64_t)total_heads * (D + 2);
   // one pass, online: all loads are independent of the running state, so they overlap
-  float mm = kNegInf, o = 0.f, l = 0.f;
+  float mm = kNegInf, l = 0.f, o[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) o[e] = 0.f;
 #pragma unroll 4
   for (int sp = 0; sp < splits; ++sp) {
-    const float m_sp = base[sp * stride + D];
-    const float l_sp = base[sp * stride + D + 1];
-    const float a_sp = base[sp * stride + d];
-    const float m_new = fmaxf(mm, m_sp);
+    const float* record = base + sp * stride;
+    const float2 ml = *reinterpret_cast<const float2*>(record + D);
+    float a[E];
+    if constexpr (E == 2) {
+      const float2 v = *reinterpret_cast<const float2*>(record + d);
+      a[0] = v.x;
+      a[1] = v.y;
+    } else {
+      a[0] = record[d];
+    }
+    const float m_new = fmaxf(mm, ml.x);
     const float ms = m_new == kNegInf ? 0.f : m_new;
-    const float w_old = __builtin_amdgcn_exp2f(mm - ms), w_new = __builtin_amdgcn_exp2f(m_sp - ms);
-    l = fmaf(l, w_old, l_sp * w_new);
-    o = fmaf(o, w_old, a_sp * w_new);
+    const float w_old = __builtin_amdgcn_exp2f(mm - ms), w_new = __builtin_amdgcn_exp2f(ml.x - ms);
+    l = fmaf(l, w_old, ml.y * w_new);
+#pragma unroll
+    for (int e = 0; e < E; ++e) o[e] = fmaf(o[e], w_old, a[e] * w_new);
     mm = m_new;
   }
-  const float r = l > 0.f ? o / l : 0.f;
   const int64_t off = (int64_t)sh * D + d;
-  if constexpr (sizeof(T) == 4) {
-    static_cast<float*>(out)[off] = r;
-  } else {
-    static_cast<uint16_t*>(out)[off] = f32_to_bf16(r);
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const float r = l > 0.f ? o[e] / l : 0.f;
+    if constexpr (sizeof(T) == 4) {
+      static_cast<float*>(out)[off + e] = r;
+    } else {
+      static_cast<uint16_t*>(out)[off + e] = f32_to_bf16(r);
+    }
   }
 }
 
@@ -457,8 +474,11 @@ hipError_t launch_group(const DecodeArgs& a, hipStream_t stream) {
 
 template <typename T, int D>
 void launch_reduce(const DecodeArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL((paged_decode_reduce_kernel<T, D>), dim3((unsigned)(a.num_seqs * a.num_q_heads)), dim3(D), 0, stream,
-                     a.partials, a.out, a.num_seqs * a.num_q_heads, a.splits);
+  const int64_t rows = (int64_t)a.num_seqs * a.num_kv_heads;
+  const int heads = a.num_seqs * a.num_q_heads;
+  const int group = D == 128 && a.xcd_map && rows % 8 == 0 && rows / 8 <= 65535 ? a.num_q_heads / a.num_kv_heads : 0;
+  const dim3 blocks = group > 0 ? dim3((unsigned)(8 * group), (unsigned)(rows / 8)) : dim3((unsigned)heads);
+  hipLaunchKernelGGL((paged_decode_reduce_kernel<T, D>), blocks, dim3(kWave), 0, stream, a.partials, a.out, heads, a.splits, group);
 }
 
 }  // namespace
