@@ -398,17 +398,22 @@ __global__ __launch_bounds__(kWaves * kWave) void paged_decode_kernel(
 }
 
 // Merge the split partials of one (sequence, query head): one wave, D / 64 elements a lane.  What a launch of it costs is the
-// launch and one round trip to the records.  `group` > 0: eight rows of so many heads a grid row, so that a row's records are read
-// on the XCD that wrote them (D = 128, 32 rows x 4096 in eight splits 16.4 us a layer, with this and 8-byte loads 16.2; 192 ragged
-// rows with eight query heads 78.4 and 77.6; D = 64 40.8 and 41.0: there without).
+// launch and one round trip to the records, which lie together for a row ([row][split][head]: with the heads of all rows under
+// each split 0.4 us more for 32 rows of D = 128 in eight splits, 1.1 us for 16 rows in 16).  The grid: the query heads of a row
+// side by side, one row a grid row; with kMergeXcd eight rows a grid row, so that a row's records are read on the XCD that wrote
+// them (D = 128, 32 rows x 4096 in eight splits 16.4 us a layer, with this and 8-byte loads 16.2; 192 ragged rows with eight
+// query heads 78.4 and 77.6; D = 64 40.8 and 41.0: there without); kMergeLinear: more rows than a grid has, divided.
+enum { kMergeLinear, kMergeRows, kMergeXcd };
 template <typename T, int D>
 __global__ __launch_bounds__(kWave) void paged_decode_reduce_kernel(const float* __restrict__ partials, void* __restrict__ out,
-                                                                    int total_heads, int splits, int group) {
+                                                                    int g_real, int splits, int order) {
   constexpr int E = D / kWave;
-  const int sh = group > 0 ? ((int)blockIdx.y * 8 + ((int)blockIdx.x & 7)) * group + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
+  const int x = (int)blockIdx.x, y = (int)blockIdx.y;
+  const int row = order == kMergeLinear ? x / g_real : order == kMergeXcd ? y * 8 + (x & 7) : y;
+  const int h = order == kMergeLinear ? x - row * g_real : order == kMergeXcd ? x >> 3 : x;
   const int d = (int)threadIdx.x * E;
-  const float* base = partials + (int64_t)sh * (D + 2);  // sh = s * Hq + hq
-  const int64_t stride = (int64_t)total_heads * (D + 2);
+  const float* base = partials + ((int64_t)row * splits * g_real + h) * (D + 2);
+  const int64_t stride = (int64_t)g_real * (D + 2);
   // one pass, online: all loads are independent of the running state, so they overlap
   float mm = kNegInf, l = 0.f, o[E];
 #pragma unroll
@@ -433,7 +438,7 @@ __global__ __launch_bounds__(kWave) void paged_decode_reduce_kernel(const float*
     for (int e = 0; e < E; ++e) o[e] = fmaf(o[e], w_old, a[e] * w_new);
     mm = m_new;
   }
-  const int64_t off = (int64_t)sh * D + d;
+  const int64_t off = ((int64_t)row * g_real + h) * D + d;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const float r = l > 0.f ? o[e] / l : 0.f;
@@ -475,10 +480,12 @@ hipError_t launch_group(const DecodeArgs& a, hipStream_t stream) {
 template <typename T, int D>
 void launch_reduce(const DecodeArgs& a, hipStream_t stream) {
   const int64_t rows = (int64_t)a.num_seqs * a.num_kv_heads;
-  const int heads = a.num_seqs * a.num_q_heads;
-  const int group = D == 128 && a.xcd_map && rows % 8 == 0 && rows / 8 <= 65535 ? a.num_q_heads / a.num_kv_heads : 0;
-  const dim3 blocks = group > 0 ? dim3((unsigned)(8 * group), (unsigned)(rows / 8)) : dim3((unsigned)heads);
-  hipLaunchKernelGGL((paged_decode_reduce_kernel<T, D>), blocks, dim3(kWave), 0, stream, a.partials, a.out, heads, a.splits, group);
+  const int g = a.num_q_heads / a.num_kv_heads;
+  const bool xcd = D == 128 && a.xcd_map && rows % 8 == 0;
+  const int64_t grid_rows = xcd ? rows / 8 : rows;
+  const int order = grid_rows > 65535 ? kMergeLinear : xcd ? kMergeXcd : kMergeRows;
+  const dim3 blocks = order == kMergeLinear ? dim3((unsigned)(rows * g)) : dim3((unsigned)(xcd ? 8 * g : g), (unsigned)grid_rows);
+  hipLaunchKernelGGL((paged_decode_reduce_kernel<T, D>), blocks, dim3(kWave), 0, stream, a.partials, a.out, g, a.splits, order);
 }
 
 }  // namespace

@@ -23,7 +23,6 @@ namespace pe {
 struct DecodeParams {
   void* out;
   float* partials;
-  int total_heads;  // S * Hq: partial records of a split
   float scale_log2e;
   // fused append (FUSED kernels only)
   int n_spare;
@@ -60,8 +59,8 @@ inline bool decode_kernel_args(const DecodeArgs& a, DecodeKernelArgs* k, dim3* b
   *k = DecodeKernelArgs{a.seq_lens, a.block_table, a.q, a.k_pool, a.v_pool, a.num_kv_heads, a.max_blocks, g.inv_heads,
                         (uint32_t)log2_block | (uint32_t)(a.num_q_heads / a.num_kv_heads) << 3 | (g.xcd ? kShapeXcd : 0u) |
                             (g.linear ? kShapeLinear : 0u) | (uint32_t)a.splits << 9,
-                        DecodeParams{a.out, a.partials, a.num_seqs * a.num_q_heads, a.scale * 1.4426950408889634f, a.n_spare,
-                                     a.new_k, a.new_v, a.freed_phys, a.spare, a.spare_used, a.seq_lens_out}};
+                        DecodeParams{a.out, a.partials, a.scale * 1.4426950408889634f, a.n_spare, a.new_k, a.new_v, a.freed_phys,
+                                     a.spare, a.spare_used, a.seq_lens_out}};
   return true;
 }
 
@@ -77,8 +76,8 @@ __device__ __forceinline__ DecodeParams decode_params(int behind) {
   uint64_t args = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(DecodeKernelArgs, p);
   asm("" : "+s"(args) : "s"(behind));
   const auto* a = reinterpret_cast<const __attribute__((address_space(4))) DecodeParams*>(args);
-  return DecodeParams{a->out,   a->partials,   a->total_heads, a->scale_log2e, a->n_spare,     a->new_k,
-                      a->new_v, a->freed_phys, a->spare,       a->spare_used,  a->seq_lens_out};
+  return DecodeParams{a->out,   a->partials,   a->scale_log2e, a->n_spare,    a->new_k,
+                      a->new_v, a->freed_phys, a->spare,       a->spare_used, a->seq_lens_out};
 }
 
 // Two neighbouring elements of the output in one store, at any boundary of their own size.
@@ -132,7 +131,7 @@ __device__ __forceinline__ void merge_waves(const WaveStates<WAVES, GH, D>& sm, 
         static_cast<Bf16Pair*>(p.out)[pair].v = (uint32_t)f32_to_bf16(r0) | ((uint32_t)f32_to_bf16(r1) << 16);
       }
     } else {
-      float* record = p.partials + ((int64_t)split * p.total_heads + head) * (D + 2);
+      float* record = p.partials + (((int64_t)row * splits + split) * g_real + h) * (D + 2);
       *reinterpret_cast<float2*>(record + d) = make_float2(o0, o1);
       if (d == 0) *reinterpret_cast<float2*>(record + D) = make_float2(mm, ll);
     }

@@ -72,7 +72,7 @@ struct DecodeArgs {
   const int32_t* block_table;
   const int32_t* seq_lens;
   void* out;
-  float* partials;  // workspace: [splits][S * Hq][D + 2] fp32 (unused when splits == 1)
+  float* partials;  // workspace: [rows][splits][G][D + 2] fp32 (unused when splits == 1)
   float scale;
   int num_seqs, num_kv_heads, num_q_heads, head_dim, block_size, max_blocks;
   int splits;
