@@ -170,13 +170,5 @@ __device__ __forceinline__ uint4 load_vec_stream(const void* base, int64_t vec_i
   const u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(base) + vec_index);
   return make_uint4(v.x, v.y, v.z, v.w);
 }
-template <bool STREAM>
-__device__ __forceinline__ void store_vec(uint4* base, int64_t vec_index, const uint4& v) {
-  if constexpr (STREAM) {
-    __builtin_nontemporal_store(u32x4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4_t*>(base) + vec_index);
-  } else {
-    base[vec_index] = v;
-  }
-}
 
 }  // namespace pe

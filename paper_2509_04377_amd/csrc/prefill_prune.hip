@@ -609,8 +609,8 @@ SelectKernel select_kernel_for(int max_seqlen) {
 // One workgroup per (row, chunk) copies the kept token rows of one head.  SHARED: the heads of a sequence share its selection and its
 // table row, their token rows lie num_kv_heads apart in the pages (whole records by one workgroup were a division per
 // 16 bytes and an eighth of the workgroups: 16 prompts of 2048 to 8192 tokens, 8 heads, 1024 kept 204 us a prune, now 98; 8 x 4096 of
-// D = 64 54.8, now 31.1).  STREAM: stores with the non-temporal hint.
-template <int VEC_PER_ROW, bool SHARED, bool STREAM>
+// D = 64 54.8, now 31.1).
+template <int VEC_PER_ROW, bool SHARED>
 __global__ __launch_bounds__(kThreads) void gather_kernel(const uint4* __restrict__ k_in, const uint4* __restrict__ v_in,
                                                           const float* __restrict__ scores,
                                                           const int32_t* __restrict__ cu_seqlens,
@@ -698,8 +698,8 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(const uint4* __restric
     const int64_t src = ((int64_t)(t0 + src_tok[e]) * num_kv_heads + h) * VEC_PER_ROW + u;
     const int64_t slot = ((int64_t)bt[pos >> log2_block] << log2_block) + (pos & block_mask);
     const int64_t dst = (SHARED ? slot * num_kv_heads + h : slot) * VEC_PER_ROW + u;
-    store_vec<STREAM>(k_pool, dst, k_in[src]);
-    store_vec<STREAM>(v_pool, dst, v_in[src]);
+    k_pool[dst] = k_in[src];
+    v_pool[dst] = v_in[src];
   }
 }
 
@@ -751,13 +751,10 @@ hipError_t launch(const PruneArgs& a, hipStream_t stream) {
   const int64_t grid2 = (int64_t)copied * chunks_per_row;
   if (grid2 > 0x7fffffffLL) return hipErrorInvalidValue;
   constexpr int VPR = G::kLanesPerRow;
-  // Kept rows of a prompt that is larger than the Infinity Cache go past the caches: what the gather reads is not there either, and
-  // what it writes need not push it out (whole prunes, plain stores / with the hint: 2.1 GB of prompt, 268 MB kept 465 / 453 us,
-  // 134 MB kept 418 / 409; 0.6 GB, 67 MB kept 141 / 137, fp32 110 / 106; 0.5 GB, 67 MB kept 127 / 122, written right before 133 / 136; smaller
-  // ones, written right before, 268 MB 84 / 87, 67 MB 33.8 / 34.9).
-  const bool streamed = a.total_tokens * row_bytes > (int64_t)256 << 20;
-  const auto gather = a.shared ? (streamed ? gather_kernel<VPR, true, true> : gather_kernel<VPR, true, false>)
-                               : (streamed ? gather_kernel<VPR, false, true> : gather_kernel<VPR, false, false>);
+  // Plain stores for what is kept.  With the non-temporal hint prunes of 32 x 16384 tokens that go into the same pools again and
+  // again take 454 us instead of 467, but those of a model's layers, one after the other and each into its own pool, 475 instead of
+  // 457 (four prompts of 65536 229 and 223, 3B prompts 141 and 137, the head-shared layout 455 and 436).
+  const auto gather = a.shared ? gather_kernel<VPR, true> : gather_kernel<VPR, false>;
   hipLaunchKernelGGL(gather, dim3((unsigned)grid2), dim3(kThreads), 0, stream, (const uint4*)a.k_in, (const uint4*)a.v_in,
                      sel_scores, a.cu_seqlens, w.sel, w.before, a.block_table, (uint4*)a.k_pool, (uint4*)a.v_pool,
                      a.kept_idx_out, a.total_tokens, w.chunk_slots, a.num_kv_heads, copied, ilog2(a.block_size), a.max_blocks,
