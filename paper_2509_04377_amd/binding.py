@@ -166,7 +166,16 @@ def _addr_opt(t, name, dtype=None):
 
 
 def _ws(workspace):
-    return (None, 0) if workspace is None else (workspace.data_ptr(), workspace.nbytes)
+    if workspace is None:
+        return None, 0
+    if not workspace.is_cuda:
+        raise ValueError("workspace must be a GPU tensor")
+    # its bytes are its own only if nothing else lies between them, whatever the order of its dimensions
+    if not workspace.is_contiguous():
+        by_stride = sorted(range(workspace.dim()), key=workspace.stride, reverse=True)
+        if not workspace.permute(by_stride).is_contiguous():
+            raise ValueError("workspace must be dense")
+    return workspace.data_ptr(), workspace.nbytes
 
 
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
@@ -191,10 +200,10 @@ def alloc_workspace(op: int, desc: pe_cache_desc, total_tokens: int = 0, device=
 
 
 def pe_score_blocks(desc, k_pool, v_pool, block_table, seq_lens, scores_out, workspace=None):
-    wp, wn = _ws(workspace)
+    # (the call needs no workspace; whatever is given is not looked at)
     check(lib().pe_score_blocks(ctypes.byref(desc), _addr(k_pool, "k_pool"), _addr(v_pool, "v_pool"),
                                  _addr(block_table, "block_table", torch.int32), _addr(seq_lens, "seq_lens", torch.int32),
-                                 _addr(scores_out, "scores_out", torch.float32), wp, wn, _stream()), "pe_score_blocks")
+                                 _addr(scores_out, "scores_out", torch.float32), None, 0, _stream()), "pe_score_blocks")
 
 
 def pe_prefill_prune(desc, k_in, v_in, cu_seqlens, total_tokens, max_seqlen, budget_tokens, k_pool, v_pool,

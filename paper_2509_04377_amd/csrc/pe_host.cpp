@@ -88,6 +88,8 @@ struct Workspace {
     if (o == Py_None) return true;
     if (!THPVariable_Check(o)) return false;
     const at::Tensor& t = THPVariable_Unpack(o);
+    // (its bytes are its own only if nothing else lies between them, whatever the order of its dimensions)
+    if (!t.defined() || !t.is_cuda() || t.layout() != at::kStrided || !t.is_non_overlapping_and_dense()) return false;
     std::get<0>(c).p = t.data_ptr();
     std::get<1>(c) = t.nbytes();
     return true;

@@ -33,6 +33,12 @@ def test_what_is_not_a_dense_gpu_tensor_is_left_to_ctypes():
         pe._host.paged_decode(0, desc, q, k, v, table, lens, 0.1, q, None)
 
 
+def test_workspace_in_host_memory_is_refused():
+    assert pe._ws(None) == (None, 0)
+    with pytest.raises(ValueError, match="workspace must be a GPU tensor"):
+        pe._ws(torch.empty(1 << 16, dtype=torch.uint8))
+
+
 def test_descriptor_is_the_structure_of_the_header():
     assert ctypes.sizeof(pe.pe_cache_desc) == 56
 
@@ -65,6 +71,32 @@ def test_gpu_arguments_that_are_refused():
         pe.pe_paged_decode(pe.make_desc(torch.float32, S, Hk, Hq, 96, B, PAGES, S * Hk * PAGES), q, k, v, table, lens, 0.1, out)
     with pytest.raises(pe.PeError):
         pe.pe_paged_decode(desc, None, k, v, table, lens, 0.1, out)
+
+
+@pytest.mark.gpu
+def test_workspace_that_is_not_a_dense_gpu_tensor():
+    """What a workspace claims to hold has to be device memory of its own.  The native call gets a stand-in for the C function:
+    nothing is launched with any of these."""
+    desc, q, k, v, table, lens = _args("cuda")
+    desc.decode_splits = 4
+    need = pe.pe_workspace_bytes(pe.PE_OP_PAGED_DECODE, desc)
+    given = []
+    vp = ctypes.c_void_p
+    stand_in = ctypes.CFUNCTYPE(ctypes.c_int, vp, vp, vp, vp, vp, vp, ctypes.c_float, vp, vp, ctypes.c_size_t, vp)(
+        lambda *a: given.append((a[8], a[9])) or 0)
+    address = ctypes.cast(stand_in, vp).value
+    whole = torch.empty((2, need), dtype=torch.uint8, device="cuda")
+    bad = {"host": torch.empty(need, dtype=torch.uint8), "gaps": whole.view(-1)[::2], "columns": whole[:, :need // 2],
+           "repeated": whole[0, :1].expand(need), "sparse": torch.zeros((4, need), device="cuda").to_sparse()}
+    for kind, ws in bad.items():
+        assert pe._host.paged_decode(address, desc, q, k, v, table, lens, 0.125, q, ws) is None and not given, kind
+    for kind, ws in bad.items():
+        if kind != "sparse":
+            with pytest.raises(ValueError, match="workspace must be"):
+                pe.pe_paged_decode(desc, q, k, v, table, lens, 0.125, torch.empty_like(q), ws)
+    for ws in (whole, whole[1], whole.t(), None):
+        assert pe._host.paged_decode(address, desc, q, k, v, table, lens, 0.125, q, ws) == 0
+        assert pe._ws(ws) == given[-1]
 
 
 @pytest.mark.gpu
