@@ -50,6 +50,12 @@ class PeError(RuntimeError):
         super().__init__("%s failed: %s (%d)" % (where, status_string(status), status))
 
 
+def _layout(structure):
+    """Size, then name, offset and size of each field of a ctypes structure."""
+    fields = ((name, getattr(structure, name).offset, getattr(structure, name).size) for name, _ in structure._fields_)
+    return (ctypes.sizeof(structure),) + tuple(fields)
+
+
 _lib = None
 _host = None   # the native marshalling of the calls that come once a layer (csrc/pe_host.cpp), loaded with the library
 
@@ -65,6 +71,8 @@ def lib():
             raise RuntimeError("_pe_host.so is not built (%s): build as for libpe.so" % HOST_PATH)
         global _host
         from . import _pe_host as _host
+        if _host.bind_descriptor(pe_cache_desc) != _layout(pe_cache_desc):
+            raise RuntimeError("_pe_host.so has another pe_cache_desc: build again")
         L = ctypes.CDLL(LIB_PATH)
         vp, i32, i64, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_size_t
         dp = ctypes.POINTER(pe_cache_desc)

@@ -96,10 +96,14 @@ struct Workspace {
   }
 };
 
-// The descriptor: a ctypes structure of the size of the C one, read through the buffer protocol.
+// binding.py's ctypes structure (see bind_descriptor); nullptr: not named yet.
+PyTypeObject* descriptor_type = nullptr;
+
+// The descriptor: an object of that type and of no other, read through the buffer protocol.
 struct Desc {
   pe_cache_desc d;
   bool get(PyObject* o) {
+    if (descriptor_type == nullptr || Py_TYPE(o) != descriptor_type) return false;
     Py_buffer b;
     if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) {
       PyErr_Clear();
@@ -151,7 +155,29 @@ PyMethodDef method(const char* name) {
   return {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(F)), METH_FASTCALL, nullptr};
 }
 
+// Names the type of the descriptor, once, when the library is loaded.  Returns the C structure's layout for a comparison with
+// it: its size, then name, offset and size of each field.
+PyObject* bind_descriptor(PyObject*, PyObject* type) {
+  if (!PyType_Check(type)) {
+    PyErr_SetString(PyExc_TypeError, "the type of the descriptor");
+    return nullptr;
+  }
+#define PE_FIELD(f) #f, (Py_ssize_t)offsetof(pe_cache_desc, f), (Py_ssize_t)sizeof(pe_cache_desc::f)
+  PyObject* layout = Py_BuildValue(
+      "(n(snn)(snn)(snn)(snn)(snn)(snn)(snn)(snn)(snn)(snn)(snn)(snn))", (Py_ssize_t)sizeof(pe_cache_desc), PE_FIELD(dtype),
+      PE_FIELD(num_seqs), PE_FIELD(num_kv_heads), PE_FIELD(num_q_heads), PE_FIELD(head_dim), PE_FIELD(block_size),
+      PE_FIELD(max_blocks), PE_FIELD(num_phys_blocks), PE_FIELD(layout), PE_FIELD(decode_splits), PE_FIELD(decode_shape),
+      PE_FIELD(decode_flat_order));
+#undef PE_FIELD
+  if (layout == nullptr) return nullptr;
+  Py_INCREF(type);
+  Py_XDECREF((PyObject*)descriptor_type);
+  descriptor_type = reinterpret_cast<PyTypeObject*>(type);
+  return layout;
+}
+
 PyMethodDef methods[] = {
+    {"bind_descriptor", bind_descriptor, METH_O, nullptr},
     // q, k_pool, v_pool, block_table, seq_lens, softmax_scale, out, workspace
     method<call<decltype(&pe_paged_decode), Tensor, Tensor, Tensor, Ints, Ints, Float, Tensor, Workspace>>("paged_decode"),
     // new_k, new_v, q, k_pool, v_pool, block_table, seq_lens, seq_lens_out, freed_phys, spare, spare_used, spare, softmax_scale,

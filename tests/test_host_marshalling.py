@@ -24,7 +24,6 @@ def test_what_is_not_a_dense_gpu_tensor_is_left_to_ctypes():
     L = pe.lib()
     desc, q, k, v, table, lens = _args("cpu")
     assert pe._host.paged_decode(L.addr_paged_decode, desc, q, k, v, table, lens, 0.1, q, None) is None
-    assert pe._host.paged_decode(L.addr_paged_decode, b"short", q, k, v, table, lens, 0.1, q, None) is None
     with pytest.raises(ValueError, match="q must be a GPU tensor"):
         pe.pe_paged_decode(desc, q, k, v, table, lens, 0.1, torch.empty_like(q))
     with pytest.raises(TypeError):
@@ -40,7 +39,20 @@ def test_workspace_in_host_memory_is_refused():
 
 
 def test_descriptor_is_the_structure_of_the_header():
+    """The extension is compiled from include/pe.h: size, and name, offset and size of every field."""
+    pe.lib()
     assert ctypes.sizeof(pe.pe_cache_desc) == 56
+    assert pe._host.bind_descriptor(pe.pe_cache_desc) == pe._layout(pe.pe_cache_desc)
+    with pytest.raises(TypeError):
+        pe._host.bind_descriptor(pe.pe_cache_desc())
+
+
+class _LongerDesc(pe.pe_cache_desc):
+    _fields_ = [("more", ctypes.c_int32)]
+
+
+class _SameDesc(pe.pe_cache_desc):
+    pass
 
 
 @pytest.mark.gpu
@@ -71,6 +83,32 @@ def test_gpu_arguments_that_are_refused():
         pe.pe_paged_decode(pe.make_desc(torch.float32, S, Hk, Hq, 96, B, PAGES, S * Hk * PAGES), q, k, v, table, lens, 0.1, out)
     with pytest.raises(pe.PeError):
         pe.pe_paged_decode(desc, None, k, v, table, lens, 0.1, out)
+
+
+@pytest.mark.gpu
+def test_descriptor_of_another_type():
+    """56 bytes of anything are no descriptor: what ctypes.byref refuses stays refused, what it takes (a structure derived from
+    the descriptor) goes that way."""
+    desc, q, k, v, table, lens = _args("cuda")
+    given = []
+    vp = ctypes.c_void_p
+    stand_in = ctypes.CFUNCTYPE(ctypes.c_int, vp, vp, vp, vp, vp, vp, ctypes.c_float, vp, vp, ctypes.c_size_t, vp)(
+        lambda *a: given.append(a) or 0)
+    address = ctypes.cast(stand_in, vp).value
+    raw = bytes(desc)
+    values = [getattr(desc, name) for name, _ in desc._fields_]
+    others = [raw, raw[:-1], bytearray(raw), memoryview(raw), (ctypes.c_char * len(raw))(*raw), torch.zeros(7), None]
+    for other in others + [_LongerDesc(*values), _SameDesc(*values)]:
+        assert pe._host.paged_decode(address, other, q, k, v, table, lens, 0.125, q, None) is None and not given
+    assert pe._host.paged_decode(address, desc, q, k, v, table, lens, 0.125, q, None) == 0 and len(given) == 1
+    want, got = torch.empty_like(q), torch.empty_like(q)
+    pe.pe_paged_decode(desc, q, k, v, table, lens, 0.125, want)
+    for other in others:
+        with pytest.raises((TypeError, ctypes.ArgumentError)):
+            pe.pe_paged_decode(other, q, k, v, table, lens, 0.125, got)
+    for other in (_LongerDesc(*values), _SameDesc(*values)):
+        pe.pe_paged_decode(other, q, k, v, table, lens, 0.125, got.zero_())
+        assert torch.equal(want, got)
 
 
 @pytest.mark.gpu
