@@ -2,6 +2,7 @@
 // a division: a division by a run-time number is some forty dependent instructions, and two of them stood in front of a wave's
 // first load.  One row a grid row, its splits side by side; in the order that keeps the splits of a row on one XCD (workgroup
 // number b runs on XCD b % 8) eight rows a grid row.  Counts that do not fit that (`linear`) are divided as before.
+// And how many (row, chunk) workgroups go into one launch.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -26,6 +27,21 @@ inline bool place_grid(int num_seqs, int num_kv_heads, int splits, bool xcd_map,
   g->x = (uint32_t)(g->linear ? total : g->xcd ? 8 * splits : splits);
   g->y = (uint32_t)(g->linear ? 1 : grid_rows);
   g->inv_heads = num_kv_heads > 1 ? (uint32_t)((1ull << 32) / (uint32_t)num_kv_heads + 1) : 0u;
+  return true;
+}
+
+// (row, chunk) pairs of several sequences in launches of fewer than 2^32 threads: f(first sequence, sequences, first chunk, chunks) for
+// each of them until one gives false.  A launch covers all chunks of its sequences or some chunks of all its sequences.
+template <typename F>
+inline bool launch_pieces(int num_seqs, int rows_per_seq, int chunks, int threads, F f) {
+  const int64_t most = ((1LL << 32) - 1) / threads;
+  if (rows_per_seq > most) return false;
+  const int64_t seqs = most / rows_per_seq < num_seqs ? most / rows_per_seq : num_seqs;
+  for (int64_t s0 = 0; s0 < num_seqs; s0 += seqs) {
+    const int64_t ns = num_seqs - s0 < seqs ? num_seqs - s0 : seqs, some = most / (ns * rows_per_seq);
+    for (int64_t c0 = 0; c0 < chunks; c0 += some)
+      if (!f((int)s0, (int)ns, (int)c0, (int)(chunks - c0 < some ? chunks - c0 : some))) return false;
+  }
   return true;
 }
 

@@ -19,6 +19,7 @@
 #include "pe_device.h"
 #include "pe_launch.h"
 #include "pe_norms.h"
+#include "pe_place.h"
 
 namespace pe {
 namespace {
@@ -620,15 +621,16 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(const uint4* __restric
                                                           uint4* __restrict__ k_pool, uint4* __restrict__ v_pool,
                                                           int32_t* __restrict__ kept_idx_out, int64_t total_tokens,
                                                           int64_t chunk_slots, int num_kv_heads, int rows,
-                                                          int log2_block, int max_blocks, int budget) {
+                                                          int log2_block, int max_blocks, int budget, int row0,
+                                                          int chunk0) {
   __shared__ uint32_t wave_sum[kWaves];
   __shared__ int32_t src_tok[kChunk];  // kept tokens of this chunk, in order: in-sequence index
   __shared__ int n_kept_sh;
   // Rows fastest: the first chunks of a ragged batch, which short sequences keep most of, spread over all XCDs (workgroup
   // number % 8).  Chunks fastest put the first chunks of all sequences on one: 47 us instead of 30 for 16 sequences of
   // 2048 to 16384 tokens, 8 heads, 1024 kept of each (134 MB moved; the other prompts below did not change).
-  const int row = (int)(blockIdx.x % (unsigned)rows);
-  const int chunk = (int)(blockIdx.x / (unsigned)rows);
+  const int row = row0 + (int)(blockIdx.x % (unsigned)rows);
+  const int chunk = chunk0 + (int)(blockIdx.x / (unsigned)rows);
   const int s = row / num_kv_heads, h = row % num_kv_heads;
   const int sel_row = SHARED ? s : row, sel_h = SHARED ? 0 : h;  // whose scores decide
   const int t0 = cu_seqlens[s];
@@ -747,19 +749,22 @@ hipError_t launch(const PruneArgs& a, hipStream_t stream) {
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const int chunks_per_row = (a.max_seqlen + kChunk - 1) / kChunk;
   if (chunks_per_row == 0) return hipSuccess;
-  const int copied = a.num_seqs * a.num_kv_heads;  // (row, head) pairs that the gather copies
-  const int64_t grid2 = (int64_t)copied * chunks_per_row;
-  if (grid2 > 0x7fffffffLL) return hipErrorInvalidValue;
+  if ((int64_t)rows * chunks_per_row >= (1LL << 32) / kThreads) return hipErrorInvalidValue;
   constexpr int VPR = G::kLanesPerRow;
   // Plain stores for what is kept.  With the non-temporal hint prunes of 32 x 16384 tokens that go into the same pools again and
   // again take 454 us instead of 467, but those of a model's layers, one after the other and each into its own pool, 475 instead of
   // 457 (four prompts of 65536 229 and 223, 3B prompts 141 and 137, the head-shared layout 455 and 436).
   const auto gather = a.shared ? gather_kernel<VPR, true> : gather_kernel<VPR, false>;
-  hipLaunchKernelGGL(gather, dim3((unsigned)grid2), dim3(kThreads), 0, stream, (const uint4*)a.k_in, (const uint4*)a.v_in,
-                     sel_scores, a.cu_seqlens, w.sel, w.before, a.block_table, (uint4*)a.k_pool, (uint4*)a.v_pool,
-                     a.kept_idx_out, a.total_tokens, w.chunk_slots, a.num_kv_heads, copied, ilog2(a.block_size), a.max_blocks,
-                     a.budget);
-  return hipGetLastError();
+  e = hipErrorInvalidValue;  // (one launch, but where a head-shared batch has more than 2^24 (head, chunk) pairs)
+  launch_pieces(a.num_seqs, a.num_kv_heads, chunks_per_row, kThreads, [&](int s0, int ns, int c0, int nc) {
+    const int copied = ns * a.num_kv_heads;  // (row, head) pairs that this launch copies
+    hipLaunchKernelGGL(gather, dim3((unsigned)copied * (unsigned)nc), dim3(kThreads), 0, stream, (const uint4*)a.k_in,
+                       (const uint4*)a.v_in, sel_scores, a.cu_seqlens, w.sel, w.before, a.block_table, (uint4*)a.k_pool,
+                       (uint4*)a.v_pool, a.kept_idx_out, a.total_tokens, w.chunk_slots, a.num_kv_heads, copied,
+                       ilog2(a.block_size), a.max_blocks, a.budget, s0 * a.num_kv_heads, c0);
+    return (e = hipGetLastError()) == hipSuccess;
+  });
+  return e;
 }
 
 }  // namespace

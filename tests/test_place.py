@@ -83,3 +83,72 @@ def test_attention_over_many_rows(dt, S, Hk, splits):
         got = out[s0:s0 + step].float().view(want.shape)
         err = (got - want).norm(dim=-1) / want.norm(dim=-1)
         assert float(err.max()) <= tol, (s0, float(err.max()))
+
+
+PIECES = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+#include "%s/pe_place.h"
+int main(int argc, char** argv) {
+  const int S = atoi(argv[1]), rows = atoi(argv[2]), chunks = atoi(argv[3]), threads = 256;
+  std::vector<int64_t> next(1, 0);   // pairs come in whole rectangles, sequences slowest
+  int64_t covered = 0, launches = 0, s_at = 0, c_at = 0;
+  const bool all = pe::launch_pieces(S, rows, chunks, threads, [&](int s0, int ns, int c0, int nc) {
+    if (ns < 1 || nc < 1 || (int64_t)ns * rows * nc * threads >= (1LL << 32)) exit(2);
+    if (s0 != s_at || c0 != c_at || s0 + ns > S || c0 + nc > chunks) exit(3);
+    c_at += nc;
+    if (c_at == chunks) c_at = 0, s_at += ns;
+    covered += (int64_t)ns * nc;
+    return ++launches < 1000000;
+  });
+  if (all != (rows < (1 << 24))) return 4;
+  if (all && (covered != (int64_t)S * chunks || s_at != S)) return 5;
+  printf("%%lld\n", (long long)launches);
+  return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def pieces(tmp_path_factory):
+    d = tmp_path_factory.mktemp("pieces")
+    src, exe = d / "pieces.hip", d / "pieces"
+    src.write_text(PIECES % build.CSRC)
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    subprocess.run([hipcc] + build.FLAGS + [str(src), "-o", str(exe)], check=True, stderr=subprocess.DEVNULL)
+    return str(exe)
+
+
+@pytest.mark.parametrize("S,rows,chunks,launches", [
+    (1, 1, 1, 1), (32, 8, 16, 1), (4096, 8, 511, 1), (4096, 8, 512, 2), (4095, 8, 512, 1), (65536, 8, 100, 4), (1 << 21, 8, 1, 2),
+    (4194303, 7, 3, 6), (3, (1 << 24) - 1, 2, 6), (1, 1 << 24, 1, 0), (1, 5, 1 << 21, 1), (1, 1, (1 << 24) - 1, 1), (1, 1, 1 << 24, 2)])
+def test_launch_pieces_cover_every_pair_once(pieces, S, rows, chunks, launches):
+    r = subprocess.run([pieces, str(S), str(rows), str(chunks)], stdout=subprocess.PIPE, text=True)
+    assert r.returncode == 0 and int(r.stdout) == launches
+
+
+@pytest.mark.gpu
+def test_head_shared_prune_of_many_head_chunk_pairs():
+    """2^24 (head, chunk) pairs, more than one launch takes: the bound on the lengths sizes the launch, not the lengths."""
+    dev, S, Hk, D, B, n = "cuda", 4096, 8, 64, 16, 128
+    total = S * n
+    k, v = (torch.zeros((total, Hk, D), dtype=torch.bfloat16, device=dev) for _ in range(2))
+    g = torch.Generator(device=dev)
+    g.manual_seed(11)
+    k[:, :, 0] = 1.0
+    score = torch.rand((S, n), generator=g, device=dev).argsort(-1).float() + 1.0    # 1 .. 128, exact in bfloat16
+    v[:, :, 1] = score.view(-1, 1).to(torch.bfloat16)
+    v[:, :, 2] = torch.arange(Hk, device=dev) / 1024.0   # too small to change the order; tells the heads apart
+    table = torch.randperm(S, generator=g, device=dev).int().view(S, 1)
+    k_pool, v_pool = (torch.zeros((S, B, Hk, D), dtype=torch.bfloat16, device=dev) for _ in range(2))
+    lens, kept = torch.zeros(S, dtype=torch.int32, device=dev), torch.zeros((S, B), dtype=torch.int32, device=dev)
+    desc = pe.make_desc(torch.bfloat16, S, Hk, Hk, D, B, 1, S, pe.PE_LAYOUT_SHARED)
+    cu = torch.arange(S + 1, dtype=torch.int32, device=dev) * n
+    ws = pe.alloc_workspace(pe.PE_OP_PREFILL_PRUNE, desc, total, device=dev)
+    pe.pe_prefill_prune(desc, k, v, cu, total, total, B, k_pool, v_pool, table, lens, kept, ws)
+    stay = score.topk(B, -1).indices.sort(-1).values
+    assert bool((lens == B).all()) and torch.equal(kept.long(), stay)
+    src = (stay + torch.arange(S, device=dev)[:, None] * n).view(-1)
+    assert torch.equal(v_pool[table[:, 0].long()].view(S * B, Hk, D), v[src])
+    assert torch.equal(k_pool[table[:, 0].long()].view(S * B, Hk, D), k[src])
