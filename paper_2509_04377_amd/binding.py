@@ -4,10 +4,13 @@ Every function below has the name and argument order of the C-ABI entry point it
 (include/pe.h), takes torch tensors that already live on the GPU, and enqueues the library's HIP
 kernels on torch's current stream.  No step of the path is computed here or on the CPU and no
 control flow of the method lives here (the host-side sequencing of calls is engine.py); if libpe.so
-has not been built, the first call raises.
+has not been built, the first call raises.  Without _pe_host.so, the native form of the same
+marshalling, calls go through ctypes.
 """
 import ctypes
 import os
+import warnings
+
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -56,6 +59,29 @@ def _layout(structure):
     return (ctypes.sizeof(structure),) + tuple(fields)
 
 
+class _NoHost:
+    """In place of the native marshalling: takes no call, so that every call goes through ctypes."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _load_host():
+    """The native marshalling, or, where it is not built or does not load, the reason as a warning and the way through ctypes."""
+    why = "is not built"
+    if os.path.exists(HOST_PATH):
+        try:
+            from . import _pe_host
+            if _pe_host.bind_descriptor(pe_cache_desc) == _layout(pe_cache_desc):
+                return _pe_host
+            why = "has another pe_cache_desc"
+        except (ImportError, AttributeError) as e:
+            why = "does not load: %s" % e
+    warnings.warn("_pe_host.so %s (%s): arguments are checked in Python, some 3 us more a call; build as for libpe.so" % (why, HOST_PATH),
+                  RuntimeWarning, stacklevel=3)
+    return _NoHost()
+
+
 _lib = None
 _host = None   # the native marshalling of the calls that come once a layer (csrc/pe_host.cpp), loaded with the library
 
@@ -67,12 +93,8 @@ def lib():
         if not os.path.exists(LIB_PATH):
             raise RuntimeError("libpe.so is not built (%s): run `python -c 'import __graft_entry__ as g; g.build()'` "
                                "or `python paper_2509_04377_amd/build.py`" % LIB_PATH)
-        if not os.path.exists(HOST_PATH):
-            raise RuntimeError("_pe_host.so is not built (%s): build as for libpe.so" % HOST_PATH)
         global _host
-        from . import _pe_host as _host
-        if _host.bind_descriptor(pe_cache_desc) != _layout(pe_cache_desc):
-            raise RuntimeError("_pe_host.so has another pe_cache_desc: build again")
+        _host = _load_host()
         L = ctypes.CDLL(LIB_PATH)
         vp, i32, i64, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_size_t
         dp = ctypes.POINTER(pe_cache_desc)

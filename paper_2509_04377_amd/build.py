@@ -1,5 +1,5 @@
-"""Build libpe.so (the C-ABI library of HIP kernels) for gfx950 with hipcc, and _pe_host.so (argument marshalling of its Python
-front end) with g++, in-tree."""
+"""Build libpe.so (the C-ABI library of HIP kernels) for gfx950 with hipcc, and behind it _pe_host.so (native argument marshalling of
+its Python front end) with g++ where there is torch, in-tree."""
 import os
 import subprocess
 import sys
@@ -27,7 +27,6 @@ def build(verbose: bool = False, extra_flags=()) -> str:
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, obj, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
-    host_tmp, host = start_host_build(verbose)
     objs, failed = [], []
     for src, obj, p in procs:
         out, _ = p.communicate()
@@ -37,22 +36,23 @@ def build(verbose: bool = False, extra_flags=()) -> str:
         elif out and verbose:
             print(out)
         objs.append(obj)
-    out, _ = host.communicate()
-    if host.returncode != 0:
-        failed.append(("pe_host.cpp", out))
     if failed:
         raise RuntimeError("hipcc failed:\n" + "\n".join("%s:\n%s" % f for f in failed))
     tmp = LIB + ".tmp.%d" % os.getpid()
     subprocess.run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs, check=True)
     os.replace(tmp, LIB)
-    os.replace(host_tmp, HOST_LIB)
     build_c_smoke()
+    build_host(verbose)
     return LIB
 
 
-def start_host_build(verbose: bool = False):
-    """Start the compiler on the Python extension (host code only).  Returns where it writes to, and the process."""
+def build_host(verbose: bool = False):
+    """Compile the Python extension (host code only).  The C library is there without it, and needs neither Python nor torch: without
+    torch there is no Python front end to build it for."""
+    import importlib.util
     import sysconfig
+    if importlib.util.find_spec("torch") is None:
+        return None
     import torch
     from torch.utils import cpp_extension
     tmp = HOST_LIB + ".tmp.%d" % os.getpid()
@@ -64,7 +64,11 @@ def start_host_build(verbose: bool = False):
     cmd += ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
     if verbose:
         print(" ".join(cmd), flush=True)
-    return tmp, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    p = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if p.returncode != 0:
+        raise RuntimeError("g++ failed on pe_host.cpp (libpe.so is built):\n" + p.stdout)
+    os.replace(tmp, HOST_LIB)
+    return HOST_LIB
 
 
 C_SMOKE_SRC = os.path.join(os.path.dirname(HERE), "tests", "c_abi", "pe_c_smoke.c")
