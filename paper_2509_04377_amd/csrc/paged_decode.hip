@@ -460,9 +460,7 @@ hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
   const auto kernel = a.shared             ? paged_decode_kernel<T, D, G, false, true>
                       : a.new_k != nullptr ? paged_decode_kernel<T, D, G, true, false>
                                            : paged_decode_kernel<T, D, G, false, false>;
-  hipLaunchKernelGGL(kernel, blocks, threads, 0, stream, k.seq_lens, k.block_table, k.q, k.k_pool, k.v_pool, k.num_kv_heads,
-                     k.max_blocks, k.inv_heads, k.shape, k.p);
-  return hipGetLastError();
+  return launch_decode(kernel, blocks, threads, stream, k);
 }
 
 template <int D>

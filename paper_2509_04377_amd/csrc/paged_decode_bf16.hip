@@ -448,9 +448,7 @@ hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
                                         : paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, false, kShared>)
                                : (fused ? paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, true, false>
                                         : paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, false, false>);
-  hipLaunchKernelGGL(kernel, blocks, threads, 0, stream, k.seq_lens, k.block_table, k.q, k.k_pool, k.v_pool, k.num_kv_heads,
-                     k.max_blocks, k.inv_heads, k.shape, k.p);
-  return hipGetLastError();
+  return launch_decode(kernel, blocks, threads, stream, k);
 }
 
 // The workgroup forms that the rule in front of the launch chooses from, and one (4 x 3) for tuning.  Three and four tiles in flight were no faster than

@@ -44,6 +44,27 @@ struct DecodeKernelArgs {
   DecodeParams p;
 };
 
+// The kernels' parameters.  decode_params() below reads the last one out of the argument segment by itself, so a kernel must have
+// these and no others (launch_decode takes no other), and the struct must lie as the segment does.
+using DecodeKernel = void (*)(const int32_t* seq_lens, const int32_t* block_table, const void* q, const void* k_pool,
+                              const void* v_pool, int num_kv_heads, int max_blocks, uint32_t inv_heads, uint32_t shape,
+                              DecodeParams p);
+
+// Where a kernel's last argument lies in the segment: each one at the next multiple of its own alignment.
+template <typename... A>
+constexpr size_t last_argument_offset(void (*)(A...)) {
+  size_t at = 0, end = 0;
+  ((at = (end + alignof(A) - 1) / alignof(A) * alignof(A), end = at + sizeof(A)), ...);
+  return at;
+}
+static_assert(last_argument_offset(DecodeKernel(nullptr)) == offsetof(DecodeKernelArgs, p), "decode_params() reads elsewhere");
+
+inline hipError_t launch_decode(DecodeKernel kernel, dim3 blocks, dim3 threads, hipStream_t stream, const DecodeKernelArgs& k) {
+  hipLaunchKernelGGL(kernel, blocks, threads, 0, stream, k.seq_lens, k.block_table, k.q, k.k_pool, k.v_pool, k.num_kv_heads,
+                     k.max_blocks, k.inv_heads, k.shape, k.p);
+  return hipGetLastError();
+}
+
 // `shape`: log2 of the page size, query heads per KV head, order of the workgroups, splits
 constexpr uint32_t kShapeXcd = 128u, kShapeLinear = 256u;
 __host__ __device__ inline int shape_log2_block(uint32_t shape) { return (int)(shape & 7u); }

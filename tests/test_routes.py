@@ -90,3 +90,24 @@ def test_bf16_form(host_layer, kw, want):
     (dict(num_q_heads=16, max_blocks=4), False), (dict(layout=pe.PE_LAYOUT_SHARED, max_blocks=4), False)])
 def test_bf16_vector_units(host_layer, kw, want):
     assert _vector(host_layer, **dict(dict(num_q_heads=8), **kw)) is want
+
+
+KERNEL = r"""
+#include "%s/pe_decode_common.h"
+__global__ void kernel(const int32_t* seq_lens, const int32_t* block_table, const void* q, const void* k_pool, const void* v_pool,
+                       const int num_kv_heads, const int max_blocks, %s const uint32_t inv_heads, %s shape, const pe::DecodeParams) {}
+hipError_t launch(const pe::DecodeKernelArgs& k) { return pe::launch_decode(kernel, dim3(1), dim3(64), nullptr, k); }
+"""
+
+
+@pytest.mark.parametrize("more,last,compiles", [("", "const uint32_t", True), ("const int more,", "const uint32_t", False),
+                                                ("", "const uint64_t", False)])
+def test_attention_kernels_have_the_parameters_that_are_read_by_offset(tmp_path, more, last, compiles):
+    """The kernels read their later arguments out of the argument segment; one with other parameters must not build."""
+    src = tmp_path / "kernel.hip"
+    src.write_text(KERNEL % (build.CSRC, more, last))
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    r = subprocess.run([hipcc] + build.FLAGS + ["--cuda-host-only", "-fsyntax-only", str(src)], stdout=subprocess.PIPE,
+                       stderr=subprocess.STDOUT, text=True)
+    assert (r.returncode == 0) == compiles, r.stdout
+    assert compiles or "parameter of type 'DecodeKernel'" in r.stdout, r.stdout
