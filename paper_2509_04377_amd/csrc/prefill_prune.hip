@@ -196,9 +196,11 @@ struct __attribute__((packed, aligned(4))) Unaligned4 {  // 16 bytes at any 4-by
   uint32_t v[4];
 };
 
-// The scores of a row as its workgroup holds them, (NV + LV) * 256 consecutive ones a wave (so that a chunk of 1024 is counted
-// by as few waves as possible): score 256*j + 4*lane + e of a wave is element e of vector j of a lane, the first NV vectors in
-// registers, the next LV in LDS (a thread reads back only what it has written).
+// The scores of a row as its workgroup holds them, n * 256 consecutive ones a wave (so that a chunk of 1024 is counted by as few
+// waves as possible): score 256*j + 4*lane + e of a wave is element e of vector j of a lane, the first NV vectors in registers, the
+// next LV in LDS (a thread reads back only what it has written).  n, at most NV + LV, follows from the row itself, so that all waves
+// share a row that is much shorter than the longest of its call (prunes of 127 prompts of 4096 tokens beside one of 40000, 8 heads
+// of D = 64: 383 us with NV + LV for every row, now 353; of 63 of 1500 beside it 146 and 136).
 template <int NV, int LV>
 struct RowScores {
   static constexpr int kHeld = 4 * (NV + LV) * kSelThreads;
@@ -206,19 +208,26 @@ struct RowScores {
   const uint32_t* bits;
   uint4* lds;
   int L, tid;
-  int wave0;  // first score of the wave
+  int n, wave0, end;  // vectors of a wave; first score of this wave, and where its scores end
   Unaligned4 reg[NV];
 
+  __device__ __forceinline__ void deal(int wave) {
+    constexpr int kRound = kSelWaves * kVector;
+    n = 1;
+    if constexpr (NV + LV > 1) n = L >= kHeld ? NV + LV : (L + kRound - 1) / kRound;
+    wave0 = wave * n * kVector;
+    end = wave0 + n * kVector < L ? wave0 + n * kVector : L;
+  }
   __device__ __forceinline__ int index(int j) const { return wave0 + j * kVector + 4 * (tid & (kWave - 1)); }
 
   __device__ __forceinline__ Unaligned4 request(int j) const {  // past the end the row's last four again
-    const int i = index(j);
+    const int i = j < n ? index(j) : L;
     const int last = L >= 4 ? L - 4 : 0;
     return L >= 4 ? *reinterpret_cast<const Unaligned4*>(bits + (i < last ? i : last)) : Unaligned4{{0u, 0u, 0u, 0u}};
   }
   __device__ __forceinline__ void mend(int j, Unaligned4& r) const {  // the one vector that the row's end cuts
     const int i = index(j);
-    if (i < L && i + 4 > L) {
+    if (i < end && i + 4 > L) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) r.v[e] = i + e < L ? bits[i + e] : 0u;
     }
@@ -229,6 +238,7 @@ struct RowScores {
     constexpr int kStep = 4;
 #pragma unroll
     for (int j0 = 0; j0 < LV; j0 += kStep) {
+      if (NV + j0 >= n) break;
       Unaligned4 r[kStep];
 #pragma unroll
       for (int j = 0; j < kStep; ++j) r[j] = request(NV + j0 + j);
@@ -250,9 +260,9 @@ struct RowScores {
   // held ones ...
   template <typename F4, typename F1>
   __device__ __forceinline__ void visit_vector(int j, const Unaligned4& r, F4 four, F1 one) const {
-    if (wave0 + (j + 1) * kVector <= L) {  // the same for all lanes
+    if (wave0 + (j + 1) * kVector <= end) {  // the same for all lanes
       four(r);
-    } else if (wave0 + j * kVector < L) {
+    } else if (wave0 + j * kVector < end) {
       const int left = L - index(j);
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -264,7 +274,7 @@ struct RowScores {
 #pragma unroll
     for (int j = 0; j < NV; ++j) visit_vector(j, reg[j], four, one);
 #pragma unroll 1
-    for (int j = NV; j < NV + LV; ++j) visit_vector(j, in_lds(j), four, one);
+    for (int j = NV; j < n; ++j) visit_vector(j, in_lds(j), four, one);
     // ... and the rest, from memory: 16 bytes a load, past the end the row's last four again
     constexpr int kUnroll = LV > 0 ? kSelUnroll : 1;  // a smaller holding covers every row of its call
     for (int i0 = kHeld + 4 * tid; i0 < L; i0 += kUnroll * 4 * kSelThreads) {
@@ -374,7 +384,7 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
   rs.lds = held_lds;
   rs.L = L;
   rs.tid = tid;
-  rs.wave0 = wave * (NV + LV) * Row::kVector;
+  rs.deal(wave);
   rs.load();
 
   if (h == 0 && tid == 0) seq_lens_out[s] = keep;
@@ -543,7 +553,7 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
   constexpr int kVectorsPerChunk = kChunk / Row::kVector;
   uint32_t n = 0u;  // of this lane, of the chunk at hand
   const auto count_vector = [&](int j, const Unaligned4& r) {
-    const int left = rs.wave0 + (j + 1) * Row::kVector <= L ? 4 : L - rs.index(j);
+    const int left = rs.wave0 + (j + 1) * Row::kVector <= rs.end ? 4 : rs.end - rs.index(j);
 #pragma unroll
     for (int e = 0; e < 4; ++e) n += e < left && r.v[e] > T ? 1u : 0u;
     if (!all_go) {
@@ -551,16 +561,17 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
       for (int e = 0; e < 4; ++e) n += e < left && r.v[e] == T ? 0x10000u : 0u;
     }
     const int v = rs.wave0 / Row::kVector + j;  // number of the vector in the row
-    if (v % kVectorsPerChunk == kVectorsPerChunk - 1 || j == NV + LV - 1) {
+    if (v % kVectorsPerChunk == kVectorsPerChunk - 1 || j == rs.n - 1) {
       n = wave_prefix_sum_u32(n);
       if (lane == kWave - 1) atomicAdd(&held_count[v / kVectorsPerChunk], n);
       n = 0u;
     }
   };
 #pragma unroll
-  for (int j = 0; j < NV; ++j) count_vector(j, rs.reg[j]);
+  for (int j = 0; j < NV; ++j)
+    if (j < rs.n) count_vector(j, rs.reg[j]);
 #pragma unroll 1
-  for (int j = NV; j < NV + LV; ++j) count_vector(j, rs.in_lds(j));
+  for (int j = NV; j < rs.n; ++j) count_vector(j, rs.in_lds(j));
   int gt_total = 0, eq_total = 0;  // of the pieces done
   for (int c0 = 0; c0 < nchunks; c0 += kSelBins) {
     const int nc = nchunks - c0 < kSelBins ? nchunks - c0 : kSelBins;
