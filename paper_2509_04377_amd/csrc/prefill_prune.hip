@@ -164,8 +164,9 @@ __global__ __launch_bounds__(kThreads) void head_mean_kernel(const float* __rest
 
 // ---- 2. per-row select + per-chunk counts ------------------------------------------------------------
 // One workgroup of 1024 threads per row finds the threshold on the row's fp32 bit patterns, which order like unsigned integers.
-// A histogram of 4096 equal bins is laid over the range of a sample (one score a thread; what lies outside falls into the
-// first or the last bin), so that few scores share a bin whatever their magnitude and spread.
+// A histogram of 4096 equal bins is laid over the range of a sample (one score a thread, without zeros and infinities where the
+// threshold is likely none; what lies outside falls into the first or the last bin), so that few scores share a bin whatever their
+// magnitude and spread.
 // The bin that holds rank k is found with a workgroup-wide scan; a row of some ten thousand scores leaves some ten candidates
 // in it.  They are collected in LDS, and one wave settles the remaining bits of the threshold, bit by bit, with ballots over
 // the candidates in its registers: no barriers in between.  More than 256 candidates go through further digits of up to 12
@@ -179,7 +180,9 @@ __global__ __launch_bounds__(kThreads) void head_mean_kernel(const float* __rest
 // there; only what a row has beyond is read from memory in each pass.
 // Measured on an MI355X (kernel trace), digits of 12, 10 and 10 plain bits with a histogram each and 32768 scores held / this: 64
 // rows x 4096 scores 7.3 / 6.6 us, 128 ragged rows of up to 16384 10.4 / 9.0, 256 x 16384 13.4 / 11.1, 32 x 65536 25.9 / 20.5; whole
-// prunes of 4 x 131072 tokens 444 / 430, with all scores equal 686 / 527, with zeros and infinities among them 422 / 429.  (What
+// prunes of 4 x 131072 tokens 451 / 441, with all scores equal 704 / 543, with zeros or infinities among them 451 / 444 (as part of the
+// range they spread the bins: 458; equal scores, where they were collected like others, took 105 ragged prompts of up to 1659 tokens
+// 115 us a prune, 108 before and now 97).  (What
 // bounds a long row is the vector issue of its one compute unit, 0.43 us per operation on each of 65536 scores: so equal scores
 // are counted only where some of them stay, a wave's scores are consecutive, and candidates are looked for four at a time.)
 constexpr int kSelThreads = 1024;
@@ -190,6 +193,7 @@ constexpr int kSelUnroll = 4;   // 16-byte loads in flight per thread beyond the
 constexpr int kSelCand = 2048;  // candidates kept in LDS after the first digit
 constexpr int kSelFew = 256;    // candidates that a wave settles in its registers
 constexpr int kSelMaxVecs = 8;
+constexpr uint32_t kInfBits = 0x7f800000u;
 constexpr int kSelMaxHeldChunks = 2 * kSelMaxVecs * 4;
 
 struct __attribute__((packed, aligned(4))) Unaligned4 {  // 16 bytes at any 4-byte boundary, in one load
@@ -432,8 +436,16 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
   if (tid < kSelMaxHeldChunks) held_count[tid] = 0u;
   if (tid == 0) sh_ncand = 0u;
   {
-    const bool in = rs.index(0) < L;
-    publish_range(in ? rs.reg[0].v[0] : 0xffffffffu, in ? rs.reg[0].v[0] : 0u);
+    const uint32_t b = rs.reg[0].v[0];
+    bool in = rs.index(0) < L;
+    const bool extreme = in && b - 1u >= kInfBits - 1u;  // zero, or infinity
+    if (__builtin_amdgcn_ballot_w64(extreme) != 0ull) {   // they count where more of them were sampled than are to go, or to stay
+      const uint32_t zeros = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(extreme && b == 0u));
+      const uint32_t infs = (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(extreme && b != 0u));
+      const uint32_t share = (uint32_t)L / kWave;  // scores that one of a wave's sample stands for
+      in = in && (!extreme || (b == 0u ? zeros * share > (uint32_t)E : infs * share > (uint32_t)keep));
+    }
+    publish_range(in ? b : 0xffffffffu, in ? b : 0u);
   }
   __syncthreads();
   // E == 0, nothing to evict: T = +0.0, q = 0 keeps every token (scores are >= +0)
@@ -442,6 +454,7 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
     uint32_t low, top;
     read_range(low, top);
     const int shift0 = top_bit(top - low, 0u) < kSelDigit ? 0 : top_bit(top - low, 0u) + 1 - kSelDigit;
+    low -= low < 1u << shift0 ? low : 1u << shift0;  // the first bin: all below the sample, and its least begins the second
     const auto count_one = [&](uint32_t b) {
       const uint32_t up = __builtin_elementwise_sub_sat(b, low) >> shift0;
       atomicAdd(&hist[up < (uint32_t)kSelBins - 1u ? up : (uint32_t)kSelBins - 1u], 1u);
@@ -452,11 +465,13 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
     }, count_one);
     __syncthreads();
     find_bin(k);
-    const uint32_t bin = sh_bin, n = sh_in_bin;
+    const uint32_t bin = sh_bin;
+    uint32_t n = sh_in_bin;
     k = sh_k;
     uint32_t lo = bin == 0u ? 0u : low + (bin << shift0);
     uint32_t hi = bin == (uint32_t)kSelBins - 1u ? 0xffffffffu : low + ((bin + 1u) << shift0) - 1u;
     const uint32_t span = hi - lo;
+    if (span == 0u) n = (uint32_t)kSelCand + 1u;  // one number, as with equal scores: it is the threshold, nothing to collect
     if (n <= (uint32_t)kSelCand) {  // collect the bin's scores (their order does not matter: only values are counted)
       const auto keep_one = [&](uint32_t b) {
         if (b - lo <= span) cand[atomicAdd(&sh_ncand, 1u)] = b;
@@ -497,17 +512,21 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
       T = sh_bin;
       k = sh_k;
     } else {
-      if (n > (uint32_t)kSelCand) {
+      if (span != 0u) {
         uint32_t mn = 0xffffffffu, mx = 0u;
         const auto widen = [&](uint32_t b) {
           const bool in = b - lo <= span;
           mn = in && b < mn ? b : mn;
           mx = in && b > mx ? b : mx;
         };
-        rs.visit([&](const Unaligned4& r) {
+        if (n <= (uint32_t)kSelCand) {
+          for (uint32_t i = (uint32_t)tid; i < n; i += kSelThreads) widen(cand[i]);
+        } else {
+          rs.visit([&](const Unaligned4& r) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) widen(r.v[e]);
-        }, widen);
+            for (int e = 0; e < 4; ++e) widen(r.v[e]);
+          }, widen);
+        }
         publish_range(mn, mx);
         __syncthreads();
         read_range(lo, hi);

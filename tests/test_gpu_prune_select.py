@@ -8,7 +8,8 @@ from paper_2509_04377_amd import binding as pe
 pytestmark = pytest.mark.gpu
 
 HOLDINGS = [[1, 3, 255, 257, 1023, 4095, 4096], [4097, 2, 8191, 8192], [16383, 16384, 1025, 8193], [16385, 6, 32767, 32768, 1024],
-            [32769, 40001, 65535, 65536, 100], [65537, 70001, 5, 131075]]
+            [32769, 40001, 65535, 65536, 100], [65537, 70001, 5, 131075],
+            [40000, 1, 4095, 4097, 8192, 12289, 61440, 61441, 300]]
 
 
 def _scores(kind, n, g):
@@ -28,6 +29,12 @@ def _scores(kind, n, g):
         s = bits.view(torch.float32).clone()
         s[n // 2] = 1e30
         return s
+    if kind in ("zeros", "infinities"):   # so many that the threshold is one of them for some of the budgets
+        s = torch.exp(0.7 * z)
+        s[torch.rand(n, generator=g, device=dev) < 0.6] = 0.0 if kind == "zeros" else float("inf")
+        return s
+    if kind == "neither":     # nothing else: no sample to lay a histogram over
+        return torch.where(torch.rand(n, generator=g, device=dev) < 0.5, 0.0, float("inf"))
     s = torch.exp(0.7 * z)    # "edges": zeros and infinities among them
     s[::37] = 0.0
     s[5::41] = float("inf")
@@ -35,7 +42,8 @@ def _scores(kind, n, g):
 
 
 @pytest.mark.parametrize("lens", HOLDINGS, ids=lambda v: str(max(v)))
-@pytest.mark.parametrize("kind", ["lognormal", "wide", "equal", "few", "neighbours", "edges"])
+@pytest.mark.parametrize("kind", ["lognormal", "wide", "equal", "few", "neighbours", "edges", "zeros", "infinities",
+                                  "neither"])
 def test_selection_is_a_stable_sort(lens, kind):
     dev, D, B, Hk = "cuda", 64, 16, 2
     g = torch.Generator(device=dev)
