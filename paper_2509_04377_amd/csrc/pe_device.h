@@ -95,28 +95,37 @@ __device__ __forceinline__ double lane_xor_f64(double v) {
 struct Swapped {
   float a, b;
 };
-__device__ __forceinline__ Swapped swap_halves(float v) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+__device__ __forceinline__ Swapped swap_halves(float v, float w) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(w), false, false);
   return {__uint_as_float(r[0]), __uint_as_float(r[1])};
 }
-__device__ __forceinline__ Swapped swap_rows(float v) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+__device__ __forceinline__ Swapped swap_rows(float v, float w) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(w), false, false);
   return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+// Of two values, the first in the lower half (in even rows) and the second in the upper half (in odd rows).
+__device__ __forceinline__ float halves_sum(float v, float w) {
+  const Swapped r = swap_halves(v, w);
+  return r.a + r.b;
+}
+__device__ __forceinline__ float pairs_sum(float v, float w) {
+  const Swapped r = swap_rows(v, w);
+  return r.a + r.b;
 }
 __device__ __forceinline__ float halves_sum(float v) {
-  const Swapped r = swap_halves(v);
+  const Swapped r = swap_halves(v, v);
   return r.a + r.b;
 }
 __device__ __forceinline__ float halves_max(float v) {
-  const Swapped r = swap_halves(v);
+  const Swapped r = swap_halves(v, v);
   return fmaxf(r.a, r.b);
 }
 __device__ __forceinline__ float rows_sum(float v) {
-  const Swapped r = swap_rows(v);
+  const Swapped r = swap_rows(v, v);
   return halves_sum(r.a + r.b);
 }
 __device__ __forceinline__ float rows_max(float v) {
-  const Swapped r = swap_rows(v);
+  const Swapped r = swap_rows(v, v);
   return halves_max(fmaxf(r.a, r.b));
 }
 
