@@ -429,9 +429,11 @@ __global__ __launch_bounds__(kWaves * kWave) void paged_decode_kernel(
 // Merge the split partials of one (sequence, query head): one wave, D / 64 elements a lane.  What a launch of it costs is the
 // launch and one round trip to the records, which lie together for a row ([row][split][head]: with the heads of all rows under
 // each split 0.4 us more for 32 rows of D = 128 in eight splits, 1.1 us for 16 rows in 16).  The grid: the query heads of a row
-// side by side, one row a grid row; with kMergeXcd eight rows a grid row, so that a row's records are read on the XCD that wrote
-// them (D = 128, 32 rows x 4096 in eight splits 16.4 us a layer, with this and 8-byte loads 16.2; 192 ragged rows with eight
-// query heads 78.4 and 77.6; D = 64 40.8 and 41.0: there without); kMergeLinear: more rows than a grid has, divided.
+// side by side, one row a grid row; with kMergeXcd, wherever the attention kernel keeps a row on one XCD, eight rows a grid row, so
+// that a row's records are read on the XCD that wrote them (append, attention and merge out of a HIP graph, side by side / so: D =
+// 128, four query heads a KV head, 8 rows x 4096 8.8 / 8.0 us, 16 x 5280 12.4 / 11.4, 32 x 4096 14.6 / 13.95, 32 x 8192 24.3 / 23.9,
+// 264 x 4096 94.2 / 93.8; D = 64 7.7 / 6.9, 9.3 / 8.4, 9.5 / 9.0, 13.9 / 13.6, 51.5 / 51.2; one query head: the same order);
+// kMergeLinear: more rows than a grid has, divided.
 enum { kMergeLinear, kMergeRows, kMergeXcd };
 template <typename T, int D>
 __global__ __launch_bounds__(kWave) void paged_decode_reduce_kernel(const float* __restrict__ partials, void* __restrict__ out,
@@ -508,7 +510,7 @@ template <typename T, int D>
 void launch_reduce(const DecodeArgs& a, hipStream_t stream) {
   const int64_t rows = (int64_t)a.num_seqs * a.num_kv_heads;
   const int g = a.num_q_heads / a.num_kv_heads;
-  const bool xcd = D == 128 && a.xcd_map && rows % 8 == 0;
+  const bool xcd = a.xcd_map && rows % 8 == 0;
   const int64_t grid_rows = xcd ? rows / 8 : rows;
   const int order = grid_rows > 65535 ? kMergeLinear : xcd ? kMergeXcd : kMergeRows;
   const dim3 blocks = order == kMergeLinear ? dim3((unsigned)(rows * g)) : dim3((unsigned)(xcd ? 8 * g : g), (unsigned)grid_rows);
