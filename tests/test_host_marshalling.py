@@ -6,6 +6,8 @@ import pytest
 import torch
 
 from paper_2509_04377_amd import binding as pe
+from paper_2509_04377_amd import synth
+from paper_2509_04377_amd.engine import LayeredCache, PagedCache
 
 S, Hk, Hq, D, B, PAGES = 3, 2, 4, 64, 16, 4
 
@@ -177,3 +179,108 @@ def test_score_and_evict_marshalling():
         pe.pe_evict_blocks(desc, outs[0][2].double(), *outs[0][:2], 48, *outs[0][3:])
     with pytest.raises(pe.PeError):   # no multiple of the page
         pe.pe_evict_blocks(desc, outs[0][2], *outs[0][:2], 40, *outs[0][3:])
+
+
+CALLS = {"paged_decode", "append_paged_decode", "append_paged_decode_layers", "prefill_prune", "score_triggered_blocks",
+         "score_recent_blocks", "evict_blocks", "evict_blocks_cached"}
+
+
+class _Recorder:
+    """The native marshalling, with a record of what each call returned."""
+
+    def __init__(self, host):
+        self.host, self.seen = host, []
+
+    def __getattr__(self, name):
+        def call(*args):
+            status = getattr(self.host, name)(*args)
+            self.seen.append((name, status))
+            return status
+        return call
+
+
+def _engine_run(shared):
+    """Prompts pruned and decode steps over two page boundaries, as engine.py makes the calls; every tensor that a call writes."""
+    wl = synth.LLAMA32_1B.with_(dtype="f32", layers=2, num_kv_heads=Hk, num_q_heads=Hq, num_seqs=S, budget=64, steps=40)
+    lens, written = [90, 64, 41], []
+
+    def inputs(layers, step):
+        per = [synth.decode_inputs(wl, l, step, 5, device="cuda") for l in range(layers)]
+        return [torch.stack(t) for t in zip(*per)]
+
+    for cached in (False, True):
+        cache = PagedCache.create(torch.float32, S, Hk, Hq, D, B, synth.page_layout(wl, lens, 5, shared=shared), 64,
+                                  shared=shared, decode_opts={"decode_splits": 2})
+        cache.cached_scores = cached
+        kept = torch.full((S, 64) if shared else (S, Hk, 64), -7, dtype=torch.int32, device="cuda")
+        k, v, cu = synth.prompt_kv(wl, 0, lens, 5, device="cuda")
+        cache.prefill_prune(k, v, cu, max(lens), kept)
+        cache.set_host_lens(lens)
+        cache.scores.fill_(float("inf"))
+        for step in range(36):
+            nk, nv, q = (t[0] for t in inputs(1, step))
+            out = torch.empty_like(q)
+            cache.decode_step(nk, nv, q, out, fused=step % 3 != 2)
+            written.append(out)
+        written += [kept, cache.block_table, cache.seq_lens, cache.k_pool, cache.v_pool, cache.scores, cache.freed_phys,
+                    cache.evicted_logical, cache.spare_used]
+    model = LayeredCache(torch.float32, 2, S, Hk, Hq, D, B, synth.page_layout(wl, lens * 2, 5, shared=shared), 64, shared=shared)
+    for l in range(2):
+        k, v, cu = synth.prompt_kv(wl, l, lens, 5, device="cuda")
+        model.prefill_prune_layer(l, k, v, cu, max(lens))
+    model.set_host_lens(lens)
+    for step in range(36):
+        nk, nv, q = inputs(2, step)
+        out = torch.empty_like(q)
+        model.decode_step(nk, nv, q, out)
+        written.append(out)
+    f = model.folded
+    return written + [f.block_table, f.seq_lens, f.k_pool, f.v_pool, f.freed_phys, f.spare_used]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shared", [False, True], ids=["per_head", "shared"])
+def test_every_call_of_the_engine_goes_the_native_way_and_as_through_ctypes(monkeypatch, shared):
+    pe.lib()
+    recorder = _Recorder(pe._host)
+    monkeypatch.setattr(pe, "_host", recorder)
+    native = _engine_run(shared)
+    assert {name for name, _ in recorder.seen} == CALLS and all(status == pe.PE_OK for _, status in recorder.seen)
+    monkeypatch.setattr(pe, "_host", pe._NoHost())
+    through_ctypes = _engine_run(shared)
+    assert len(native) == len(through_ctypes) and all(torch.equal(a, b) for a, b in zip(native, through_ctypes))
+
+
+@pytest.mark.gpu
+def test_numbers_that_only_int_understands_go_through_ctypes(monkeypatch):
+    """Budgets, lengths and counts as tensors of one element: taken before the native marshalling, and by the way through ctypes."""
+    pe.lib()
+    desc, q, k, v, table, lens = _args("cuda")
+    lens = torch.tensor([16, 64, 48], dtype=torch.int32, device="cuda")
+    i32 = dict(dtype=torch.int32, device="cuda")
+    n = lambda x: torch.tensor(x)   # noqa: E731
+    outs = []
+    for wrap in (int, n):
+        recorder = _Recorder(pe._host)
+        with monkeypatch.context() as m:
+            m.setattr(pe, "_host", recorder)
+            t, sl, sl2, kp, vp = table.clone(), lens.clone(), torch.zeros(S, **i32), k.clone(), v.clone()
+            scores = torch.zeros((S, Hk, PAGES), device="cuda")
+            gone, freed, used = torch.full((S, Hk), -7, **i32), torch.full((S, Hk), -1, **i32), torch.zeros((S, Hk), **i32)
+            pe.pe_score_recent_blocks(desc, kp, vp, t, sl, wrap(4), scores)
+            pe.pe_evict_blocks_cached(desc, scores, t, sl, wrap(48), gone, freed)
+            spare = torch.zeros((S, Hk, 1), **i32)
+            new, out = torch.randn((S, Hk, D), generator=torch.Generator().manual_seed(1)).cuda(), torch.zeros_like(q)
+            scale = 0.125 if wrap is int else n(0.125)
+            one = sl.clone() - 1   # the tail pages have room
+            pe.pe_append_paged_decode(desc, new, new, q, kp, vp, t, one, sl2, freed, spare, used, scale, out)
+            out2 = torch.zeros_like(q)
+            pe.pe_append_paged_decode_layers(desc, wrap(1), new, new, q, kp, vp, t, one, sl2, freed, spare, used, scale, out2)
+            kp2, vp2, kept = torch.zeros_like(kp), torch.zeros_like(vp), torch.zeros((S, Hk, 32), **i32)
+            tok = torch.randn((100, Hk, D), generator=torch.Generator().manual_seed(2)).cuda()
+            cu = torch.tensor([0, 40, 80, 100], **i32)
+            ws = pe.alloc_workspace(pe.PE_OP_PREFILL_PRUNE, desc, 100)
+            pe.pe_prefill_prune(desc, tok, tok.flip(0), cu, wrap(100), wrap(40), wrap(32), kp2, vp2, table, sl2, kept, ws)
+        assert [status for _, status in recorder.seen] == [pe.PE_OK if wrap is int else None] * 5
+        outs.append([t, sl, sl2, kp, vp, scores, gone, freed, used, out, out2, kp2, vp2, kept])
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
