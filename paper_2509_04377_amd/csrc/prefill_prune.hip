@@ -13,9 +13,9 @@
 //                     of every kept token; token rows are then copied with 16-byte lane accesses.
 // A token is kept iff score > T, or score == T and at least q equal-score tokens precede it.
 //
-// Head-shared mode (one decision per sequence, pages [B][Hk][D]): after kernel 1 the per-head scores are
-// averaged over the heads (head order, fp64, one rounding) into one more score row, and kernels 2-3 run on
-// that row with the whole (token, all heads) record as the unit that is copied.
+// Head-shared mode (one decision per sequence, pages [B][Hk][D]): a token's score is the mean of its heads' scores (head
+// order, fp64, one rounding), taken by the sweep itself where none of its workgroups ends inside a token, else by a
+// kernel behind it.  Kernel 2 runs on that one score row; kernel 3 copies head by head with its result.
 #include "pe_device.h"
 #include "pe_launch.h"
 #include "pe_norms.h"
@@ -167,11 +167,11 @@ __global__ __launch_bounds__(kThreads) void head_mean_kernel(const float* __rest
 // A histogram of 4096 equal bins is laid over the range of a sample (one score a thread, without zeros and infinities where the
 // threshold is likely none; what lies outside falls into the first or the last bin), so that few scores share a bin whatever their
 // magnitude and spread.
-// The bin that holds rank k is found with a workgroup-wide scan; a row of some ten thousand scores leaves some ten candidates
-// in it.  They are collected in LDS, and one wave settles the remaining bits of the threshold, bit by bit, with ballots over
+// The bin that holds rank k is found with a workgroup-wide scan; a row of some ten thousand ordinary scores leaves some ten
+// candidates in it.  They are collected in LDS, and one wave settles the remaining bits of the threshold, bit by bit, with ballots over
 // the candidates in its registers: no barriers in between.  More than 256 candidates go through further digits of up to 12
-// bits, with a histogram each; more than LDS holds (e.g. many equal scores) go over all scores of the row again for each, and
-// once before for their range.
+// bits, with a histogram each, between the least and the largest of them; more than LDS holds (e.g. scores of few distinct values)
+// are looked for in the whole row again, for their range and for each digit.  A bin of one number, as with equal scores, is done.
 // With the threshold known the same workgroup counts, per chunk of 1024 tokens, how many scores are > T and how many == T: the
 // gather turns these into destinations.
 // A row is worked on by one compute unit, and one compute unit pulls about 45 GB/s from L2 however many loads it keeps
@@ -184,7 +184,8 @@ __global__ __launch_bounds__(kThreads) void head_mean_kernel(const float* __rest
 // range they spread the bins: 458; equal scores, where they were collected like others, took 105 ragged prompts of up to 1659 tokens
 // 115 us a prune, 108 before and now 97).  (What
 // bounds a long row is the vector issue of its one compute unit, 0.43 us per operation on each of 65536 scores: so equal scores
-// are counted only where some of them stay, a wave's scores are consecutive, and candidates are looked for four at a time.)
+// are counted only where some of them stay, a wave's scores are consecutive, and candidates are looked for four at a time.  Part
+// of that issue are 46 to 212 scalar registers, by the size of the holding, that the compiler keeps in lanes of vector registers.)
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / kWave;
 constexpr int kSelBins = 4096;
@@ -479,7 +480,7 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
       rs.visit([&](const Unaligned4& r) {
         const uint32_t d0 = r.v[0] - lo, d1 = r.v[1] - lo, d2 = r.v[2] - lo, d3 = r.v[3] - lo;
         const uint32_t d01 = d0 < d1 ? d0 : d1, d23 = d2 < d3 ? d2 : d3;
-        if (__builtin_amdgcn_ballot_w64((d01 < d23 ? d01 : d23) <= span) != 0ull) {  // one vector of a wave in some ten
+        if (__builtin_amdgcn_ballot_w64((d01 < d23 ? d01 : d23) <= span) != 0ull) {  // false for most vectors
           const uint32_t d[4] = {d0, d1, d2, d3};
           uint64_t who[4];
           uint32_t all = 0u, at = 0u;
@@ -743,6 +744,7 @@ hipError_t launch(const PruneArgs& a, hipStream_t stream) {
   // Head-shared: where no sweep workgroup ends inside a token it averages the heads itself; their scores are then not written (16
   // prompts of 2048 to 8192 tokens, 8 heads 99 us a prune, now 94, 32 x 16384 465 and 434).
   constexpr int rows_per_group = kWaves * kSweepIters * kSweepLoads * G::kTokensPerLoad;
+  static_assert(rows_per_group <= kThreads, "one thread a token averages its heads");
   const bool mean_in_sweep = a.shared && rows_per_group % a.num_kv_heads == 0;
   float* mean = w.scores + (size_t)a.num_kv_heads * (size_t)a.total_tokens;
   hipError_t e;
@@ -750,18 +752,23 @@ hipError_t launch(const PruneArgs& a, hipStream_t stream) {
   if (total_rows > 0) {
     const int64_t grid = (total_rows + rows_per_group - 1) / rows_per_group;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-    // Prompts of 96 MiB are swept without the hint: they then lie in the Infinity Cache (256 MB) when the gather comes, and what
-    // the model has just written is found there (whole prunes of D = 64, 1024 of 4096 kept, with / without the hint, K and V
-    // written right before: 17 MB 27.3 / 25.2 us, 34 MB 30.2 / 27.8, 67 MB 33.8 / 29.5, 134 MB 50.6 / 45.7, 268 MB 83.8 / 83.8, 537 MB
-    // 133 / 165; out of memory: 67 MB 31.5 / 31.7, 134 MB 49.6 / 51.3, 268 MB 85.4 / 94.8)
+    // Prompts of up to 96 MiB are swept without the hint: they then lie in the Infinity Cache (256 MB) when the gather comes, and
+    // what the model has just written, as in a prefill, is found there.  The line is where that costs nothing out of memory either
+    // as long as a quarter of the prompt or more is kept.  Whole prunes of some 4500 tokens a prompt, 8 heads, with / without the hint
+    // (256, 1024 or 2048 tokens kept; D = 64, fp32 and the head-shared layout cross at the same sizes), us:
+    //   bf16, D = 128    K and V written right before                   out of memory
+    //    34 MB           23.8 / 22.2   32.8 / 27.9   42.8 / 34.1        21.4 / 21.8   30.5 / 28.1   41.8 / 34.7
+    //    84 MB           32.3 / 29.1   41.8 / 35.0   54.7 / 42.5        29.5 / 31.4   41.6 / 39.6   55.9 / 47.9
+    //   100 MB           34.7 / 31.5   42.4 / 36.2   53.0 / 42.7        31.5 / 34.0   41.4 / 40.9   53.9 / 48.4
+    //   134 MB           39.4 / 37.5   50.4 / 43.7   63.4 / 52.6        37.3 / 40.3   48.8 / 51.1   64.3 / 64.3
+    //   200 MB           53.1 / 48.4   65.8 / 57.7   82.7 / 80.2        49.3 / 54.9   64.0 / 71.9   85.1 / 97.4
     const bool streamed = a.total_tokens * row_bytes > (int64_t)96 << 20;
     const auto sweep = streamed ? token_scores_kernel<T, D, true> : token_scores_kernel<T, D, false>;
     hipLaunchKernelGGL(sweep, dim3((unsigned)grid), dim3(kThreads), 0, stream, (const T*)a.k_in, (const T*)a.v_in,
                        mean_in_sweep ? mean : w.scores, total_rows, a.total_tokens, a.num_kv_heads, mean_in_sweep ? 1 : 0);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  // what kernels 2-3 see: per-head rows, or (shared) one row per sequence whose score is the head mean and
-  // whose record is the token's K (or V) of all heads
+  // what kernel 2 sees: per-head rows, or (shared) one row per sequence whose scores are the head means
   const int heads = a.shared ? 1 : a.num_kv_heads;
   const float* sel_scores = w.scores;
   if (a.shared) {
