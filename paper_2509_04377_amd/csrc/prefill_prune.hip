@@ -185,7 +185,7 @@ __global__ __launch_bounds__(kThreads) void head_mean_kernel(const float* __rest
 // 115 us a prune, 108 before and now 97).  (What
 // bounds a long row is the vector issue of its one compute unit, 0.43 us per operation on each of 65536 scores: so equal scores
 // are counted only where some of them stay, a wave's scores are consecutive, and candidates are looked for four at a time.  Part
-// of that issue are 46 to 212 scalar registers, by the size of the holding, that the compiler keeps in lanes of vector registers.)
+// of that issue are 44 to 221 scalar registers, by the size of the holding, that the compiler keeps in lanes of vector registers.)
 // The ways that ordinary scores don't take are kept out of the straight line (8 x 4096 tokens, 8 heads of D = 64, 26.7 us a prune
 // with them in it, 26.2 without).
 constexpr int kSelThreads = 1024;
