@@ -179,7 +179,7 @@ __global__ __launch_bounds__(kThreads) void head_mean_kernel(const float* __rest
 // held, 32768 in registers (32 a thread: 64 would leave too few for the rest) and as many in LDS, and every pass works from
 // there; only what a row has beyond is read from memory in each pass.
 // Measured on an MI355X (kernel trace), digits of 12, 10 and 10 plain bits with a histogram each and 32768 scores held / this: 64
-// rows x 4096 scores 7.3 / 6.6 us, 128 ragged rows of up to 16384 10.4 / 9.0, 256 x 16384 13.4 / 11.1, 32 x 65536 25.9 / 20.5; whole
+// rows x 4096 scores 6.6 / 6.1 us, 128 ragged rows of up to 16384 11.5 / 8.6, 256 x 16384 14.0 / 11.3, 32 x 65536 27.7 / 21.0; whole
 // prunes of 4 x 131072 tokens 451 / 441, with all scores equal 704 / 543, with zeros or infinities among them 451 / 444 (as part of the
 // range they spread the bins: 458; equal scores, where they were collected like others, took 105 ragged prompts of up to 1659 tokens
 // 115 us a prune, 108 before and now 97).  (What
