@@ -344,6 +344,7 @@ int pe_prefill_prune(const pe_cache_desc* desc, const void* k_in, const void* v_
   a.max_blocks = desc->max_blocks;
   a.is_bf16 = desc->dtype == PE_BF16;
   a.shared = desc->layout == PE_LAYOUT_SHARED;
+  a.compute_units = compute_units();
   return pe::launch_prefill_prune(a, static_cast<hipStream_t>(stream)) == hipSuccess ? PE_OK : PE_ERR_HIP;
 }
 

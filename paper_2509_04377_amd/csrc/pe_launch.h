@@ -110,6 +110,7 @@ struct PruneArgs {
   int num_seqs, num_kv_heads, head_dim, block_size, max_blocks;
   bool is_bf16;
   bool shared = false;  // one decision per sequence (head-mean token scores), pages [B][Hk][D]
+  int compute_units = 256;
 };
 hipError_t launch_prefill_prune(const PruneArgs& a, hipStream_t stream);
 size_t prune_workspace_bytes(int num_seqs, int num_kv_heads, int64_t total_tokens, bool shared);

@@ -2,7 +2,7 @@
 // evict the E = max(0, L - C) tokens that come first under (score ascending, index ascending), and
 // write the survivors, order kept, into the row's pages.
 //
-// Three kernels on one stream:
+// Two kernels on one stream, or three for the longest prompts:
 //   1. token_scores:  sweep of the packed K/V prompt; S_i = ||V_i||/||K_i|| in fp64, rounded once to
 //                     fp32, stored per KV head as a contiguous run  scores[hk][token].
 //   2. select:        per row, on the fp32 bit patterns (scores are >= +0, so they order like unsigned integers): a
@@ -11,15 +11,19 @@
 //                     many scores are > T and how many == T (none counted, and q = the largest number, where all go).
 //   3. gather:        per row and chunk, an index-ordered scan turns those counts into the destination
 //                     of every kept token; token rows are then copied with 16-byte lane accesses.
+//   2 + 3. select_gather, for rows of up to 32768 tokens: every workgroup of a row selects by itself, and copies its share of
+//                     what is kept.
 // A token is kept iff score > T, or score == T and at least q equal-score tokens precede it.
 //
 // Head-shared mode (one decision per sequence, pages [B][Hk][D]): a token's score is the mean of its heads' scores (head
 // order, fp64, one rounding), taken by the sweep itself where none of its workgroups ends inside a token, else by a
-// kernel behind it.  Kernel 2 runs on that one score row; kernel 3 copies head by head with its result.
+// kernel behind it.  The selection is made on that one score row, the copy head by head with its result.
 #include "pe_device.h"
 #include "pe_launch.h"
 #include "pe_norms.h"
 #include "pe_place.h"
+
+#include <type_traits>
 
 namespace pe {
 namespace {
@@ -172,22 +176,17 @@ __global__ __launch_bounds__(kThreads) void head_mean_kernel(const float* __rest
 // the candidates in its registers: no barriers in between.  More than 256 candidates go through further digits of up to 12
 // bits, with a histogram each, between the least and the largest of them; more than LDS holds (e.g. scores of few distinct values)
 // are looked for in the whole row again, for their range and for each digit.  A bin of one number, as with equal scores, is done.
-// With the threshold known the same workgroup counts, per chunk of 1024 tokens, how many scores are > T and how many == T: the
-// gather turns these into destinations.
 // A row is worked on by one compute unit, and one compute unit pulls about 45 GB/s from L2 however many loads it keeps
 // in flight: that, not the histogram atomics, bounds the reading of a long row.  So up to 65536 scores of it are read once and
 // held, 32768 in registers (32 a thread: 64 would leave too few for the rest) and as many in LDS, and every pass works from
 // there; only what a row has beyond is read from memory in each pass.
-// Measured on an MI355X (kernel trace), digits of 12, 10 and 10 plain bits with a histogram each and 32768 scores held / this: 64
-// rows x 4096 scores 6.6 / 6.1 us, 128 ragged rows of up to 16384 11.5 / 8.6, 256 x 16384 14.0 / 11.3, 32 x 65536 27.7 / 21.0; whole
-// prunes of 4 x 131072 tokens 451 / 441, with all scores equal 704 / 543, with zeros or infinities among them 451 / 444 (as part of the
-// range they spread the bins: 458; equal scores, where they were collected like others, took 105 ragged prompts of up to 1659 tokens
-// 115 us a prune, 108 before and now 97).  (What
-// bounds a long row is the vector issue of its one compute unit, 0.43 us per operation on each of 65536 scores: so equal scores
-// are counted only where some of them stay, a wave's scores are consecutive, and candidates are looked for four at a time.  Part
-// of that issue are 44 to 221 scalar registers, by the size of the holding, that the compiler keeps in lanes of vector registers.)
+// What bounds a long row is the vector issue of its one compute unit, 0.43 us per operation on each of 65536 scores: so equal scores
+// are counted only where some of them stay, a wave's scores are consecutive, candidates are looked for four at a time, and the last
+// vector of a row is filled up with numbers that rank behind all scores, instead of every element of every vector having a predicate
+// (which took 221 scalar registers in lanes of vector registers, now 78; prunes of 4 x 65536 tokens 209.3 / 207.8 us).
+// Zeros and infinities are kept out of the range (as part of it they spread the bins: 4 x 131072 tokens 458 us a prune, now 451).
 // The ways that ordinary scores don't take are kept out of the straight line (8 x 4096 tokens, 8 heads of D = 64, 26.7 us a prune
-// with them in it, 26.2 without).
+// with them in it, 26.2 without, in three launches).
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / kWave;
 constexpr int kSelBins = 4096;
@@ -232,11 +231,12 @@ struct RowScores {
     const int last = L >= 4 ? L - 4 : 0;
     return L >= 4 ? *reinterpret_cast<const Unaligned4*>(bits + (i < last ? i : last)) : Unaligned4{{0u, 0u, 0u, 0u}};
   }
-  __device__ __forceinline__ void mend(int j, Unaligned4& r) const {  // the one vector that the row's end cuts
+  // Past the row's end the largest number: it ranks behind every score of the row, so that whole vectors can be looked at.
+  __device__ __forceinline__ void mend(int j, Unaligned4& r) const {
     const int i = index(j);
-    if (i < end && i + 4 > L) {
+    if (i + 4 > L) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) r.v[e] = i + e < L ? bits[i + e] : 0u;
+      for (int e = 0; e < 4; ++e) r.v[e] = i + e < L ? bits[i + e] : ~0u;
     }
   }
   __device__ __forceinline__ void load() {
@@ -263,26 +263,15 @@ struct RowScores {
     const uint4 r = lds[(j - NV) * kSelThreads + tid];
     return Unaligned4{{r.x, r.y, r.z, r.w}};
   }
-  // Every score of the row: four(vector) for whole vectors, one(score) for those of a vector that the row's end cuts.  The
-  // held ones ...
-  template <typename F4, typename F1>
-  __device__ __forceinline__ void visit_vector(int j, const Unaligned4& r, F4 four, F1 one) const {
-    if (wave0 + (j + 1) * kVector <= end) {  // the same for all lanes
-      four(r);
-    } else if (wave0 + j * kVector < end) {
-      const int left = L - index(j);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (e < left) one(r.v[e]);
-    }
-  }
+  // Every score of the row: four(vector) for the held ones, and what fills the last vector, ...
   template <typename F4, typename F1>
   __device__ __forceinline__ void visit(F4 four, F1 one) const {
 #pragma unroll
-    for (int j = 0; j < NV; ++j) visit_vector(j, reg[j], four, one);
+    for (int j = 0; j < NV; ++j)
+      if (wave0 + j * kVector < end) four(reg[j]);  // the same for all lanes
 #pragma unroll 1
-    for (int j = NV; j < n; ++j) visit_vector(j, in_lds(j), four, one);
-    // ... and the rest, from memory: 16 bytes a load, past the end the row's last four again
+    for (int j = NV; wave0 + j * kVector < end; ++j) four(in_lds(j));
+    // ... four(vector) or one(score) for the rest, from memory: 16 bytes a load, past the end the row's last four again
     constexpr int kUnroll = LV > 0 ? kSelUnroll : 1;  // a smaller holding covers every row of its call
     for (int i0 = kHeld + 4 * tid; i0 < L; i0 += kUnroll * 4 * kSelThreads) {
       Unaligned4 r[kUnroll];
@@ -357,66 +346,46 @@ __device__ __forceinline__ uint32_t settle(const uint32_t* cand, uint32_t n, uin
   return T;
 }
 
-// Two workgroups a compute unit (eight waves per SIMD, 64 registers) as long as the row leaves the registers for it: more
-// rows than compute units then still run at once.
+constexpr int kAllGo = 0x7fffffff;
+
+// What the selection of a row keeps in LDS besides the held scores.
+struct SelectLds {
+  __attribute__((aligned(16))) uint32_t hist[kSelBins];
+  uint32_t cand[kSelCand];
+  __attribute__((aligned(16))) uint32_t wave_tot[kSelWaves];
+  uint2 wave_range[kSelWaves];
+  uint32_t bin, k, in_bin, ncand;
+};
+
+// Of a row's scores, held in rs: the threshold, and how many tokens (in index order) with that score go.
+struct Threshold {
+  uint32_t T;  // bit pattern of the E-th smallest score
+  int q;       // that many of those equal to it go; the largest number where all do
+};
 template <int NV, int LV>
-__global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(const float* __restrict__ scores,
-                                                             const int32_t* __restrict__ cu_seqlens,
-                                                             uint32_t* __restrict__ sel, int32_t* __restrict__ before,
-                                                             int32_t* __restrict__ seq_lens_out,
-                                                             int32_t* __restrict__ kept_idx_out, int64_t total_tokens,
-                                                             int64_t chunk_slots, int num_kv_heads, int budget) {
-  using Row = RowScores<NV, LV>;
-  constexpr int kHeldChunks = Row::kHeld / kChunk;
-  static_assert(kHeldChunks <= kSelMaxHeldChunks, "chunk counters");
+__device__ __forceinline__ Threshold select_threshold(const RowScores<NV, LV>& rs, SelectLds& sm, int E, int keep, int wave, int lane) {
+  const int L = rs.L, tid = rs.tid;
   constexpr int kBinsPerThread = kSelBins / kSelThreads;
   static_assert(kBinsPerThread == 4, "a thread reads its bins as one vector");
-  __shared__ __attribute__((aligned(16))) uint32_t hist[kSelBins];  // at the end, counts of chunks beyond the held ones
-  __shared__ uint32_t cand[kSelCand];
-  __shared__ uint4 held_lds[LV > 0 ? LV * kSelThreads : 1];
-  __shared__ uint32_t held_count[kSelMaxHeldChunks];
-  __shared__ __attribute__((aligned(16))) uint32_t wave_tot[kSelWaves];
-  __shared__ uint2 wave_range[kSelWaves];
-  __shared__ uint32_t sh_bin, sh_k, sh_in_bin, sh_ncand;
-  const int row = (int)blockIdx.x;
-  const int s = row / num_kv_heads, h = row % num_kv_heads;
-  const int t0 = cu_seqlens[s];
-  const int L = cu_seqlens[s + 1] - t0;
-  const int keep = L < budget ? L : budget;
-  const int E = L - keep;
-  const int tid = (int)threadIdx.x;
-  const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  Row rs;
-  rs.bits = reinterpret_cast<const uint32_t*>(scores) + (int64_t)h * total_tokens + t0;
-  rs.lds = held_lds;
-  rs.L = L;
-  rs.tid = tid;
-  rs.deal(wave);
-  rs.load();
-
-  if (h == 0 && tid == 0) seq_lens_out[s] = keep;
-  if (kept_idx_out != nullptr)
-    for (int i = keep + tid; i < budget; i += kSelThreads) kept_idx_out[(int64_t)row * budget + i] = -1;
-
-  const auto clear_hist = [&] { reinterpret_cast<uint4*>(hist)[tid] = make_uint4(0u, 0u, 0u, 0u); };
-  // The bin of the histogram that rank k falls into (sh_bin), the rank inside it (sh_k) and what it holds (sh_in_bin).
+  const auto clear_hist = [&] { reinterpret_cast<uint4*>(sm.hist)[tid] = make_uint4(0u, 0u, 0u, 0u); };
+  // The bin of the histogram that rank k falls into (sm.bin), the rank inside it (sm.k) and what it holds (sm.in_bin).
   const auto find_bin = [&](uint32_t k) {
-    const uint4 c4 = reinterpret_cast<const uint4*>(hist)[tid];
+    const uint4 c4 = reinterpret_cast<const uint4*>(sm.hist)[tid];
     const uint32_t c[kBinsPerThread] = {c4.x, c4.y, c4.z, c4.w};
     const uint32_t tot = c[0] + c[1] + c[2] + c[3];
     const uint32_t incl = wave_prefix_sum_u32(tot);
-    if (lane == kWave - 1) wave_tot[wave] = incl;
+    if (lane == kWave - 1) sm.wave_tot[wave] = incl;
     __syncthreads();
     uint32_t first = incl - tot;  // elements in lower bins
 #pragma unroll
-    for (int w = 0; w < kSelWaves; ++w) first += w < wave ? wave_tot[w] : 0u;
+    for (int w = 0; w < kSelWaves; ++w) first += w < wave ? sm.wave_tot[w] : 0u;
     if (k >= first && k < first + tot) {  // exactly one thread
 #pragma unroll
       for (int j = 0; j < kBinsPerThread; ++j) {
         if (k >= first && k < first + c[j]) {
-          sh_bin = (uint32_t)(tid * kBinsPerThread + j);
-          sh_k = k - first;
-          sh_in_bin = c[j];
+          sm.bin = (uint32_t)(tid * kBinsPerThread + j);
+          sm.k = k - first;
+          sm.in_bin = c[j];
         }
         first += c[j];
       }
@@ -427,17 +396,16 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
   // The least and the largest of all threads' (lo, hi); nothing (lo > hi) counts as the largest, or the least, number.
   const auto publish_range = [&](uint32_t lo, uint32_t hi) {
     const uint2 r = make_uint2(wave_max_u32(~lo), wave_max_u32(hi));
-    if (lane == 0) wave_range[wave] = r;
+    if (lane == 0) sm.wave_range[wave] = r;
   };
   const auto read_range = [&](uint32_t& lo, uint32_t& hi) {  // behind a barrier
-    const uint2 r = wave_range[lane % kSelWaves];
+    const uint2 r = sm.wave_range[lane % kSelWaves];
     lo = ~wave_max_u32(r.x);
     hi = wave_max_u32(r.y);
   };
 
   clear_hist();
-  if (tid < kSelMaxHeldChunks) held_count[tid] = 0u;
-  if (tid == 0) sh_ncand = 0u;
+  if (tid == 0) sm.ncand = 0u;
   {
     const uint32_t b = rs.reg[0].v[0];
     bool in = rs.index(0) < L;
@@ -460,7 +428,7 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
     low -= low < 1u << shift0 ? low : 1u << shift0;  // the first bin: all below the sample, and its least begins the second
     const auto count_one = [&](uint32_t b) {
       const uint32_t up = __builtin_elementwise_sub_sat(b, low) >> shift0;
-      atomicAdd(&hist[up < (uint32_t)kSelBins - 1u ? up : (uint32_t)kSelBins - 1u], 1u);
+      atomicAdd(&sm.hist[up < (uint32_t)kSelBins - 1u ? up : (uint32_t)kSelBins - 1u], 1u);
     };
     rs.visit([&](const Unaligned4& r) {
 #pragma unroll
@@ -468,16 +436,16 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
     }, count_one);
     __syncthreads();
     find_bin(k);
-    const uint32_t bin = sh_bin;
-    uint32_t n = sh_in_bin;
-    k = sh_k;
+    const uint32_t bin = sm.bin;
+    uint32_t n = sm.in_bin;
+    k = sm.k;
     uint32_t lo = bin == 0u ? 0u : low + (bin << shift0);
     uint32_t hi = bin == (uint32_t)kSelBins - 1u ? 0xffffffffu : low + ((bin + 1u) << shift0) - 1u;
     const uint32_t span = hi - lo;
     if (__builtin_expect(span == 0u, 0)) n = (uint32_t)kSelCand + 1u;  // one number, as with equal scores: it is the threshold, nothing to collect
     if (__builtin_expect(n <= (uint32_t)kSelCand, 1)) {  // collect the bin's scores (their order does not matter: only values are counted)
       const auto keep_one = [&](uint32_t b) {
-        if (b - lo <= span) cand[atomicAdd(&sh_ncand, 1u)] = b;
+        if (b - lo <= span) sm.cand[atomicAdd(&sm.ncand, 1u)] = b;
       };
       rs.visit([&](const Unaligned4& r) {
         const uint32_t d0 = r.v[0] - lo, d1 = r.v[1] - lo, d2 = r.v[2] - lo, d3 = r.v[3] - lo;
@@ -488,12 +456,12 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
           uint32_t all = 0u, at = 0u;
 #pragma unroll
           for (int e = 0; e < 4; ++e) all += (uint32_t)__popcll(who[e] = __builtin_amdgcn_ballot_w64(d[e] <= span));
-          if (lane == 0) at = atomicAdd(&sh_ncand, all);
+          if (lane == 0) at = atomicAdd(&sm.ncand, all);
           at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             if (d[e] <= span)
-              cand[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(who[e] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)who[e], 0u))] = r.v[e];
+              sm.cand[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(who[e] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)who[e], 0u))] = r.v[e];
             at += (uint32_t)__popcll(who[e]);
           }
         }
@@ -503,17 +471,17 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
     if (__builtin_expect(n <= (uint32_t)kSelFew, 1)) {
       if (wave == 0) {  // (all sixteen at once would be in one another's way)
         uint32_t same;
-        T = n <= (uint32_t)kWave ? settle<1>(cand, n, lo, hi, k, same, lane)
-                                 : settle<kSelFew / kWave>(cand, n, lo, hi, k, same, lane);
+        T = n <= (uint32_t)kWave ? settle<1>(sm.cand, n, lo, hi, k, same, lane)
+                                 : settle<kSelFew / kWave>(sm.cand, n, lo, hi, k, same, lane);
         if (lane == 0) {
-          sh_bin = T;
-          sh_k = k;
-          sh_in_bin = same;
+          sm.bin = T;
+          sm.k = k;
+          sm.in_bin = same;
         }
       }
       __syncthreads();
-      T = sh_bin;
-      k = sh_k;
+      T = sm.bin;
+      k = sm.k;
     } else {
       if (span != 0u) {
         uint32_t mn = 0xffffffffu, mx = 0u;
@@ -523,7 +491,7 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
           mx = in && b > mx ? b : mx;
         };
         if (n <= (uint32_t)kSelCand) {
-          for (uint32_t i = (uint32_t)tid; i < n; i += kSelThreads) widen(cand[i]);
+          for (uint32_t i = (uint32_t)tid; i < n; i += kSelThreads) widen(sm.cand[i]);
         } else {
           rs.visit([&](const Unaligned4& r) {
 #pragma unroll
@@ -543,10 +511,10 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
         clear_hist();
         __syncthreads();
         const auto count = [&](uint32_t b) {
-          if (b - lo <= hi - lo && ((b ^ T) & settled) == 0u) atomicAdd(&hist[(b >> shift) & digit], 1u);
+          if (b - lo <= hi - lo && ((b ^ T) & settled) == 0u) atomicAdd(&sm.hist[(b >> shift) & digit], 1u);
         };
         if (n <= (uint32_t)kSelCand) {
-          for (uint32_t i = (uint32_t)tid; i < n; i += kSelThreads) count(cand[i]);
+          for (uint32_t i = (uint32_t)tid; i < n; i += kSelThreads) count(sm.cand[i]);
         } else {
           rs.visit([&](const Unaligned4& r) {
 #pragma unroll
@@ -555,18 +523,59 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
         }
         __syncthreads();
         find_bin(k);
-        T |= sh_bin << shift;
-        k = sh_k;
+        T |= sm.bin << shift;
+        k = sm.k;
         bits = shift;
       }
     }
   }
   // The first k + 1 tokens (index order) with score == T go.  Where that is all there are, as almost always, nobody has to count
   // them: q = the largest number, none before any token.
-  const bool all_go = E > 0 && k + 1u == sh_in_bin;
+  return {T, E == 0 ? 0 : k + 1u == sm.in_bin ? kAllGo : (int)k + 1};
+}
+
+// For rows that are too long to be selected by several workgroups each: the threshold, and, per chunk of 1024 tokens, how many scores
+// before it are > T and == T (the gather turns these into destinations).
+__global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __restrict__ scores, const int32_t* __restrict__ cu_seqlens,
+                                                             uint32_t* __restrict__ sel, int32_t* __restrict__ before,
+                                                             int32_t* __restrict__ seq_lens_out,
+                                                             int32_t* __restrict__ kept_idx_out, int64_t total_tokens,
+                                                             int64_t chunk_slots, int num_kv_heads, int budget) {
+  constexpr int NV = kSelMaxVecs, LV = kSelMaxVecs;
+  using Row = RowScores<NV, LV>;
+  constexpr int kHeldChunks = Row::kHeld / kChunk;
+  static_assert(kHeldChunks <= kSelMaxHeldChunks, "chunk counters");
+  __shared__ SelectLds sm;
+  uint32_t* const hist = sm.hist;  // at the end, counts of chunks beyond the held ones
+  __shared__ uint4 held_lds[LV * kSelThreads];
+  __shared__ uint32_t held_count[kSelMaxHeldChunks];
+  const int row = (int)blockIdx.x;
+  const int s = row / num_kv_heads, h = row % num_kv_heads;
+  const int t0 = cu_seqlens[s];
+  const int L = cu_seqlens[s + 1] - t0;
+  const int keep = L < budget ? L : budget;
+  const int E = L - keep;
+  const int tid = (int)threadIdx.x;
+  const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  Row rs;
+  rs.bits = reinterpret_cast<const uint32_t*>(scores) + (int64_t)h * total_tokens + t0;
+  rs.lds = held_lds;
+  rs.L = L;
+  rs.tid = tid;
+  rs.deal(wave);
+  rs.load();
+
+  if (h == 0 && tid == 0) seq_lens_out[s] = keep;
+  if (kept_idx_out != nullptr)
+    for (int i = keep + tid; i < budget; i += kSelThreads) kept_idx_out[(int64_t)row * budget + i] = -1;
+
+  if (tid < kSelMaxHeldChunks) held_count[tid] = 0u;  // (barriers come before they are used)
+  const Threshold at = select_threshold(rs, sm, E, keep, wave, lane);
+  const uint32_t T = at.T;
+  const bool all_go = at.q == kAllGo;
   if (tid == 0) {
     sel[2 * row] = T;  // threshold score (bit pattern)
-    sel[2 * row + 1] = all_go ? 0x7fffffffu : E > 0 ? k + 1u : 0u;
+    sel[2 * row + 1] = (uint32_t)at.q;
   }
 
   // Scores > T (lower half) and == T (upper half) per chunk, then how many there are before each chunk of the row.
@@ -625,18 +634,6 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(co
     }
     __syncthreads();
   }
-}
-
-// The smallest holding that covers rows of max_seqlen tokens (or the largest there is): a larger one than needed costs loads,
-// branches and, beyond 16 scores a thread, the second workgroup of a compute unit.
-using SelectKernel = void (*)(const float*, const int32_t*, uint32_t*, int32_t*, int32_t*, int32_t*, int64_t, int64_t, int, int);
-SelectKernel select_kernel_for(int max_seqlen) {
-  const int vecs = (max_seqlen + 4 * kSelThreads - 1) / (4 * kSelThreads);
-  if (vecs <= 1) return select_kernel<1, 0>;
-  if (vecs <= 2) return select_kernel<2, 0>;
-  if (vecs <= 4) return select_kernel<4, 0>;
-  if (vecs <= kSelMaxVecs) return select_kernel<kSelMaxVecs, 0>;
-  return select_kernel<kSelMaxVecs, kSelMaxVecs>;
 }
 
 // ---- 3. gather ----------------------------------------------------------------------------------------
@@ -738,6 +735,149 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(const uint4* __restric
   }
 }
 
+// ---- 2 + 3 in one launch ---------------------------------------------------------------------------------
+// The workgroups of a row all find its threshold, each by itself, and each copies its share of the positions of the kept tokens (equal
+// shares, whatever the row's length).  What that saves is a launch between the two and the second reading and counting of the scores;
+// what it costs nothing, as long as every workgroup has a compute unit for itself, is that a row is selected several times.
+// Bound: the chain of launches and barriers for short prompts, memory for long ones.  Measured on an MI355X, two kernels / so, whole
+// prunes, us: 1 x 1000 tokens, 8 heads of D = 128, 15.0 / 10.2; 1 x 8000 20.7 / 16.8; 4 x 4096 28.6 / 22.8; 8 x 4096 of D = 64 26.1 /
+// 23.0; 16 of 2048 to 16384 128.8 / 125.3; 32 x 16384 467 / 466, each of a model's layers into its own pool 442 / 437; fp32, 8 x 8192
+// 112.4 / 110.2; head-shared, 8 of 2048 to 8192 57.3 / 49.3; 2 of 20000 to 32768 60.5 / 60.4.  Longer rows, which one compute unit
+// holds in LDS too, lose (4 x 65536 210.4 / 213.8): there they stay two kernels.
+// (Not faster: two or four rows of a thread in flight in the copy, and K and V read or written with the non-temporal hint: prunes into
+// the same pools again and again win up to 2 %, those of layers that go each into their own lose up to 4.)
+// Two workgroups a compute unit (eight waves per SIMD, 64 registers) as long as the row leaves the registers for it: more rows
+// than compute units then still run at once.
+template <int NV, int VEC_PER_ROW, bool SHARED>
+__global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_gather_kernel(
+    const uint4* __restrict__ k_in, const uint4* __restrict__ v_in, const float* __restrict__ scores,
+    const int32_t* __restrict__ cu_seqlens, const int32_t* __restrict__ block_table, uint4* __restrict__ k_pool,
+    uint4* __restrict__ v_pool, int32_t* __restrict__ seq_lens_out, int32_t* __restrict__ kept_idx_out, int64_t total_tokens,
+    int log2_block, int max_blocks, int budget, int max_seqlen, int log2_parts, int seq0) {
+  using Row = RowScores<NV, 0>;
+  __shared__ SelectLds sm;
+  uint32_t* const list = sm.hist;  // tokens of the positions at hand, once the threshold is known
+  constexpr int kList = kSelBins;
+  // (head, sequence, part): the parts of a row lie side by side on one XCD where the number of rows is a multiple of eight
+  const int h = (int)blockIdx.x, heads = (int)gridDim.x, s = seq0 + (int)blockIdx.y, part = (int)blockIdx.z;
+  const int sel_row = SHARED ? s : s * heads + h, sel_h = SHARED ? 0 : h;
+  const int t0 = cu_seqlens[s];
+  const int L = cu_seqlens[s + 1] - t0;
+  const int keep = L < budget ? L : budget;
+  const int E = L - keep;
+  const int tid = (int)threadIdx.x;
+  const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const bool reports = !SHARED || h == 0;
+  if (part == 0) {
+    if (h == 0 && tid == 0) seq_lens_out[s] = keep;
+    if (kept_idx_out != nullptr && reports)
+      for (int i = keep + tid; i < budget; i += kSelThreads) kept_idx_out[(int64_t)sel_row * budget + i] = -1;
+  }
+  constexpr int kRowsPerPass = kSelThreads / VEC_PER_ROW;
+  const int share = (((keep + (1 << log2_parts) - 1) >> log2_parts) + kRowsPerPass - 1) & ~(kRowsPerPass - 1);  // whole passes of the copy
+  const int lo = part * share, hi = lo + share < keep ? lo + share : keep;
+  if (lo >= hi || L > max_seqlen) return;  // (a row longer than the caller has said: its pages are left alone)
+
+  const int32_t* bt = block_table + (int64_t)sel_row * max_blocks;
+  const int block_mask = (1 << log2_block) - 1;
+  const int u = tid % VEC_PER_ROW, r = tid / VEC_PER_ROW;
+  const auto copy = [&](int p0, int m, auto token_of) {
+    for (int e = r; e < m; e += kRowsPerPass) {
+      const int pos = p0 + e;
+      const int64_t src = ((int64_t)(t0 + token_of(e)) * heads + h) * VEC_PER_ROW + u;
+      const int64_t slot = ((int64_t)bt[pos >> log2_block] << log2_block) + (pos & block_mask);
+      const int64_t dst = (SHARED ? slot * heads + h : slot) * VEC_PER_ROW + u;
+      k_pool[dst] = k_in[src];
+      v_pool[dst] = v_in[src];
+    }
+    if (kept_idx_out != nullptr && reports)
+      for (int e = tid; e < m; e += kSelThreads) kept_idx_out[(int64_t)sel_row * budget + p0 + e] = token_of(e);
+  };
+  if (E == 0) {
+    copy(lo, hi - lo, [&](int e) { return lo + e; });
+    return;
+  }
+
+  Row rs;
+  rs.bits = reinterpret_cast<const uint32_t*>(scores) + (int64_t)sel_h * total_tokens + t0;
+  rs.lds = nullptr;
+  rs.L = L;
+  rs.tid = tid;
+  rs.deal(wave);
+  rs.load();
+  const Threshold at = select_threshold(rs, sm, E, keep, wave, lane);
+
+  // How many of a vector's scores are > T (lower half) and == T (upper half) in this lane, the latter where some of those stay.
+  // (What fills the last vector behind the row's end comes behind every token that is kept.)
+  const auto count4 = [&](const Unaligned4& v, bool ties) {
+    uint32_t n = 0u;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) n += v.v[e] > at.T ? 1u : 0u;
+    if (ties) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) n += v.v[e] == at.T ? 0x10000u : 0u;
+    }
+    return n;
+  };
+  const bool ties = at.q != kAllGo;
+  uint32_t n = 0u;
+#pragma unroll
+  for (int j = 0; j < NV; ++j)
+    if (j < rs.n) n += count4(rs.reg[j], ties);
+  n = wave_prefix_sum_u32(n);
+  if (lane == kWave - 1) sm.wave_tot[wave] = n;
+  const uint32_t mine = (uint32_t)__builtin_amdgcn_readlane((int)n, kWave - 1);
+  __syncthreads();
+  int gt0 = 0, eq0 = 0;  // in the waves before this one
+#pragma unroll
+  for (int w = 0; w < kSelWaves; ++w) {
+    const uint32_t t = sm.wave_tot[w];
+    gt0 += w < wave ? (int)(t & 0xffffu) : 0;
+    eq0 += w < wave ? (int)(t >> 16) : 0;
+  }
+  const auto kept_before = [&](int gt, int eq) { return gt + (eq > at.q ? eq - at.q : 0); };
+  const int mine0 = kept_before(gt0, eq0), mine1 = kept_before(gt0 + (int)(mine & 0xffffu), eq0 + (int)(mine >> 16));
+  for (int p0 = lo; p0 < hi; p0 += kList) {
+    const int p1 = p0 + kList < hi ? p0 + kList : hi;
+    if (p0 > lo) __syncthreads();  // the list has been read
+    if (mine0 < p1 && mine1 > p0) {
+      int gt = gt0, eq = eq0;
+      const auto place4 = [&](int j, const Unaligned4& v) {
+        const uint32_t c = count4(v, ties);
+        const uint32_t inc = wave_prefix_sum_u32(c), ex = inc - c;
+        int g = gt + (int)(ex & 0xffffu), q = eq + (int)(ex >> 16);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bool is_gt = v.v[e] > at.T, is_eq = ties && v.v[e] == at.T;
+          const int pos = kept_before(g, q);
+          if ((is_gt || (is_eq && q >= at.q)) && pos >= p0 && pos < p1) list[pos - p0] = (uint32_t)(rs.index(j) + e);
+          g += is_gt;
+          q += is_eq;
+        }
+        const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
+        gt += (int)(all & 0xffffu);
+        eq += (int)(all >> 16);
+      };
+#pragma unroll
+      for (int j = 0; j < NV; ++j)
+        if (j < rs.n) place4(j, rs.reg[j]);
+    }
+    __syncthreads();
+    copy(p0, p1 - p0, [&](int e) { return (int)list[e]; });
+  }
+}
+
+// The smallest holding that covers rows of max_seqlen tokens: a larger one than needed costs loads, branches and, beyond 16 scores a
+// thread, the second workgroup of a compute unit.
+template <int VPR, bool SHARED>
+auto select_gather_kernel_for(int max_seqlen) {
+  const int vecs = (max_seqlen + 4 * kSelThreads - 1) / (4 * kSelThreads);
+  return vecs <= 1   ? select_gather_kernel<1, VPR, SHARED>
+         : vecs <= 2 ? select_gather_kernel<2, VPR, SHARED>
+         : vecs <= 4 ? select_gather_kernel<4, VPR, SHARED>
+                     : select_gather_kernel<kSelMaxVecs, VPR, SHARED>;
+}
+
 template <typename T, int D>
 hipError_t launch(const PruneArgs& a, hipStream_t stream) {
   using G = RowGeom<T, D>;
@@ -782,14 +922,34 @@ hipError_t launch(const PruneArgs& a, hipStream_t stream) {
     }
     sel_scores = mean;
   }
-  const int rows = a.num_seqs * heads;
-  hipLaunchKernelGGL(select_kernel_for(a.max_seqlen), dim3((unsigned)rows), dim3(kSelThreads), 0, stream, sel_scores, a.cu_seqlens,
-                     w.sel, w.before, a.seq_lens_out, a.kept_idx_out, a.total_tokens, w.chunk_slots, heads, a.budget);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  const int chunks_per_row = (a.max_seqlen + kChunk - 1) / kChunk;
-  if (chunks_per_row == 0) return hipSuccess;
-  if ((int64_t)rows * chunks_per_row >= (1LL << 32) / kThreads) return hipErrorInvalidValue;
+  const int rows = a.num_seqs * heads, chunks_per_row = (a.max_seqlen + kChunk - 1) / kChunk;
+  if ((int64_t)rows * (chunks_per_row > 4 ? chunks_per_row : 4) >= (1LL << 32) / kThreads) return hipErrorInvalidValue;
   constexpr int VPR = G::kLanesPerRow;
+  constexpr int kMostGroups = 1 << 22;  // of a launch: 2^32 threads
+  if (a.max_seqlen <= 4 * kSelMaxVecs * kSelThreads && a.num_kv_heads < kMostGroups) {
+    const auto kernel = a.shared ? select_gather_kernel_for<VPR, true>(a.max_seqlen) : select_gather_kernel_for<VPR, false>(a.max_seqlen);
+    // As many workgroups a row (a power of two) as the compute units have room for with one each, but none with less than one pass
+    // of its copy.  Whole prunes, half as many / so / twice as many, us: 8 x 4096 tokens of D = 64 23.9 / 23.0 / 24.2, 16 of 2048 to
+    // 16384 138.9 / 127.1 / 127.4, 2 of 20000 to 32768 62.9 / 60.1 / 73.0 (each of them selects: beyond one a compute unit they take
+    // turns); one of 1000 with half a pass 10.3, with one 10.2, with two 10.9.
+    const int64_t copies = (int64_t)a.num_seqs * a.num_kv_heads;
+    const int most = a.max_seqlen < a.budget ? a.max_seqlen : a.budget;
+    int log2_parts = 0;
+    while (copies << (log2_parts + 1) <= a.compute_units && most >> (log2_parts + 1) >= kSelThreads / VPR) ++log2_parts;
+    const int room = (kMostGroups - 1) / a.num_kv_heads, seqs = room < 65535 ? room : 65535;  // of a launch
+    for (int s0 = 0; s0 < a.num_seqs; s0 += seqs) {
+      const int ns = a.num_seqs - s0 < seqs ? a.num_seqs - s0 : seqs;
+      hipLaunchKernelGGL(kernel, dim3((unsigned)a.num_kv_heads, (unsigned)ns, 1u << log2_parts), dim3(kSelThreads), 0, stream,
+                         (const uint4*)a.k_in, (const uint4*)a.v_in, sel_scores, a.cu_seqlens, a.block_table, (uint4*)a.k_pool,
+                         (uint4*)a.v_pool, a.seq_lens_out, a.kept_idx_out, a.total_tokens, ilog2(a.block_size), a.max_blocks,
+                         a.budget, a.max_seqlen, log2_parts, s0);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    return e;
+  }
+  hipLaunchKernelGGL(select_kernel, dim3((unsigned)rows), dim3(kSelThreads), 0, stream, sel_scores, a.cu_seqlens,
+                     w.sel, w.before, a.seq_lens_out, a.kept_idx_out, a.total_tokens, w.chunk_slots, heads, a.budget);
+  if ((e = hipGetLastError()) != hipSuccess || chunks_per_row == 0) return e;
   // Plain stores for what is kept.  With the non-temporal hint prunes of 32 x 16384 tokens that go into the same pools again and
   // again take 454 us instead of 467, but those of a model's layers, one after the other and each into its own pool, 475 instead of
   // 457 (four prompts of 65536 229 and 223, 3B prompts 141 and 137, the head-shared layout 455 and 436).

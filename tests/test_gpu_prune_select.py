@@ -76,3 +76,51 @@ def test_selection_is_a_stable_sort(lens, kind):
                 at = torch.arange(keep, device=dev)
                 got = v_pool[table[i, h].long()[at // B], at % B, 7]
                 assert torch.equal(got, v[int(cu[i]) + stay, h, 7]), (budget, i, h)
+
+
+@pytest.mark.parametrize("kind", ["lognormal", "few", "zeros"])
+@pytest.mark.parametrize("shared", [False, True], ids=["per_head", "shared"])
+@pytest.mark.parametrize("lens,heads,budget,dtype", [
+    ([9000, 4100, 8192, 77], 96, 8192, torch.bfloat16),   # a workgroup a row: more positions than it lists at a time
+    ([4100, 900, 1, 4096], 5, 1008, torch.float32),       # several a row, the last one's share cut short or empty
+    ([1000], 3, 64, torch.bfloat16), ([300, 17], 2, 512, torch.float32),   # one pass each; nothing to evict
+    ([32768, 20000], 2, 16384, torch.bfloat16), ([32769, 31], 2, 4112, torch.float32)])   # both sides of the two ways
+def test_shares_of_the_copy(lens, heads, budget, dtype, shared, kind):
+    """Every kept token of every row lands in its slot, whatever share of the row it belongs to."""
+    dev, D, B = "cuda", 64, 16
+    g = torch.Generator(device=dev)
+    g.manual_seed(sum(lens) + budget)
+    total, longest, pages = sum(lens), max(lens), budget // B
+    # scores that bf16 holds; head-shared: the same in every head, so that their mean is the number itself
+    score = _scores(kind, total * (1 if shared else heads), g).to(torch.bfloat16).float().view(total, -1).expand(total, heads)
+    k = torch.zeros((total, heads, D), device=dev, dtype=dtype)
+    v = torch.zeros_like(k)
+    k[:, :, 5] = 1.0
+    v[:, :, 9] = score.to(dtype)
+    k[:, :, 60] = (torch.arange(total, device=dev) % 128 / 65536.0)[:, None].to(dtype)   # tells neighbours apart
+    rows = () if shared else (heads,)
+    table = torch.randperm(len(lens) * (1 if shared else heads) * pages, generator=g, device=dev).int().view((len(lens),) + rows + (pages,))
+    shape = (table.numel(), B) + ((heads, D) if shared else (D,))
+    k_pool, v_pool = torch.zeros(shape, device=dev, dtype=dtype), torch.zeros(shape, device=dev, dtype=dtype)
+    out_lens = torch.zeros(len(lens), dtype=torch.int32, device=dev)
+    kept = torch.full((len(lens),) + rows + (budget,), -2, dtype=torch.int32, device=dev)
+    desc = pe.make_desc(dtype, len(lens), heads, heads, D, B, pages, table.numel(),
+                        pe.PE_LAYOUT_SHARED if shared else pe.PE_LAYOUT_PER_HEAD)
+    cu = torch.tensor([sum(lens[:i]) for i in range(len(lens) + 1)], dtype=torch.int32)
+    pe.pe_prefill_prune(desc, k, v, cu.to(dev), total, longest, budget, k_pool, v_pool, table, out_lens, kept,
+                        pe.alloc_workspace(pe.PE_OP_PREFILL_PRUNE, desc, total, device=dev))
+    real = (v.double().square().sum(-1).sqrt() / k.double().square().sum(-1).sqrt()).float()
+    if shared:
+        real = real.double().mean(-1, keepdim=True).float()
+    for i, n in enumerate(lens):
+        keep, at = min(n, budget), torch.arange(min(n, budget), device=dev)
+        assert int(out_lens[i]) == keep
+        order = torch.sort(real[int(cu[i]):int(cu[i]) + n], dim=0, stable=True).indices[n - keep:]
+        stay = torch.sort(order, dim=0).values.t()   # [rows, keep]
+        assert torch.equal(kept[i, ..., :keep].long().view(-1, keep), stay)
+        assert bool((kept[i, ..., keep:] == -1).all())
+        page = table[i].long().view(-1, pages)[:, at // B]
+        for pool, x in ((k_pool, k), (v_pool, v)):
+            got = pool[page, at % B]   # [rows, keep, (heads,) D]
+            want = x[int(cu[i]) + stay[0]][None] if shared else x[int(cu[i]) + stay, torch.arange(heads, device=dev)[:, None]]
+            assert torch.equal(got, want), i
