@@ -318,8 +318,10 @@ int pe_append_paged_decode(const pe_cache_desc* desc, const void* new_k, const v
  * folded into the sequence dimension: new_k, new_v [layers*S][Hk][D]; q, out [layers*S][Hq][D]; block_table
  * [layers*S][Hk][max_blocks]; seq_lens, seq_lens_out [layers*S]; freed_phys, spare_used [layers*S][Hk]; spare
  * [layers*S][Hk][n_spare] (shared layout: the shapes that layout gives, stacked the same way).  The one workspace
- * (pe_workspace_bytes(PE_OP_APPEND_PAGED_DECODE, desc, 0)) serves every layer.  Returns the first non-OK status;
- * layers before it have been enqueued.
+ * (pe_workspace_bytes(PE_OP_APPEND_PAGED_DECODE, desc, 0)) serves every layer.  `out` is the library's until the call's
+ * launches are through: where rows are split, a layer's output may hold counts of the splits before its own launch.  (Not where
+ * `out` overlaps q, new_k or new_v, or is not 4-byte aligned: launches of their own then merge the splits, as in the call above.)
+ * Returns the first non-OK status; layers before it have been enqueued.
  */
 int pe_append_paged_decode_layers(const pe_cache_desc* desc, int32_t num_layers, const void* new_k, const void* new_v,
                                   const void* q, void* k_pool, void* v_pool, int32_t* block_table,

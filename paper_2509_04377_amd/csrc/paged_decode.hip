@@ -263,7 +263,7 @@ struct Tile {
   }
 };
 
-template <typename T, int D, int G, bool FUSED, bool SHARED>
+template <typename T, int D, int G, bool FUSED, bool SHARED, bool ARRIVALS = false>
 __global__ __launch_bounds__(kWaves * kWave) void paged_decode_kernel(
     const int32_t* seq_lens, const int32_t* block_table, const void* q, const void* k_pool_p, const void* v_pool_p,
     const int num_kv_heads, const int max_blocks, const uint32_t inv_heads, const uint32_t shape, const DecodeParams) {
@@ -397,7 +397,10 @@ __global__ __launch_bounds__(kWaves * kWave) void paged_decode_kernel(
     }
   }
   __syncthreads();
-  merge_waves<T>(sm, p, row, split, splits, g_real);
+  if constexpr (ARRIVALS)
+    merge_arrived<T>(sm, p, row, split, splits, g_real);
+  else
+    merge_waves<T>(sm, p, row, split, splits, g_real);
 
   // FUSED: the first lane group of the last split's last wave stores the new token into the pool, linking a new page first when
   // the tail page is full.  Last of all, so that nothing of this launch waits for a store.
@@ -435,9 +438,9 @@ __global__ __launch_bounds__(kWaves * kWave) void paged_decode_kernel(
 // 264 x 4096 94.2 / 93.8; D = 64 7.7 / 6.9, 9.3 / 8.4, 9.5 / 9.0, 13.9 / 13.6, 51.5 / 51.2; one query head: the same order);
 // kMergeLinear: more rows than a grid has, divided.
 enum { kMergeLinear, kMergeRows, kMergeXcd };
-template <typename T, int D>
+template <typename T, int D, bool CLEAR>
 __global__ __launch_bounds__(kWave) void paged_decode_reduce_kernel(const float* __restrict__ partials, void* __restrict__ out,
-                                                                    int g_real, int splits, int order) {
+                                                                    int g_real, int splits, int order, void* next_out) {
   constexpr int E = D / kWave;
   const int x = (int)blockIdx.x, y = (int)blockIdx.y;
   const int row = order == kMergeLinear ? x / g_real : order == kMergeXcd ? y * 8 + (x & 7) : y;
@@ -470,6 +473,8 @@ __global__ __launch_bounds__(kWave) void paged_decode_reduce_kernel(const float*
     mm = m_new;
   }
   const int64_t off = ((int64_t)row * g_real + h) * D + d;
+  // (the counts of the launch behind this one: one for every 128 elements of a row)
+  if (CLEAR && (h * D + d) % (2 * kWave) == 0) *arrival_count<T>(next_out, off / 2) = 0u;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const float r = l > 0.f ? o[e] / l : 0.f;
@@ -488,6 +493,11 @@ hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
   if (!decode_kernel_args(a, &k, &blocks)) return hipErrorInvalidValue;
   const dim3 threads(kWaves * kWave);
   if (a.shared && a.new_k != nullptr) return hipErrorInvalidValue;
+  if (a.counted) {
+    if constexpr (one_part_a_wave<next_pow2(G), D, kWaves>)
+      return launch_decode(paged_decode_kernel<T, D, G, true, false, true>, blocks, threads, stream, k);
+    return hipErrorInvalidValue;
+  }
   const auto kernel = a.shared             ? paged_decode_kernel<T, D, G, false, true>
                       : a.new_k != nullptr ? paged_decode_kernel<T, D, G, true, false>
                                            : paged_decode_kernel<T, D, G, false, false>;
@@ -514,7 +524,8 @@ void launch_reduce(const DecodeArgs& a, hipStream_t stream) {
   const int64_t grid_rows = xcd ? rows / 8 : rows;
   const int order = grid_rows > 65535 ? kMergeLinear : xcd ? kMergeXcd : kMergeRows;
   const dim3 blocks = order == kMergeLinear ? dim3((unsigned)(rows * g)) : dim3((unsigned)(xcd ? 8 * g : g), (unsigned)grid_rows);
-  hipLaunchKernelGGL((paged_decode_reduce_kernel<T, D>), blocks, dim3(kWave), 0, stream, a.partials, a.out, g, a.splits, order);
+  const auto kernel = a.next_out != nullptr ? paged_decode_reduce_kernel<T, D, true> : paged_decode_reduce_kernel<T, D, false>;
+  hipLaunchKernelGGL(kernel, blocks, dim3(kWave), 0, stream, a.partials, a.out, g, a.splits, order, a.next_out);
 }
 
 }  // namespace
@@ -534,7 +545,7 @@ hipError_t launch_paged_decode(const DecodeArgs& a, hipStream_t stream) {
     e = d64 ? launch_one<bf16_t, 64, 1>(a, stream) : launch_one<bf16_t, 128, 1>(a, stream);
   else
     e = launch_paged_decode_bf16(a, stream);
-  if (e != hipSuccess || a.splits == 1) return e;
+  if (e != hipSuccess || a.splits == 1 || a.counted) return e;
   if (a.is_bf16)
     d64 ? launch_reduce<bf16_t, 64>(a, stream) : launch_reduce<bf16_t, 128>(a, stream);
   else

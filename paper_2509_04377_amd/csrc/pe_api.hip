@@ -514,11 +514,26 @@ int pe_paged_decode_static(const pe_cache_desc* desc, const void* q, const void*
   return pe::launch_paged_decode(a, static_cast<hipStream_t>(stream)) == hipSuccess ? PE_OK : PE_ERR_HIP;
 }
 
-int pe_append_paged_decode(const pe_cache_desc* desc, const void* new_k, const void* new_v, const void* q,
-                           void* k_pool, void* v_pool, int32_t* block_table, const int32_t* seq_lens,
-                           int32_t* seq_lens_out, int32_t* freed_phys, const int32_t* spare, int32_t* spare_used,
-                           int32_t n_spare, float softmax_scale, void* out, void* workspace, size_t workspace_bytes,
-                           void* stream) {
+namespace {
+// Whether the splits of a row are counted where the caller can provide for it (pe_decode_common.h says when that pays).
+bool splits_counted(const pe_cache_desc* d, const pe::DecodeArgs& a) {
+  const int64_t groups = (int64_t)d->num_seqs * d->num_kv_heads * a.splits;
+  const bool built = a.waves == 4 && a.depth <= 2 && !(a.shared && !a.is_bf16);
+  return built && a.splits > 1 && a.splits <= pe::kMostArrivals && d->num_q_heads / d->num_kv_heads * d->head_dim <= 512 &&
+         groups <= 2 * (int64_t)compute_units();
+}
+
+bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + b_bytes && y < x + a_bytes;
+}
+
+// `counted`: the arrival counts in `out` are clear (by the call for the layer before); next_out: where this call is to clear them for
+// the layer behind it, or null.
+int append_paged_decode(const pe_cache_desc* desc, const void* new_k, const void* new_v, const void* q, void* k_pool, void* v_pool,
+                        int32_t* block_table, const int32_t* seq_lens, int32_t* seq_lens_out, int32_t* freed_phys,
+                        const int32_t* spare, int32_t* spare_used, int32_t n_spare, float softmax_scale, void* out, void* workspace,
+                        size_t workspace_bytes, void* stream, bool counted, void* next_out) {
   const int st = check_desc(desc);
   if (st != PE_OK) return st;
   if (!new_k || !new_v || !q || !k_pool || !v_pool || !block_table || !seq_lens || !seq_lens_out || !freed_phys ||
@@ -550,6 +565,10 @@ int pe_append_paged_decode(const pe_cache_desc* desc, const void* new_k, const v
   a.spare_used = spare_used;
   a.seq_lens_out = seq_lens_out;
   a.n_spare = n_spare;
+  if (splits_counted(desc, a)) {
+    a.counted = counted;
+    a.next_out = next_out;
+  }
   if (desc->layout == PE_LAYOUT_SHARED && desc->dtype == PE_F32) {
     // One table row per sequence: the workgroups of a sequence's heads would race on its page bookkeeping inside one
     // launch of the fp32 kernel, so the same effect is produced by two launches (append, then attention over the new
@@ -581,6 +600,17 @@ int pe_append_paged_decode(const pe_cache_desc* desc, const void* new_k, const v
   return pe::launch_paged_decode(a, static_cast<hipStream_t>(stream)) == hipSuccess ? PE_OK : PE_ERR_HIP;
 }
 
+}  // namespace
+
+int pe_append_paged_decode(const pe_cache_desc* desc, const void* new_k, const void* new_v, const void* q,
+                           void* k_pool, void* v_pool, int32_t* block_table, const int32_t* seq_lens,
+                           int32_t* seq_lens_out, int32_t* freed_phys, const int32_t* spare, int32_t* spare_used,
+                           int32_t n_spare, float softmax_scale, void* out, void* workspace, size_t workspace_bytes,
+                           void* stream) {
+  return append_paged_decode(desc, new_k, new_v, q, k_pool, v_pool, block_table, seq_lens, seq_lens_out, freed_phys, spare, spare_used,
+                             n_spare, softmax_scale, out, workspace, workspace_bytes, stream, false, nullptr);
+}
+
 int pe_append_paged_decode_layers(const pe_cache_desc* desc, int32_t num_layers, const void* new_k, const void* new_v,
                                   const void* q, void* k_pool, void* v_pool, int32_t* block_table,
                                   const int32_t* seq_lens, int32_t* seq_lens_out, int32_t* freed_phys,
@@ -597,12 +627,17 @@ int pe_append_paged_decode_layers(const pe_cache_desc* desc, int32_t num_layers,
   const int64_t rows = shared ? S : S * desc->num_kv_heads;  // table rows, spare lists, freed pages per layer
   const size_t kv_bytes = (size_t)S * desc->num_kv_heads * desc->head_dim * elem;
   const size_t q_bytes = (size_t)S * desc->num_q_heads * desc->head_dim * elem;
+  // The output of a layer holds counts before its launch: not if something that is read still lies there, or at an odd address.
+  const bool free_out = aligned(out, 4) && !overlap(out, num_layers * q_bytes, q, num_layers * q_bytes) &&
+                        !overlap(out, num_layers * q_bytes, new_k, num_layers * kv_bytes) &&
+                        !overlap(out, num_layers * q_bytes, new_v, num_layers * kv_bytes);
   for (int32_t l = 0; l < num_layers; ++l) {
-    const int rc = pe_append_paged_decode(
+    const int rc = append_paged_decode(
         desc, static_cast<const char*>(new_k) + l * kv_bytes, static_cast<const char*>(new_v) + l * kv_bytes,
         static_cast<const char*>(q) + l * q_bytes, k_pool, v_pool, block_table + l * rows * desc->max_blocks,
         seq_lens + l * S, seq_lens_out + l * S, freed_phys + l * rows, spare + l * rows * n_spare, spare_used + l * rows,
-        n_spare, softmax_scale, static_cast<char*>(out) + l * q_bytes, workspace, workspace_bytes, stream);
+        n_spare, softmax_scale, static_cast<char*>(out) + l * q_bytes, workspace, workspace_bytes, stream,
+        free_out && l > 0, free_out && l + 1 < num_layers ? static_cast<char*>(out) + (l + 1) * q_bytes : nullptr);
     if (rc != PE_OK) return rc;
   }
   return PE_OK;

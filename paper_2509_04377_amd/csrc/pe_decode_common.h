@@ -32,6 +32,7 @@ struct DecodeParams {
   const int32_t* spare;
   int32_t* spare_used;
   int32_t* seq_lens_out;  // [S], must not alias seq_lens
+  void* next_out;         // output of the launch behind this one, whose arrival counts are to be cleared, or null (merge_arrived)
 };
 
 // All of them as they lie in the kernel-argument segment (in order, each at its own alignment).
@@ -81,7 +82,7 @@ inline bool decode_kernel_args(const DecodeArgs& a, DecodeKernelArgs* k, dim3* b
                         (uint32_t)log2_block | (uint32_t)(a.num_q_heads / a.num_kv_heads) << 3 | (g.xcd ? kShapeXcd : 0u) |
                             (g.linear ? kShapeLinear : 0u) | (uint32_t)a.splits << 9,
                         DecodeParams{a.out, a.partials, a.scale * 1.4426950408889634f, a.n_spare, a.new_k, a.new_v, a.freed_phys,
-                                     a.spare, a.spare_used, a.seq_lens_out}};
+                                     a.spare, a.spare_used, a.seq_lens_out, a.next_out}};
   return true;
 }
 
@@ -98,7 +99,7 @@ __device__ __forceinline__ DecodeParams decode_params(int behind) {
   asm("" : "+s"(args) : "s"(behind));
   const auto* a = reinterpret_cast<const __attribute__((address_space(4))) DecodeParams*>(args);
   return DecodeParams{a->out,   a->partials,   a->scale_log2e, a->n_spare,    a->new_k,
-                      a->new_v, a->freed_phys, a->spare,       a->spare_used, a->seq_lens_out};
+                      a->new_v, a->freed_phys, a->spare,       a->spare_used, a->seq_lens_out, a->next_out};
 }
 
 // Two neighbouring elements of the output in one store, at any boundary of their own size.
@@ -116,6 +117,117 @@ struct WaveStates {
   float2 ml[WAVES][GH];
 };
 
+// Two elements of a head over its splits, four of them at a time: read(split, ml, o) gets a split's (m, l) and elements.  The next four
+// are on their way while four are added.
+template <typename Read>
+__device__ __forceinline__ float2 merge_splits(int splits, Read read) {
+  float m = -__builtin_inff(), l = 0.f, o0 = 0.f, o1 = 0.f;
+  float2 ml[4], o[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) read(j < splits ? j : splits - 1, ml[j], o[j]);
+  for (int s = 0;;) {
+    const int next = s + 4;
+    float2 ml_next[4], o_next[4];
+    if (next < splits) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) read(next + j < splits ? next + j : splits - 1, ml_next[j], o_next[j]);
+    }
+    float mm = m;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) mm = fmaxf(mm, ml[j].x);  // (those past the last are the last again)
+    const float ms = mm == -__builtin_inff() ? 0.f : mm;
+    const float old = __builtin_amdgcn_exp2f(m - ms);
+    l *= old;
+    o0 *= old;
+    o1 *= old;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float w = s + j < splits ? __builtin_amdgcn_exp2f(ml[j].x - ms) : 0.f;
+      l = fmaf(ml[j].y, w, l);
+      o0 = fmaf(o[j].x, w, o0);
+      o1 = fmaf(o[j].y, w, o1);
+    }
+    m = mm;
+    if (next >= splits) break;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) ml[j] = ml_next[j], o[j] = o_next[j];
+    s = next;
+  }
+  return l > 0.f ? make_float2(o0 / l, o1 / l) : make_float2(0.f, 0.f);
+}
+
+// ---- splits merged by the last of them to arrive ---------------------------------------------------------------
+// A launch whose rows' splits are counted needs no merge launch behind it.  Every wave of a workgroup stores its part of the split's
+// record, waits until that is where all compute dies see it, and counts its arrival; the one that finds all others there before it
+// reads the records back and writes the output, in the order of the splits, whoever it is.  Records are stored and loaded as relaxed
+// atomics at agent scope (write-through, past the first-level cache), so that nothing rests on which compute die a workgroup is on.
+//
+// The counts have to be zero when the launch begins.  There is nowhere to keep them from one call to the next (a workspace may hold
+// anything), so they live in the output itself: the first word of what a wave will write there is its count until it does.  Only a
+// call that knows the next launch's output can use this, the one for all layers of a step: a layer's launch (of the first layer, the
+// merge launch behind it) clears the words of the next layer's output.
+//
+// Bound: a chain of three round trips, cycles (2.4 GHz) from a clock in the kernel: records stored 530, counted 960, read back 720,
+// merged 570; a merge launch costs 1.9 us.  16 layers of 64 rows x 1024 tokens of D = 64 in four splits 2056 / 1812 us for 16 steps,
+// 32 layers of 32 rows x 4096 of D = 128 in eight 8295 / 8090 us.  Where it pays (merge launch / this, us a layer, D = 128 unless said):
+//   - up to some dozen splits, merged four at a time one after the other: 20 rows x 2048 in twelve 10.1 / 9.5 (fp32 13.4 / 12.6), 16
+//     rows x 2048 in sixteen 9.1 / 9.3 (8.9 / 9.1 with eight query heads of D = 64);
+//   - one part of a row a wave: with two (more than four query heads) 32 rows x 2048 in eight 11.9 / 12.7;
+//   - workgroups that are all there from the beginning, two a compute unit: 128 rows x 2048 of fp32 in four 48.8 / 48.3; of 640 and
+//     more, those that wait for memory at their ends keep others out (160 rows x 4096 in four 62.3 / 65.5, 264 x 2048 52.9 / 54.4).
+template <int GH, int D, int WAVES>
+constexpr bool one_part_a_wave = GH * (D / 2) <= WAVES * kWave;
+
+__device__ __forceinline__ void store_for_all(float* to, float a, float b) {
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(to), __builtin_bit_cast(uint64_t, make_float2(a, b)), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 load_of_all(const float* from) {
+  return __builtin_bit_cast(float2, __hip_atomic_load(reinterpret_cast<const uint64_t*>(from), __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT));
+}
+
+template <typename T>
+__device__ __forceinline__ void store_pair(void* out, int64_t pair, float a, float b) {
+  if constexpr (sizeof(T) == 4) {
+    static_cast<F32Pair*>(out)[pair] = F32Pair{a, b};
+  } else {
+    static_cast<Bf16Pair*>(out)[pair].v = (uint32_t)f32_to_bf16(a) | ((uint32_t)f32_to_bf16(b) << 16);
+  }
+}
+// `pair`: the first of a wave's part of a row
+template <typename T>
+__device__ __forceinline__ uint32_t* arrival_count(void* out, int64_t pair) {
+  return reinterpret_cast<uint32_t*>(static_cast<char*>(out) + pair * (2 * (int64_t)sizeof(T)));
+}
+
+// (m, l) and two elements of a head over the waves of a workgroup
+struct WavesMerged {
+  float m, l, o0, o1;
+};
+template <int WAVES, int GH, int D>
+__device__ __forceinline__ WavesMerged over_waves(const WaveStates<WAVES, GH, D>& sm, int h, int d) {
+  float2 ml[WAVES], part[WAVES];
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) {
+    ml[w] = sm.ml[w][h];
+    part[w] = *reinterpret_cast<const float2*>(&sm.acc[w][h][d]);
+  }
+  __builtin_amdgcn_sched_barrier(0);  // all are asked for before the first is used
+  WavesMerged r{-__builtin_inff(), 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) r.m = fmaxf(r.m, ml[w].x);
+  const float ms = r.m == -__builtin_inff() ? 0.f : r.m;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) {
+    const float f = __builtin_amdgcn_exp2f(ml[w].x - ms);
+    r.l = fmaf(ml[w].y, f, r.l);
+    r.o0 = fmaf(part[w].x, f, r.o0);
+    r.o1 = fmaf(part[w].y, f, r.o1);
+  }
+  return r;
+}
+
 // The end of a workgroup: its waves' states merged into the normalised output, or with several splits into the record of this
 // one (accumulators, m, l).
 template <typename T, int WAVES, int GH, int D>
@@ -123,40 +235,47 @@ __device__ __forceinline__ void merge_waves(const WaveStates<WAVES, GH, D>& sm, 
                                             int splits, int g_real) {
   for (int idx = (int)threadIdx.x; idx < g_real * (D / 2); idx += WAVES * kWave) {
     const int h = idx / (D / 2), d = idx % (D / 2) * 2;
-    float2 ml[WAVES], part[WAVES];
-#pragma unroll
-    for (int w = 0; w < WAVES; ++w) {
-      ml[w] = sm.ml[w][h];
-      part[w] = *reinterpret_cast<const float2*>(&sm.acc[w][h][d]);
-    }
-    __builtin_amdgcn_sched_barrier(0);  // all are asked for before the first is used
-    float mm = -__builtin_inff();
-#pragma unroll
-    for (int w = 0; w < WAVES; ++w) mm = fmaxf(mm, ml[w].x);
-    const float ms = mm == -__builtin_inff() ? 0.f : mm;
-    float ll = 0.f, o0 = 0.f, o1 = 0.f;
-#pragma unroll
-    for (int w = 0; w < WAVES; ++w) {
-      const float f = __builtin_amdgcn_exp2f(ml[w].x - ms);
-      ll = fmaf(ml[w].y, f, ll);
-      o0 = fmaf(part[w].x, f, o0);
-      o1 = fmaf(part[w].y, f, o1);
-    }
+    const WavesMerged r = over_waves(sm, h, d);
     const int64_t head = (int64_t)row * g_real + h;  // s * Hq + query head
     if (splits == 1) {
-      const float r0 = ll > 0.f ? o0 / ll : 0.f, r1 = ll > 0.f ? o1 / ll : 0.f;
-      const int64_t pair = (head * D + d) / 2;
-      if constexpr (sizeof(T) == 4) {
-        static_cast<F32Pair*>(p.out)[pair] = F32Pair{r0, r1};
-      } else {
-        static_cast<Bf16Pair*>(p.out)[pair].v = (uint32_t)f32_to_bf16(r0) | ((uint32_t)f32_to_bf16(r1) << 16);
-      }
+      store_pair<T>(p.out, (head * D + d) / 2, r.l > 0.f ? r.o0 / r.l : 0.f, r.l > 0.f ? r.o1 / r.l : 0.f);
     } else {
       float* record = p.partials + (((int64_t)row * splits + split) * g_real + h) * (D + 2);
-      *reinterpret_cast<float2*>(record + d) = make_float2(o0, o1);
-      if (d == 0) *reinterpret_cast<float2*>(record + D) = make_float2(mm, ll);
+      *reinterpret_cast<float2*>(record + d) = make_float2(r.o0, r.o1);
+      if (d == 0) *reinterpret_cast<float2*>(record + D) = make_float2(r.m, r.l);
     }
   }
+}
+
+// The same where the splits are counted (every wave has one part of the row: 64 pairs of elements).
+template <typename T, int WAVES, int GH, int D>
+__device__ __forceinline__ void merge_arrived(const WaveStates<WAVES, GH, D>& sm, const DecodeParams& p, int row, int split, int splits,
+                                              int g_real) {
+  static_assert(one_part_a_wave<GH, D, WAVES>, "one part of a row a wave");
+  const int pairs = g_real * (D / 2), idx = (int)threadIdx.x, lane = lane_id();
+  if (idx >= pairs) return;
+  const int h = idx / (D / 2), d = idx % (D / 2) * 2;
+  const int record = g_real * (D + 2);  // floats of a split
+  const WavesMerged r = over_waves(sm, h, d);
+  float* const base = p.partials + (int64_t)row * splits * record;
+  float* const to = base + split * record + h * (D + 2);
+  store_for_all(to + d, r.o0, r.o1);
+  if (d == 0) store_for_all(to + D, r.m, r.l);
+  const int64_t pair0 = (int64_t)row * pairs;
+  const uint32_t ml_at = (uint32_t)(h * (D + 2) + D), o_at = (uint32_t)(h * (D + 2) + d);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the records are where everyone sees them
+  uint32_t before = 0;
+  if (lane == 0) before = __hip_atomic_fetch_add(arrival_count<T>(p.out, pair0 + idx), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (__builtin_amdgcn_readfirstlane((int)before) == splits - 1) {
+    asm volatile("" ::: "memory");  // (the loads below do not move up)
+    const float2 o = merge_splits(splits, [&](int s, float2& ml, float2& v) {
+      const float* of = base + s * record;
+      ml = load_of_all(of + ml_at);
+      v = load_of_all(of + o_at);
+    });
+    store_pair<T>(p.out, pair0 + idx, o.x, o.y);
+  }
+  if (p.next_out != nullptr && split == 0 && lane == 0) *arrival_count<T>(p.next_out, pair0 + idx) = 0u;
 }
 
 // The page that a new token goes to, and the bookkeeping of one that has to be linked for it (by lane 0): the page freed by
