@@ -1,6 +1,6 @@
 // Block importance scores (Alg. 1, block mode; Alg. 3 "Compute Score of Page i"):
 //   S_j = (1/B) * sum_{i in page j} ||V_i||_2 / ||K_i||_2
-// One wave sweeps one page: every lane loads 16 bytes, consecutive lanes consecutive addresses, so a
+// One wave sweeps one page at a time: every lane loads 16 bytes, consecutive lanes consecutive addresses, so a
 // wave-load covers 1 KiB of the page.  Sums of squares are accumulated in fp64, reduced over the
 // lanes of a token row, and the page mean is summed in slot order and rounded once to fp32.
 //
@@ -17,8 +17,6 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
-constexpr int kPagesPerWave = 4;
-constexpr int kPagesPerGroup = kWaves * kPagesPerWave;
 
 // A chunk of CH token rows (a whole page, or 32 tokens of a larger one) scored by one wave.
 template <typename T, int D, int CH>
@@ -80,7 +78,8 @@ struct PageGeom {
   }
 };
 
-template <typename T, int D, int B>
+// PAGES: of a wave, every fourth of its workgroup's.
+template <typename T, int D, int B, int PAGES>
 __global__ __launch_bounds__(kThreads) void score_blocks_kernel(const T* __restrict__ k_pool,
                                                                 const T* __restrict__ v_pool,
                                                                 const int32_t* __restrict__ block_table,
@@ -92,7 +91,7 @@ __global__ __launch_bounds__(kThreads) void score_blocks_kernel(const T* __restr
   using CS = typename PG::CS;
   constexpr int NL = CS::NL;
   constexpr int NCH = PG::NCH;
-  constexpr int kUnits = kPagesPerWave * NCH;  // (page, chunk) units of one wave, in order
+  constexpr int kUnits = PAGES * NCH;  // (page, chunk) units of one wave, in order
 
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
@@ -114,7 +113,7 @@ __global__ __launch_bounds__(kThreads) void score_blocks_kernel(const T* __restr
   // recent == 0: every entry of the row; else only the last `recent` full pages
   const int j_first = recent > 0 ? (nfull > recent ? nfull - recent : 0) : 0;
   const int j_end = recent > 0 ? nfull : max_blocks;
-  const int j0 = j_first + grp * kPagesPerGroup + wave;
+  const int j0 = j_first + grp * (kWaves * PAGES) + wave;
 
   uint4 kb[2][NL], vb[2][NL];
   if (j0 < nfull) CS::issue(kb[0], vb[0], k_pool, v_pool, PG::chunk_base(bt[j0], 0) * row_mul, lane_vec, load_stride);
@@ -261,17 +260,37 @@ __global__ __launch_bounds__(kThreads) void score_evict_lens_kernel(int32_t* __r
   if (len > 0 && (len % block_size) == 0 && len >= budget && n <= max_blocks) seq_lens[s] = len - block_size;
 }
 
-template <typename T, int D, int B>
-hipError_t launch(const ScoreArgs& a, hipStream_t stream) {
-  const int span = a.recent > 0 ? (a.recent < a.max_blocks ? a.recent : a.max_blocks) : a.max_blocks;
-  const int groups_per_row = (span + kPagesPerGroup - 1) / kPagesPerGroup;
-  const int64_t rows = (int64_t)a.num_seqs * a.num_kv_heads;
+template <typename T, int D, int B, int PAGES>
+hipError_t launch_pages(const ScoreArgs& a, int64_t rows, int groups_per_row, hipStream_t stream) {
   const int64_t grid = rows * groups_per_row;
   if (grid <= 0 || grid > 0x7fffffffLL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((score_blocks_kernel<T, D, B>), dim3((unsigned)grid), dim3(kThreads), 0, stream,
+  hipLaunchKernelGGL((score_blocks_kernel<T, D, B, PAGES>), dim3((unsigned)grid), dim3(kThreads), 0, stream,
                      (const T*)a.k_pool, (const T*)a.v_pool, a.block_table, a.seq_lens, a.scores,
                      a.num_kv_heads, a.max_blocks, groups_per_row, a.recent, a.shared ? 1 : 0, a.budget);
   return hipGetLastError();
+}
+
+// One, two or four pages a wave.  Few pages a wave finish sooner where few rows are scored (those of the sequences that evict now);
+// many workgroups cost some 0.4 ns each where most of them have nothing to do, and a long sweep runs better with larger ones.  So: the
+// fewest that make no more than 8192 workgroups, or 16384 of 128 KiB or more.  Measured on an MI355X, no sequence of the batch evicts /
+// one / all, four | two | one pages a wave, us (bf16, D = 128, 16-token pages unless said): one layer of 32 x 8 rows x 2048 tokens 3.8
+// / 7.1 / 43 | 3.8 / 4.4 / 43 | 4.3 / 4.9 / 41; 16 layers of 8 x 8 x 1024, D = 64, 3.3 / 17.8 / 46 | 4.3 / 10.4 / 44 | 7.4 / 10.9 / 42; the
+// same of 64-token pages 3.2 / 29 / 46 | 3.2 / 21 / 47 | 3.1 / 13 / 44; 28 layers of 16 x 8 x 1024 7.0 / 26 / 284 | 12 / 24 / 286 | 22 / 29 /
+// 288; of 32-token pages 5.8 / 38 / 281 | 8.1 / 26 / 281 | 12 / 23 / 283; 32 layers of 32 x 8 x 2048 of 32-token pages 19 / 59 / 1258 | 31 / 58
+// / 1283 | 49 / 63 / 1297, of 128 6.3 / 110 / 1261 | 11 / 81 / 1251 | 19 / 59 / 1249; fp32, 4 layers of 2 x 2 x 8192, 128-token pages 3.2 /
+// 46 / 50 | 3.2 / 30 / 34 | 3.1 / 19 / 24.
+template <typename T, int D, int B>
+hipError_t launch(const ScoreArgs& a, hipStream_t stream) {
+  const int span = a.recent > 0 ? (a.recent < a.max_blocks ? a.recent : a.max_blocks) : a.max_blocks;
+  const int64_t rows = (int64_t)a.num_seqs * a.num_kv_heads;
+  const auto groups = [&](int pages) { return (span + kWaves * pages - 1) / (kWaves * pages); };
+  const auto fits = [&](int pages) {
+    const int64_t grid = rows * groups(pages);
+    return grid <= 8192 || (grid <= 16384 && (int64_t)kWaves * pages * B * D * 2 * (int64_t)sizeof(T) >= 128 << 10);
+  };
+  if (fits(1)) return launch_pages<T, D, B, 1>(a, rows, groups(1), stream);
+  if (fits(2)) return launch_pages<T, D, B, 2>(a, rows, groups(2), stream);
+  return launch_pages<T, D, B, 4>(a, rows, groups(4), stream);
 }
 
 template <typename T, int D, int B>
