@@ -429,23 +429,27 @@ __global__ __launch_bounds__(kWaves * kWave) void paged_decode_kernel(
     }
 }
 
-// Merge the split partials of one (sequence, query head): one wave, D / 64 elements a lane.  What a launch of it costs is the
-// launch and one round trip to the records, which lie together for a row ([row][split][head]: with the heads of all rows under
-// each split 0.4 us more for 32 rows of D = 128 in eight splits, 1.1 us for 16 rows in 16).  The grid: the query heads of a row
-// side by side, one row a grid row; with kMergeXcd, wherever the attention kernel keeps a row on one XCD, eight rows a grid row, so
-// that a row's records are read on the XCD that wrote them (append, attention and merge out of a HIP graph, side by side / so: D =
-// 128, four query heads a KV head, 8 rows x 4096 8.8 / 8.0 us, 16 x 5280 12.4 / 11.4, 32 x 4096 14.6 / 13.95, 32 x 8192 24.3 / 23.9,
-// 264 x 4096 94.2 / 93.8; D = 64 7.7 / 6.9, 9.3 / 8.4, 9.5 / 9.0, 13.9 / 13.6, 51.5 / 51.2; one query head: the same order);
-// kMergeLinear: more rows than a grid has, divided.
+// Merge the split partials of one (sequence, query head): a wave, D / 64 elements a lane, walks over the splits with four records in
+// flight.  More than eight splits are shared by four waves, more than 32 by eight, whose states meet in LDS (attention and merge out of
+// a HIP graph, one wave / four / eight, us: 24 heads of D = 64 in 19 splits 8.7 / 7.3 / 7.6, 64 of D = 128 in 16 8.5 / 7.9 / 8.1, 32 in 32
+// 9.6 / 8.1 / 8.1, 32 of D = 64 in 36 12.7 / 10.2 / 9.9, four of D = 128 in 64 14.8 / 9.5 / 8.8, 80 in twelve 7.9 / 7.7 / 7.5; up to eight
+// no difference).  What a launch of it costs besides is the launch and one round trip to the records, which lie together for a row
+// ([row][split][head]: with the heads of all rows under each split 0.4 us more for 32 rows of D = 128 in eight splits, 1.1 us for 16 rows
+// in 16).  The grid: the query heads of a row side by side, one row a grid row; with kMergeXcd, wherever the attention kernel keeps a row
+// on one XCD, eight rows a grid row, so that a row's records are read on the XCD that wrote them (append, attention and merge out of a HIP
+// graph, side by side / so, one wave each: D = 128, four query heads a KV head, 8 rows x 4096 8.8 / 8.0 us, 16 x 5280 12.4 / 11.4, 32 x
+// 4096 14.6 / 13.95, 32 x 8192 24.3 / 23.9, 264 x 4096 94.2 / 93.8; D = 64 7.7 / 6.9, 9.3 / 8.4, 9.5 / 9.0, 13.9 / 13.6, 51.5 / 51.2; one
+// query head: the same order); kMergeLinear: more rows than a grid has, divided.
 enum { kMergeLinear, kMergeRows, kMergeXcd };
-template <typename T, int D, bool CLEAR>
-__global__ __launch_bounds__(kWave) void paged_decode_reduce_kernel(const float* __restrict__ partials, void* __restrict__ out,
-                                                                    int g_real, int splits, int order, void* next_out) {
+template <typename T, int D, bool CLEAR, int WAVES>
+__global__ __launch_bounds__(WAVES * kWave) void paged_decode_reduce_kernel(const float* __restrict__ partials, void* __restrict__ out,
+                                                                            int g_real, int splits, int order, void* next_out) {
   constexpr int E = D / kWave;
   const int x = (int)blockIdx.x, y = (int)blockIdx.y;
   const int row = order == kMergeLinear ? x / g_real : order == kMergeXcd ? y * 8 + (x & 7) : y;
   const int h = order == kMergeLinear ? x - row * g_real : order == kMergeXcd ? x >> 3 : x;
-  const int d = (int)threadIdx.x * E;
+  const int wave = WAVES == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const int d = (int)(threadIdx.x % kWave) * E;
   const float* base = partials + ((int64_t)row * splits * g_real + h) * (D + 2);
   const int64_t stride = (int64_t)g_real * (D + 2);
   // one pass, online: all loads are independent of the running state, so they overlap
@@ -453,7 +457,7 @@ __global__ __launch_bounds__(kWave) void paged_decode_reduce_kernel(const float*
 #pragma unroll
   for (int e = 0; e < E; ++e) o[e] = 0.f;
 #pragma unroll 4
-  for (int sp = 0; sp < splits; ++sp) {
+  for (int sp = wave; sp < splits; sp += WAVES) {
     const float* record = base + sp * stride;
     const float2 ml = *reinterpret_cast<const float2*>(record + D);
     float a[E];
@@ -471,6 +475,26 @@ __global__ __launch_bounds__(kWave) void paged_decode_reduce_kernel(const float*
 #pragma unroll
     for (int e = 0; e < E; ++e) o[e] = fmaf(o[e], w_old, a[e] * w_new);
     mm = m_new;
+  }
+  if constexpr (WAVES > 1) {
+    __shared__ float sm[WAVES][D + 2];
+    if (wave > 0) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) sm[wave][d + e] = o[e];
+      if (d == 0) sm[wave][D] = mm, sm[wave][D + 1] = l;
+    }
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) {
+      const float m_w = sm[w][D], m_new = fmaxf(mm, m_w);
+      const float ms = m_new == kNegInf ? 0.f : m_new;
+      const float w_old = __builtin_amdgcn_exp2f(mm - ms), w_new = __builtin_amdgcn_exp2f(m_w - ms);
+      l = fmaf(l, w_old, sm[w][D + 1] * w_new);
+#pragma unroll
+      for (int e = 0; e < E; ++e) o[e] = fmaf(o[e], w_old, sm[w][d + e] * w_new);
+      mm = m_new;
+    }
   }
   const int64_t off = ((int64_t)row * g_real + h) * D + d;
   // (the counts of the launch behind this one: one for every 128 elements of a row)
@@ -524,8 +548,13 @@ void launch_reduce(const DecodeArgs& a, hipStream_t stream) {
   const int64_t grid_rows = xcd ? rows / 8 : rows;
   const int order = grid_rows > 65535 ? kMergeLinear : xcd ? kMergeXcd : kMergeRows;
   const dim3 blocks = order == kMergeLinear ? dim3((unsigned)(rows * g)) : dim3((unsigned)(xcd ? 8 * g : g), (unsigned)grid_rows);
-  const auto kernel = a.next_out != nullptr ? paged_decode_reduce_kernel<T, D, true> : paged_decode_reduce_kernel<T, D, false>;
-  hipLaunchKernelGGL(kernel, blocks, dim3(kWave), 0, stream, a.partials, a.out, g, a.splits, order, a.next_out);
+  const bool clear = a.next_out != nullptr;
+  const int waves = a.splits > 32 ? 8 : a.splits > 8 ? 4 : 1;
+  const auto kernel = waves == 8   ? paged_decode_reduce_kernel<T, D, false, 8>
+                      : waves == 4 ? (clear ? paged_decode_reduce_kernel<T, D, true, 4> : paged_decode_reduce_kernel<T, D, false, 4>)
+                                   : (clear ? paged_decode_reduce_kernel<T, D, true, 1> : paged_decode_reduce_kernel<T, D, false, 1>);
+  static_assert(kMostArrivals <= 32, "counts are cleared for no more splits");
+  hipLaunchKernelGGL(kernel, blocks, dim3(waves * kWave), 0, stream, a.partials, a.out, g, a.splits, order, a.next_out);
 }
 
 }  // namespace
