@@ -177,9 +177,9 @@ __device__ __forceinline__ void accumulate_pv(float (&acc)[G][EPL], float prob, 
   }
 }
 
-// Four waves, two register buffers, two wave-loads of K and of V per tile (4 KiB per tile, 8 KiB per wave in flight
+// Four or eight waves, two register buffers, two wave-loads of K and of V per tile (4 KiB per tile, 8 KiB per wave in flight
 // while it waits): the stream runs fastest at about 8 MiB in flight over the chip.
-constexpr int kWaves = 4, kDepth = 2, kLoads = 2;
+constexpr int kDepth = 2, kLoads = 2;
 
 template <typename T, int D, int G>
 struct Tile {
@@ -263,13 +263,13 @@ struct Tile {
   }
 };
 
-template <typename T, int D, int G, bool FUSED, bool SHARED, bool ARRIVALS = false>
-__global__ __launch_bounds__(kWaves * kWave) void paged_decode_kernel(
+template <typename T, int D, int G, int WAVES, bool FUSED, bool SHARED, bool ARRIVALS = false>
+__global__ __launch_bounds__(WAVES * kWave) void paged_decode_kernel(
     const int32_t* seq_lens, const int32_t* block_table, const void* q, const void* k_pool_p, const void* v_pool_p,
     const int num_kv_heads, const int max_blocks, const uint32_t inv_heads, const uint32_t shape, const DecodeParams) {
   static_assert(!(FUSED && SHARED), "the fused append is per-head only");
   using TL = Tile<T, D, G>;
-  constexpr int WAVES = kWaves, DEPTH = kDepth;
+  constexpr int DEPTH = kDepth;
   constexpr int EPL = TL::EPL, LPR = TL::LPR, NLT = TL::NLT, TT = TL::TT, GP = TL::GP;
   constexpr int GBITS = ilog2(GP);
 
@@ -510,22 +510,26 @@ __global__ __launch_bounds__(WAVES * kWave) void paged_decode_reduce_kernel(cons
   }
 }
 
-template <typename T, int D, int G>
-hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
+template <typename T, int D, int G, int WAVES>
+hipError_t launch_waves(const DecodeArgs& a, hipStream_t stream) {
   DecodeKernelArgs k;
   dim3 blocks;
   if (!decode_kernel_args(a, &k, &blocks)) return hipErrorInvalidValue;
-  const dim3 threads(kWaves * kWave);
+  const dim3 threads(WAVES * kWave);
   if (a.shared && a.new_k != nullptr) return hipErrorInvalidValue;
   if (a.counted) {
-    if constexpr (one_part_a_wave<next_pow2(G), D, kWaves>)
-      return launch_decode(paged_decode_kernel<T, D, G, true, false, true>, blocks, threads, stream, k);
+    if constexpr (one_part_a_wave<next_pow2(G), D, WAVES>)
+      return launch_decode(paged_decode_kernel<T, D, G, WAVES, true, false, true>, blocks, threads, stream, k);
     return hipErrorInvalidValue;
   }
-  const auto kernel = a.shared             ? paged_decode_kernel<T, D, G, false, true>
-                      : a.new_k != nullptr ? paged_decode_kernel<T, D, G, true, false>
-                                           : paged_decode_kernel<T, D, G, false, false>;
+  const auto kernel = a.shared             ? paged_decode_kernel<T, D, G, WAVES, false, true>
+                      : a.new_k != nullptr ? paged_decode_kernel<T, D, G, WAVES, true, false>
+                                           : paged_decode_kernel<T, D, G, WAVES, false, false>;
   return launch_decode(kernel, blocks, threads, stream, k);
+}
+template <typename T, int D, int G>
+hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
+  return a.waves == 8 ? launch_waves<T, D, G, 8>(a, stream) : launch_waves<T, D, G, 4>(a, stream);
 }
 
 template <int D>

@@ -211,6 +211,16 @@ pe::DecodeArgs decode_args(const pe_cache_desc* desc, int splits) {
   const bool few = (int64_t)desc->num_seqs * desc->num_kv_heads <= cus;
   a.vector = a.is_bf16 && !shared && desc->num_q_heads == desc->num_kv_heads &&
              tokens <= (few ? (d128 ? 192 : 1024) : (d128 ? 64 : 128));
+  // On the vector units: eight waves where no compute unit gets two workgroups, but for four query heads a KV head or fewer in pieces of 1
+  // MiB and more, which stream as well with four.  Four waves / eight, us: fp32, D = 128, four rows x 256 tokens, one query head a KV head
+  // 6.0 / 4.5, eight 13.4 / 9.8; 52 rows x 256 9.3 / 7.4 with four; D = 64, two query heads, four rows 4.3 / 3.7; 64 rows x 1024 in four
+  // splits, four heads 13.1 / 12.5 (D = 64 8.7 / 8.0), 32 x 4096 in eight 22.6 / 22.4, with eight heads 26.9 / 24.1; 256 whole rows x 300 13.0
+  // / 12.4; x 2048 77.4 / 78.8, with eight heads 86.4 / 80.7; 384 rows x 1024 62.6 / 64.9, with eight heads 63.7 / 68.3; 128 rows x 1024 of D =
+  // 64 in four, eight heads, 13.5 / 14.0.  bfloat16: 64 rows x 190 of D = 64 3.5 / 3.3, 384 x 60 3.4 / 3.7.
+  if (!a.is_bf16 || a.vector) {
+    const bool wide = desc->num_q_heads / desc->num_kv_heads > 4;
+    a.waves = groups <= cus && (wide || row_bytes(desc) / splits < (1 << 20)) ? 8 : 4;
+  }
   return a;
 }
 
@@ -518,8 +528,8 @@ namespace {
 // Whether the splits of a row are counted where the caller can provide for it (pe_decode_common.h says when that pays).
 bool splits_counted(const pe_cache_desc* d, const pe::DecodeArgs& a) {
   const int64_t groups = (int64_t)d->num_seqs * d->num_kv_heads * a.splits;
-  const bool built = a.waves == 4 && a.depth <= 2 && !(a.shared && !a.is_bf16);
-  return built && a.splits > 1 && a.splits <= pe::kMostArrivals && d->num_q_heads / d->num_kv_heads * d->head_dim <= 512 &&
+  const bool built = !a.is_bf16 || a.vector ? !a.shared : a.waves == 4 && a.depth <= 2;
+  return built && a.splits > 1 && a.splits <= pe::kMostArrivals && d->num_q_heads / d->num_kv_heads * d->head_dim <= 128 * a.waves &&
          groups <= 2 * (int64_t)compute_units();
 }
 
