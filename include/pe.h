@@ -319,8 +319,8 @@ int pe_append_paged_decode(const pe_cache_desc* desc, const void* new_k, const v
  * [layers*S][Hk][max_blocks]; seq_lens, seq_lens_out [layers*S]; freed_phys, spare_used [layers*S][Hk]; spare
  * [layers*S][Hk][n_spare] (shared layout: the shapes that layout gives, stacked the same way).  The one workspace
  * (pe_workspace_bytes(PE_OP_APPEND_PAGED_DECODE, desc, 0)) serves every layer.  `out` is the library's until the call's
- * launches are through: where rows are split, a layer's output may hold counts of the splits before its own launch.  (Not where
- * `out` overlaps q, new_k or new_v, or is not 4-byte aligned: launches of their own then merge the splits, as in the call above.)
+ * launches are through, here and in the calls for one layer: where rows are split, it may hold counts and tags of the splits before the
+ * results.  (Not where it overlaps q, new_k or new_v, or is not 8-byte aligned: launches of their own then merge the splits.)
  * Returns the first non-OK status; layers before it have been enqueued.
  */
 int pe_append_paged_decode_layers(const pe_cache_desc* desc, int32_t num_layers, const void* new_k, const void* new_v,

@@ -263,7 +263,7 @@ struct Tile {
   }
 };
 
-template <typename T, int D, int G, int WAVES, bool FUSED, bool SHARED, bool ARRIVALS = false>
+template <typename T, int D, int G, int WAVES, bool FUSED, bool SHARED, int ARRIVALS = kMergeLaunch>
 __global__ __launch_bounds__(WAVES * kWave) void paged_decode_kernel(
     const int32_t* seq_lens, const int32_t* block_table, const void* q, const void* k_pool_p, const void* v_pool_p,
     const int num_kv_heads, const int max_blocks, const uint32_t inv_heads, const uint32_t shape, const DecodeParams) {
@@ -397,8 +397,8 @@ __global__ __launch_bounds__(WAVES * kWave) void paged_decode_kernel(
     }
   }
   __syncthreads();
-  if constexpr (ARRIVALS)
-    merge_arrived<T>(sm, p, row, split, splits, g_real);
+  if constexpr (ARRIVALS != kMergeLaunch)
+    merge_arrived<T, ARRIVALS == kTagged>(sm, p, row, split, splits, g_real);
   else
     merge_waves<T>(sm, p, row, split, splits, g_real);
 
@@ -517,9 +517,11 @@ hipError_t launch_waves(const DecodeArgs& a, hipStream_t stream) {
   if (!decode_kernel_args(a, &k, &blocks)) return hipErrorInvalidValue;
   const dim3 threads(WAVES * kWave);
   if (a.shared && a.new_k != nullptr) return hipErrorInvalidValue;
-  if (a.counted) {
+  if (a.counted || a.tagged) {
     if constexpr (one_part_a_wave<next_pow2(G), D, WAVES>)
-      return launch_decode(paged_decode_kernel<T, D, G, WAVES, true, false, true>, blocks, threads, stream, k);
+      return launch_decode(a.counted             ? paged_decode_kernel<T, D, G, WAVES, true, false, kCounted>
+                           : a.new_k != nullptr ? paged_decode_kernel<T, D, G, WAVES, true, false, kTagged>
+                                                : paged_decode_kernel<T, D, G, WAVES, false, false, kTagged>, blocks, threads, stream, k);
     return hipErrorInvalidValue;
   }
   const auto kernel = a.shared             ? paged_decode_kernel<T, D, G, WAVES, false, true>
@@ -578,7 +580,7 @@ hipError_t launch_paged_decode(const DecodeArgs& a, hipStream_t stream) {
     e = d64 ? launch_one<bf16_t, 64, 1>(a, stream) : launch_one<bf16_t, 128, 1>(a, stream);
   else
     e = launch_paged_decode_bf16(a, stream);
-  if (e != hipSuccess || a.splits == 1 || a.counted) return e;
+  if (e != hipSuccess || a.splits == 1 || a.counted || a.tagged) return e;
   if (a.is_bf16)
     d64 ? launch_reduce<bf16_t, 64>(a, stream) : launch_reduce<bf16_t, 128>(a, stream);
   else

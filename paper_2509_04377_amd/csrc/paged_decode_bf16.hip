@@ -203,7 +203,7 @@ __device__ __forceinline__ int lookup(const int32_t* bt, int tile, int max_block
   return __builtin_amdgcn_readfirstlane(bt[pi]);
 }
 
-template <int D, int HG, int WAVES, int DEPTH, bool FUSED, bool SHARED, bool ARRIVALS = false>
+template <int D, int HG, int WAVES, int DEPTH, bool FUSED, bool SHARED, int ARRIVALS = kMergeLaunch>
 // (the 2 asks for two waves per SIMD at least, i.e. at most 256 registers: the compiler then keeps the accumulators in
 // vector registers instead of moving them to and from accumulation registers in every step.  The 3, at most 168: head-shared,
 // appending, with D = 64 and more than four query heads it would take 170, and 176 rows x 2000 23.9 us instead of 21.6 (192 ragged
@@ -421,8 +421,8 @@ void paged_decode_bf16_kernel(
     }
   }
   __syncthreads();
-  if constexpr (ARRIVALS)
-    merge_arrived<bf16_t>(sm, p, row, split, splits, g_real);
+  if constexpr (ARRIVALS != kMergeLaunch)
+    merge_arrived<bf16_t, ARRIVALS == kTagged>(sm, p, row, split, splits, g_real);
   else
     merge_waves<bf16_t>(sm, p, row, split, splits, g_real);
 
@@ -482,10 +482,15 @@ hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
   if (!decode_kernel_args(a, &k, &blocks)) return hipErrorInvalidValue;
   const dim3 threads(WAVES * kWave);
   const bool fused = a.new_k != nullptr;
-  if (a.counted) {
+  if (a.counted || a.tagged) {
     if constexpr (kShared && one_part_a_wave<4 * HG, D, WAVES>)
-      return launch_decode(a.shared ? paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, true, true, true>
-                                    : paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, true, false, true>, blocks, threads, stream, k);
+      return launch_decode(a.counted ? (a.shared ? paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, true, true, kCounted>
+                                                 : paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, true, false, kCounted>)
+                           : a.shared ? (fused ? paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, true, true, kTagged>
+                                               : paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, false, true, kTagged>)
+                                      : (fused ? paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, true, false, kTagged>
+                                               : paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, false, false, kTagged>),
+                           blocks, threads, stream, k);
     return hipErrorInvalidValue;
   }
   const auto kernel = a.shared ? (fused ? paged_decode_bf16_kernel<D, HG, WAVES, DEPTH, true, kShared>

@@ -3,6 +3,7 @@
 #include "../../include/pe.h"
 
 #include <atomic>
+#include <chrono>
 #include <mutex>
 
 #include "pe_launch.h"
@@ -222,6 +223,41 @@ pe::DecodeArgs decode_args(const pe_cache_desc* desc, int splits) {
     a.waves = groups <= cus && (wide || row_bytes(desc) / splits < (1 << 20)) ? 8 : 4;
   }
   return a;
+}
+
+// Whether the splits of a row are merged by the last of them to arrive, counted or tagged (pe_decode_common.h says where that pays).
+bool splits_counted(const pe_cache_desc* d, const pe::DecodeArgs& a) {
+  const int64_t groups = (int64_t)d->num_seqs * d->num_kv_heads * a.splits;
+  const int heads = d->num_q_heads / d->num_kv_heads;
+  const bool built = !a.is_bf16 || a.vector ? !a.shared : a.waves == 4 && a.depth <= 2;
+  return built && a.splits > 1 && a.splits <= (heads > 4 ? 8 : pe::kMostArrivals) && heads * d->head_dim <= 128 * a.waves &&
+         groups <= 2 * (int64_t)compute_units();
+}
+bool splits_tagged(const pe_cache_desc* d, const pe::DecodeArgs& a) {
+  return splits_counted(d, a) && (a.splits < 8 || (a.splits == 8 && row_bytes(d) / 8 < (256 << 10)));
+}
+
+bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + b_bytes && y < x + a_bytes;
+}
+
+// A launch's own tag: no two of a process are the same (the mixing is one to one), and what lies in memory is none by chance.
+uint64_t launch_tag() {
+  static std::atomic<uint64_t> calls{(uint64_t)std::chrono::system_clock::now().time_since_epoch().count()};
+  uint64_t x = calls.fetch_add(1, std::memory_order_relaxed) * 0x9e3779b97f4a7c15ull;
+  x = (x ^ x >> 30) * 0xbf58476d1ce4e5b9ull;
+  x = (x ^ x >> 27) * 0x94d049bb133111ebull;
+  return x ^ x >> 31;
+}
+
+// For a call of the attention alone: tags its launch where that pays and the output can hold tags before it is written, that is, nothing
+// that is read lies there.
+void tag_attention(const pe_cache_desc* d, pe::DecodeArgs* a) {
+  const size_t bytes = (size_t)d->num_seqs * d->num_q_heads * d->head_dim * (a->is_bf16 ? 2 : 4);
+  if (!splits_tagged(d, *a) || !aligned(a->out, 8) || overlap(a->out, bytes, a->q, bytes)) return;
+  a->tagged = true;
+  a->tag = launch_tag();
 }
 
 }  // namespace
@@ -470,6 +506,7 @@ int pe_paged_decode(const pe_cache_desc* desc, const void* q, const void* k_pool
   a.out = out;
   a.partials = static_cast<float*>(workspace);
   a.scale = softmax_scale;
+  tag_attention(desc, &a);
   return pe::launch_paged_decode(a, static_cast<hipStream_t>(stream)) == hipSuccess ? PE_OK : PE_ERR_HIP;
 }
 
@@ -521,29 +558,25 @@ int pe_paged_decode_static(const pe_cache_desc* desc, const void* q, const void*
   // splits write (acc, m, l) = (0, -inf, 0)), so what an earlier call left in the array never shows
   a.partials = static_cast<float*>(partials);
   a.scale = softmax_scale;
+  tag_attention(desc, &a);
   return pe::launch_paged_decode(a, static_cast<hipStream_t>(stream)) == hipSuccess ? PE_OK : PE_ERR_HIP;
 }
 
 namespace {
-// Whether the splits of a row are counted where the caller can provide for it (pe_decode_common.h says when that pays).
-bool splits_counted(const pe_cache_desc* d, const pe::DecodeArgs& a) {
-  const int64_t groups = (int64_t)d->num_seqs * d->num_kv_heads * a.splits;
-  const bool built = !a.is_bf16 || a.vector ? !a.shared : a.waves == 4 && a.depth <= 2;
-  return built && a.splits > 1 && a.splits <= pe::kMostArrivals && d->num_q_heads / d->num_kv_heads * d->head_dim <= 128 * a.waves &&
-         groups <= 2 * (int64_t)compute_units();
+// The output holds tags and counts before it is written: not if something that is read still lies there, or at an odd address.
+bool out_is_free(const pe_cache_desc* d, int32_t layers, const void* out, const void* q, const void* new_k, const void* new_v) {
+  if (d == nullptr) return false;
+  const size_t head = (size_t)layers * d->num_seqs * d->head_dim * (d->dtype == PE_F32 ? 4 : 2);
+  const size_t o = head * d->num_q_heads, kv = head * d->num_kv_heads;
+  return aligned(out, 8) && !overlap(out, o, q, o) && !overlap(out, o, new_k, kv) && !overlap(out, o, new_v, kv);
 }
 
-bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
-  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
-  return x < y + b_bytes && y < x + a_bytes;
-}
-
-// `counted`: the arrival counts in `out` are clear (by the call for the layer before); next_out: where this call is to clear them for
-// the layer behind it, or null.
+// `free_out`: nothing that is read lies in `out`, and tags and counts can; `counted`: the counts there are clear (by the call for the
+// layer before); next_out: where this call is to clear them for the layer behind it, or null.
 int append_paged_decode(const pe_cache_desc* desc, const void* new_k, const void* new_v, const void* q, void* k_pool, void* v_pool,
                         int32_t* block_table, const int32_t* seq_lens, int32_t* seq_lens_out, int32_t* freed_phys,
                         const int32_t* spare, int32_t* spare_used, int32_t n_spare, float softmax_scale, void* out, void* workspace,
-                        size_t workspace_bytes, void* stream, bool counted, void* next_out) {
+                        size_t workspace_bytes, void* stream, bool free_out, bool counted, void* next_out) {
   const int st = check_desc(desc);
   if (st != PE_OK) return st;
   if (!new_k || !new_v || !q || !k_pool || !v_pool || !block_table || !seq_lens || !seq_lens_out || !freed_phys ||
@@ -575,9 +608,11 @@ int append_paged_decode(const pe_cache_desc* desc, const void* new_k, const void
   a.spare_used = spare_used;
   a.seq_lens_out = seq_lens_out;
   a.n_spare = n_spare;
-  if (splits_counted(desc, a)) {
+  if (free_out && splits_counted(desc, a)) {
     a.counted = counted;
     a.next_out = next_out;
+    a.tagged = !counted && splits_tagged(desc, a);
+    if (a.tagged) a.tag = launch_tag();
   }
   if (desc->layout == PE_LAYOUT_SHARED && desc->dtype == PE_F32) {
     // One table row per sequence: the workgroups of a sequence's heads would race on its page bookkeeping inside one
@@ -618,7 +653,8 @@ int pe_append_paged_decode(const pe_cache_desc* desc, const void* new_k, const v
                            int32_t n_spare, float softmax_scale, void* out, void* workspace, size_t workspace_bytes,
                            void* stream) {
   return append_paged_decode(desc, new_k, new_v, q, k_pool, v_pool, block_table, seq_lens, seq_lens_out, freed_phys, spare, spare_used,
-                             n_spare, softmax_scale, out, workspace, workspace_bytes, stream, false, nullptr);
+                             n_spare, softmax_scale, out, workspace, workspace_bytes, stream, out_is_free(desc, 1, out, q, new_k, new_v),
+                             false, nullptr);
 }
 
 int pe_append_paged_decode_layers(const pe_cache_desc* desc, int32_t num_layers, const void* new_k, const void* new_v,
@@ -637,17 +673,14 @@ int pe_append_paged_decode_layers(const pe_cache_desc* desc, int32_t num_layers,
   const int64_t rows = shared ? S : S * desc->num_kv_heads;  // table rows, spare lists, freed pages per layer
   const size_t kv_bytes = (size_t)S * desc->num_kv_heads * desc->head_dim * elem;
   const size_t q_bytes = (size_t)S * desc->num_q_heads * desc->head_dim * elem;
-  // The output of a layer holds counts before its launch: not if something that is read still lies there, or at an odd address.
-  const bool free_out = aligned(out, 4) && !overlap(out, num_layers * q_bytes, q, num_layers * q_bytes) &&
-                        !overlap(out, num_layers * q_bytes, new_k, num_layers * kv_bytes) &&
-                        !overlap(out, num_layers * q_bytes, new_v, num_layers * kv_bytes);
+  const bool free_out = out_is_free(desc, num_layers, out, q, new_k, new_v);
   for (int32_t l = 0; l < num_layers; ++l) {
     const int rc = append_paged_decode(
         desc, static_cast<const char*>(new_k) + l * kv_bytes, static_cast<const char*>(new_v) + l * kv_bytes,
         static_cast<const char*>(q) + l * q_bytes, k_pool, v_pool, block_table + l * rows * desc->max_blocks,
         seq_lens + l * S, seq_lens_out + l * S, freed_phys + l * rows, spare + l * rows * n_spare, spare_used + l * rows,
         n_spare, softmax_scale, static_cast<char*>(out) + l * q_bytes, workspace, workspace_bytes, stream,
-        free_out && l > 0, free_out && l + 1 < num_layers ? static_cast<char*>(out) + (l + 1) * q_bytes : nullptr);
+        free_out, free_out && l > 0, free_out && l + 1 < num_layers ? static_cast<char*>(out) + (l + 1) * q_bytes : nullptr);
     if (rc != PE_OK) return rc;
   }
   return PE_OK;

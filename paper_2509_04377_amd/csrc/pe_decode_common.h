@@ -33,6 +33,7 @@ struct DecodeParams {
   int32_t* spare_used;
   int32_t* seq_lens_out;  // [S], must not alias seq_lens
   void* next_out;         // output of the launch behind this one, whose arrival counts are to be cleared, or null (merge_arrived)
+  uint64_t tag;           // of this launch (merge_arrived)
 };
 
 // All of them as they lie in the kernel-argument segment (in order, each at its own alignment).
@@ -82,7 +83,7 @@ inline bool decode_kernel_args(const DecodeArgs& a, DecodeKernelArgs* k, dim3* b
                         (uint32_t)log2_block | (uint32_t)(a.num_q_heads / a.num_kv_heads) << 3 | (g.xcd ? kShapeXcd : 0u) |
                             (g.linear ? kShapeLinear : 0u) | (uint32_t)a.splits << 9,
                         DecodeParams{a.out, a.partials, a.scale * 1.4426950408889634f, a.n_spare, a.new_k, a.new_v, a.freed_phys,
-                                     a.spare, a.spare_used, a.seq_lens_out, a.next_out}};
+                                     a.spare, a.spare_used, a.seq_lens_out, a.next_out, a.tag}};
   return true;
 }
 
@@ -99,7 +100,7 @@ __device__ __forceinline__ DecodeParams decode_params(int behind) {
   asm("" : "+s"(args) : "s"(behind));
   const auto* a = reinterpret_cast<const __attribute__((address_space(4))) DecodeParams*>(args);
   return DecodeParams{a->out,   a->partials,   a->scale_log2e, a->n_spare,    a->new_k,
-                      a->new_v, a->freed_phys, a->spare,       a->spare_used, a->seq_lens_out, a->next_out};
+                      a->new_v, a->freed_phys, a->spare,       a->spare_used, a->seq_lens_out, a->next_out, a->tag};
 }
 
 // Two neighbouring elements of the output in one store, at any boundary of their own size.
@@ -156,25 +157,37 @@ __device__ __forceinline__ float2 merge_splits(int splits, Read read) {
   return l > 0.f ? make_float2(o0 / l, o1 / l) : make_float2(0.f, 0.f);
 }
 
+// How the splits of a row come together: by a launch of its own, or by the last of them to arrive.
+enum { kMergeLaunch, kCounted, kTagged };
+
 // ---- splits merged by the last of them to arrive ---------------------------------------------------------------
-// A launch whose rows' splits are counted needs no merge launch behind it.  Every wave of a workgroup stores its part of the split's
-// record, waits until that is where all compute dies see it, and counts its arrival; the one that finds all others there before it
-// reads the records back and writes the output, in the order of the splits, whoever it is.  Records are stored and loaded as relaxed
-// atomics at agent scope (write-through, past the first-level cache), so that nothing rests on which compute die a workgroup is on.
+// No merge launch behind it then.  Every wave of a workgroup stores its part of the split's record, waits until that is where all compute
+// dies see it, and makes its arrival known; one that finds all others there reads the records back and writes the output, in the order
+// of the splits, whoever it is.  Records are stored and loaded as relaxed atomics at agent scope (write-through, past the first-level
+// cache), so that nothing rests on which compute die a workgroup is on.
 //
-// The counts have to be zero when the launch begins.  There is nowhere to keep them from one call to the next (a workspace may hold
-// anything), so they live in the output itself: the first word of what a wave will write there is its count until it does.  Only a
-// call that knows the next launch's output can use this, the one for all layers of a step: a layer's launch (of the first layer, the
-// merge launch behind it) clears the words of the next layer's output.
+// There is nowhere to keep arrivals from one call to the next (a workspace may hold anything), so they are made known in the output
+// itself, at the beginning of what a wave will write there:
+//   - kCounted: its first word is a count.  It has to be zero when the launch begins: only the call that knows the next launch's output
+//     can provide for that, the one for all layers of a step, whose launch for a layer clears the words of the next layer's output.
+//   - kTagged: its first words are a tag for each split, a number that no other launch of the process has.  A wave stores its own, waits
+//     until everyone sees that too, and then looks at all of them: the last to arrive finds every one, and where others do as well
+//     they write the same.  What lay in the output before is no tag of this launch; a graph that is replayed has the same tag each
+//     time, but the output, by then written, lies over it.  (Of a launch from another process with the same tag nothing is in memory.)
 //
-// Bound: a chain of three round trips, cycles (2.4 GHz) from a clock in the kernel: records stored 530, counted 960, read back 720,
-// merged 570; a merge launch costs 1.9 us.  16 layers of 64 rows x 1024 tokens of D = 64 in four splits 2056 / 1812 us for 16 steps,
-// 32 layers of 32 rows x 4096 of D = 128 in eight 8295 / 8090 us.  Where it pays (merge launch / this, us a layer, D = 128 unless said):
-//   - up to some dozen splits, merged four at a time one after the other: 20 rows x 2048 in twelve 10.1 / 9.5 (fp32 13.4 / 12.6), 16
-//     rows x 2048 in sixteen 9.1 / 9.3 (8.9 / 9.1 with eight query heads of D = 64);
-//   - one part of a row a wave: with two (more than four query heads) 32 rows x 2048 in eight 11.9 / 12.7;
-//   - workgroups that are all there from the beginning, two a compute unit: 128 rows x 2048 of fp32 in four 48.8 / 48.3; of 640 and
-//     more, those that wait for memory at their ends keep others out (160 rows x 4096 in four 62.3 / 65.5, 264 x 2048 52.9 / 54.4).
+// Bound: a chain of round trips, cycles (2.4 GHz) from a clock in the kernel: records stored 530, counted 960 (tags: one more round trip,
+// some 500), read back 720, merged 570; a merge launch costs 1.9 us.  16 layers of 64 rows x 1024 tokens of D = 64 in four splits 2056 /
+// 1812 us for 16 steps, 32 layers of 32 rows x 4096 of D = 128 in eight 8295 / 8090; one layer of 64 rows x 2048 of D = 64 in four,
+// called by itself, 16 steps 191 / 152 (out of a graph 9.9 / 9.4 us a call: the launch costs the host more than the GPU).
+// Where it pays (merge launch / tagged / counted, us a layer out of a graph, D = 128 unless said):
+//   - up to eight or twelve splits, merged four at a time one after the other: 16 rows x 2048 in two 14.5 / 13.9 / 13.7, four 10.7 / 10.2
+//     / 9.9, six 10.1 / 9.9 / 9.6, seven 10.3 / 9.9 / 9.7, eight 8.7 / 8.6 / 8.3 (D = 64 7.2 / 7.2 / 6.7), ten 8.9 / 9.3 / 8.9, twelve 8.5 /
+//     9.0 / 8.5, fifteen 8.8 / 9.7 / 9.2; 20 rows x 2048 in twelve 9.7 / 9.8 / 9.2; with eight query heads of D = 64, 32 rows x 2048 in eight
+//     9.3 / 9.2 / 8.7, 8 x 4096 in ten 10.8 / 11.1 / 10.9.  Eight are tagged in pieces of less than 256 KiB, as no slower, for the
+//     host's sake: larger ones, which it does not wait for, take 14.5 / 14.7 (fp32 15.4 / 15.6);
+//   - one part of a row a wave: with two (more than four query heads) 32 rows x 2048 in eight 11.9 / 12.7 counted;
+//   - workgroups that are all there from the beginning, two a compute unit: 128 rows x 2048 of fp32 in four 43.9 / 43.8 tagged; of 640 and
+//     more, those that wait for memory at their ends keep others out (160 rows x 4096 in four 62.3 / 65.5, 264 x 2048 52.9 / 54.4 counted).
 template <int GH, int D, int WAVES>
 constexpr bool one_part_a_wave = GH * (D / 2) <= WAVES * kWave;
 
@@ -247,11 +260,12 @@ __device__ __forceinline__ void merge_waves(const WaveStates<WAVES, GH, D>& sm, 
   }
 }
 
-// The same where the splits are counted (every wave has one part of the row: 64 pairs of elements).
-template <typename T, int WAVES, int GH, int D>
+// The same where the splits are counted or tagged (every wave has one part of the row: 64 pairs of elements).
+template <typename T, bool TAGGED, int WAVES, int GH, int D>
 __device__ __forceinline__ void merge_arrived(const WaveStates<WAVES, GH, D>& sm, const DecodeParams& p, int row, int split, int splits,
                                               int g_real) {
   static_assert(one_part_a_wave<GH, D, WAVES>, "one part of a row a wave");
+  static_assert(kMostArrivals <= kWave / 2 && kMostArrivals * 8 <= kWave * (int)sizeof(T), "a tag a lane, in the output of half a wave");
   const int pairs = g_real * (D / 2), idx = (int)threadIdx.x, lane = lane_id();
   if (idx >= pairs) return;
   const int h = idx / (D / 2), d = idx % (D / 2) * 2;
@@ -264,9 +278,20 @@ __device__ __forceinline__ void merge_arrived(const WaveStates<WAVES, GH, D>& sm
   const int64_t pair0 = (int64_t)row * pairs;
   const uint32_t ml_at = (uint32_t)(h * (D + 2) + D), o_at = (uint32_t)(h * (D + 2) + d);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the records are where everyone sees them
-  uint32_t before = 0;
-  if (lane == 0) before = __hip_atomic_fetch_add(arrival_count<T>(p.out, pair0 + idx), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (__builtin_amdgcn_readfirstlane((int)before) == splits - 1) {
+  bool last;
+  if constexpr (TAGGED) {
+    uint64_t* const tags = reinterpret_cast<uint64_t*>(arrival_count<T>(p.out, pair0 + (idx - lane)));
+    if (lane == 0) __hip_atomic_store(tags + split, p.tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // and so is the tag, before the others' are looked at
+    uint64_t seen = p.tag;
+    if (lane < splits) seen = __hip_atomic_load(tags + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last = __builtin_amdgcn_ballot_w64(seen != p.tag) == 0;
+  } else {
+    uint32_t before = 0;
+    if (lane == 0) before = __hip_atomic_fetch_add(arrival_count<T>(p.out, pair0 + idx), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last = __builtin_amdgcn_readfirstlane((int)before) == splits - 1;
+  }
+  if (last) {
     asm volatile("" ::: "memory");  // (the loads below do not move up)
     const float2 o = merge_splits(splits, [&](int s, float2& ml, float2& v) {
       const float* of = base + s * record;

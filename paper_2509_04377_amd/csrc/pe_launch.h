@@ -90,13 +90,16 @@ struct DecodeArgs {
   int32_t* seq_lens_out = nullptr;
   int n_spare = 0;
   bool shared = false;  // one table row per sequence, pages [B][Hk][D]; with fp32 plain attention only
-  bool counted = false;      // the arrival counts in `out` are clear: the last split of a row to arrive merges it, no merge launch
+  // Splits merged by the last of a row to arrive, without a merge launch:
+  bool counted = false;      // the arrival counts in `out` are clear
+  bool tagged = false;       // `out` may hold anything but `tag`, which is this launch's own
+  uint64_t tag = 0;
   void* next_out = nullptr;  // output of the launch behind this one, whose counts this one is to clear
 };
 hipError_t launch_paged_decode(const DecodeArgs& a, hipStream_t stream);
 hipError_t launch_paged_decode_bf16(const DecodeArgs& a, hipStream_t stream);  // the attention kernel alone (no merge)
 size_t decode_partials_bytes(int num_seqs, int num_q_heads, int head_dim, int splits);
-constexpr int kMostArrivals = 15;  // splits of a row that are counted
+constexpr int kMostArrivals = 12;  // splits of a row that are counted or tagged
 
 struct PruneArgs {
   const void* k_in;
