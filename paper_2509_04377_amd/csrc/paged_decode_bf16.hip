@@ -472,10 +472,10 @@ void paged_decode_bf16_kernel(
   }
 }
 
-// (the forms that the head-shared layout never takes are not built for it)
+// (the forms that the head-shared layout never takes, and that are never counted or tagged, are not built for it)
 template <int D, int HG, int WAVES, int DEPTH>
 hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
-  constexpr bool kShared = WAVES == 4 && DEPTH <= 2;
+  constexpr bool kShared = DEPTH == 1 || (WAVES == 4 && DEPTH == 2);
   if (a.shared && !kShared) return hipErrorInvalidValue;
   DecodeKernelArgs k;
   dim3 blocks;
@@ -508,6 +508,7 @@ template <int D>
 hipError_t launch_shape(const DecodeArgs& a, hipStream_t stream) {
   const bool wide = a.num_q_heads / a.num_kv_heads > 4;
   if constexpr (D == 128) {
+    if (a.waves == 8 && a.depth == 1) return wide ? launch_one<D, 2, 8, 1>(a, stream) : hipErrorInvalidValue;
     if (a.waves == 8) return wide ? launch_one<D, 2, 8, 2>(a, stream) : launch_one<D, 1, 8, 2>(a, stream);
     if (a.depth == 3) return wide ? hipErrorInvalidValue : launch_one<D, 1, 4, 3>(a, stream);
   }

@@ -188,15 +188,24 @@ pe::DecodeArgs decode_args(const pe_cache_desc* desc, int splits) {
   //   - eight x two for whole rows of 1 MiB or more of D = 128, one for every compute unit (append and attention of 256 rows x 2048
   //     out of a pool of 8.6 GB 43.9, four x two and four x one 44.2; no faster with fewer rows); in the head-shared layout,
   //     whose wave-loads are runs of 256 bytes, four x one there too (45.6; with two tiles 47.2, with eight waves 47.1);
+  //   - eight x one for more than four query heads a KV head where rows of D = 128 are split for three quarters of the compute units or
+  //     more, in pieces of 192 tokens or more: each wave then has one part of the row at the end, so that the splits can be counted
+  //     (append and attention of all layers, four x one and a merge launch / so, full | ragged | 64 tokens a row: six query heads, 80 rows x
+  //     800 in three 12.1 / 10.5 | 10.6 / 9.0 | 7.1 / 6.3, eight, 64 x 1024 in four 11.5 / 10.5, 64 x 4096 in four 26.4 / 25.8 | 19.9 / 19.8 |
+  //     7.2 / 6.6; fewer workgroups, 16 x 2048 in eight, four x two 9.1, so 9.5).  With up to four, whose splits are counted with four
+  //     waves, it is the same within 2 %;
   //   - four x two else (136 whole rows x 2048 26.8, four x one 28.2; D = 64, 128 rows in 256 splits of 8192 82.7 and 98.2).
   const int64_t groups = (int64_t)desc->num_seqs * desc->num_kv_heads * splits;
   const int64_t cus = compute_units();
   const bool shared = desc->layout == PE_LAYOUT_SHARED;
   const bool d128 = desc->head_dim == 128;
   const bool large = d128 && splits == 1 && groups == cus && row_bytes(desc) >= (1 << 20);
+  const int64_t piece = (int64_t)desc->max_blocks * desc->block_size / splits;
+  const bool most = d128 && splits > 1 && groups * 4 >= cus * 3;
   const bool one_tile = (int64_t)desc->max_blocks * desc->block_size <= (int64_t)64 * splits;
-  a.waves = large && !shared ? 8 : 4;
-  a.depth = groups > cus || one_tile || (d128 && splits > 1 && groups * 4 >= cus * 3) || (large && shared) ? 1 : 2;
+  const bool eight = most && groups <= cus && desc->num_q_heads / desc->num_kv_heads > 4 && piece >= 192;
+  a.waves = eight || (large && !shared) ? 8 : 4;
+  a.depth = groups > cus || one_tile || most || (large && shared) ? 1 : 2;
   if (desc->decode_shape == 424) a.waves = 4, a.depth = 2;
   if (desc->decode_shape == 432) a.waves = 4, a.depth = 3;
   if (desc->decode_shape == 822) a.waves = 8, a.depth = 2;
@@ -229,12 +238,12 @@ pe::DecodeArgs decode_args(const pe_cache_desc* desc, int splits) {
 bool splits_counted(const pe_cache_desc* d, const pe::DecodeArgs& a) {
   const int64_t groups = (int64_t)d->num_seqs * d->num_kv_heads * a.splits;
   const int heads = d->num_q_heads / d->num_kv_heads;
-  const bool built = !a.is_bf16 || a.vector ? !a.shared : a.waves == 4 && a.depth <= 2;
+  const bool built = !a.is_bf16 || a.vector ? !a.shared : a.depth == 1 || (a.waves == 4 && a.depth == 2);
   return built && a.splits > 1 && a.splits <= (heads > 4 ? 8 : pe::kMostArrivals) && heads * d->head_dim <= 128 * a.waves &&
-         groups <= 2 * (int64_t)compute_units();
+         groups <= (a.splits > 8 ? 1 : 2) * (int64_t)compute_units();
 }
 bool splits_tagged(const pe_cache_desc* d, const pe::DecodeArgs& a) {
-  return splits_counted(d, a) && (a.splits < 8 || (a.splits == 8 && row_bytes(d) / 8 < (256 << 10)));
+  return splits_counted(d, a) && (a.splits < 8 || (a.splits == 8 && a.waves == 4 && row_bytes(d) / 8 < (256 << 10)));
 }
 
 bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {

@@ -183,10 +183,11 @@ enum { kMergeLaunch, kCounted, kTagged };
 //   - up to eight or twelve splits, merged four at a time one after the other: 16 rows x 2048 in two 14.5 / 13.9 / 13.7, four 10.7 / 10.2
 //     / 9.9, six 10.1 / 9.9 / 9.6, seven 10.3 / 9.9 / 9.7, eight 8.7 / 8.6 / 8.3 (D = 64 7.2 / 7.2 / 6.7), ten 8.9 / 9.3 / 8.9, twelve 8.5 /
 //     9.0 / 8.5, fifteen 8.8 / 9.7 / 9.2; 20 rows x 2048 in twelve 9.7 / 9.8 / 9.2; with eight query heads of D = 64, 32 rows x 2048 in eight
-//     9.3 / 9.2 / 8.7, 8 x 4096 in ten 10.8 / 11.1 / 10.9.  Eight are tagged in pieces of less than 256 KiB, as no slower, for the
+//     9.3 / 9.2 / 8.7, 8 x 4096 in ten 10.8 / 11.1 / 10.9.  Eight are tagged in workgroups of four waves and pieces of less than 256 KiB, as no slower, for the
 //     host's sake: larger ones, which it does not wait for, take 14.5 / 14.7 (fp32 15.4 / 15.6);
-//   - one part of a row a wave: with two (more than four query heads) 32 rows x 2048 in eight 11.9 / 12.7 counted;
-//   - workgroups that are all there from the beginning, two a compute unit: 128 rows x 2048 of fp32 in four 43.9 / 43.8 tagged; of 640 and
+//   - one part of a row a wave: with two (four waves, more than four query heads) 32 rows x 2048 in eight 11.9 / 12.7 counted;
+//   - workgroups that are all there from the beginning, two a compute unit (one with more than eight splits: 32 rows x 4096 in eight 15.5 /
+//     15.1 counted, ten 17.9 / 18.0, twelve 16.0 / 16.7): 128 rows x 2048 of fp32 in four 43.9 / 43.8 tagged; of 640 and
 //     more, those that wait for memory at their ends keep others out (160 rows x 4096 in four 62.3 / 65.5, 264 x 2048 52.9 / 54.4 counted).
 template <int GH, int D, int WAVES>
 constexpr bool one_part_a_wave = GH * (D / 2) <= WAVES * kWave;

@@ -78,7 +78,7 @@ struct DecodeArgs {
   int splits;
   int xcd_map;
   int waves, depth;  // bfloat16 kernel: workgroup size in waves, tiles in flight per wave: 4 x 2, 4 x 1; D = 128,
-                     // per-head layout: 8 x 2, and with up to four query heads per KV head 4 x 3 too.  Vector units: 4 or 8 waves
+                     // per-head layout: 8 x 2, and with up to four query heads per KV head 4 x 3 too; D = 128 with more, 8 x 1.  Vector units: 4 or 8 waves
   bool is_bf16;
   bool vector = false;  // bfloat16 on the vector units: one query head per KV head, no append in the head-shared layout
   // fused append: all null / 0 for plain attention
