@@ -143,10 +143,11 @@ __device__ __forceinline__ float2 merge_splits(int splits, Read read) {
     o1 *= old;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const float w = s + j < splits ? __builtin_amdgcn_exp2f(ml[j].x - ms) : 0.f;
-      l = fmaf(ml[j].y, w, l);
-      o0 = fmaf(o[j].x, w, o0);
-      o1 = fmaf(o[j].y, w, o1);
+      const bool real = s + j < splits;  // what is no split adds nothing, an infinity of the last one included (0 * inf)
+      const float w = __builtin_amdgcn_exp2f(ml[j].x - ms);
+      l = fmaf(real ? ml[j].y : 0.f, real ? w : 0.f, l);
+      o0 = fmaf(real ? o[j].x : 0.f, real ? w : 0.f, o0);
+      o1 = fmaf(real ? o[j].y : 0.f, real ? w : 0.f, o1);
     }
     m = mm;
     if (next >= splits) break;

@@ -226,3 +226,32 @@ def test_counted_splits_from_a_graph(dtype, S, Hk, G, D, budget, B, shared, spli
         assert torch.equal(out_g.view(torch.uint8), out_e.view(torch.uint8)), step
         out_g.fill_(float(step))   # what lies in the output between two steps does not matter
     _same_state(eager, graphed)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("splits", [2, 3, 5, 6, 7, 8, 11])
+@pytest.mark.parametrize("D,G", [(64, 3), (128, 1)])
+def test_an_infinity_stays_one(D, G, splits):
+    """fp32, an infinite element in the first and in the last token of every row, so in the first and in the last split that is merged: these
+    two elements of the results are infinite, as in a row that is not split, and every other one is what it is there (at most splits + 8 +
+    len roundings of sums no larger than the largest value on either side, eight times the root of their number)."""
+    shape, budget = ("f32", 2, 2, G, D, 640, 16, False), 640
+    wl, (counted, merged, tagged) = _engines(*shape, splits, 3)
+    _, (whole,) = _engines(*shape, 1, 1)
+    merged.native_layers = tagged.native_layers = False
+    k, v, q = _inputs(wl, 0)
+    q = q * 0.1
+    largest = float(max(whole.folded.v_pool.abs().max(), v.abs().max()))
+    v[..., 3] = math.inf
+    size = q.numel()
+    outs = [torch.full((size + 1,), 7.0, device="cuda")[o:][:size].view(q.shape) for o in (0, 1, 0, 0)]
+    for e, o in zip((counted, merged, tagged, whole), outs):
+        e.folded.v_pool[e.folded.block_table[:, :, 0].long(), 0, 5] = -math.inf
+        e.decode_step(k, v, q, o)
+    want = outs[3]
+    assert bool((want[..., 3] == math.inf).all()) and bool((want[..., 5] == -math.inf).all())
+    finite = [d for d in range(D) if d not in (3, 5)]
+    tol = 8 * (splits + 8 + budget) ** 0.5 * 2.0 ** -24 * largest
+    for name, o in zip(("counted", "merged by a launch", "tagged"), outs):
+        assert torch.equal(o[..., [3, 5]], want[..., [3, 5]]), name
+        assert bool(((o - want)[..., finite].abs() <= tol).all()), name
