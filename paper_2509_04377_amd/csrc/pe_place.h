@@ -2,7 +2,7 @@
 // a division: a division by a run-time number is some forty dependent instructions, and two of them stood in front of a wave's
 // first load.  One row a grid row, its splits side by side; in the order that keeps the splits of a row on one XCD (workgroup
 // number b runs on XCD b % 8) eight rows a grid row.  Counts that do not fit that (`linear`) are divided as before.
-// And how many (row, chunk) workgroups go into one launch.
+// And how many (row, chunk) workgroups go into one launch, and the workgroups of a prune's rows.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -43,6 +43,42 @@ inline bool launch_pieces(int num_seqs, int rows_per_seq, int chunks, int thread
       if (!f((int)s0, (int)ns, (int)c0, (int)(chunks - c0 < some ? chunks - c0 : some))) return false;
   }
   return true;
+}
+
+// Prefill prune: into how many workgroups (the logarithm) a row goes whose selection and copy are one launch; -1: two launches, one
+// workgroup a row that selects, and one for every 1024 tokens of it that copies.  `token_bytes`: K and V of a token and head, read and
+// written.  The host knows how many tokens there are and how long the longest row is, not how long the others are.
+//
+// As many (a power of two) as the compute units have room for with one each, but none with less than one pass of its copy.  Whole prunes,
+// half as many / so / twice as many, us: 8 x 4096 tokens of D = 64 23.9 / 23.0 / 24.2, 16 of 2048 to 16384 138.9 / 127.1 / 127.4, 2 of 20000
+// to 32768 62.9 / 60.1 / 73.0 (each of them selects: beyond one a compute unit they take turns); one of 1000 with half a pass 10.3, with one
+// 10.2, with two 10.9.
+//
+// One launch saves the second one and the second reading of the scores, some 4 us.  It costs where a long row's share is copied by one
+// compute unit (58 GB/s) while the others have nothing to do.  So a share has to be (two launches / one, us, 8 heads of D = 128)
+//   - no more than 640 KiB (16 of 2048 to 16384, 1024 kept, 512 KiB 141 / 137; 17 x 4096, 256 kept 64.6 / 64.5, 1024 kept, 1 MiB, 82.5 /
+//     86.9; one of 32768 beside 31 of 512, 16384 kept, 16 MiB, 155 / 410);
+//   - or no more than a workgroup of the second of two launches copies: 1024 tokens, less what goes of a row of full or of average length
+//     (64 x 1000, 1024 kept 157 / 153; 4 x 4096, 4096 kept 42 / 36);
+//   - or rows of full length, of which there are total / longest at the least, have to fill three quarters of the compute units, and the
+//     workgroups whole rounds of them, but for a tenth (32 x 16384, 8192 kept 805 / 802; 17 x 8192, 136 workgroups, 229 / 251; 33 x 4096,
+//     264, 4096 kept 341 / 396; 60 of D = 64 of 370 to 9893, 7808 kept, 176 of 480 workgroups 294 / 352).
+// Rows of more than 8192 tokens of which less than a sixteenth of the average row is kept have little to copy, and the counting in front
+// of it takes the launch's time or more: one of 30335 tokens, 1120 kept 19.6 / 23.1, nine of up to 28254, 320 kept 59.2 / 62.1, 8 x 32768,
+// 1024 kept 198 / 199; a tenth: 21 of up to 8274, 1024 kept 62.2 / 57.3.  Longer rows than 32768 are held in LDS too, by one compute unit.
+inline int prune_log2_parts(int num_seqs, int num_kv_heads, int64_t total_tokens, int max_seqlen, int budget, int token_bytes,
+                            int compute_units) {
+  const int64_t rows = (int64_t)num_seqs * num_kv_heads, cus = compute_units, average = total_tokens / num_seqs;
+  if (max_seqlen > 32768 || (max_seqlen > 8192 && (int64_t)budget * 16 < average)) return -1;
+  const int64_t most = max_seqlen < budget ? max_seqlen : budget;
+  int log2_parts = 0;
+  while (rows << (log2_parts + 1) <= cus && most >> (log2_parts + 1) >= 65536 / token_bytes) ++log2_parts;
+  const int64_t share = (most + (1 << log2_parts) - 1) >> log2_parts;
+  if (share * token_bytes <= 640 << 10) return log2_parts;
+  const int64_t of_full = 1024 * most / max_seqlen, of_average = average > budget ? 1024 * (int64_t)budget / average : average;
+  if (share <= of_full || share <= (of_average < 1024 ? of_average : 1024)) return log2_parts;
+  const int64_t groups = rows << log2_parts, full = (total_tokens / max_seqlen * num_kv_heads) << log2_parts;
+  return full * 4 >= cus * 3 && groups * 10 >= (groups + cus - 1) / cus * cus * 9 ? log2_parts : -1;
 }
 
 struct Place {

@@ -2,7 +2,7 @@
 // evict the E = max(0, L - C) tokens that come first under (score ascending, index ascending), and
 // write the survivors, order kept, into the row's pages.
 //
-// Two kernels on one stream, or three for the longest prompts:
+// Three kernels on one stream, or two:
 //   1. token_scores:  sweep of the packed K/V prompt; S_i = ||V_i||/||K_i|| in fp64, rounded once to
 //                     fp32, stored per KV head as a contiguous run  scores[hk][token].
 //   2. select:        per row, on the fp32 bit patterns (scores are >= +0, so they order like unsigned integers): a
@@ -11,8 +11,8 @@
 //                     many scores are > T and how many == T (none counted, and q = the largest number, where all go).
 //   3. gather:        per row and chunk, an index-ordered scan turns those counts into the destination
 //                     of every kept token; token rows are then copied with 16-byte lane accesses.
-//   2 + 3. select_gather, for rows of up to 32768 tokens: every workgroup of a row selects by itself, and copies its share of
-//                     what is kept.
+//   2 + 3. select_gather, where that is faster (prune_log2_parts): every workgroup of a row selects by itself, and copies its
+//                     share of what is kept.
 // A token is kept iff score > T, or score == T and at least q equal-score tokens precede it.
 //
 // Head-shared mode (one decision per sequence, pages [B][Hk][D]): a token's score is the mean of its heads' scores (head
@@ -30,8 +30,10 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
-constexpr int kChunk = 1024;  // tokens per chunk in the count pass and in the gather (4 per gather thread)
-constexpr int kTokPerThread = kChunk / kThreads;
+constexpr int kChunk = 1024;  // tokens per chunk in the count pass and in the gather
+constexpr int kGatherThreads = 512;
+constexpr int kGatherWaves = kGatherThreads / kWave;
+constexpr int kTokPerThread = kChunk / kGatherThreads;
 constexpr int kSweepLoads = 4;  // token sweep: wave-loads of K (and of V) per step
 constexpr int kSweepIters = 2;  // and steps per wave (4 and 8: the same on 2 GB of prompt, 5 us slower on 1 GB: longer tail)
 
@@ -534,20 +536,22 @@ __device__ __forceinline__ Threshold select_threshold(const RowScores<NV, LV>& r
   return {T, E == 0 ? 0 : k + 1u == sm.in_bin ? kAllGo : (int)k + 1};
 }
 
-// For rows that are too long to be selected by several workgroups each: the threshold, and, per chunk of 1024 tokens, how many scores
-// before it are > T and == T (the gather turns these into destinations).
-__global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __restrict__ scores, const int32_t* __restrict__ cu_seqlens,
+// The selection by itself: the threshold, and, per chunk of 1024 tokens, how many scores before it are > T and == T (the gather turns
+// these into destinations).  Two workgroups a compute unit (eight waves per SIMD, 64 registers) as long as the row leaves the
+// registers for it: more rows than compute units then still run at once.
+template <int NV, int LV>
+__global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_kernel(const float* __restrict__ scores,
+                                                             const int32_t* __restrict__ cu_seqlens,
                                                              uint32_t* __restrict__ sel, int32_t* __restrict__ before,
                                                              int32_t* __restrict__ seq_lens_out,
                                                              int32_t* __restrict__ kept_idx_out, int64_t total_tokens,
                                                              int64_t chunk_slots, int num_kv_heads, int budget) {
-  constexpr int NV = kSelMaxVecs, LV = kSelMaxVecs;
   using Row = RowScores<NV, LV>;
   constexpr int kHeldChunks = Row::kHeld / kChunk;
   static_assert(kHeldChunks <= kSelMaxHeldChunks, "chunk counters");
   __shared__ SelectLds sm;
   uint32_t* const hist = sm.hist;  // at the end, counts of chunks beyond the held ones
-  __shared__ uint4 held_lds[LV * kSelThreads];
+  __shared__ uint4 held_lds[LV > 0 ? LV * kSelThreads : 1];
   __shared__ uint32_t held_count[kSelMaxHeldChunks];
   const int row = (int)blockIdx.x;
   const int s = row / num_kv_heads, h = row % num_kv_heads;
@@ -636,13 +640,28 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
   }
 }
 
+// The smallest holding that covers rows of max_seqlen tokens (or the largest there is): a larger one than needed costs loads,
+// branches and, beyond 16 scores a thread, the second workgroup of a compute unit.
+using SelectKernel = void (*)(const float*, const int32_t*, uint32_t*, int32_t*, int32_t*, int32_t*, int64_t, int64_t, int, int);
+SelectKernel select_kernel_for(int max_seqlen) {
+  const int vecs = (max_seqlen + 4 * kSelThreads - 1) / (4 * kSelThreads);
+  if (vecs <= 1) return select_kernel<1, 0>;
+  if (vecs <= 2) return select_kernel<2, 0>;
+  if (vecs <= 4) return select_kernel<4, 0>;
+  if (vecs <= kSelMaxVecs) return select_kernel<kSelMaxVecs, 0>;
+  return select_kernel<kSelMaxVecs, kSelMaxVecs>;
+}
+
 // ---- 3. gather ----------------------------------------------------------------------------------------
-// One workgroup per (row, chunk) copies the kept token rows of one head.  SHARED: the heads of a sequence share its selection and its
+// One workgroup per (row, chunk) copies the kept token rows of one head.  512 threads: a chunk that is kept whole, as of short rows
+// beside a long one, is a long way for 256 (whole prunes, 256 / 512 / 1024 threads, us: fp32, 39 of D = 128 of up to 1459 tokens 74.7 /
+// 54.1 / 54.4, one of 9802 beside eleven of 980, 1280 kept 67.7 / 49.9 / 50.0), and chunks of which little is kept leave 1024 without work
+// (14 x 14652 of D = 64, 336 kept 81.6 / 83.3 / 88.4).  SHARED: the heads of a sequence share its selection and its
 // table row, their token rows lie num_kv_heads apart in the pages (whole records by one workgroup were a division per
 // 16 bytes and an eighth of the workgroups: 16 prompts of 2048 to 8192 tokens, 8 heads, 1024 kept 204 us a prune, now 98; 8 x 4096 of
 // D = 64 54.8, now 31.1).
 template <int VEC_PER_ROW, bool SHARED>
-__global__ __launch_bounds__(kThreads) void gather_kernel(const uint4* __restrict__ k_in, const uint4* __restrict__ v_in,
+__global__ __launch_bounds__(kGatherThreads) void gather_kernel(const uint4* __restrict__ k_in, const uint4* __restrict__ v_in,
                                                           const float* __restrict__ scores,
                                                           const int32_t* __restrict__ cu_seqlens,
                                                           const uint32_t* __restrict__ sel,
@@ -653,7 +672,7 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(const uint4* __restric
                                                           int64_t chunk_slots, int num_kv_heads, int rows,
                                                           int log2_block, int max_blocks, int budget, int row0,
                                                           int chunk0) {
-  __shared__ uint32_t wave_sum[kWaves];
+  __shared__ uint32_t wave_sum[kGatherWaves];
   __shared__ int32_t src_tok[kChunk];  // kept tokens of this chunk, in order: in-sequence index
   __shared__ int n_kept_sh;
   // Rows fastest: the first chunks of a ragged batch, which short sequences keep most of, spread over all XCDs (workgroup
@@ -688,14 +707,14 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(const uint4* __restric
     n_gt += in && b[j] > T;
     n_eq += in && b[j] == T;
   }
-  // exclusive scan of (n_gt, n_eq) over the 256 threads, in thread (= index) order; each fits 16 bits
+  // exclusive scan of (n_gt, n_eq) over the threads, in thread (= index) order; each fits 16 bits
   const uint32_t n_both = (uint32_t)n_gt | ((uint32_t)n_eq << 16);
   const uint32_t inc = wave_prefix_sum_u32(n_both);
   if (lane == kWave - 1) wave_sum[wave] = inc;
   __syncthreads();
   uint32_t ex = inc - n_both;
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) ex += w < wave ? wave_sum[w] : 0u;
+  for (int w = 0; w < kGatherWaves; ++w) ex += w < wave ? wave_sum[w] : 0u;
   int ex_gt = (int)(ex & 0xffffu) + gt_before, ex_eq = (int)(ex >> 16) + eq_before;
   // kept tokens before this chunk's start: the chunk's kept tokens take consecutive positions from here
   const int kept_before_chunk = gt_before + (eq_before > q ? eq_before - q : 0);
@@ -712,18 +731,18 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(const uint4* __restric
     ex_gt += is_gt;
     ex_eq += is_eq;
   }
-  if (tid == kThreads - 1) n_kept_sh = ex_gt + (ex_eq > q ? ex_eq - q : 0) - kept_before_chunk;
+  if (tid == kGatherThreads - 1) n_kept_sh = ex_gt + (ex_eq > q ? ex_eq - q : 0) - kept_before_chunk;
   __syncthreads();
   const int n_kept = n_kept_sh;
 
   if (kept_idx_out != nullptr && (!SHARED || h == 0))  // consecutive positions: whole lines
-    for (int e = tid; e < n_kept; e += kThreads) kept_idx_out[(int64_t)sel_row * budget + kept_before_chunk + e] = src_tok[e];
+    for (int e = tid; e < n_kept; e += kGatherThreads) kept_idx_out[(int64_t)sel_row * budget + kept_before_chunk + e] = src_tok[e];
 
   // copy the kept rows: VEC_PER_ROW lanes per token row, K and V (two or four rows of a thread in flight, or the pages looked up
   // beforehand: no faster)
   const int32_t* bt = block_table + (int64_t)sel_row * max_blocks;
   const int block_mask = (1 << log2_block) - 1;
-  constexpr int kRowsPerPass = kThreads / VEC_PER_ROW;
+  constexpr int kRowsPerPass = kGatherThreads / VEC_PER_ROW;
   const int u = tid % VEC_PER_ROW, r = tid / VEC_PER_ROW;
   for (int e = r; e < n_kept; e += kRowsPerPass) {
     const int pos = kept_before_chunk + e;
@@ -867,8 +886,7 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_gather_ke
   }
 }
 
-// The smallest holding that covers rows of max_seqlen tokens: a larger one than needed costs loads, branches and, beyond 16 scores a
-// thread, the second workgroup of a compute unit.
+// The smallest holding again.
 template <int VPR, bool SHARED>
 auto select_gather_kernel_for(int max_seqlen) {
   const int vecs = (max_seqlen + 4 * kSelThreads - 1) / (4 * kSelThreads);
@@ -926,16 +944,11 @@ hipError_t launch(const PruneArgs& a, hipStream_t stream) {
   if ((int64_t)rows * (chunks_per_row > 4 ? chunks_per_row : 4) >= (1LL << 32) / kThreads) return hipErrorInvalidValue;
   constexpr int VPR = G::kLanesPerRow;
   constexpr int kMostGroups = 1 << 22;  // of a launch: 2^32 threads
-  if (a.max_seqlen <= 4 * kSelMaxVecs * kSelThreads && a.num_kv_heads < kMostGroups) {
+  static_assert(4 * kSelMaxVecs * kSelThreads == 32768 && kChunk == 1024 && kSelThreads == 1024, "as prune_log2_parts has it");
+  const int log2_parts = prune_log2_parts(a.num_seqs, a.num_kv_heads, a.total_tokens, a.max_seqlen, a.budget, 4 * D * (int)sizeof(T),
+                                          a.compute_units);
+  if (log2_parts >= 0 && a.num_kv_heads < kMostGroups) {
     const auto kernel = a.shared ? select_gather_kernel_for<VPR, true>(a.max_seqlen) : select_gather_kernel_for<VPR, false>(a.max_seqlen);
-    // As many workgroups a row (a power of two) as the compute units have room for with one each, but none with less than one pass
-    // of its copy.  Whole prunes, half as many / so / twice as many, us: 8 x 4096 tokens of D = 64 23.9 / 23.0 / 24.2, 16 of 2048 to
-    // 16384 138.9 / 127.1 / 127.4, 2 of 20000 to 32768 62.9 / 60.1 / 73.0 (each of them selects: beyond one a compute unit they take
-    // turns); one of 1000 with half a pass 10.3, with one 10.2, with two 10.9.
-    const int64_t copies = (int64_t)a.num_seqs * a.num_kv_heads;
-    const int most = a.max_seqlen < a.budget ? a.max_seqlen : a.budget;
-    int log2_parts = 0;
-    while (copies << (log2_parts + 1) <= a.compute_units && most >> (log2_parts + 1) >= kSelThreads / VPR) ++log2_parts;
     const int room = (kMostGroups - 1) / a.num_kv_heads, seqs = room < 65535 ? room : 65535;  // of a launch
     for (int s0 = 0; s0 < a.num_seqs; s0 += seqs) {
       const int ns = a.num_seqs - s0 < seqs ? a.num_seqs - s0 : seqs;
@@ -947,7 +960,7 @@ hipError_t launch(const PruneArgs& a, hipStream_t stream) {
     }
     return e;
   }
-  hipLaunchKernelGGL(select_kernel, dim3((unsigned)rows), dim3(kSelThreads), 0, stream, sel_scores, a.cu_seqlens,
+  hipLaunchKernelGGL(select_kernel_for(a.max_seqlen), dim3((unsigned)rows), dim3(kSelThreads), 0, stream, sel_scores, a.cu_seqlens,
                      w.sel, w.before, a.seq_lens_out, a.kept_idx_out, a.total_tokens, w.chunk_slots, heads, a.budget);
   if ((e = hipGetLastError()) != hipSuccess || chunks_per_row == 0) return e;
   // Plain stores for what is kept.  With the non-temporal hint prunes of 32 x 16384 tokens that go into the same pools again and
@@ -955,9 +968,9 @@ hipError_t launch(const PruneArgs& a, hipStream_t stream) {
   // 457 (four prompts of 65536 229 and 223, 3B prompts 141 and 137, the head-shared layout 455 and 436).
   const auto gather = a.shared ? gather_kernel<VPR, true> : gather_kernel<VPR, false>;
   e = hipErrorInvalidValue;  // (one launch, but where a head-shared batch has more than 2^24 (head, chunk) pairs)
-  launch_pieces(a.num_seqs, a.num_kv_heads, chunks_per_row, kThreads, [&](int s0, int ns, int c0, int nc) {
+  launch_pieces(a.num_seqs, a.num_kv_heads, chunks_per_row, kGatherThreads, [&](int s0, int ns, int c0, int nc) {
     const int copied = ns * a.num_kv_heads;  // (row, head) pairs that this launch copies
-    hipLaunchKernelGGL(gather, dim3((unsigned)copied * (unsigned)nc), dim3(kThreads), 0, stream, (const uint4*)a.k_in,
+    hipLaunchKernelGGL(gather, dim3((unsigned)copied * (unsigned)nc), dim3(kGatherThreads), 0, stream, (const uint4*)a.k_in,
                        (const uint4*)a.v_in, sel_scores, a.cu_seqlens, w.sel, w.before, a.block_table, (uint4*)a.k_pool,
                        (uint4*)a.v_pool, a.kept_idx_out, a.total_tokens, w.chunk_slots, a.num_kv_heads, copied,
                        ilog2(a.block_size), a.max_blocks, a.budget, s0 * a.num_kv_heads, c0);
