@@ -772,7 +772,7 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_gather_ke
     const uint4* __restrict__ k_in, const uint4* __restrict__ v_in, const float* __restrict__ scores,
     const int32_t* __restrict__ cu_seqlens, const int32_t* __restrict__ block_table, uint4* __restrict__ k_pool,
     uint4* __restrict__ v_pool, int32_t* __restrict__ seq_lens_out, int32_t* __restrict__ kept_idx_out, int64_t total_tokens,
-    int log2_block, int max_blocks, int budget, int max_seqlen, int log2_parts, int seq0) {
+    int log2_block, int max_blocks, int budget, int log2_parts, int seq0) {
   using Row = RowScores<NV, 0>;
   __shared__ SelectLds sm;
   uint32_t* const list = sm.hist;  // tokens of the positions at hand, once the threshold is known
@@ -795,7 +795,9 @@ __global__ __launch_bounds__(kSelThreads, NV <= 4 ? 8 : 4) void select_gather_ke
   constexpr int kRowsPerPass = kSelThreads / VEC_PER_ROW;
   const int share = (((keep + (1 << log2_parts) - 1) >> log2_parts) + kRowsPerPass - 1) & ~(kRowsPerPass - 1);  // whole passes of the copy
   const int lo = part * share, hi = lo + share < keep ? lo + share : keep;
-  if (lo >= hi || L > max_seqlen) return;  // (a row longer than the caller has said: its pages are left alone)
+  // (a row longer than the caller has said is pruned like any other as long as it is held here and its table row holds it, else its
+  // pages are left alone)
+  if (lo >= hi || L > Row::kHeld || (keep - 1) >> log2_block >= max_blocks) return;
 
   const int32_t* bt = block_table + (int64_t)sel_row * max_blocks;
   const int block_mask = (1 << log2_block) - 1;
@@ -955,7 +957,7 @@ hipError_t launch(const PruneArgs& a, hipStream_t stream) {
       hipLaunchKernelGGL(kernel, dim3((unsigned)a.num_kv_heads, (unsigned)ns, 1u << log2_parts), dim3(kSelThreads), 0, stream,
                          (const uint4*)a.k_in, (const uint4*)a.v_in, sel_scores, a.cu_seqlens, a.block_table, (uint4*)a.k_pool,
                          (uint4*)a.v_pool, a.seq_lens_out, a.kept_idx_out, a.total_tokens, ilog2(a.block_size), a.max_blocks,
-                         a.budget, a.max_seqlen, log2_parts, s0);
+                         a.budget, log2_parts, s0);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return e;

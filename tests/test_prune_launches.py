@@ -87,3 +87,30 @@ def test_one_launch_and_two(log2_parts, dtype, D, L, shared):
     assert bool((results[0][0][:, 1:] > results[0][0][:, :-1]).all()) and int(results[0][0].min()) >= 0
     for a, b in zip(*results):
         assert torch.equal(a, b)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("L,said", [(1010, 1000), (1024, 513), (4000, 3073)])
+def test_a_row_somewhat_longer_than_said(log2_parts, L, said):
+    """A bound on the lengths that is too small by less than 1024 tokens, as it was taken by launches for whole chunks of them: the same
+    result as with the right one."""
+    Hk, B, D, budget = 4, 16, 64, 512
+    assert log2_parts([L], Hk, budget, D, 2, said) >= 0
+    g = torch.Generator(device="cuda")
+    g.manual_seed(L)
+    k, v = (torch.randn((L, Hk, D), generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
+    blocks = budget // B
+    table = torch.arange(Hk * blocks, dtype=torch.int32, device="cuda").view(1, Hk, blocks)
+    desc = pe.make_desc(torch.bfloat16, 1, Hk, Hk, D, B, blocks, Hk * blocks)
+    cu = torch.tensor([0, L], dtype=torch.int32, device="cuda")
+    results = []
+    for longest in (L, said):
+        pools = [torch.zeros((Hk * blocks, B, D), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+        out = torch.zeros(1, dtype=torch.int32, device="cuda")
+        kept = torch.full((1, Hk, budget), -7, dtype=torch.int32, device="cuda")
+        pe.pe_prefill_prune(desc, k, v, cu, L, longest, budget, *pools, table, out, kept,
+                            pe.alloc_workspace(pe.PE_OP_PREFILL_PRUNE, desc, L, device="cuda"))
+        results.append(pools + [out, kept])
+    assert int(results[0][3].min()) >= 0
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
