@@ -81,6 +81,24 @@ inline int prune_log2_parts(int num_seqs, int num_kv_heads, int64_t total_tokens
   return full * 4 >= cus * 3 && groups * 10 >= (groups + cus - 1) / cus * cus * 9 ? log2_parts : -1;
 }
 
+// Block scores: which part of its row workgroup b has, of `parts` a row.  Workgroup b runs on XCD b % 8, there on one shader engine after the
+// other, and the last parts of all rows have nothing to do where the tables hold more pages than are in use: with an even number of
+// parts, side by side, some of the chip had all the work (972 rows of four pages of 128 tokens, eight heads of D = 128, in tables of six,
+// two parts, 452 us, now 311).  So the parts begin somewhere else in each row, by a multiplicative hash of its number, `turn` (in two steps: fp32,
+// 96 x 8 rows of 209 pages of 32 tokens in tables of 315, 20 parts 900 us side by side, 994 in one step, 874 in two).  An odd number
+// spreads by itself, and better where few rows are scored (26 rows of 36 pages of 128 tokens in tables of 74, 19 parts 12.6 us, hashed 17.5).
+// Head-shared, the heads of a sequence begin at the same one: their tokens lie side by side (13 sequences x 8 layers x 8 heads, fp32 719 us,
+// each by itself 798).
+__host__ __device__ inline uint32_t score_part(uint32_t b, uint32_t row, uint32_t parts, uint32_t turn) {
+  uint32_t at = b - row * parts;
+  if (parts % 2u == 0u) {
+    uint32_t hash = turn * 0x9e3779b1u;  // 2^32 / the golden ratio
+    hash = (hash ^ hash >> 16) * 0x9e3779b1u;
+    at += (uint32_t)((uint64_t)hash * parts >> 32);
+  }
+  return at < parts ? at : at - parts;
+}
+
 struct Place {
   int row, split, seq, head;
 };

@@ -11,6 +11,7 @@
 #include "pe_evict_common.h"
 #include "pe_launch.h"
 #include "pe_norms.h"
+#include "pe_place.h"
 
 namespace pe {
 namespace {
@@ -96,11 +97,11 @@ __global__ __launch_bounds__(kThreads) void score_blocks_kernel(const T* __restr
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const int row = (int)(blockIdx.x / groups_per_row);
-  const int grp = (int)(blockIdx.x % groups_per_row);
   const int s = row / num_kv_heads;
   const int len = seq_lens[s];
   // budget > 0: only sequences that are about to evict (newest page just filled, at budget) are scored
   if (budget > 0 && !(len > 0 && len % B == 0 && len >= budget)) return;
+  const int grp = (int)score_part(blockIdx.x, (uint32_t)row, (uint32_t)groups_per_row, (uint32_t)(shared ? s : row));
   const int nfull_raw = len / B;
   const int nfull = nfull_raw < max_blocks ? nfull_raw : max_blocks;  // never index past the table row
   // shared: one table row per sequence and pages of [B][Hk][D]: the token rows of this head are Hk rows apart
