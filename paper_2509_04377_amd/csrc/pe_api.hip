@@ -227,9 +227,14 @@ pe::DecodeArgs decode_args(const pe_cache_desc* desc, int splits) {
   // splits, four heads 13.1 / 12.5 (D = 64 8.7 / 8.0), 32 x 4096 in eight 22.6 / 22.4, with eight heads 26.9 / 24.1; 256 whole rows x 300 13.0
   // / 12.4; x 2048 77.4 / 78.8, with eight heads 86.4 / 80.7; 384 rows x 1024 62.6 / 64.9, with eight heads 63.7 / 68.3; 128 rows x 1024 of D =
   // 64 in four, eight heads, 13.5 / 14.0.  bfloat16: 64 rows x 190 of D = 64 3.5 / 3.3, 384 x 60 3.4 / 3.7.
+  // Four too where a whole row has ten tiles of 4 KiB or fewer, twelve with up to four query heads: eight waves then have little or nothing
+  // each (64 | 256 rows, fp32, D = 64, four heads x 30 tokens 3.7 / 3.9 | 4.6 / 4.8, x 63 4.7 / 4.7 | 5.2 / 5.5, x 111 5.4 / 5.0 | 6.2 / 5.9; D = 128,
+  // one x 30 4.1 / 4.2 | 4.7 / 5.1, x 47 4.6 / 4.3 | 5.5 / 5.3; eight heads of D = 64 x 63 5.7 / 5.6 | 6.0 / 6.0, x 79 6.5 / 5.8 | 6.9 / 6.3; bfloat16,
+  // D = 128 x 63 4.3 / 4.4 | 4.9 / 5.2, x 111 4.9 / 4.6 | 5.8 / 5.6).
   if (!a.is_bf16 || a.vector) {
     const bool wide = desc->num_q_heads / desc->num_kv_heads > 4;
-    a.waves = groups <= cus && (wide || row_bytes(desc) / splits < (1 << 20)) ? 8 : 4;
+    const bool short_row = splits == 1 && row_bytes(desc) <= (wide ? 40 : 48) << 10;
+    a.waves = groups <= cus && (wide || row_bytes(desc) / splits < (1 << 20)) && !short_row ? 8 : 4;
   }
   return a;
 }

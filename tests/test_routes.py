@@ -100,6 +100,21 @@ hipError_t launch(const pe::DecodeKernelArgs& k) { return pe::launch_decode(kern
 """
 
 
+@pytest.mark.parametrize("kw,waves", [
+    # whole rows: a table of 40 KiB with more than four query heads a KV head, of 48 KiB with fewer, and the next larger ones
+    (dict(dtype=pe.PE_F32, num_q_heads=64, head_dim=64, max_blocks=5), 4), (dict(dtype=pe.PE_F32, num_q_heads=64, head_dim=64, max_blocks=6), 8),
+    (dict(dtype=pe.PE_F32, head_dim=64, max_blocks=6), 4), (dict(dtype=pe.PE_F32, head_dim=64, max_blocks=7), 8),
+    (dict(dtype=pe.PE_F32, max_blocks=3), 4), (dict(dtype=pe.PE_F32, max_blocks=4), 8), (dict(dtype=pe.PE_F32, num_seqs=1, max_blocks=1), 4),
+    (dict(num_q_heads=8, max_blocks=6), 4), (dict(num_q_heads=8, max_blocks=7), 8),
+    (dict(num_q_heads=8, head_dim=64, max_blocks=12), 4), (dict(num_q_heads=8, head_dim=64, max_blocks=13), 8),
+    (dict(dtype=pe.PE_F32, num_seqs=33), 4), (dict(dtype=pe.PE_F32, num_seqs=8, max_blocks=64), 8), (dict(dtype=pe.PE_F32, num_seqs=32), 4),
+    # split rows: eight wherever the workgroups are no more than the compute units
+    (dict(num_seqs=1, num_q_heads=8, head_dim=64, max_blocks=57), 8), (dict(dtype=pe.PE_F32, num_seqs=1, head_dim=64, max_blocks=8, decode_splits=8), 8)])
+def test_waves_on_the_vector_units(host_layer, kw, waves):
+    assert _form(host_layer, **kw)[1] == waves
+
+
+
 @pytest.mark.parametrize("more,last,compiles", [("", "const uint32_t", True), ("const int more,", "const uint32_t", False),
                                                 ("", "const uint64_t", False)])
 def test_attention_kernels_have_the_parameters_that_are_read_by_offset(tmp_path, more, last, compiles):
