@@ -189,11 +189,15 @@ pe::DecodeArgs decode_args(const pe_cache_desc* desc, int splits) {
   //     out of a pool of 8.6 GB 43.9, four x two and four x one 44.2; no faster with fewer rows); in the head-shared layout,
   //     whose wave-loads are runs of 256 bytes, four x one there too (45.6; with two tiles 47.2, with eight waves 47.1);
   //   - eight x one for more than four query heads a KV head where rows of D = 128 are split for three quarters of the compute units or
-  //     more, in pieces of 192 tokens or more: each wave then has one part of the row at the end, so that the splits can be counted
+  //     more, in pieces of 192 tokens or more.  Up to eight splits can be counted then, as each wave has one part of the row at the end
   //     (append and attention of all layers, four x one and a merge launch / so, full | ragged | 64 tokens a row: six query heads, 80 rows x
   //     800 in three 12.1 / 10.5 | 10.6 / 9.0 | 7.1 / 6.3, eight, 64 x 1024 in four 11.5 / 10.5, 64 x 4096 in four 26.4 / 25.8 | 19.9 / 19.8 |
-  //     7.2 / 6.6; fewer workgroups, 16 x 2048 in eight, four x two 9.1, so 9.5).  With up to four, whose splits are counted with four
-  //     waves, it is the same within 2 %;
+  //     7.2 / 6.6; fewer workgroups, 16 x 2048 in eight, four x two 9.1, so 9.5).  With a merge launch behind either form, which is what
+  //     single calls in eight splits have and every one in more, eight x one is no slower: 32 rows x 2048 in eight 11.4 / 11.2, x 8192 26.6 /
+  //     26.6; 28 x 2048 in nine 12.1 / 11.8, 20 x 4096 in twelve 14.2 / 13.6 | 12.5 / 12.1 | 8.2 / 8.0.  With up to four query heads, whose
+  //     splits are counted with four waves, it is the same within 2 %.
+  //     (Slower are some shapes whose last round is half empty with eight waves, 48 x 2048 in five 14.0 / 14.5, 40 x 4096 in six 19.1 / 19.5;
+  //     others are not, 36 x 2048 in seven 13.0 / 12.7 | 13.4 / 12.7 from the second layer on: no line drawn for them.)
   //   - four x two else (136 whole rows x 2048 26.8, four x one 28.2; D = 64, 128 rows in 256 splits of 8192 82.7 and 98.2).
   const int64_t groups = (int64_t)desc->num_seqs * desc->num_kv_heads * splits;
   const int64_t cus = compute_units();

@@ -10,7 +10,8 @@ DEV = "cuda"
 
 @pytest.mark.parametrize("splits", [2, 8, 9, 12, 32, 33, 64, 131, 256])
 @pytest.mark.parametrize("dtype,D,G,Hk,n", [(torch.float32, 64, 3, 2, 3001), (torch.float32, 128, 1, 8, 517), (torch.bfloat16, 64, 8, 1, 9000),
-                                            (torch.bfloat16, 128, 4, 8, 2100), (torch.bfloat16, 64, 1, 3, 40)])
+                                            (torch.bfloat16, 128, 4, 8, 2100), (torch.bfloat16, 64, 1, 3, 40),
+                                            (torch.bfloat16, 128, 8, 8, 2500)])   # (in twelve: eight waves by one, and a merge launch)
 def test_merge_of_many_splits(dtype, D, G, Hk, n, splits):
     """Either side adds the same products in its own order: at most n + splits roundings to fp32, of sums that are no larger than the
     largest value, but what is rounded at random adds up as the root of their number (eight times that is allowed); for bf16 one

@@ -100,6 +100,14 @@ hipError_t launch(const pe::DecodeKernelArgs& k) { return pe::launch_decode(kern
 """
 
 
+@pytest.mark.parametrize("rows,max_blocks,want", [
+    (64, 65, (4, 8, 1)), (80, 51, (3, 8, 1)), (40, 129, (6, 8, 1)), (32, 129, (8, 8, 1)), (20, 257, (12, 8, 1)), (8, 1025, (32, 8, 1)),
+    (80, 35, (3, 4, 1)), (16, 129, (16, 4, 1)), (47, 257, (5, 8, 1)), (14, 257, (16, 8, 1))])
+def test_bf16_eight_waves_by_one(host_layer, rows, max_blocks, want):
+    """In eight splits and fewer, and in more, which are merged by a launch; not in pieces of fewer than 192 tokens."""
+    assert _form(host_layer, num_seqs=rows, num_kv_heads=1, num_q_heads=8, max_blocks=max_blocks) == want
+
+
 @pytest.mark.parametrize("kw,waves", [
     # whole rows: a table of 40 KiB with more than four query heads a KV head, of 48 KiB with fewer, and the next larger ones
     (dict(dtype=pe.PE_F32, num_q_heads=64, head_dim=64, max_blocks=5), 4), (dict(dtype=pe.PE_F32, num_q_heads=64, head_dim=64, max_blocks=6), 8),
