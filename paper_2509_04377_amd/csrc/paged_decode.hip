@@ -429,11 +429,12 @@ __global__ __launch_bounds__(WAVES * kWave) void paged_decode_kernel(
     }
 }
 
-// Merge the split partials of one (sequence, query head): a wave, D / 64 elements a lane, walks over the splits with four records in
-// flight.  More than eight splits are shared by four waves, more than 32 by eight, whose states meet in LDS (attention and merge out of
-// a HIP graph, one wave / four / eight, us: 24 heads of D = 64 in 19 splits 8.7 / 7.3 / 7.6, 64 of D = 128 in 16 8.5 / 7.9 / 8.1, 32 in 32
-// 9.6 / 8.1 / 8.1, 32 of D = 64 in 36 12.7 / 10.2 / 9.9, four of D = 128 in 64 14.8 / 9.5 / 8.8, 80 in twelve 7.9 / 7.7 / 7.5; up to eight
-// no difference).  What a launch of it costs besides is the launch and one round trip to the records, which lie together for a row
+// Merge the split partials of one (sequence, query head), D / 64 elements a lane: by one wave where their number is one that may be
+// counted, in the order that has there; more are shared by four waves and more than 32 by eight, whose states meet in LDS (attention and
+// merge out of a HIP graph, one wave / four / eight, us: 24 heads of D = 64 in 19 splits 8.7 / 7.3 / 7.6, 64 of D = 128 in 16 8.5 / 7.9 / 8.1, 32
+// in 32 9.6 / 8.1 / 8.1, 32 of D = 64 in 36 12.7 / 10.2 / 9.9, four of D = 128 in 64 14.8 / 9.5 / 8.8; nine to twelve, one wave as it is here /
+// four, 25 rows of D = 128 x 4096 in nine 14.5 / 14.3, in twelve 15.4 / 15.4, 24 of D = 64 in nine 10.3 / 10.1, in ten 10.2 / 10.2; up to eight
+no difference).  What a launch of it costs besides is the launch and one round trip to the records, which lie together for a row
 // ([row][split][head]: with the heads of all rows under each split 0.4 us more for 32 rows of D = 128 in eight splits, 1.1 us for 16 rows
 // in 16).  The grid: the query heads of a row side by side, one row a grid row; with kMergeXcd, wherever the attention kernel keeps a row
 // on one XCD, eight rows a grid row, so that a row's records are read on the XCD that wrote them (append, attention and merge out of a HIP
@@ -452,31 +453,39 @@ __global__ __launch_bounds__(WAVES * kWave) void paged_decode_reduce_kernel(cons
   const int d = (int)(threadIdx.x % kWave) * E;
   const float* base = partials + ((int64_t)row * splits * g_real + h) * (D + 2);
   const int64_t stride = (int64_t)g_real * (D + 2);
-  // one pass, online: all loads are independent of the running state, so they overlap
-  float mm = kNegInf, l = 0.f, o[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) o[e] = 0.f;
-#pragma unroll 4
-  for (int sp = wave; sp < splits; sp += WAVES) {
-    const float* record = base + sp * stride;
-    const float2 ml = *reinterpret_cast<const float2*>(record + D);
-    float a[E];
+  const auto read = [&](int split, float2& ml, float (&v)[E]) {
+    const float* record = base + split * stride;
+    ml = *reinterpret_cast<const float2*>(record + D);
     if constexpr (E == 2) {
-      const float2 v = *reinterpret_cast<const float2*>(record + d);
-      a[0] = v.x;
-      a[1] = v.y;
+      const float2 pair = *reinterpret_cast<const float2*>(record + d);
+      v[0] = pair.x, v[1] = pair.y;
     } else {
-      a[0] = record[d];
+      v[0] = record[d];
     }
-    const float m_new = fmaxf(mm, ml.x);
-    const float ms = m_new == kNegInf ? 0.f : m_new;
-    const float w_old = __builtin_amdgcn_exp2f(mm - ms), w_new = __builtin_amdgcn_exp2f(ml.x - ms);
-    l = fmaf(l, w_old, ml.y * w_new);
+  };
+  float o[E] = {};
+  if constexpr (WAVES == 1) {
+    merge_splits(splits, o, read);
+  } else {
+    // online: all loads are independent of the running state, so they overlap
+    float mm = kNegInf, l = 0.f;
+    const auto add = [&](const float2& ml, const float (&v)[E]) {
+      const float m_new = fmaxf(mm, ml.x);
+      // all splits so far empty (m_new = -inf): reference 0, else -inf - -inf = NaN
+      const float ms = m_new == kNegInf ? 0.f : m_new;
+      const float w_old = __builtin_amdgcn_exp2f(mm - ms), w_new = __builtin_amdgcn_exp2f(ml.x - ms);
+      l = fmaf(l, w_old, ml.y * w_new);
 #pragma unroll
-    for (int e = 0; e < E; ++e) o[e] = fmaf(o[e], w_old, a[e] * w_new);
-    mm = m_new;
-  }
-  if constexpr (WAVES > 1) {
+      for (int e = 0; e < E; ++e) o[e] = fmaf(o[e], w_old, v[e] * w_new);
+      mm = m_new;
+    };
+#pragma unroll 4
+    for (int split = wave; split < splits; split += WAVES) {
+      float2 ml;
+      float v[E];
+      read(split, ml, v);
+      add(ml, v);
+    }
     __shared__ float sm[WAVES][D + 2];
     if (wave > 0) {
 #pragma unroll
@@ -487,26 +496,23 @@ __global__ __launch_bounds__(WAVES * kWave) void paged_decode_reduce_kernel(cons
     if (wave > 0) return;
 #pragma unroll
     for (int w = 1; w < WAVES; ++w) {
-      const float m_w = sm[w][D], m_new = fmaxf(mm, m_w);
-      const float ms = m_new == kNegInf ? 0.f : m_new;
-      const float w_old = __builtin_amdgcn_exp2f(mm - ms), w_new = __builtin_amdgcn_exp2f(m_w - ms);
-      l = fmaf(l, w_old, sm[w][D + 1] * w_new);
+      float v[E];
 #pragma unroll
-      for (int e = 0; e < E; ++e) o[e] = fmaf(o[e], w_old, sm[w][d + e] * w_new);
-      mm = m_new;
+      for (int e = 0; e < E; ++e) v[e] = sm[w][d + e];
+      add(make_float2(sm[w][D], sm[w][D + 1]), v);
     }
+#pragma unroll
+    for (int e = 0; e < E; ++e) o[e] = l > 0.f ? o[e] / l : 0.f;
   }
   const int64_t off = ((int64_t)row * g_real + h) * D + d;
   // (the counts of the launch behind this one: one for every 128 elements of a row)
   if (CLEAR && (h * D + d) % (2 * kWave) == 0) *arrival_count<T>(next_out, off / 2) = 0u;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    const float r = l > 0.f ? o[e] / l : 0.f;
-    if constexpr (sizeof(T) == 4) {
-      static_cast<float*>(out)[off + e] = r;
-    } else {
-      static_cast<uint16_t*>(out)[off + e] = f32_to_bf16(r);
-    }
+    if constexpr (sizeof(T) == 4)
+      static_cast<float*>(out)[off + e] = o[e];
+    else
+      static_cast<uint16_t*>(out)[off + e] = f32_to_bf16(o[e]);
   }
 }
 
@@ -555,11 +561,12 @@ void launch_reduce(const DecodeArgs& a, hipStream_t stream) {
   const int order = grid_rows > 65535 ? kMergeLinear : xcd ? kMergeXcd : kMergeRows;
   const dim3 blocks = order == kMergeLinear ? dim3((unsigned)(rows * g)) : dim3((unsigned)(xcd ? 8 * g : g), (unsigned)grid_rows);
   const bool clear = a.next_out != nullptr;
-  const int waves = a.splits > 32 ? 8 : a.splits > 8 ? 4 : 1;
+  const int waves = a.splits > 32 ? 8 : a.splits > kMostArrivals ? 4 : 1;
+  // (counts are cleared for no more splits than one wave merges)
   const auto kernel = waves == 8   ? paged_decode_reduce_kernel<T, D, false, 8>
-                      : waves == 4 ? (clear ? paged_decode_reduce_kernel<T, D, true, 4> : paged_decode_reduce_kernel<T, D, false, 4>)
-                                   : (clear ? paged_decode_reduce_kernel<T, D, true, 1> : paged_decode_reduce_kernel<T, D, false, 1>);
-  static_assert(kMostArrivals <= 32, "counts are cleared for no more splits");
+                      : waves == 4 ? paged_decode_reduce_kernel<T, D, false, 4>
+                      : clear      ? paged_decode_reduce_kernel<T, D, true, 1>
+                                   : paged_decode_reduce_kernel<T, D, false, 1>;
   hipLaunchKernelGGL(kernel, blocks, dim3(waves * kWave), 0, stream, a.partials, a.out, g, a.splits, order, a.next_out);
 }
 

@@ -118,20 +118,23 @@ struct WaveStates {
   float2 ml[WAVES][GH];
 };
 
-// Two elements of a head over its splits, four of them at a time: read(split, ml, o) gets a split's (m, l) and elements.  The next four
-// are on their way while four are added.
-template <typename Read>
-__device__ __forceinline__ float2 merge_splits(int splits, Read read) {
-  float m = -__builtin_inff(), l = 0.f, o0 = 0.f, o1 = 0.f;
-  float2 ml[4], o[4];
+// E elements of a head over its splits, four of them at a time: read(split, ml, v) gets a split's (m, l) and elements.  The next four
+// are on their way while four are added.  Up to kMostArrivals splits are always added like this, whoever does it, so that a result does
+// not depend on how its splits come together.
+template <int E, typename Read>
+__device__ __forceinline__ void merge_splits(int splits, float (&result)[E], Read read) {
+  float m = -__builtin_inff(), l = 0.f, o[E] = {};
+  float2 ml[4];
+  float v[4][E];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) read(j < splits ? j : splits - 1, ml[j], o[j]);
+  for (int j = 0; j < 4; ++j) read(j < splits ? j : splits - 1, ml[j], v[j]);
   for (int s = 0;;) {
     const int next = s + 4;
-    float2 ml_next[4], o_next[4];
+    float2 ml_next[4];
+    float v_next[4][E];
     if (next < splits) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) read(next + j < splits ? next + j : splits - 1, ml_next[j], o_next[j]);
+      for (int j = 0; j < 4; ++j) read(next + j < splits ? next + j : splits - 1, ml_next[j], v_next[j]);
     }
     float mm = m;
 #pragma unroll
@@ -139,23 +142,28 @@ __device__ __forceinline__ float2 merge_splits(int splits, Read read) {
     const float ms = mm == -__builtin_inff() ? 0.f : mm;
     const float old = __builtin_amdgcn_exp2f(m - ms);
     l *= old;
-    o0 *= old;
-    o1 *= old;
+#pragma unroll
+    for (int e = 0; e < E; ++e) o[e] *= old;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const bool real = s + j < splits;  // what is no split adds nothing, an infinity of the last one included (0 * inf)
       const float w = __builtin_amdgcn_exp2f(ml[j].x - ms);
       l = fmaf(real ? ml[j].y : 0.f, real ? w : 0.f, l);
-      o0 = fmaf(real ? o[j].x : 0.f, real ? w : 0.f, o0);
-      o1 = fmaf(real ? o[j].y : 0.f, real ? w : 0.f, o1);
+#pragma unroll
+      for (int e = 0; e < E; ++e) o[e] = fmaf(real ? v[j][e] : 0.f, real ? w : 0.f, o[e]);
     }
     m = mm;
     if (next >= splits) break;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) ml[j] = ml_next[j], o[j] = o_next[j];
+    for (int j = 0; j < 4; ++j) {
+      ml[j] = ml_next[j];
+#pragma unroll
+      for (int e = 0; e < E; ++e) v[j][e] = v_next[j][e];
+    }
     s = next;
   }
-  return l > 0.f ? make_float2(o0 / l, o1 / l) : make_float2(0.f, 0.f);
+#pragma unroll
+  for (int e = 0; e < E; ++e) result[e] = l > 0.f ? o[e] / l : 0.f;
 }
 
 // How the splits of a row come together: by a launch of its own, or by the last of them to arrive.
@@ -295,12 +303,14 @@ __device__ __forceinline__ void merge_arrived(const WaveStates<WAVES, GH, D>& sm
   }
   if (last) {
     asm volatile("" ::: "memory");  // (the loads below do not move up)
-    const float2 o = merge_splits(splits, [&](int s, float2& ml, float2& v) {
+    float o[2];
+    merge_splits(splits, o, [&](int s, float2& ml, float (&v)[2]) {
       const float* of = base + s * record;
       ml = load_of_all(of + ml_at);
-      v = load_of_all(of + o_at);
+      const float2 pair = load_of_all(of + o_at);
+      v[0] = pair.x, v[1] = pair.y;
     });
-    store_pair<T>(p.out, pair0 + idx, o.x, o.y);
+    store_pair<T>(p.out, pair0 + idx, o[0], o[1]);
   }
   if (p.next_out != nullptr && split == 0 && lane == 0) *arrival_count<T>(p.next_out, pair0 + idx) = 0u;
 }

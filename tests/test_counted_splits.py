@@ -255,3 +255,30 @@ def test_an_infinity_stays_one(D, G, splits):
     for name, o in zip(("counted", "merged by a launch", "tagged"), outs):
         assert torch.equal(o[..., [3, 5]], want[..., [3, 5]]), name
         assert bool(((o - want)[..., finite].abs() <= tol).all()), name
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,S,Hk,G,D,budget,B,shared,splits", SHAPES + [
+    ("f32", 2, 3, 5, 64, 1024, 16, False, 8), ("bf16", 2, 2, 4, 64, 1024, 16, False, 9), ("f32", 1, 2, 1, 64, 640, 16, False, 10)])
+def test_every_way_gives_the_same_bits(dtype, S, Hk, G, D, budget, B, shared, splits):
+    """Counted, tagged and merged by a launch (an output in the middle of a tag), layers in one call or one by one, the attention alone with
+    a workspace and without: the splits are added in one order."""
+    wl, engines = _engines(dtype, S, Hk, G, D, budget, B, shared, splits, 4)
+    engines[2].native_layers = engines[3].native_layers = False
+    odd = 4 // wl.torch_dtype.itemsize
+    for step in range(3):
+        k, v, q = _inputs(wl, step)
+        size, outs = q.numel(), []
+        for e, at in zip(engines, (0, odd, 0, odd)):
+            out = torch.full((size + odd,), 7.0, device="cuda", dtype=wl.torch_dtype)[at:][:size].view(q.shape)
+            e.decode_step(k, v, q, out)
+            outs.append(out)
+        for o in outs[1:]:
+            assert torch.equal(outs[0], o)
+        c, layer = engines[0].per_layer[step], q[step]
+        alone = [torch.full((layer.numel() + odd,), 7.0, device="cuda", dtype=wl.torch_dtype)[at:][:layer.numel()].view(layer.shape)
+                 for at in (0, odd, 0)]
+        for o in alone[:2]:
+            pe.pe_paged_decode(c.desc, layer, c.k_pool, c.v_pool, c.block_table, c.seq_lens, D ** -0.5, o, c.decode_ws)
+        pe.pe_paged_decode_static(c.desc, layer, c.k_pool, c.v_pool, c.block_table, c.seq_lens, D ** -0.5, alone[2])
+        assert torch.equal(alone[0], alone[1]) and torch.equal(alone[0], alone[2])
