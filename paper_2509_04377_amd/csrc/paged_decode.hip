@@ -434,7 +434,7 @@ __global__ __launch_bounds__(WAVES * kWave) void paged_decode_kernel(
 // merge out of a HIP graph, one wave / four / eight, us: 24 heads of D = 64 in 19 splits 8.7 / 7.3 / 7.6, 64 of D = 128 in 16 8.5 / 7.9 / 8.1, 32
 // in 32 9.6 / 8.1 / 8.1, 32 of D = 64 in 36 12.7 / 10.2 / 9.9, four of D = 128 in 64 14.8 / 9.5 / 8.8; nine to twelve, one wave as it is here /
 // four, 25 rows of D = 128 x 4096 in nine 14.5 / 14.3, in twelve 15.4 / 15.4, 24 of D = 64 in nine 10.3 / 10.1, in ten 10.2 / 10.2; up to eight
-no difference).  What a launch of it costs besides is the launch and one round trip to the records, which lie together for a row
+// no difference).  What a launch of it costs besides is the launch and one round trip to the records, which lie together for a row
 // ([row][split][head]: with the heads of all rows under each split 0.4 us more for 32 rows of D = 128 in eight splits, 1.1 us for 16 rows
 // in 16).  The grid: the query heads of a row side by side, one row a grid row; with kMergeXcd, wherever the attention kernel keeps a row
 // on one XCD, eight rows a grid row, so that a row's records are read on the XCD that wrote them (append, attention and merge out of a HIP
