@@ -87,14 +87,15 @@ def kernel_source_hash():
 
 
 def attention_kernels(wl, splits):
-    """The kernels of one attention call, as a kernel trace names them."""
+    """The kernels of the attention calls, as a kernel trace names them.  Which calls have a merge launch is the library's choice, by
+    the number of splits, their length and the layer's place in a step."""
     if wl.dtype == "f32":
         name = "paged_decode_kernel"
     elif wl.num_q_heads > wl.num_kv_heads:
         name = "paged_decode_bf16_kernel"
     else:   # the library's choice, by the length of the rows
         name = "paged_decode_bf16_kernel or paged_decode_kernel"
-    return name + (" + paged_decode_reduce_kernel" if splits > 1 else "")
+    return name + (", splits merged in its launch, or behind it by paged_decode_reduce_kernel" if splits > 1 else "")
 
 
 def traffic_from_profiles(workload):

@@ -21,6 +21,13 @@ def test_the_report_names_kernels_that_exist(name, splits):
     assert ("paged_decode_reduce_kernel" in kernels) == (splits > 1)
 
 
+def test_the_report_leaves_open_who_merges_splits():
+    """Rows in up to twelve splits have a merge launch in the first layer of a step or in none: the report does not add it to every call."""
+    for wl in synth.WORKLOADS.values():
+        label = bench.attention_kernels(wl, 4)
+        assert "+ paged_decode_reduce_kernel" not in label and "in its launch, or" in label
+
+
 def test_the_source_hash_covers_what_chooses_and_builds_the_kernel(tmp_path, monkeypatch):
     root = tmp_path / "paper_2509_04377_amd"
     shutil.copytree(build.CSRC, root / "csrc")
