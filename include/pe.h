@@ -109,8 +109,9 @@ int pe_version(void);
  * when that is set, else the library's choice from the type, the number of rows, the length of a TABLE row (not of the
  * sequences, which the host does not see) and the device's compute units: as many as there is room for with one workgroup per
  * compute unit, fewer for short rows, more for long ones, at most 64, none shorter than 128 tokens nor of rows under 512.  A
- * table that holds little pays for splits without tokens and their merge (measured: up to 5.2 us a call for rows of 64 tokens
- * in tables of 2048 and more, 2 to 3 us for most shapes): a caller who knows that its rows are short may set 1.
+ * table that holds little pays for splits without tokens and their merge (measured, rows of 64 tokens in tables of 1024 and
+ * more: 1 to 2 us a call for most shapes, up to 7.4 where rows slightly outnumber the compute units): a caller who knows that
+ * its rows are short may set 1.
  * (A call that is given a smaller workspace than pe_workspace_bytes() asks for uses fewer, down to one workgroup per
  * compute unit; below that it is refused.)  0 for an invalid desc.  (The compute-unit count is read from the HIP runtime
  * once per device; without a device it is taken as 256, an MI355X.) */
@@ -139,7 +140,7 @@ int pe_score_blocks(const pe_cache_desc* desc, const void* k_pool, const void* v
  *     block_table[s][hk][i / B], slot i % B.  seq_lens_out[s] = min(L_s, C).
  *     k_in, v_in: packed prompt [total_tokens][Hk][D] (the layout before paging), read only.
  *     cu_seqlens: [S+1] int32 prefix sums of the prompt lengths, cu_seqlens[S] == total_tokens.
- *     max_seqlen: an upper bound on every L_s (host value, sizes the launch).
+ *     max_seqlen: an upper bound on every L_s (host value, sizes and chooses the launches).
  *     budget_tokens: C, a positive multiple of B.
  *     block_table is an INPUT: the caller has put ceil(min(L_s, C)/B) distinct physical pages in each
  *     row (ceil(min(max_seqlen, C)/B) > max_blocks is refused with PE_ERR_INVALID_ARG).  Slots of the tail
@@ -256,6 +257,11 @@ int pe_evict_blocks_ex(const pe_cache_desc* desc, const pe_evict_opts* opts, flo
  *     several tokens and heads at once, with zeros for those that do not take part, and 0 * inf is NaN).  Finite values give
  *     finite results as long as the sums over the tokens, relative to the largest weight, fit an fp32.
  *     q, out: [S][Hq][D].  workspace: pe_workspace_bytes(PE_OP_PAGED_DECODE, desc, 0) (split partials).
+ *     `out` is the library's until the call's launches are through, in all calls of (4): where rows are split it may hold tags or
+ *     counts of the splits before the results, so nothing else may read or write it meanwhile.  Where it overlaps q (below:
+ *     or new_k, new_v), or is not 8-byte aligned, a launch of its own merges the splits instead.  The results are the same bits
+ *     either way, as in a call with a workspace or without, for one layer or for all; another number of splits (a smaller
+ *     workspace, another desc) adds in another order.
  *     shared: block_table [S][max_blocks]; query head h reads head h/(Hq/Hk) of the sequence's pages.
  */
 int pe_paged_decode(const pe_cache_desc* desc, const void* q, const void* k_pool, const void* v_pool,
@@ -264,7 +270,7 @@ int pe_paged_decode(const pe_cache_desc* desc, const void* q, const void* k_pool
 
 /*
  * (4) for callers that cannot allocate device memory or pass a workspace: code under HIP graph capture, tight
- * serving loops, harnesses that forbid hipMalloc.  Same arguments, kernels and results as pe_paged_decode, but
+ * serving loops, harnesses that forbid hipMalloc.  Same arguments, kernels, results and use of `out` as pe_paged_decode, but
  * the split partials live in a static device array inside the library (PE_STATIC_SCRATCH_BYTES per GPU, held
  * until the process ends) instead of a caller workspace.  The call allocates and frees nothing.  A shape whose
  * partials, pe_workspace_bytes(PE_OP_PAGED_DECODE, desc, 0), exceed PE_STATIC_SCRATCH_BYTES is refused with
@@ -301,6 +307,7 @@ int pe_append_kv(const pe_cache_desc* desc, const void* new_k, const void* new_v
  * of being read back from the pool.  seq_lens is only read; the new lengths seq_lens[s] + 1 are written
  * to seq_lens_out [S], which must not alias seq_lens (callers keep two arrays and swap them), so that no
  * workgroup of the launch can observe a length that another one has already bumped.
+ * `out` is the library's until the launch is through, as in pe_paged_decode.
  * workspace: pe_workspace_bytes(PE_OP_APPEND_PAGED_DECODE, desc, 0).
  * shared: same contract and shapes as pe_append_kv / pe_paged_decode in that layout (fp32: carried out as two launches, the
  * append before the attention).
@@ -318,9 +325,8 @@ int pe_append_paged_decode(const pe_cache_desc* desc, const void* new_k, const v
  * folded into the sequence dimension: new_k, new_v [layers*S][Hk][D]; q, out [layers*S][Hq][D]; block_table
  * [layers*S][Hk][max_blocks]; seq_lens, seq_lens_out [layers*S]; freed_phys, spare_used [layers*S][Hk]; spare
  * [layers*S][Hk][n_spare] (shared layout: the shapes that layout gives, stacked the same way).  The one workspace
- * (pe_workspace_bytes(PE_OP_APPEND_PAGED_DECODE, desc, 0)) serves every layer.  `out` is the library's until the call's
- * launches are through, here and in the calls for one layer: where rows are split, it may hold counts and tags of the splits before the
- * results.  (Not where it overlaps q, new_k or new_v, or is not 8-byte aligned: launches of their own then merge the splits.)
+ * (pe_workspace_bytes(PE_OP_APPEND_PAGED_DECODE, desc, 0)) serves every layer.  All of `out` is the library's until the call's
+ * launches are through, as in pe_paged_decode: a layer's launch prepares the next one's part of it.
  * Returns the first non-OK status; layers before it have been enqueued.
  */
 int pe_append_paged_decode_layers(const pe_cache_desc* desc, int32_t num_layers, const void* new_k, const void* new_v,

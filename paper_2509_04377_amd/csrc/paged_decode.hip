@@ -419,7 +419,7 @@ __global__ __launch_bounds__(WAVES * kWave) void paged_decode_kernel(
     }
   }
   // The placeholder loads behind a wave's last tile are still on their way during the merge; their registers are in use until
-  // here, so that nothing there waits for them.
+  // here, so that nothing there waits for them but the arrival of splits that are counted or tagged (merge_arrived).
 #pragma unroll
   for (int d = 0; d < DEPTH; ++d)
 #pragma unroll

@@ -463,7 +463,8 @@ void paged_decode_bf16_kernel(
     }
   }
   // The loads behind a wave's last tiles are still on their way while the rows are merged.  Their registers are not to be given
-  // to anything before (whatever is written to a register waits for the load into it): they are in use until here.
+  // to anything before (whatever is written to a register waits for the load into it): they are in use until here.  (The arrival of splits
+  // that are counted or tagged waits for them all the same: merge_arrived.)
   if (first < ntiles) {
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d)

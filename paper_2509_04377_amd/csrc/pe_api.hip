@@ -260,7 +260,8 @@ bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
   return x < y + b_bytes && y < x + a_bytes;
 }
 
-// A launch's own tag: no two of a process are the same (the mixing is one to one), and what lies in memory is none by chance.
+// A launch's own tag: a counter from the time of the first call on, mixed as in SplitMix64 (Steele, Lea and Flood, 2014: its increment, shifts and
+// multipliers).  No two of a process are the same (the mixing is one to one), and what lies in memory is none by chance.
 uint64_t launch_tag() {
   static std::atomic<uint64_t> calls{(uint64_t)std::chrono::system_clock::now().time_since_epoch().count()};
   uint64_t x = calls.fetch_add(1, std::memory_order_relaxed) * 0x9e3779b97f4a7c15ull;

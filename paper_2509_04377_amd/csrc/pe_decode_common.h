@@ -3,8 +3,8 @@
 // Small launches are bound by the chain of dependent steps before the first K/V load and behind the last one, not by traffic.
 // What shortened it, measured together on an MI355X (microseconds a launch, before / after; splits include the merge launch):
 // page lookups first and without a division in front of them (pe_place.h), K and V next, queries and the remaining arguments
-// behind them; tiles counted without a division; no wait for the placeholder loads behind a wave's last tile; reductions over
-// lane rows on the vector units, wave states read from LDS at once.  bfloat16, 64 rows of D = 64 x 1024 8.3 / 8.0, 32 rows of
+// behind them; tiles counted without a division; no wait for the placeholder loads behind a wave's last tile (where splits are merged by the
+// last to arrive there is one, see there); reductions over lane rows on the vector units, wave states read from LDS at once.  bfloat16, 64 rows of D = 64 x 1024 8.3 / 8.0, 32 rows of
 // D = 128 x 4096 16.3 / 15.8, 128 rows x 1024 15.1 / 14.8; vector units, 64 rows of D = 64 x 256, one query head per KV head
 // 5.3 / 4.6, fp32 with two 6.5 / 6.1.
 #pragma once
@@ -179,12 +179,14 @@ enum { kMergeLaunch, kCounted, kTagged };
 // itself, at the beginning of what a wave will write there:
 //   - kCounted: its first word is a count.  It has to be zero when the launch begins: only the call that knows the next launch's output
 //     can provide for that, the one for all layers of a step, whose launch for a layer clears the words of the next layer's output.
-//   - kTagged: its first words are a tag for each split, a number that no other launch of the process has.  A wave stores its own, waits
+//   - kTagged: its first words are a tag for each split, a number that no other launch of the process has (a counter in the host layer
+//     makes them: the one thing that a call leaves behind).  A wave stores its own, waits
 //     until everyone sees that too, and then looks at all of them: the last to arrive finds every one, and where others do as well
 //     they write the same.  What lay in the output before is no tag of this launch; a graph that is replayed has the same tag each
 //     time, but the output, by then written, lies over it.  (Of a launch from another process with the same tag nothing is in memory.)
 //
-// Bound: a chain of round trips, cycles (2.4 GHz) from a clock in the kernel: records stored 530, counted 960 (tags: one more round trip,
+// Bound: a chain of round trips, cycles (2.4 GHz) from a clock in the kernel: records stored 530 (the wait is for all that the wave has
+// outstanding, the placeholder loads behind its last tile included: loads and stores count alike), counted 960 (tags: one more round trip,
 // some 500), read back 720, merged 570; a merge launch costs 1.9 us.  16 layers of 64 rows x 1024 tokens of D = 64 in four splits 2056 /
 // 1812 us for 16 steps, 32 layers of 32 rows x 4096 of D = 128 in eight 8295 / 8090; one layer of 64 rows x 2048 of D = 64 in four,
 // called by itself, 16 steps 191 / 152 (out of a graph 9.9 / 9.4 us a call: the launch costs the host more than the GPU).
@@ -287,7 +289,7 @@ __device__ __forceinline__ void merge_arrived(const WaveStates<WAVES, GH, D>& sm
   if (d == 0) store_for_all(to + D, r.m, r.l);
   const int64_t pair0 = (int64_t)row * pairs;
   const uint32_t ml_at = (uint32_t)(h * (D + 2) + D), o_at = (uint32_t)(h * (D + 2) + d);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the records are where everyone sees them
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the records are where everyone sees them (and the placeholder loads are back)
   bool last;
   if constexpr (TAGGED) {
     uint64_t* const tags = reinterpret_cast<uint64_t*>(arrival_count<T>(p.out, pair0 + (idx - lane)));

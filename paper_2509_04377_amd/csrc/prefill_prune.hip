@@ -23,8 +23,6 @@
 #include "pe_norms.h"
 #include "pe_place.h"
 
-#include <type_traits>
-
 namespace pe {
 namespace {
 
