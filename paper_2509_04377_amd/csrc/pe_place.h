@@ -60,9 +60,10 @@ inline bool launch_pieces(int num_seqs, int rows_per_seq, int chunks, int thread
 //     86.9; one of 32768 beside 31 of 512, 16384 kept, 16 MiB, 155 / 410);
 //   - or no more than a workgroup of the second of two launches copies: 1024 tokens, less what goes of a row of full or of average length
 //     (64 x 1000, 1024 kept 157 / 153; 4 x 4096, 4096 kept 42 / 36);
-//   - or rows of full length, of which there are total / longest at the least, have to fill three quarters of the compute units, and the
-//     workgroups whole rounds of them, but for a tenth (32 x 16384, 8192 kept 805 / 802; 17 x 8192, 136 workgroups, 229 / 251; 33 x 4096,
-//     264, 4096 kept 341 / 396; 60 of D = 64 of 370 to 9893, 7808 kept, 176 of 480 workgroups 294 / 352).
+//   - or rows of full length, of which there are total / longest at the least, have to be half of the workgroups and half of the compute
+//     units, and the workgroups whole rounds of these, but for a tenth (32 x 16384, 8192 kept 805 / 802; 31 x 4 heads of 5265 to 17104, 3520
+//     kept, 160 of 248 workgroups 233 / 227; 17 x 8192, 136 workgroups, 229 / 251; 33 x 4096, 264, 4096 kept 341 / 396; 60 of D = 64 of 370
+//     to 9893, 7808 kept, 176 of 480 workgroups 294 / 352).
 // Rows of more than 8192 tokens of which less than a sixteenth of the average row is kept have little to copy, and the counting in front
 // of it takes the launch's time or more: one of 30335 tokens, 1120 kept 19.6 / 23.1, nine of up to 28254, 320 kept 59.2 / 62.1, 8 x 32768,
 // 1024 kept 198 / 199; a tenth: 21 of up to 8274, 1024 kept 62.2 / 57.3.  Longer rows than 32768 are held in LDS too, by one compute unit.
@@ -78,7 +79,7 @@ inline int prune_log2_parts(int num_seqs, int num_kv_heads, int64_t total_tokens
   const int64_t of_full = 1024 * most / max_seqlen, of_average = average > budget ? 1024 * (int64_t)budget / average : average;
   if (share <= of_full || share <= (of_average < 1024 ? of_average : 1024)) return log2_parts;
   const int64_t groups = rows << log2_parts, full = (total_tokens / max_seqlen * num_kv_heads) << log2_parts;
-  return full * 4 >= cus * 3 && groups * 10 >= (groups + cus - 1) / cus * cus * 9 ? log2_parts : -1;
+  return full * 2 >= cus && full * 2 >= groups && groups * 10 >= (groups + cus - 1) / cus * cus * 9 ? log2_parts : -1;
 }
 
 // Block scores: which part of its row workgroup b has, of `parts` a row.  Workgroup b runs on XCD b % 8, there on one shader engine after the

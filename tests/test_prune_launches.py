@@ -41,6 +41,7 @@ def log2_parts(tmp_path_factory):
     # nearly half of the compute units, or of a second round of them, without work
     ([8192] * 17, 8, 4096, 128, 2, -1), ([4096] * 33, 8, 2048, 128, 2, -1), ([9000] * 48, 8, 4096, 128, 2, -1),
     ([4096] * 32, 8, 4096, 128, 2, 0), ([16384] * 32, 8, 8192, 128, 2, 0), ([16384] * 16, 8, 8192, 128, 2, 1),
+    ([17104] * 12 + [8000] * 19, 4, 3520, 128, 2, 1), ([9893] * 20 + [650] * 40, 8, 7808, 64, 2, -1),
     # large shares, but no larger than what two launches copy at a time
     ([1000] * 64, 8, 1024, 128, 2, 0), ([2000] * 64, 8, 1024, 64, 2, 0), ([4096] * 4, 8, 4096, 128, 2, 3),
     # long rows of which little is kept, and what no workgroup holds
