@@ -561,7 +561,7 @@ void launch_reduce(const DecodeArgs& a, hipStream_t stream) {
   const int order = grid_rows > 65535 ? kMergeLinear : xcd ? kMergeXcd : kMergeRows;
   const dim3 blocks = order == kMergeLinear ? dim3((unsigned)(rows * g)) : dim3((unsigned)(xcd ? 8 * g : g), (unsigned)grid_rows);
   const bool clear = a.next_out != nullptr;
-  const int waves = a.splits > 32 ? 8 : a.splits > kMostArrivals ? 4 : 1;
+  const int waves = a.splits > 32 ? 8 : a.splits > most_arrivals(g) ? 4 : 1;
   // (counts are cleared for no more splits than one wave merges)
   const auto kernel = waves == 8   ? paged_decode_reduce_kernel<T, D, false, 8>
                       : waves == 4 ? paged_decode_reduce_kernel<T, D, false, 4>

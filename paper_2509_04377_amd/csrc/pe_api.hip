@@ -248,7 +248,7 @@ bool splits_counted(const pe_cache_desc* d, const pe::DecodeArgs& a) {
   const int64_t groups = (int64_t)d->num_seqs * d->num_kv_heads * a.splits;
   const int heads = d->num_q_heads / d->num_kv_heads;
   const bool built = !a.is_bf16 || a.vector ? !a.shared : a.depth == 1 || (a.waves == 4 && a.depth == 2);
-  return built && a.splits > 1 && a.splits <= (heads > 4 ? 8 : pe::kMostArrivals) && heads * d->head_dim <= 128 * a.waves &&
+  return built && a.splits > 1 && a.splits <= pe::most_arrivals(heads) && heads * d->head_dim <= 128 * a.waves &&
          groups <= (a.splits > 8 ? 1 : 2) * (int64_t)compute_units();
 }
 bool splits_tagged(const pe_cache_desc* d, const pe::DecodeArgs& a) {

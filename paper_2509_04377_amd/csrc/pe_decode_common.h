@@ -119,7 +119,7 @@ struct WaveStates {
 };
 
 // E elements of a head over its splits, four of them at a time: read(split, ml, v) gets a split's (m, l) and elements.  The next four
-// are on their way while four are added.  Up to kMostArrivals splits are always added like this, whoever does it, so that a result does
+// are on their way while four are added.  Up to most_arrivals splits are always added like this, whoever does it, so that a result does
 // not depend on how its splits come together.
 template <int E, typename Read>
 __device__ __forceinline__ void merge_splits(int splits, float (&result)[E], Read read) {

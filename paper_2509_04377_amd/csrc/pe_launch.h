@@ -99,7 +99,10 @@ struct DecodeArgs {
 hipError_t launch_paged_decode(const DecodeArgs& a, hipStream_t stream);
 hipError_t launch_paged_decode_bf16(const DecodeArgs& a, hipStream_t stream);  // the attention kernel alone (no merge)
 size_t decode_partials_bytes(int num_seqs, int num_q_heads, int head_dim, int splits);
-constexpr int kMostArrivals = 12;  // the most splits of a row that are counted or tagged; up to here they are added in one order on every way
+// The most splits of a row that are counted or tagged, and with so many query heads a KV head; up to here they are added in one order on
+// every way.
+constexpr int kMostArrivals = 12;
+constexpr int most_arrivals(int group) { return group > 4 ? 8 : kMostArrivals; }
 
 struct PruneArgs {
   const void* k_in;
