@@ -60,8 +60,8 @@ inline bool launch_pieces(int num_seqs, int rows_per_seq, int chunks, int thread
 //     86.9; one of 32768 beside 31 of 512, 16384 kept, 16 MiB, 155 / 410);
 //   - or no more than a workgroup of the second of two launches copies: 1024 tokens, less what goes of a row of full or of average length
 //     (64 x 1000, 1024 kept 157 / 153; 4 x 4096, 4096 kept 42 / 36);
-//   - or rows of full length, of which there are total / longest at the least, have to be half of the workgroups and half of the compute
-//     units, and the workgroups whole rounds of these, but for a tenth (32 x 16384, 8192 kept 805 / 802; 31 x 4 heads of 5265 to 17104, 3520
+//   - or the tokens have to be as many full rows, total / longest, as make half of the workgroups and occupy half of the compute units, and
+//     the workgroups whole rounds of these, but for a tenth (32 x 16384, 8192 kept 805 / 802; 31 x 4 heads of 5265 to 17104, 3520
 //     kept, 160 of 248 workgroups 233 / 227; 17 x 8192, 136 workgroups, 229 / 251; 33 x 4096, 264, 4096 kept 341 / 396; 60 of D = 64 of 370
 //     to 9893, 7808 kept, 176 of 480 workgroups 294 / 352).
 // Rows of more than 8192 tokens of which less than a sixteenth of the average row is kept have little to copy, and the counting in front

@@ -122,7 +122,6 @@ def test_waves_on_the_vector_units(host_layer, kw, waves):
     assert _form(host_layer, **kw)[1] == waves
 
 
-
 @pytest.mark.parametrize("more,last,compiles", [("", "const uint32_t", True), ("const int more,", "const uint32_t", False),
                                                 ("", "const uint64_t", False)])
 def test_attention_kernels_have_the_parameters_that_are_read_by_offset(tmp_path, more, last, compiles):
