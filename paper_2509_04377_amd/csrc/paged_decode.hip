@@ -432,9 +432,9 @@ __global__ __launch_bounds__(WAVES * kWave) void paged_decode_kernel(
 // Merge the split partials of one (sequence, query head), D / 64 elements a lane: by one wave where their number is one that may be
 // counted, in the order that has there; more are shared by four waves and more than 32 by eight, whose states meet in LDS (attention and
 // merge out of a HIP graph, one wave / four / eight, us: 24 heads of D = 64 in 19 splits 8.7 / 7.3 / 7.6, 64 of D = 128 in 16 8.5 / 7.9 / 8.1, 32
-// in 32 9.6 / 8.1 / 8.1, 32 of D = 64 in 36 12.7 / 10.2 / 9.9, four of D = 128 in 64 14.8 / 9.5 / 8.8; nine to twelve, one wave as it is here /
-// four, 25 rows of D = 128 x 4096 in nine 14.5 / 14.3, in twelve 15.4 / 15.4, 24 of D = 64 in nine 10.3 / 10.1, in ten 10.2 / 10.2; up to eight
-// no difference).  What a launch of it costs besides is the launch and one round trip to the records, which lie together for a row
+// in 32 9.6 / 8.1 / 8.1, 32 of D = 64 in 36 12.7 / 10.2 / 9.9, four of D = 128 in 64 14.8 / 9.5 / 8.8; nine to twelve, one wave with all records
+// asked for at once / four, attention out of calls, 25 rows of D = 128 x 4096 in ten 12.44 / 12.66, 21 in twelve 11.18 / 11.39, 28 x 2048 in nine
+// 8.86 / 8.99, fp32, 24 x 2500 of D = 64 in ten 8.46 / 8.43; up to eight no difference).  What a launch of it costs besides is the launch and one round trip to the records, which lie together for a row
 // ([row][split][head]: with the heads of all rows under each split 0.4 us more for 32 rows of D = 128 in eight splits, 1.1 us for 16 rows
 // in 16).  The grid: the query heads of a row side by side, one row a grid row; with kMergeXcd, wherever the attention kernel keeps a row
 // on one XCD, eight rows a grid row, so that a row's records are read on the XCD that wrote them (append, attention and merge out of a HIP
@@ -465,7 +465,22 @@ __global__ __launch_bounds__(WAVES * kWave) void paged_decode_reduce_kernel(cons
   };
   float o[E] = {};
   if constexpr (WAVES == 1) {
-    merge_splits(splits, o, read);
+    // all on their way before the first is used
+    constexpr int kFours = kMostArrivals / 4;
+    static_assert(kMostArrivals % 4 == 0, "fours");
+    float2 ml[kFours][4];
+    float v[kFours][4][E];
+    SplitSum<E> sum;
+#pragma unroll
+    for (int i = 0; i < kFours; ++i)
+      if (i == 0 || 4 * i < splits) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) read(4 * i + j < splits ? 4 * i + j : splits - 1, ml[i][j], v[i][j]);
+      }
+#pragma unroll
+    for (int i = 0; i < kFours; ++i)
+      if (i == 0 || 4 * i < splits) sum.add(splits - 4 * i, ml[i], v[i]);
+    sum.normalised(o);
   } else {
     // online: all loads are independent of the running state, so they overlap
     float mm = kNegInf, l = 0.f;
