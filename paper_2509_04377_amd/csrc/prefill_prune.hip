@@ -29,9 +29,6 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
 constexpr int kChunk = 1024;  // tokens per chunk in the count pass and in the gather
-constexpr int kGatherThreads = 512;
-constexpr int kGatherWaves = kGatherThreads / kWave;
-constexpr int kTokPerThread = kChunk / kGatherThreads;
 constexpr int kSweepLoads = 4;  // token sweep: wave-loads of K (and of V) per step
 constexpr int kSweepIters = 2;  // and steps per wave (4 and 8: the same on 2 GB of prompt, 5 us slower on 1 GB: longer tail)
 
@@ -651,26 +648,29 @@ SelectKernel select_kernel_for(int max_seqlen) {
 }
 
 // ---- 3. gather ----------------------------------------------------------------------------------------
-// One workgroup per (row, chunk) copies the kept token rows of one head.  512 threads: a chunk that is kept whole, as of short rows
+// One workgroup per (row, chunk) copies the kept token rows of one head, with 512 threads: a chunk that is kept whole, as of short rows
 // beside a long one, is a long way for 256 (whole prunes, 256 / 512 / 1024 threads, us: fp32, 39 of D = 128 of up to 1459 tokens 74.7 /
-// 54.1 / 54.4, one of 9802 beside eleven of 980, 1280 kept 67.7 / 49.9 / 50.0), and chunks of which little is kept leave 1024 without work
-// (14 x 14652 of D = 64, 336 kept 81.6 / 83.3 / 88.4).  SHARED: the heads of a sequence share its selection and its
+// 54.1 / 54.4, one of 9802 beside eleven of 980, 1280 kept 67.7 / 49.9 / 50.0).  Where less than a thirty-second of the average row is
+// kept they have little to copy, and it takes 256 (256 / 512: 14 of up to 14652 of D = 64, 224 kept 72.4 / 73.8, 448 kept 74.8 / 74.9, 912 79.2 /
+// 79.2; 4 x 40960 of D = 128, 640 kept 124.8 / 126.4, 1280 127.8 / 128.0, 20480 263.5 / 262.1; 2 x 40960, four heads of D = 64, 1280 kept 30.6 /
+// 30.4).  SHARED: the heads of a sequence share its selection and its
 // table row, their token rows lie num_kv_heads apart in the pages (whole records by one workgroup were a division per
 // 16 bytes and an eighth of the workgroups: 16 prompts of 2048 to 8192 tokens, 8 heads, 1024 kept 204 us a prune, now 98; 8 x 4096 of
 // D = 64 54.8, now 31.1).
-template <int VEC_PER_ROW, bool SHARED>
-__global__ __launch_bounds__(kGatherThreads) void gather_kernel(const uint4* __restrict__ k_in, const uint4* __restrict__ v_in,
-                                                          const float* __restrict__ scores,
-                                                          const int32_t* __restrict__ cu_seqlens,
-                                                          const uint32_t* __restrict__ sel,
-                                                          const int32_t* __restrict__ before,
-                                                          const int32_t* __restrict__ block_table,
-                                                          uint4* __restrict__ k_pool, uint4* __restrict__ v_pool,
-                                                          int32_t* __restrict__ kept_idx_out, int64_t total_tokens,
-                                                          int64_t chunk_slots, int num_kv_heads, int rows,
-                                                          int log2_block, int max_blocks, int budget, int row0,
-                                                          int chunk0) {
-  __shared__ uint32_t wave_sum[kGatherWaves];
+template <int VEC_PER_ROW, bool SHARED, int THREADS>
+__global__ __launch_bounds__(THREADS) void gather_kernel(const uint4* __restrict__ k_in, const uint4* __restrict__ v_in,
+                                                         const float* __restrict__ scores,
+                                                         const int32_t* __restrict__ cu_seqlens,
+                                                         const uint32_t* __restrict__ sel,
+                                                         const int32_t* __restrict__ before,
+                                                         const int32_t* __restrict__ block_table,
+                                                         uint4* __restrict__ k_pool, uint4* __restrict__ v_pool,
+                                                         int32_t* __restrict__ kept_idx_out, int64_t total_tokens,
+                                                         int64_t chunk_slots, int num_kv_heads, int rows,
+                                                         int log2_block, int max_blocks, int budget, int row0,
+                                                         int chunk0) {
+  constexpr int kTokPerThread = kChunk / THREADS;
+  __shared__ uint32_t wave_sum[THREADS / kWave];
   __shared__ int32_t src_tok[kChunk];  // kept tokens of this chunk, in order: in-sequence index
   __shared__ int n_kept_sh;
   // Rows fastest: the first chunks of a ragged batch, which short sequences keep most of, spread over all XCDs (workgroup
@@ -712,7 +712,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(const uint4* __r
   __syncthreads();
   uint32_t ex = inc - n_both;
 #pragma unroll
-  for (int w = 0; w < kGatherWaves; ++w) ex += w < wave ? wave_sum[w] : 0u;
+  for (int w = 0; w < THREADS / kWave; ++w) ex += w < wave ? wave_sum[w] : 0u;
   int ex_gt = (int)(ex & 0xffffu) + gt_before, ex_eq = (int)(ex >> 16) + eq_before;
   // kept tokens before this chunk's start: the chunk's kept tokens take consecutive positions from here
   const int kept_before_chunk = gt_before + (eq_before > q ? eq_before - q : 0);
@@ -729,18 +729,18 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(const uint4* __r
     ex_gt += is_gt;
     ex_eq += is_eq;
   }
-  if (tid == kGatherThreads - 1) n_kept_sh = ex_gt + (ex_eq > q ? ex_eq - q : 0) - kept_before_chunk;
+  if (tid == THREADS - 1) n_kept_sh = ex_gt + (ex_eq > q ? ex_eq - q : 0) - kept_before_chunk;
   __syncthreads();
   const int n_kept = n_kept_sh;
 
   if (kept_idx_out != nullptr && (!SHARED || h == 0))  // consecutive positions: whole lines
-    for (int e = tid; e < n_kept; e += kGatherThreads) kept_idx_out[(int64_t)sel_row * budget + kept_before_chunk + e] = src_tok[e];
+    for (int e = tid; e < n_kept; e += THREADS) kept_idx_out[(int64_t)sel_row * budget + kept_before_chunk + e] = src_tok[e];
 
   // copy the kept rows: VEC_PER_ROW lanes per token row, K and V (two or four rows of a thread in flight, or the pages looked up
   // beforehand: no faster)
   const int32_t* bt = block_table + (int64_t)sel_row * max_blocks;
   const int block_mask = (1 << log2_block) - 1;
-  constexpr int kRowsPerPass = kGatherThreads / VEC_PER_ROW;
+  constexpr int kRowsPerPass = THREADS / VEC_PER_ROW;
   const int u = tid % VEC_PER_ROW, r = tid / VEC_PER_ROW;
   for (int e = r; e < n_kept; e += kRowsPerPass) {
     const int pos = kept_before_chunk + e;
@@ -966,11 +966,14 @@ hipError_t launch(const PruneArgs& a, hipStream_t stream) {
   // Plain stores for what is kept.  With the non-temporal hint prunes of 32 x 16384 tokens that go into the same pools again and
   // again take 454 us instead of 467, but those of a model's layers, one after the other and each into its own pool, 475 instead of
   // 457 (four prompts of 65536 229 and 223, 3B prompts 141 and 137, the head-shared layout 455 and 436).
-  const auto gather = a.shared ? gather_kernel<VPR, true> : gather_kernel<VPR, false>;
-  e = hipErrorInvalidValue;  // (one launch, but where a head-shared batch has more than 2^24 (head, chunk) pairs)
-  launch_pieces(a.num_seqs, a.num_kv_heads, chunks_per_row, kGatherThreads, [&](int s0, int ns, int c0, int nc) {
+  const bool little = (int64_t)a.budget * 32 < a.total_tokens / a.num_seqs;
+  const int threads = little ? 256 : 512;
+  const auto gather = little ? (a.shared ? gather_kernel<VPR, true, 256> : gather_kernel<VPR, false, 256>)
+                             : (a.shared ? gather_kernel<VPR, true, 512> : gather_kernel<VPR, false, 512>);
+  e = hipErrorInvalidValue;  // (one launch, but where a batch has more (head, chunk) pairs than 2^32 threads)
+  launch_pieces(a.num_seqs, a.num_kv_heads, chunks_per_row, threads, [&](int s0, int ns, int c0, int nc) {
     const int copied = ns * a.num_kv_heads;  // (row, head) pairs that this launch copies
-    hipLaunchKernelGGL(gather, dim3((unsigned)copied * (unsigned)nc), dim3(kGatherThreads), 0, stream, (const uint4*)a.k_in,
+    hipLaunchKernelGGL(gather, dim3((unsigned)copied * (unsigned)nc), dim3(threads), 0, stream, (const uint4*)a.k_in,
                        (const uint4*)a.v_in, sel_scores, a.cu_seqlens, w.sel, w.before, a.block_table, (uint4*)a.k_pool,
                        (uint4*)a.v_pool, a.kept_idx_out, a.total_tokens, w.chunk_slots, a.num_kv_heads, copied,
                        ilog2(a.block_size), a.max_blocks, a.budget, s0 * a.num_kv_heads, c0);

@@ -84,7 +84,9 @@ def test_selection_is_a_stable_sort(lens, kind):
     ([9000, 4100, 8192, 77], 96, 8192, torch.bfloat16),   # a workgroup a row: more positions than it lists at a time
     ([4100, 900, 1, 4096], 5, 1008, torch.float32),       # several a row, the last one's share cut short or empty
     ([1000], 3, 64, torch.bfloat16), ([300, 17], 2, 512, torch.float32),   # one pass each; nothing to evict
-    ([32768, 20000], 2, 16384, torch.bfloat16), ([32769, 31], 2, 4112, torch.float32)])   # both sides of the two ways
+    ([32768, 20000], 2, 16384, torch.bfloat16), ([32769, 31], 2, 4112, torch.float32),   # both sides of the two ways
+    # two launches, little kept: 256 threads a chunk where the average row is longer than 32 budgets, else 512
+    ([16400, 9000], 3, 256, torch.bfloat16), ([33000, 32536], 2, 1024, torch.float32), ([33000, 32538], 2, 1024, torch.bfloat16)])
 def test_shares_of_the_copy(lens, heads, budget, dtype, shared, kind):
     """Every kept token of every row lands in its slot, whatever share of the row it belongs to."""
     dev, D, B = "cuda", 64, 16
