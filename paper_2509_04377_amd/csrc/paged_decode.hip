@@ -470,7 +470,7 @@ __global__ __launch_bounds__(WAVES * kWave) void paged_decode_reduce_kernel(cons
     static_assert(kMostArrivals % 4 == 0, "fours");
     float2 ml[kFours][4];
     float v[kFours][4][E];
-    SplitSum<E> sum;
+    float m = kNegInf, l = 0.f;
 #pragma unroll
     for (int i = 0; i < kFours; ++i)
       if (i == 0 || 4 * i < splits) {
@@ -479,8 +479,9 @@ __global__ __launch_bounds__(WAVES * kWave) void paged_decode_reduce_kernel(cons
       }
 #pragma unroll
     for (int i = 0; i < kFours; ++i)
-      if (i == 0 || 4 * i < splits) sum.add(splits - 4 * i, ml[i], v[i]);
-    sum.normalised(o);
+      if (i == 0 || 4 * i < splits) add_splits(4 * i, splits, ml[i], v[i], m, l, o);
+#pragma unroll
+    for (int e = 0; e < E; ++e) o[e] = l > 0.f ? o[e] / l : 0.f;
   } else {
     // online: all loads are independent of the running state, so they overlap
     float mm = kNegInf, l = 0.f;

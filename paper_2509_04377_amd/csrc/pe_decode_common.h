@@ -118,41 +118,34 @@ struct WaveStates {
   float2 ml[WAVES][GH];
 };
 
-// E elements of a head over its splits, added four at a time.  Up to most_arrivals splits are always added like this, whoever does it,
-// so that a result does not depend on how its splits come together.
+// E elements of a head over its splits, and l, relative to the largest m: added four at a time, those past the last being the last again.  Up to
+// most_arrivals splits are always added like this, whoever does it, so that a result does not depend on how its splits come together.
 template <int E>
-struct SplitSum {
-  float m = -__builtin_inff(), l = 0.f, o[E] = {};
-  // (m, l) and elements of four splits, of which `left` are real and the others the last one again
-  __device__ __forceinline__ void add(int left, const float2 (&ml)[4], const float (&v)[4][E]) {
-    float mm = m;
+__device__ __forceinline__ void add_splits(int s, int splits, const float2 (&ml)[4], const float (&v)[4][E], float& m, float& l,
+                                           float (&o)[E]) {
+  float mm = m;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) mm = fmaxf(mm, ml[j].x);
-    const float ms = mm == -__builtin_inff() ? 0.f : mm;
-    const float old = __builtin_amdgcn_exp2f(m - ms);
-    l *= old;
+  for (int j = 0; j < 4; ++j) mm = fmaxf(mm, ml[j].x);
+  const float ms = mm == -__builtin_inff() ? 0.f : mm;
+  const float old = __builtin_amdgcn_exp2f(m - ms);
+  l *= old;
 #pragma unroll
-    for (int e = 0; e < E; ++e) o[e] *= old;
+  for (int e = 0; e < E; ++e) o[e] *= old;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const bool real = j < left;  // what is no split adds nothing, an infinity of the last one included (0 * inf)
-      const float w = __builtin_amdgcn_exp2f(ml[j].x - ms);
-      l = fmaf(real ? ml[j].y : 0.f, real ? w : 0.f, l);
+  for (int j = 0; j < 4; ++j) {
+    const bool real = s + j < splits;  // what is no split adds nothing, an infinity of the last one included (0 * inf)
+    const float w = __builtin_amdgcn_exp2f(ml[j].x - ms);
+    l = fmaf(real ? ml[j].y : 0.f, real ? w : 0.f, l);
 #pragma unroll
-      for (int e = 0; e < E; ++e) o[e] = fmaf(real ? v[j][e] : 0.f, real ? w : 0.f, o[e]);
-    }
-    m = mm;
+    for (int e = 0; e < E; ++e) o[e] = fmaf(real ? v[j][e] : 0.f, real ? w : 0.f, o[e]);
   }
-  __device__ __forceinline__ void normalised(float (&result)[E]) const {
-#pragma unroll
-    for (int e = 0; e < E; ++e) result[e] = l > 0.f ? o[e] / l : 0.f;
-  }
-};
+  m = mm;
+}
 
-// read(split, ml, v) gets a split's (m, l) and elements.  The next four are on their way while four are added.
+// All of them: read(split, ml, v) gets a split's (m, l) and elements.  The next four are on their way while four are added.
 template <int E, typename Read>
 __device__ __forceinline__ void merge_splits(int splits, float (&result)[E], Read read) {
-  SplitSum<E> sum;
+  float m = -__builtin_inff(), l = 0.f, o[E] = {};
   float2 ml[4];
   float v[4][E];
 #pragma unroll
@@ -165,7 +158,7 @@ __device__ __forceinline__ void merge_splits(int splits, float (&result)[E], Rea
 #pragma unroll
       for (int j = 0; j < 4; ++j) read(next + j < splits ? next + j : splits - 1, ml_next[j], v_next[j]);
     }
-    sum.add(splits - s, ml, v);
+    add_splits(s, splits, ml, v, m, l, o);
     if (next >= splits) break;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -175,7 +168,8 @@ __device__ __forceinline__ void merge_splits(int splits, float (&result)[E], Rea
     }
     s = next;
   }
-  sum.normalised(result);
+#pragma unroll
+  for (int e = 0; e < E; ++e) result[e] = l > 0.f ? o[e] / l : 0.f;
 }
 
 // How the splits of a row come together: by a launch of its own, or by the last of them to arrive.
