@@ -59,11 +59,18 @@ inline bool launch_pieces(int num_seqs, int rows_per_seq, int chunks, int thread
 //   - no more than 640 KiB (16 of 2048 to 16384, 1024 kept, 512 KiB 141 / 137; 17 x 4096, 256 kept 64.6 / 64.5, 1024 kept, 1 MiB, 82.5 /
 //     86.9; one of 32768 beside 31 of 512, 16384 kept, 16 MiB, 155 / 410);
 //   - or no more than a workgroup of the second of two launches copies: 1024 tokens, less what goes of a row of full or of average length
-//     (64 x 1000, 1024 kept 157 / 153; 4 x 4096, 4096 kept 42 / 36);
-//   - or the tokens have to be as many full rows, total / longest, as make half of the workgroups and occupy half of the compute units, and
-//     the workgroups whole rounds of these, but for a tenth (32 x 16384, 8192 kept 805 / 802; 31 x 4 heads of 5265 to 17104, 3520
-//     kept, 160 of 248 workgroups 233 / 227; 17 x 8192, 136 workgroups, 229 / 251; 33 x 4096, 264, 4096 kept 341 / 396; 60 of D = 64 of 370
-//     to 9893, 7808 kept, 176 of 480 workgroups 294 / 352).
+//     (64 x 1000, 1024 kept 157 / 153; 4 x 4096, 4096 kept 42 / 36); or three times what it copies of an average row, where the workgroups
+//     of full rows, of which the tokens make total / longest, are four ninths of the compute units or more: two launches then have few
+//     workgroups too, of unequal shares (24 x 2 heads of 3927 to 7783, 3776 kept 85.1 / 73.6, 20 x 2 74.5 / 66.3, 12 of 2048 to 6000, 2048
+//     kept 99.4 / 89.8, 6 of 4096 to 8192, 4096 kept 92.1 / 82.0, 9 x 4096, 2048 kept 74.9 / 72.0; at three eighths, three of 16384 beside five
+//     of 512, 8192 kept, 113 / 127; at four times, 9 x 8192, 4096 kept 129.8 / 133.1);
+//   - or the workgroups of full rows have to be five eighths of all and occupy five eighths of the compute units, and all of them be whole
+//     rounds of these, but for a tenth (32 x 16384, 8192 kept 805 / 802; 31 x 4 heads of 5265 to 17104, 3520 kept, 160 of 248 workgroups
+//     233 / 227; 20 of 16384 beside eleven of 512, 8192 kept, as many, 521 / 564, but 16 of them 426 / 504; 17 x 8192, 136 workgroups, 229 /
+//     251; 24 x 8192, 192, 4096 kept 307 / 315; 33 x 4096, 264, 4096 kept 341 / 396; 60 of D = 64 of 370 to 9893, 7808 kept, 176 of 480
+//     workgroups 294 / 352).
+// (On the slower side of these lines: fp32, 13 of 3400 to 18500, 5248 kept, in two 465 / 448; four of 16384 beside four of 512, 8192 kept, in
+// one 130 / 140.)
 // Rows of more than 8192 tokens of which less than a sixteenth of the average row is kept have little to copy, and the counting in front
 // of it takes the launch's time or more: one of 30335 tokens, 1120 kept 19.6 / 23.1, nine of up to 28254, 320 kept 59.2 / 62.1, 8 x 32768,
 // 1024 kept 198 / 199; a tenth: 21 of up to 8274, 1024 kept 62.2 / 57.3.  Longer rows than 32768 are held in LDS too, by one compute unit.
@@ -77,9 +84,10 @@ inline int prune_log2_parts(int num_seqs, int num_kv_heads, int64_t total_tokens
   const int64_t share = (most + (1 << log2_parts) - 1) >> log2_parts;
   if (share * token_bytes <= 640 << 10) return log2_parts;
   const int64_t of_full = 1024 * most / max_seqlen, of_average = average > budget ? 1024 * (int64_t)budget / average : average;
-  if (share <= of_full || share <= (of_average < 1024 ? of_average : 1024)) return log2_parts;
+  const int64_t chunk = of_average < 1024 ? of_average : 1024;
   const int64_t groups = rows << log2_parts, full = (total_tokens / max_seqlen * num_kv_heads) << log2_parts;
-  return full * 2 >= cus && full * 2 >= groups && groups * 10 >= (groups + cus - 1) / cus * cus * 9 ? log2_parts : -1;
+  if (share <= of_full || share <= (full * 9 >= cus * 4 ? 3 * chunk : chunk)) return log2_parts;
+  return full * 8 >= cus * 5 && full * 8 >= groups * 5 && groups * 10 >= (groups + cus - 1) / cus * cus * 9 ? log2_parts : -1;
 }
 
 // Block scores: which part of its row workgroup b has, of `parts` a row.  Workgroup b runs on XCD b % 8, there on one shader engine after the

@@ -42,6 +42,11 @@ def log2_parts(tmp_path_factory):
     ([8192] * 17, 8, 4096, 128, 2, -1), ([4096] * 33, 8, 2048, 128, 2, -1), ([9000] * 48, 8, 4096, 128, 2, -1),
     ([4096] * 32, 8, 4096, 128, 2, 0), ([16384] * 32, 8, 8192, 128, 2, 0), ([16384] * 16, 8, 8192, 128, 2, 1),
     ([17104] * 12 + [8000] * 19, 4, 3520, 128, 2, 1), ([9893] * 20 + [650] * 40, 8, 7808, 64, 2, -1),
+    # half of the workgroups with a long row's share are too few
+    ([16384] * 16 + [512] * 15, 8, 8192, 128, 2, -1), ([16384] * 8 + [512] * 8, 8, 8192, 128, 2, -1), ([16384] * 20 + [512] * 11, 8, 8192, 128, 2, 0),
+    # up to three times what two launches copy at a time, if most compute units have a share
+    ([7783] * 12 + [3927] * 12, 2, 3776, 128, 2, 2), ([4096] * 9, 8, 2048, 128, 2, 1), ([8192] * 9, 8, 4096, 128, 2, -1),
+    ([16384] * 3 + [512] * 5, 8, 8192, 128, 2, -1), ([16384] * 4 + [512] * 4, 8, 8192, 128, 2, 2),
     # large shares, but no larger than what two launches copy at a time
     ([1000] * 64, 8, 1024, 128, 2, 0), ([2000] * 64, 8, 1024, 64, 2, 0), ([4096] * 4, 8, 4096, 128, 2, 3),
     # long rows of which little is kept, and what no workgroup holds
